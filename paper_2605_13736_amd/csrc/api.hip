@@ -137,7 +137,7 @@ Layout make_layout(const mds_dims &d, int nb, bool pingpong, int precision, int 
   bytes[S_GRHS] = bytes[S_GX] = bytes[S_GW] = mixed ? 8 * nK : 0;
   bytes[S_GPART] = 8 * (size_t)kDotBlocks * (R + 2);
   bytes[S_GCOEF] = 8 * (R + 2);
-  bytes[S_XCH] = 8 * 2 * (size_t)kCoopMaxP * kCoopSlotWords;
+  bytes[S_XCH] = kCoopXchBytes;
   bytes[S_SRC] = 4 * N;
   bytes[S_W] = 8 * N * (size_t)(nb + 2);
   // look-ahead (ping-pong layout): second map and W, two staging buffers
@@ -228,15 +228,16 @@ int panel_threads_of(const mds_options *o, int N) {
 }
 
 // Panel choice.  panel option 1: memory panel; 2: register panel (N <= 4096);
-// 3: cooperative register panel over several workgroups (any N); 4: the
-// whole M in one workgroup's LDS (FP64, N <= bk_lds_max_n());
-// 0 (automatic): the register panel while its tile keeps nb >= 16
-// (N <= 2048 with 512 threads), else the cooperative panel (nb = 32, about
-// 6 us per pivot at N = 4096 against 7-8 us for the memory panel, and half
-// the trailing-update traffic), which hands over to the register panel once
-// at most bk_reg_tail_rows() rows remain (option 3 keeps the cooperative
-// panel to the end).  The mixed-precision modes need a register-resident
-// panel (2 or 3).
+// 3: cooperative panel over ceil(N / 256) workgroups (any N); 4: the whole M
+// in one workgroup's LDS (FP64, N <= bk_lds_max_n()).
+// 0 (automatic): the cooperative panel, except in mixed precision while the
+// register panel's tile keeps nb >= 16 (N <= 2048) or when panel_threads
+// asks for the register panel.  Newton step, register / cooperative panel:
+// N = 101 0.55 / 0.42 ms, 771 2.9 / 1.5, 2051 8.6 (former cooperative panel
+// and register tail) / 3.4.
+// Cooperative nb: 64 in FP64 above N = 2048, where the trailing update's
+// traffic (inverse to the width) counts; 32 below and in mixed precision,
+// whose trailing update stages at most 48 columns.
 PanelChoice panel_of(const mds_dims &d, const mds_options *o) {
   const int N = d.n_d + d.m;
   const int popt = o ? o->panel : 0;
@@ -255,17 +256,19 @@ PanelChoice panel_of(const mds_dims &d, const mds_options *o) {
     return PanelChoice{false, false, nb, nb, (t == 256) ? 256 : 512, true};
   }
   if (popt == 2 && rnb == 0) return c;
-  const bool use_reg = rnb > 0 && (popt == 2 || (popt == 0 && rnb >= 16));
+  const bool use_reg =
+      rnb > 0 && (popt == 2 || (popt == 0 && rnb >= 16 && (prec != MDS_FP64 || (o && o->panel_threads != 0))));
   const bool use_coop = !use_reg && (popt == 3 || popt == 0);
   if (use_reg) {
     int nb = (o && o->nb > 0) ? o->nb : rnb;
     nb = std::min(std::max(nb, 2), rnb);
     c = {true, false, nb, std::max(nb - 1, 1), thr, false};
   } else if (use_coop) {
-    int nb = (o && o->nb > 0) ? o->nb : bk_coop_nb();
-    nb = std::min(std::max(nb, 2), bk_coop_nb());
+    const int cnb = (prec == MDS_FP64 && N > 2048) ? bk_coop_nb() : 32;
+    int nb = (o && o->nb > 0) ? o->nb : cnb;
+    nb = std::min(std::max(nb, 2), cnb);
     c = {true, true, nb, std::max(nb - 1, 1), 512, false};
-    c.tail = (popt == 0);
+    c.tail = (popt == 0 && prec != MDS_FP64);
   } else {
     int nb = (o && o->nb > 0) ? o->nb : default_nb(N);
     nb = std::min(std::max(nb, 2), kMaxNb);
@@ -393,6 +396,8 @@ void factor_launches(mds_handle *h, hipStream_t s) {
     }
   }
   const bool fp64 = h->precision == MDS_FP64 || h->force64;
+  // the cooperative panel never passes nb columns, the others end on a 2x2
+  const int wmax = h->panel_coop ? h->nb : h->nb + 1;
   for (int b = 0; b < (fp64 && !h->panel_lds ? slots : 0); ++b) {
     // register panel: slot b reads buffer b%2 and writes its L and the
     // updated trailing matrix into the other buffer
@@ -409,7 +414,7 @@ void factor_launches(mds_handle *h, hipStream_t s) {
     }
     if (h->plan[b].rows_after > 0) {
       TimedLaunch t(h, MDS_T_TRAILING);
-      launch_bk_trailing(s, N, h->nb, h->plan[b].rows_after, b, h->w.W, X, Y, Y,
+      launch_bk_trailing(s, N, h->nb, wmax, h->plan[b].rows_after, b, h->w.W, X, Y, Y,
                          h->panel_reg ? h->w.src : nullptr, h->w.fst, h->w.panel_k0);
     }
   }
@@ -522,7 +527,7 @@ void factor_launches_la(mds_handle *h, hipStream_t s) {
           launch_trailing_lp(A, h->precision, N, nb, rem, b, w.W, X32, Y32, w.M, w.src, w.fst,
                              w.panel_k0);
         else
-          launch_bk_trailing(A, N, nb, rem, b, w.W, X, Y, Y, w.src, w.fst, w.panel_k0);
+          launch_bk_trailing(A, N, nb, nb + 1, rem, b, w.W, X, Y, Y, w.src, w.fst, w.panel_k0);
       }
     }
   }
@@ -614,7 +619,7 @@ void factor_launches_mem(mds_handle *h, hipStream_t s) {
     }
     if ((long)N - (long)(b + 1) * nb > 0) {
       TimedLaunch t(h, MDS_T_TRAILING);
-      launch_bk_trailing(s, N, nb, (long)N - (long)(b + 1) * nb, b, h->w.W, h->w.M, h->w.M,
+      launch_bk_trailing(s, N, nb, nb + 1, (long)N - (long)(b + 1) * nb, b, h->w.W, h->w.M, h->w.M,
                          h->w.M, nullptr, h->w.fst, h->w.panel_k0);
     }
   }
@@ -1371,7 +1376,7 @@ int mds_create(mds_handle **out, const mds_dims *dims, const mds_options *opts, 
   if (std_prepare() != hipSuccess || bk_lds_prepare() != hipSuccess ||
       hipMemsetAsync(w.trsv, 0, std_trsv_bytes(h->N), h->stream) !=
           hipSuccess ||
-      hipMemsetAsync(w.xch, 0, 8 * 2 * (size_t)kCoopMaxP * kCoopSlotWords, h->stream) !=
+      hipMemsetAsync(w.xch, 0, kCoopXchBytes, h->stream) !=
           hipSuccess ||
       hipMemsetAsync(w.fst, 0, sizeof(FacState), h->stream) != hipSuccess ||
       hipStreamSynchronize(h->stream) != hipSuccess) {

@@ -311,9 +311,10 @@ __global__ __launch_bounds__(NT) void k_bk_panel(int N, int nb, double alpha,
 // l holds A[l%16][l/16], operand B lane l holds B[l/16][l%16], and result
 // register r of lane l holds D[l/16 + 4r][l%16].
 constexpr int TT = 64;
-static_assert(TT == kNearCols, "the near strip is one tile column");
+static_assert(TT * kNearTiles == kNearCols, "near strip");
 constexpr int TS = 36;        // panel columns staged in LDS per chunk (multiple of 4)
 constexpr int TS1 = TS + 1;   // odd row stride of the staged panels
+constexpr int TSB = 64;       // ... of the persistent form for wide panels
 constexpr int TSTAGE = TT * TS / 256;  // staged entries per thread and panel
 constexpr int kTrailingGrid = kTileGrid;  // persistent trailing update: 512 workgroups (2 per CU at 194 VGPRs)
 static_assert(TT * TS % 256 == 0, "staging");
@@ -340,8 +341,8 @@ __global__ __launch_bounds__(256) void k_bk_trailing(int N, int nb, const double
   // N is a multiple of 16); rows and columns below kend are masked
   const int a0 = kend & ~15;
   const int nt = (N - a0 + TT - 1) / TT;
-  // look-ahead's near strip (part 1): tile (blockIdx.x, 0), the multipliers
-  // staged; otherwise triangular tile index -> (ti >= tj)
+  // look-ahead's near strip (part 1): the first kNearTiles tile columns, the
+  // multipliers staged; otherwise triangular tile index -> (ti >= tj)
   const int lk0 = (part == 1) ? 0 : k0;
   const int x = blockIdx.x;
   int ti = (int)((sqrt(8.0 * (double)x + 1.0) - 1.0) * 0.5);
@@ -349,8 +350,9 @@ __global__ __launch_bounds__(256) void k_bk_trailing(int N, int nb, const double
   while (ti * (ti + 1) / 2 > x) --ti;
   int tj = x - ti * (ti + 1) / 2;
   if (part == 1) {
-    ti = x;
-    tj = 0;
+    tj = x / nt;
+    ti = x % nt;
+    if (tj >= kNearTiles || ti < tj) return;
   }
   if (ti >= nt) return;
   const int i0 = a0 + ti * TT, c0 = a0 + tj * TT;
@@ -449,11 +451,12 @@ __global__ __launch_bounds__(256) void k_bk_trailing(int N, int nb, const double
 // loads of its next tile (the entries it updates and the panel rows it
 // stages) are already in flight.  Per entry the arithmetic is the one of
 // k_bk_trailing, in the same order.
+template <int TSW>
 __device__ inline void tr_load(int i0, int c0, bool diag, int N, int kend, int lk0, int jw,
                                const double *__restrict__ W, const double *X,
                                const double *Lsrc, const int32_t *__restrict__ src,
-                               double (&xv)[2][2][4], double (&vw)[TSTAGE],
-                               double (&vl)[TSTAGE]) {
+                               double (&xv)[2][2][4], double (&vw)[TT * TSW / 256],
+                               double (&vl)[TT * TSW / 256]) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int l16 = lane & 15, l4 = lane >> 4;
   const size_t ld = (size_t)N;
@@ -485,7 +488,7 @@ __device__ inline void tr_load(int i0, int c0, bool diag, int N, int kend, int l
                           : 0.0;
       }
 #pragma unroll
-  for (int u = 0; u < TSTAGE; ++u) {
+  for (int u = 0; u < TT * TSW / 256; ++u) {
     const int e = tid + 256 * u, r = e & (TT - 1), t = e >> 6;
     const int c = c0 + r, i = i0 + r;
     vw[u] = (t < jw && c >= kend && c < N) ? W[(size_t)c + (size_t)t * ld] : 0.0;
@@ -494,7 +497,8 @@ __device__ inline void tr_load(int i0, int c0, bool diag, int N, int kend, int l
 }
 
 
-__global__ __launch_bounds__(256) void k_bk_trailing_ps(int N, int nb,
+template <int TSW>
+__global__ __launch_bounds__(256, 2) void k_bk_trailing_ps(int N, int nb,
                                                         const double *__restrict__ W,
                                                         const double *X, double *Y,
                                                         const double *Lsrc,
@@ -502,11 +506,12 @@ __global__ __launch_bounds__(256) void k_bk_trailing_ps(int N, int nb,
                                                         const FacState *__restrict__ st,
                                                         const int32_t *__restrict__ panel_k0,
                                                         int slot, int part) {
+  constexpr int TS1 = TSW + 1, TSTAGE = TT * TSW / 256;
   __shared__ double s_buf[2 * TT * TS1];
   double *s_w = s_buf, *s_l = s_buf + TT * TS1;
   if (slot >= st->npanel) return;
   const int k0 = panel_k0[slot], kend = panel_k0[slot + 1];
-  if (kend >= N || kend <= k0 || kend - k0 > nb + 1 || kend - k0 > TS) return;
+  if (kend >= N || kend <= k0 || kend - k0 > nb + 1 || kend - k0 > TSW) return;
   const int jw = kend - k0;
   // the look-ahead parts read the panel's multipliers from its staging buffer
   const int lk0 = (part == 0) ? k0 : 0;
@@ -528,7 +533,7 @@ __global__ __launch_bounds__(256) void k_bk_trailing_ps(int N, int nb,
   while (x < nslots && !part_tile(part, x, nt, xcd, ti, tj)) x += gridDim.x;
   if (x >= nslots) return;
   double xn[2][2][4], vwn[TSTAGE], vln[TSTAGE];
-  tr_load(a0 + ti * TT, a0 + tj * TT, ti == tj, N, kend, lk0, jw, W, X, Lsrc, src, xn, vwn, vln);
+  tr_load<TSW>(a0 + ti * TT, a0 + tj * TT, ti == tj, N, kend, lk0, jw, W, X, Lsrc, src, xn, vwn, vln);
   while (x < nslots) {
     const int i0 = a0 + ti * TT, c0 = a0 + tj * TT;
     const bool diag = (ti == tj);
@@ -542,7 +547,7 @@ __global__ __launch_bounds__(256) void k_bk_trailing_ps(int N, int nb,
         for (int r = 0; r < 4; ++r) xv[a][b][r] = xn[a][b][r];
     __syncthreads();  // the previous tile is done with the staging buffer
 #pragma unroll
-    for (int u = 0; u < TSTAGE; ++u) {
+    for (int u = 0; u < TT * TSW / 256; ++u) {
       const int e = tid + 256 * u, r = e & (TT - 1), t = e >> 6;
       s_w[r * TS1 + t] = vwn[u];
       s_l[r * TS1 + t] = vln[u];
@@ -553,7 +558,7 @@ __global__ __launch_bounds__(256) void k_bk_trailing_ps(int N, int nb,
     int tin = 0, tjn = 0;
     while (xnext < nslots && !part_tile(part, xnext, nt, xcd, tin, tjn)) xnext += gridDim.x;
     if (xnext < nslots)
-      tr_load(a0 + tin * TT, a0 + tjn * TT, tin == tjn, N, kend, lk0, jw, W, X, Lsrc, src, xn, vwn,
+      tr_load<TSW>(a0 + tin * TT, a0 + tjn * TT, tin == tjn, N, kend, lk0, jw, W, X, Lsrc, src, xn, vwn,
               vln);
     d4 acc[2][2];
 #pragma unroll
@@ -618,7 +623,7 @@ void launch_bk_panel(hipStream_t s, int N, int nb, double alpha, double *M, doub
   k_bk_panel<<<1, NT, 0, s>>>(N, nb, alpha, M, W, dd, ds, ipiv, blk, st, panel_k0);
 }
 
-void launch_bk_trailing(hipStream_t s, int N, int nb, long rem, int slot, const double *W,
+void launch_bk_trailing(hipStream_t s, int N, int nb, int wmax, long rem, int slot, const double *W,
                         const double *X, double *Y, const double *Lsrc, const int32_t *src,
                         const FacState *st, const int32_t *panel_k0) {
   // rem bounds the rows of the trailing matrix after slot `slot`; the
@@ -626,11 +631,12 @@ void launch_bk_trailing(hipStream_t s, int N, int nb, long rem, int slot, const 
   if (rem <= 0) return;
   const long nt = (rem + 15 + TT - 1) / TT;
   const long tiles = nt * (nt + 1) / 2;
-  if (nb + 1 <= TS) {
-    // persistent: a few workgroups per compute unit walk the tiles
-    const long grid = std::min(tiles, (long)kTrailingGrid);
-    k_bk_trailing_ps<<<(unsigned)grid, 256, 0, s>>>(N, nb, W, X, Y, Lsrc, src, st, panel_k0,
-                                                     slot, 0);
+  // persistent: a few workgroups per compute unit walk the tiles
+  const unsigned grid = (unsigned)std::min(tiles, (long)kTrailingGrid);
+  if (wmax <= TS) {
+    k_bk_trailing_ps<TS><<<grid, 256, 0, s>>>(N, nb, W, X, Y, Lsrc, src, st, panel_k0, slot, 0);
+  } else if (wmax <= TSB) {
+    k_bk_trailing_ps<TSB><<<grid, 256, 0, s>>>(N, nb, W, X, Y, Lsrc, src, st, panel_k0, slot, 0);
   } else {
     k_bk_trailing<<<(unsigned)tiles, 256, 0, s>>>(N, nb, W, X, Y, Lsrc, src, st, panel_k0, slot,
                                                   0);
@@ -640,19 +646,24 @@ void launch_bk_trailing(hipStream_t s, int N, int nb, long rem, int slot, const 
 void launch_bk_trailing_part(hipStream_t s, int N, int nb, long rem, int slot, int part, int grid,
                              const double *W, const double *X, double *Y, const double *Lsrc,
                              const int32_t *src, const FacState *st, const int32_t *panel_k0) {
-  if (rem <= 0 || nb + 1 > TS) return;
+  if (rem <= 0 || nb > TSB) return;
   const long nt = (rem + 15 + TT - 1) / TT;
-  const long tiles = (part == 1) ? nt : (nt - 1) * nt / 2;
+  const long tiles = (part == 1) ? kNearTiles * nt
+                     : (nt > kNearTiles) ? (nt - kNearTiles) * (nt - kNearTiles + 1) / 2 : 0;
   if (tiles <= 0) return;
   if (part == 1) {
     // one tile per workgroup (104 VGPRs: more workgroups per compute unit
     // than the persistent form's two)
-    k_bk_trailing<<<(unsigned)nt, 256, 0, s>>>(N, nb, W, X, Y, Lsrc, src, st, panel_k0, slot, 1);
+    k_bk_trailing<<<(unsigned)tiles, 256, 0, s>>>(N, nb, W, X, Y, Lsrc, src, st, panel_k0, slot, 1);
     return;
   }
   const long g = std::min(tiles, (long)std::max(grid, 1));
-  k_bk_trailing_ps<<<(unsigned)g, 256, 0, s>>>(N, nb, W, X, Y, Lsrc, src, st, panel_k0, slot,
-                                                part);
+  if (nb <= TS)
+    k_bk_trailing_ps<TS><<<(unsigned)g, 256, 0, s>>>(N, nb, W, X, Y, Lsrc, src, st, panel_k0, slot,
+                                                     part);
+  else
+    k_bk_trailing_ps<TSB><<<(unsigned)g, 256, 0, s>>>(N, nb, W, X, Y, Lsrc, src, st, panel_k0,
+                                                      slot, part);
 }
 
 void launch_lstage_copy(hipStream_t s, int N, long rows, int slot, const double *Lst, double *Lout,
@@ -660,7 +671,7 @@ void launch_lstage_copy(hipStream_t s, int N, long rows, int slot, const double 
   // rows: the rows at the panel's start, at most
   if (rows <= 0) return;
   const unsigned gx = (unsigned)std::min<long>((rows + 1023) / 1024, 64);
-  k_lstage_copy<<<dim3(gx, (unsigned)(TS + 1)), 256, 0, s>>>(N, Lst, Lout, st, panel_k0, slot);
+  k_lstage_copy<<<dim3(gx, (unsigned)TSB), 256, 0, s>>>(N, Lst, Lout, st, panel_k0, slot);
 }
 
 }  // namespace mds

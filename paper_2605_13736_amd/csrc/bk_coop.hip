@@ -1,26 +1,24 @@
-// Cooperative register-resident Bunch-Kaufman panel (Sec. 2.3) for orders
-// too large for one workgroup's registers: P workgroups (one per CU) each
-// keep the multipliers of their own block of rows in registers and take the
-// same pivot decisions from data exchanged once or twice per pivot.
+// Cooperative Bunch-Kaufman panel (Sec. 2.3): P workgroups (one per CU) each
+// keep the multipliers of their own 256 rows in LDS and take the same pivot
+// decisions from data they exchange.  One workgroup (P = 1, at most 256 rows
+// left) needs no exchange.
 //
-// Workgroup g of T threads owns the physical rows
-//   rho = k0 + g (T R) + t + T r,   t < T, r < R,
-// of the buffer X (the trailing matrix in logical order at the panel start).
-// Interchanges move logical positions, never data: pos[r] is the logical
-// position of an owned row, and s_map (replicated in every workgroup) maps a
-// logical position to its physical row, which addresses the un-updated
-// columns of X.  Each pivot step is the one of the single-workgroup register
-// panel, with its two workgroup-wide reductions widened to the grid:
+// Thread t of workgroup g owns the physical row rho = k0 + 256 g + t of the
+// buffer X (the trailing matrix in logical order at the panel start).
+// Interchanges move logical positions, never data: pos is the logical
+// position of the owned row, and s_map (replicated in every workgroup) maps
+// the panel's own positions k0 .. k0 + 65 to physical rows, which address the
+// un-updated columns of X.  Pivots come in speculative blocks (below); a
+// pivot that fails the first test is taken by a full step:
 //
-//   X1 (every step): each workgroup publishes its largest off-diagonal
-//      candidate of the updated column k (magnitude, position, signed value,
-//      L row) and, when it owns them, the rows at positions k, k+1, k+2
-//      (updated column-k value and L row).  Every workgroup reads all of it in
-//      one round trip and derives colmax, imax, a_kk, the W row of imax and,
-//      later, the L row of the next pivot.
-//   X3 (when the first test fails): per-wave partial maxima of the updated
-//      column imax, a_ii from its owner, and the column-imax values at
-//      positions k, k+1, k+2.
+//   X1: each workgroup publishes its largest off-diagonal candidate of the
+//      updated column k (magnitude, position, physical row, signed value, L
+//      row), the owner of position k also a_kk.  Every workgroup reads all
+//      the headers and derives colmax, imax and a_kk, then, when the first
+//      test fails, the winner's L row.
+//   X3 (when the first test fails): every workgroup's maximum of the updated
+//      column imax, and a_ii from its owner.
+//   XB: the window rows (L rows of the block's positions) from their owners.
 //
 // Exchange words are 64 bits: 32 data bits under a 32-bit tag that names the
 // panel launch and the exchange, written and read with relaxed agent-scope
@@ -39,13 +37,9 @@
 namespace mds {
 namespace {
 
-using panel::amax_combine;
-using panel::keep_branch;
 using panel::lds_wave_sync;
 using panel::sym_at;
-using panel::w_lane;
 
-constexpr int kCoopMaxN = 20480;  // LDS map of logical positions
 constexpr unsigned long long kCoopWaitTicks = 1ull << 26;  // ~0.67 s of the 100 MHz clock
 
 __device__ inline void put_u32(uint64_t *p, uint32_t v, uint32_t tag) {
@@ -71,90 +65,125 @@ __device__ inline double as_f64(uint64_t hi, uint64_t lo) {
 // type TX (in FP32 the result is rounded to FP32, as the trailing update
 // stores it).  The row's own L row (rho > c) or W row (rho <= c) meets the
 // candidate c's W or L row, which the caller put in LDS (pw, pl: zero past
-// jw, 40 entries).  Two rows per call (rows with on = false give 0), their
-// loads in flight together.  Not inlined: its loads then take registers only
-// while it runs, not in the pivot loop.
+// jw).  Not inlined: its loads then take registers only while it runs.
 template <typename TX>
-__device__ __attribute__((noinline)) double2 pending_entries(const TX *pX, const int32_t *psrc,
-                                                             const double *pW, const double *pL,
-                                                             int rho0, int rho1, bool on0, bool on1,
-                                                             int c, int jw, int ld,
-                                                             const double *pw, const double *pl) {
-  const int rho[2] = {rho0, rho1};
-  const bool on[2] = {on0, on1};
-  double x[2], acc[2];
-  const double *row[2], *bc[2];
-#pragma unroll
-  for (int r = 0; r < 2; ++r) {
-    const int hi = max(rho[r], c), lo = min(rho[r], c);
-    const int a = on[r] ? psrc[hi] : 0, b = on[r] ? psrc[lo] : 0;
-    const int q = (a >= b) ? a + b * ld : b + a * ld;
-    x[r] = on[r] ? (double)pX[q] : 0.0;
-    row[r] = (rho[r] > c) ? pL : pW;
-    bc[r] = (rho[r] > c) ? pw : pl;
-    acc[r] = 0.0;
-  }
+__device__ __attribute__((noinline)) double pending_entry(const TX *pX, const int32_t *psrc,
+                                                          const double *pW, const double *pL,
+                                                          int rho, int c, int jw, int ld,
+                                                          const double *pw, const double *pl) {
+  const int hi = max(rho, c), lo = min(rho, c);
+  const double x = (double)sym_at(pX, (int)psrc[hi], (int)psrc[lo], ld);
+  const double *row = (rho > c) ? pL : pW, *bc = (rho > c) ? pw : pl;
+  double acc = 0.0;
   for (int t0 = 0; t0 < jw; t0 += 8) {
-    double v[2][8];
+    double v[8];
 #pragma unroll
-    for (int r = 0; r < 2; ++r)
+    for (int u = 0; u < 8; ++u) v[u] = (t0 + u < jw) ? row[rho + (t0 + u) * ld] : 0.0;
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[r][u] = (on[r] && t0 + u < jw) ? row[r][rho[r] + (t0 + u) * ld] : 0.0;
-#pragma unroll
-    for (int r = 0; r < 2; ++r)
-#pragma unroll
-      for (int u = 0; u < 8; ++u) acc[r] = fma(v[r][u], bc[r][t0 + u], acc[r]);
+    for (int u = 0; u < 8; ++u) acc = fma(v[u], bc[t0 + u], acc);
   }
-  return double2{(double)(TX)(x[0] - acc[0]), (double)(TX)(x[1] - acc[1])};
+  return (double)(TX)(x - acc);
 }
 
-template <int T, int R, int NB, int PMAX, typename TX, bool LA>
-__global__ __launch_bounds__(T) void k_bk_panel_coop(int N, int nb, double alpha, int Pmax,
-                                                     const TX *__restrict__ X,
-                                                     const PanelPrev pv,
-                                                     double *__restrict__ Lout,
-                                                     int32_t *__restrict__ src_out,
-                                                     double *__restrict__ W,
-                                                     double *__restrict__ dd,
-                                                     double *__restrict__ ds,
-                                                     int32_t *__restrict__ ipiv,
-                                                     int32_t *__restrict__ blk, FacState *st,
-                                                     int32_t *__restrict__ panel_k0,
-                                                     uint64_t *__restrict__ xch, int lstage) {
-  constexpr int NWV = T / 64;
-  constexpr int RW = T * R;
-  constexpr int NR = NB + 1;          // row record: value + L row
-  constexpr int PREC = 2 * NR;        // words of a row record
-  constexpr int X1_CAND = 3;          // [0] position, [1,2] magnitude, then the row record
-  constexpr int X1_POS = X1_CAND + PREC;
-  constexpr int X3_AII = 2 * NWV;     // after the per-wave partial maxima
-  constexpr int X3_POS = X3_AII + 2;
-  // waves that read the first exchange: all of them on the wide grids
-  constexpr int XW = (PMAX >= 12) ? NWV : 1;
-  constexpr int U1 = ((PMAX + 3) * NR + 64 * XW - 1) / (64 * XW);  // row-record pairs per lane
-  constexpr int U3 = (PMAX * NWV + 63) / 64;       // partial maxima per lane
-  static_assert(NB % 8 == 0 && NR <= 64 && NWV <= 64, "tile");
-  static_assert(X1_POS + 3 * PREC <= kCoopSlotWords && X3_POS + 6 <= kCoopSlotWords, "slot");
+// Speculative blocks.  Most pivots of a KKT system pass Bunch-Kaufman's first
+// test, |a_kk| >= alpha colmax, which neither interchanges nor needs the
+// location of the maximum; and it holds exactly when |d_q| >= alpha |w_iq| for
+// every row i below.  So a block of up to 16 columns is factored as if every
+// pivot passed, each row checks its own entries, and one exchange of the first
+// failing column per workgroup decides how many columns stand:
+//
+//   1. block columns  A = X(:, block) - L W(block, :)'           (FP64 MFMA)
+//   2. the 16 x 16 diagonal block's L D L', in every wave by itself from X and
+//      the 16 window rows of L (LDS), four columns at a time
+//   3. every row's forward substitution, four columns at a time, and the rank-4
+//      update of the columns right of them (FP64 MFMA)
+//   4. exchange XB: first failing column of each workgroup, and, from their
+//      owners, the L rows of the next 16 positions
+//
+// The columns before the first failure are committed and the failing pivot is
+// taken by a full pivot step (X1, X3 above), after which the rest of the block is
+// tried again.  Pivots, D and L are those of the one-column-at-a-time
+// elimination up to the order of the sums.  A matrix whose blocks keep
+// failing at once backs off to full steps (cool).
+//
+// Layout: 256 threads own 256 rows; the panel's multipliers live in LDS, column
+// t at s_L[t CLD ..], row = thread (a full pivot step reads its own row; an MFMA
+// operand reads 16 consecutive rows of 4 columns; CLD = 17 mod 32 keeps both and
+// the gather of one row over t free of bank conflicts).  Registers could hold
+// 32 columns of 2 rows per thread (512 threads, the former form), LDS holds 64
+// of 256 rows, and needs no static column index.  Columns t >= j are
+// never read (operands are masked), so nothing is cleared.
+//
+// What bounds it: latency.  A block costs one exchange (~1.7 us), the diagonal
+// block's chain of 16 divisions and the loads of X.
+constexpr int CT = 256;        // threads = rows of a workgroup
+constexpr int CNB = 64;        // most columns of a panel
+constexpr int CB = 16;         // columns of a speculative block
+constexpr int CLD = CT + 17;   // LDS stride of a column of multipliers
+constexpr int CWL = CNB + 2;   // stride of a window row
+constexpr int CPW = 72;        // look-ahead: the candidate's W / L row, padded
+static_assert(CNB <= kMaxNb && CNB % CB == 0 && CLD % 32 == 17, "tile");
+static_assert(8 + 2 * CNB <= kCoopSlotWords && CB * CNB * 2 <= kCoopRowWords, "exchange slot");
 
-  __shared__ double s_wk[NB], s_wi[NB], s_cA[NB], s_cB[NB], s_cC[NB], s_nrow[NB];
-  __shared__ double s_acur[R * T], s_wkc[R * T], s_wic[R * T];
-  __shared__ int s_map[kCoopMaxN];
-  __shared__ double s_cv[NWV];
-  __shared__ int s_ci[NWV];
-  __shared__ double s_crow[NWV][NR];  // wave candidates: signed value + L row
-  __shared__ double s_prow[3][NR];    // owned rows at positions k, k+1, k+2
-  __shared__ double s_xb[PMAX + 3][NR];  // X1: candidate rows, then position rows
-  __shared__ double s_xwic[3];
-  __shared__ double s_colmax, s_rowmax, s_aii;
-  __shared__ int s_imax, s_gw, s_k0, s_abort, s_force;
-  __shared__ int s_xok[2][NWV];  // X1 poll: bit 0 all tags seen, bit 1 wait expired
+typedef double d4 __attribute__((ext_vector_type(4)));
+
+// o[q] = x of lane (l & 15) + 16 q
+__device__ inline void rows4(double x, double (&o)[4]) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+  unsigned r[2][4];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const unsigned v = (unsigned)(b >> (32 * h));
+    // [r0 r1 r0 r1], [r2 r3 r2 r3]; then one row of each pair everywhere
+    const auto a = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    const auto lo = __builtin_amdgcn_permlane16_swap(a[0], a[0], false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(a[1], a[1], false, false);
+    r[h][0] = lo[0];
+    r[h][1] = lo[1];
+    r[h][2] = hi[0];
+    r[h][3] = hi[1];
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    o[q] = __longlong_as_double((long long)(((unsigned long long)r[1][q] << 32) | r[0][q]));
+}
+
+__device__ inline double sel4(int q, double a, double b, double c, double d) {
+  return (q < 2) ? (q == 0 ? a : b) : (q == 2 ? c : d);
+}
+
+template <typename TX, bool LA>
+__global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alpha,
+                                                      const TX *__restrict__ X, const PanelPrev pv,
+                                                      double *__restrict__ Lout,
+                                                      int32_t *__restrict__ src_out,
+                                                      double *__restrict__ W,
+                                                      double *__restrict__ dd,
+                                                      double *__restrict__ ds,
+                                                      int32_t *__restrict__ ipiv,
+                                                      int32_t *__restrict__ blk, FacState *st,
+                                                      int32_t *__restrict__ panel_k0,
+                                                      uint64_t *__restrict__ xch, int lstage) {
+  constexpr int NWV = CT / 64;
+  __shared__ double s_L[CNB * CLD];
+  __shared__ double s_lw[CB * CWL];  // L rows of the block's positions
+  __shared__ double s_cA[CNB], s_cB[CNB], s_cC[CNB];
+  __shared__ double s_wk[CNB], s_wi[CNB], s_irow[CNB];
+  __shared__ double s_pdd[CNB], s_pds[CNB], s_dn[CB];
+  __shared__ int s_pip[CNB], s_pbk[CNB];
+  __shared__ int s_map[CNB + 2];  // physical row of positions k0 .. k0 + CNB + 1
+  __shared__ int s_pos[CT];
+  __shared__ double s_hv[kCoopMaxP], s_hx[kCoopMaxP];
+  __shared__ int s_hi[kCoopMaxP], s_hp[kCoopMaxP];
+  __shared__ double s_cv[NWV], s_akk, s_aii;
+  __shared__ int s_ci[NWV], s_cs[NWV], s_fail[NWV];
+  __shared__ int s_k0, s_abort, s_force;
   __shared__ uint32_t s_tag0;
-  __shared__ double s_pdd[NB], s_pds[NB];  // the panel's D and pivot records (written at its end)
-  __shared__ int s_pip[NB], s_pbk[NB];
-  __shared__ double s_pw[40], s_pl[40];  // look-ahead: W and L rows of the candidate
-  __shared__ int s_jwp, s_kprev;         // ... and the previous panel's width and start
+  __shared__ double s_pw[CPW], s_pl[CPW];  // look-ahead: W and L rows of the candidate
+  __shared__ int s_jwp, s_kprev;
 
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const int l16 = lane & 15, l4 = lane >> 4;
   const int g = blockIdx.x;
   if (tid == 0) {
     s_k0 = st->k;
@@ -164,14 +193,7 @@ __global__ __launch_bounds__(T) void k_bk_panel_coop(int N, int nb, double alpha
     const int np = st->npanel;
     const bool pvon = pv.X != nullptr || pv.Xf != nullptr;
     s_kprev = (pvon && np > 0) ? panel_k0[np - 1] : 0;
-    s_jwp = (pvon && np > 0) ? min(s_k0 - s_kprev, NB + 1) : 0;
-  }
-  if (tid < NB) {
-    s_wk[tid] = 0.0;
-    s_wi[tid] = 0.0;
-    s_cA[tid] = 0.0;
-    s_cB[tid] = 0.0;
-    s_cC[tid] = 0.0;
+    s_jwp = (pvon && np > 0) ? min(s_k0 - s_kprev, CNB + 1) : 0;
   }
   __syncthreads();
   const int k0 = s_k0;
@@ -181,413 +203,493 @@ __global__ __launch_bounds__(T) void k_bk_panel_coop(int N, int nb, double alpha
     if (tid == 0) __hip_atomic_store(&st->xerr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return;
   }
-  const int P = min(Pmax, (N - k0 + RW - 1) / RW);
+  const int P = min((int)gridDim.x, (N - k0 + CT - 1) / CT);
   if (g >= P) return;
   const int ld = N;  // N <= 20480: every offset fits in 32 bits
-  const int gbase = k0 + g * RW;
+  const int gbase = k0 + g * CT;
+  const int rho = gbase + tid;  // this thread's physical row
   // look-ahead: columns below kstrip are up to date in X; the previous
   // panel factored jwp columns
   const int kstrip = (k0 & pv.amask) + kNearCols, jwp = s_jwp;
   const bool la = LA && (pv.X != nullptr || pv.Xf != nullptr) && jwp > 0;
-  const uint32_t tagb = ((s_tag0 % 0xffffffu) + 1u) << 8;
+  const uint32_t tagb = ((s_tag0 % 0x7fffffu) + 1u) << 9;
   auto slot = [&](int par, int wg) { return xch + (size_t)(par * kCoopMaxP + wg) * kCoopSlotWords; };
-  auto owner = [&](int phys) { return (phys - k0) / RW; };
+  auto xrow = [&](int par) {
+    return xch + (size_t)2 * kCoopMaxP * kCoopSlotWords + (size_t)par * kCoopRowWords;
+  };
+  auto owner = [&](int phys) { return (phys - k0) / CT; };
 
-  double Lr[R][NB];
-  // prefetched un-updated column values, kept in the storage type and
-  // widened where used: a widening next to a conditional load would make the
-  // compiler wait for the load there
-  TX pre1[R], pre2[R];
-  int pos[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-#pragma unroll
-    for (int t = 0; t < NB; ++t) Lr[r][t] = 0.0;
-    const int rho = gbase + tid + T * r;
-    pos[r] = (rho < N) ? rho : -1;
-    s_acur[r * T + tid] = (rho < N) ? (double)X[rho + k0 * ld] : 0.0;
-    pre1[r] = pre2[r] = (TX)0;
-  }
-  for (int i = tid; i < N - k0; i += T) s_map[i] = k0 + i;
+  int pos = (rho < N) ? rho : -1;  // logical position of this thread's row
+  s_pos[tid] = pos;
+  if (tid < CNB + 2) s_map[tid] = k0 + tid;
   __syncthreads();
 
   int k = k0, j = 0, c = 0;
-  int c_pos = 0, c_zero = 0, c_neg = 0, c_2x2 = 0, first_zero = 0, nsteps = 0;
-  int pj = -1;
-  bool p2 = false;
-  double pA0 = 0.0, pB0 = 0.0, pA1 = 0.0;
+  int c_pos = 0, c_zero = 0, c_neg = 0, c_2x2 = 0, first_zero = 0, nsteps = 0, nsec = 0;
+  bool any2 = false;      // a 2x2 pivot in this panel
+  int slow = 0, cool = 0; // full steps due; back-off after failing blocks
 
-  while (j < nb - 1 && k < N) {
-    ++nsteps;
-    if (tid == 0 && pj >= 0) {
-      s_cA[pj] = pA0;
-      s_cB[pj] = pB0;
-      if (p2) {
-        s_cA[pj + 1] = pA1;
-        s_cC[pj + 1] = pB0;
-      }
+  // un-updated entries of the block at (jj, its columns [jj % CB, ce)), in the
+  // MFMA result layout: register r of lane l holds column l/16 + 4 r of row
+  // l % 16 of each 16-row group; dacc: the diagonal block's lower triangle
+  d4 acc[4], dacc;
+  bool loaded = false;
+  auto block_cols = [&](int jj) { return min(min(CB - (jj & (CB - 1)), nb - jj), N - (k0 + jj)); };
+  auto load_block = [&](int jj) {
+    const int jb = jj & ~(CB - 1), r0 = jj - jb, ce = r0 + block_cols(jj);
+    int pc[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int cc = l4 + 4 * r;
+      pc[r] = (cc >= r0 && cc < ce) ? s_map[jb + cc] : -1;
     }
-    // ---- updated column k, this workgroup's candidates ----------------------
-    double a[R];
+    const int pi = (l16 >= r0 && l16 < ce) ? s_map[jb + l16] : -1;
 #pragma unroll
-    for (int r = 0; r < R; ++r) a[r] = s_acur[r * T + tid];
+    for (int r = 0; r < 4; ++r) {
+      const bool on = pi >= 0 && pc[r] >= 0 && l16 >= l4 + 4 * r;
+      dacc[r] = on ? (double)sym_at(X, pi, pc[r], ld) : 0.0;
+    }
 #pragma unroll
-    for (int t0 = 0; t0 < NB; t0 += 8) {
-      if (t0 < j) {
-        keep_branch();
-        // columns t >= j: L = 0 and the W entries are zeros too (a W row
-        // comes from an L row, which ends before column j), so their
-        // products add an exact zero (no per-column branch or select)
-        double wv[8];
+    for (int q = 0; q < 4; ++q) {
+      const int row = gbase + 64 * wid + 16 * q + l16;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) wv[u] = s_wk[t0 + u];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-#pragma unroll
-          for (int r = 0; r < R; ++r) a[r] = fma(-Lr[r][t0 + u], wv[u], a[r]);
+      for (int r = 0; r < 4; ++r)
+        acc[q][r] = (pc[r] >= 0 && row < N) ? (double)sym_at(X, row, pc[r], ld) : 0.0;
+    }
+  };
+  // W = L D of window row q at column t < j
+  auto wrow = [&](const double *lr, int t) {
+    double v = lr[t] * s_cA[t];
+    if (any2) {
+      if (t + 1 < j) v = v + lr[t + 1] * s_cB[t];
+      if (t >= 1) v = v + lr[t - 1] * s_cC[t];
+    }
+    return v;
+  };
+  auto expire = [&]() {
+    __hip_atomic_store(&st->xerr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    s_abort = 1;
+  };
+
+  // Exchange XB: fl of every workgroup (their minimum is returned) and, when
+  // rows, the first jv entries of the L rows of positions k0 + jn + (0..15),
+  // which replace the window rows if the minimum is at least need.  Every
+  // thread polls its own words.  The caller's LDS writes need no barrier before.
+  auto xb = [&](int fl, bool rows, int jn, int jv, int need, int jload) -> int {
+    __syncthreads();
+    if (P == 1) {
+      if (jload >= 0) load_block(jload);
+      if (rows && fl >= need) {
+        for (int e = tid; e < CB * CNB; e += CT) {
+          const int q = e / CNB, t = e % CNB;
+          if (t < jv && k0 + jn + q < N) s_lw[q * CWL + t] = s_L[t * CLD + s_map[jn + q] - gbase];
         }
       }
+      __syncthreads();
+      return fl;
     }
-    // ---- prefetch the un-updated column k+1 (needed at the end of the step;
-    //      issued after the column update's LDS reads so that no wait for
-    //      older memory operations ahead of them includes it) ----------------
-    {
-      const int sc1 = (k + 1 < N) ? s_map[k + 1 - k0] : 0;
+    const int par = c & 1;
+    const uint32_t tag = tagb + (uint32_t)c;
+    ++c;
+    constexpr int U = CB * CNB / CT;
+    uint64_t *xr = xrow(par);
+    if (tid == 0) put_u32(slot(par, g), (uint32_t)fl, tag);
+    bool on[U];
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int rho = gbase + tid + T * r;
-        if (pos[r] >= k && k + 1 < N) pre1[r] = sym_at(X, rho, sc1, ld);
+    for (int u = 0; u < U; ++u) {
+      const int e = tid + CT * u, q = e / CNB, t = e % CNB;
+      on[u] = rows && t < jv && k0 + jn + q < N;
+      const int ph = on[u] ? s_map[jn + q] : -1;
+      if (on[u] && owner(ph) == g) put_f64(xr + 2 * e, s_L[t * CLD + ph - gbase], tag);
+    }
+    if (jload >= 0) load_block(jload);
+    const bool hon = tid < P;
+    const uint64_t *hp = slot(par, hon ? tid : g);
+    uint64_t h0, whi[U], wlo[U];
+    const uint64_t t0 = wall_clock64();
+    for (;;) {
+      h0 = get_w(hp);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const uint64_t *wp = on[u] ? xr + 2 * (tid + CT * u) : hp;
+        whi[u] = get_w(wp);
+        wlo[u] = get_w(on[u] ? wp + 1 : wp);
+      }
+      bool ok = (!hon) | tag_ok(h0, tag);
+#pragma unroll
+      for (int u = 0; u < U; ++u) ok = ok & ((!on[u]) | (tag_ok(whi[u], tag) & tag_ok(wlo[u], tag)));
+      if (__ballot(!ok) == 0) break;
+      if (wall_clock64() - t0 > kCoopWaitTicks) {
+        expire();
+        break;
       }
     }
-    double bv = -1.0;
-    int bi = INT_MAX, br = -1;
+    if (hon) s_hi[tid] = (int)(uint32_t)h0;
+    __syncthreads();
+    if (s_abort) return -1;
+    int m = CB;
+    if (lane < P) m = min(m, s_hi[lane]);
+    if (lane + 64 < P) m = min(m, s_hi[lane + 64]);
+    m = wave::imin(m);
+    if (rows && m >= need) {
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      if (pos[r] >= k) {
-        s_wkc[r * T + tid] = a[r];
-        if (pos[r] != k) {
-          const double v = fabs(a[r]);
-          if (v > bv || (v == bv && pos[r] < bi)) {
-            bv = v;
-            bi = pos[r];
-            br = r;
+      for (int u = 0; u < U; ++u) {
+        const int e = tid + CT * u;
+        if (on[u]) s_lw[(e / CNB) * CWL + e % CNB] = as_f64(whi[u], wlo[u]);
+      }
+    }
+    __syncthreads();
+    return m;
+  };
+
+  while (j < nb && k < N) {
+    if (slow == 0) {
+      // ---- speculative block ---------------------------------------------------
+      const int jb = j & ~(CB - 1), r0 = j - jb, s = block_cols(j), ce = r0 + s;
+      if (!loaded) load_block(j);
+      loaded = false;
+      {
+        const bool wc = l16 >= r0 && l16 < ce;
+        for (int kk = 0; 4 * kk < j; ++kk) {
+          const int t = 4 * kk + l4;
+          const bool on = t < j;
+          const double aw = (on && wc) ? -wrow(s_lw + l16 * CWL, t) : 0.0;
+          const double dl = (on && wc) ? s_lw[l16 * CWL + t] : 0.0;
+          dacc = __builtin_amdgcn_mfma_f64_16x16x4f64(aw, dl, dacc, 0, 0, 0);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const double bl = on ? s_L[t * CLD + 64 * wid + 16 * q + l16] : 0.0;
+            acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(aw, bl, acc[q], 0, 0, 0);
           }
         }
-        const int po = pos[r] - k;
-        if (po <= 2) {
-          keep_branch();
-          s_prow[po][0] = a[r];
+      }
+      int pg[4];
 #pragma unroll
-          for (int t = 0; t < NB; ++t) s_prow[po][1 + t] = Lr[r][t];
+      for (int q = 0; q < 4; ++q) pg[q] = s_pos[64 * wid + 16 * q + l16];
+      int ff = ce;  // first failing column of this wave
+      double ldg[4], dow[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        ldg[u] = dow[u] = 0.0;
+        if (4 * u + 3 >= r0 && 4 * u < ce && ff == ce) {
+          // columns 4u + q inside the block; the 4 x 4 pivot block (row p,
+          // column q at lane 4u + p + 16 q)
+          bool on[4];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) on[q] = 4 * u + q >= r0 && 4 * u + q < ce;
+          const double m00 = wave::lane_read(dacc[u], 4 * u);
+          const double m10 = wave::lane_read(dacc[u], 4 * u + 1);
+          const double m20 = wave::lane_read(dacc[u], 4 * u + 2);
+          const double m30 = wave::lane_read(dacc[u], 4 * u + 3);
+          double m11 = wave::lane_read(dacc[u], 4 * u + 17);
+          double m21 = wave::lane_read(dacc[u], 4 * u + 18);
+          double m31 = wave::lane_read(dacc[u], 4 * u + 19);
+          double m22 = wave::lane_read(dacc[u], 4 * u + 34);
+          double m32 = wave::lane_read(dacc[u], 4 * u + 35);
+          double m33 = wave::lane_read(dacc[u], 4 * u + 51);
+          const double rd0 = on[0] ? 1.0 / m00 : 0.0;
+          const double l10 = m10 * rd0, l20 = m20 * rd0, l30 = m30 * rd0;
+          const double w10 = l10 * m00, w20 = l20 * m00, w30 = l30 * m00;
+          m11 = fma(-l10, w10, m11);
+          m21 = fma(-l20, w10, m21);
+          m31 = fma(-l30, w10, m31);
+          m22 = fma(-l20, w20, m22);
+          m32 = fma(-l30, w20, m32);
+          m33 = fma(-l30, w30, m33);
+          const double rd1 = on[1] ? 1.0 / m11 : 0.0;
+          const double l21 = m21 * rd1, l31 = m31 * rd1;
+          const double w21 = l21 * m11, w31 = l31 * m11;
+          m22 = fma(-l21, w21, m22);
+          m32 = fma(-l31, w21, m32);
+          m33 = fma(-l31, w31, m33);
+          const double rd2 = on[2] ? 1.0 / m22 : 0.0;
+          const double l32 = m32 * rd2, w32 = l32 * m22;
+          m33 = fma(-l32, w32, m33);
+          const double rd3 = on[3] ? 1.0 / m33 : 0.0;
+          const double down = sel4(l4, m00, m11, m22, m33);
+          const bool onw = 4 * u + l4 >= r0 && 4 * u + l4 < ce;
+          // forward substitution of one row over the four columns: its
+          // updated value and multiplier in this lane's column
+          auto solve4 = [&](double x, double &wo, double &lo) {
+            double o[4];
+            rows4(x, o);
+            const double l0 = o[0] * rd0;
+            const double x1 = fma(-l0, w10, o[1]);
+            const double l1 = x1 * rd1;
+            const double x2 = fma(-l1, w21, fma(-l0, w20, o[2]));
+            const double l2 = x2 * rd2;
+            const double x3 = fma(-l2, w32, fma(-l1, w31, fma(-l0, w30, o[3])));
+            const double l3 = x3 * rd3;
+            wo = sel4(l4, o[0], x1, x2, x3);
+            lo = sel4(l4, l0, l1, l2, l3);
+          };
+          double wo, lo;
+          solve4(dacc[u], wo, lo);
+          lo = (l16 > 4 * u + l4 && l16 < ce && onw) ? lo : 0.0;
+          ldg[u] = lo;
+          dow[u] = down;
+          const double aw = -(lo * (onw ? down : 0.0));
+          const bool more = 4 * u + 4 < ce;
+          if (more) dacc = __builtin_amdgcn_mfma_f64_16x16x4f64(aw, lo, dacc, 0, 0, 0);
+          // every active row below a column: |d| >= alpha |w| (false for a NaN)
+          const double dabs = fabs(down);
+          unsigned long long bad = __ballot(onw && !(dabs > 0.0));
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            double wr, lr;
+            solve4(acc[q][u], wr, lr);
+            bad |= __ballot(onw && pg[q] > k0 + jb + 4 * u + l4 && !(dabs >= alpha * fabs(wr)));
+            if (onw) s_L[(jb + 4 * u + l4) * CLD + 64 * wid + 16 * q + l16] = lr;
+            if (more)
+              acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(aw, onw ? lr : 0.0, acc[q], 0, 0, 0);
+          }
+          if (bad != 0) {
+            const int lo16 = (bad & 0xffffull) ? 0 : (bad & 0xffff0000ull) ? 1
+                             : (bad & 0xffff00000000ull) ? 2 : 3;
+            ff = 4 * u + lo16;
+          }
         }
       }
+      if (lane == 0) s_fail[wid] = ff;
+      __syncthreads();
+      int fl = ce;
+#pragma unroll
+      for (int w = 0; w < NWV; ++w) fl = min(fl, s_fail[w]);
+      if (wid == 0) {
+        // the diagonal block's L rows and D (columns before this wave's
+        // first failure; only committed columns are read)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int cc = 4 * u + l4;
+          if (cc >= r0 && cc < ce) {
+            if (l16 > cc) s_lw[l16 * CWL + jb + cc] = ldg[u];
+            if (l16 == 0) s_dn[cc] = dow[u];
+          }
+        }
+      }
+      const bool next = ce == CB && jb + CB < nb && k + s < N;
+      const int m = xb(fl, next, jb + CB, jb + CB, CB, next ? jb + CB : -1);
+      if (m < 0) return;
+      const int a = m - r0;
+      loaded = next && m == CB;
+      if (wid == 0) {
+        double d = 0.0;
+        if (lane < a) {
+          d = s_dn[r0 + lane];
+          const int t = j + lane;
+          s_cA[t] = d;
+          s_cB[t] = s_cC[t] = 0.0;
+          s_pdd[t] = d;
+          s_pds[t] = 0.0;
+          s_pip[t] = k + lane + 1;
+          s_pbk[t] = 1;
+        }
+        c_pos += __popcll(__ballot(lane < a && d > 0.0));
+        c_neg += __popcll(__ballot(lane < a && d < 0.0));
+      }
+      j += a;
+      k += a;
+      nsteps += a;
+      if (a < s) {
+        cool = (a == 0) ? min(2 * cool + 1, 15) : 0;
+        slow = 1 + (cool >> 1);
+      } else {
+        cool = 0;
+      }
+      __syncthreads();
+      continue;
     }
-    const int mybi = bi;
-    wave::amax(bv, bi);
+    // ---- full pivot step ---------------------------------------------------------
+    if (j >= nb - 1) break;  // no room for a 2x2
+    --slow;
+    ++nsteps;
+    double x = (pos >= k) ? (double)sym_at(X, rho, s_map[j], ld) : 0.0;
+    if (wid == 0) s_wk[lane] = (lane < j) ? wrow(s_lw + (j & (CB - 1)) * CWL, lane) : 0.0;
+    __syncthreads();
+#pragma unroll 4
+    for (int t = 0; t < j; ++t) x = fma(-s_L[t * CLD + tid], s_wk[t], x);
+    double bv = -1.0;
+    int bi = INT_MAX, bs = tid;
+    if (pos > k) {
+      bv = fabs(x);
+      bi = pos;
+    }
+    wave::amax(bv, bi, bs);
     if (lane == 0) {
       s_cv[wid] = bv;
       s_ci[wid] = bi;
+      s_cs[wid] = bs;
     }
-    if (mybi != INT_MAX && mybi == bi) {
-      keep_branch();
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        if (br == r) {
-          keep_branch();
-          s_crow[wid][0] = a[r];
-#pragma unroll
-          for (int t = 0; t < NB; ++t) s_crow[wid][1 + t] = Lr[r][t];
-        }
-      }
-    }
+    if (pos == k) s_akk = x;
     __syncthreads();
-
-    // ---- X1: publish (wave 0), then every wave reads its share ----------------
-    const int par = c & 1;
-    const uint32_t tag = tagb + (uint32_t)c;
-    // owners of the rows at positions k, k+1, k+2 (-1: past N)
-    const int o0 = owner(s_map[k - k0]);
-    const int o1 = (k + 1 < N) ? owner(s_map[k + 1 - k0]) : -1;
-    const int o2 = (k + 2 < N) ? owner(s_map[k + 2 - k0]) : -1;
-    if (wid == 0) {
-      double cv = -1.0;
-      int ci = INT_MAX, cw = 0;
-      if (lane < NWV) {
-        cv = s_cv[lane];
-        ci = s_ci[lane];
-        cw = lane;
-      }
-      wave::amax(cv, ci, cw);  // every lane: lanes <= NB publish the winner's row
+    bv = s_cv[0];
+    bi = s_ci[0];
+    bs = s_cs[0];
+#pragma unroll
+    for (int w = 1; w < NWV; ++w) wave::amax3(bv, bi, bs, s_cv[w], s_ci[w], s_cs[w]);
+    double colmax = bv, akk, wki = 0.0;
+    int imax = bi, iphys = gbase + bs, gw = 0;
+    if (P == 1) {
+      if (tid == bs) s_hx[0] = x;
+      if (tid < j) s_irow[tid] = s_L[tid * CLD + bs];
+      __syncthreads();
+      akk = s_akk;
+      wki = s_hx[0];
+    } else {
+      // ---- X1 -------------------------------------------------------------------
+      const int par = c & 1;
+      const uint32_t tag = tagb + (uint32_t)c;
+      ++c;
       uint64_t *mine = slot(par, g);
-      if (lane == 0) {
-        put_u32(mine, (uint32_t)ci, tag);
-        put_f64(mine + 1, cv, tag);
+      if (tid == bs) {
+        put_u32(mine, (uint32_t)bi, tag);
+        put_f64(mine + 1, bv, tag);
+        put_u32(mine + 3, (uint32_t)rho, tag);
+        put_f64(mine + 4, x, tag);
       }
-      if (lane < NR) put_f64(mine + X1_CAND + 2 * lane, s_crow[cw][lane], tag);
-      if (lane < NR) {
-        if (o0 == g) put_f64(mine + X1_POS + 2 * lane, s_prow[0][lane], tag);
-        if (o1 == g) put_f64(mine + X1_POS + PREC + 2 * lane, s_prow[1][lane], tag);
-        if (o2 == g) put_f64(mine + X1_POS + 2 * PREC + 2 * lane, s_prow[2][lane], tag);
-      }
-    }
-    // One round trip reads all: the headers in wave 0's lanes < P, the row
-    // records spread over the XW reading waves (pair p = lane + 64 (wid + XW
-    // u): record p / NR, word p % NR).  Every lane issues every load (a lane
-    // with nothing to read loads its own slot's first word and ignores it),
-    // so the loads leave back to back and one wait covers them.  With one
-    // reading wave its ballot decides; with all waves reading (the wide
-    // grids, where one wave's U1 pairs next to its register tile would spill
-    // to scratch) the waves agree through LDS after each poll
-    // (double-buffered by poll parity): done when every wave saw all its
-    // tags, time-out when any wave's wait expired.
-    if (wid < XW) {
-      const uint64_t *hp = slot(par, (wid == 0 && lane < P) ? lane : g);
-      const uint64_t *ap[U1];
-      bool need[U1];
-#pragma unroll
-      for (int u = 0; u < U1; ++u) {
-        const int p = lane + 64 * (wid + XW * u), rec = p / NR, w = p % NR;
-        const int ip = rec - P, op = (ip == 0) ? o0 : (ip == 1) ? o1 : o2;
-        need[u] = rec < P || (ip < 3 && op >= 0);
-        ap[u] = (rec < P) ? slot(par, rec) + X1_CAND + 2 * w
-                : (ip < 3 && op >= 0) ? slot(par, op) + X1_POS + ip * PREC + 2 * w
-                : slot(par, g);
-      }
-      const bool hneed = (wid == 0) && (lane < P);
-      uint64_t h0, h1, h2, whi[U1], wlo[U1];
+      if (pos == k) put_f64(mine + 6, x, tag);
+      if (tid < j) put_f64(mine + 8 + 2 * tid, s_L[tid * CLD + bs], tag);
+      const int ok_wg = owner(s_map[j]);
+      const bool hon = tid < P, aon = tid == 128;
+      const uint64_t *hp = slot(par, hon ? tid : g), *ap = slot(par, ok_wg) + 6;
+      uint64_t h[6], ah, al;
       const uint64_t t0 = wall_clock64();
-      bool done = false;
-      for (int it = 0;; ++it) {
-        h0 = get_w(hp);
-        h1 = get_w(hp + 1);
-        h2 = get_w(hp + 2);
+      for (;;) {
 #pragma unroll
-        for (int u = 0; u < U1; ++u) {
-          whi[u] = get_w(ap[u]);
-          wlo[u] = get_w(ap[u] + 1);
-        }
-        // branch-free checks: every load is consumed on every path, so no
-        // later wait mistakes one of them for an outstanding one
-        bool ok = (!hneed) | (tag_ok(h0, tag) & tag_ok(h1, tag) & tag_ok(h2, tag));
+        for (int u = 0; u < 6; ++u) h[u] = get_w(hp + u);
+        ah = get_w(ap);
+        al = get_w(ap + 1);
+        bool ok = true;
 #pragma unroll
-        for (int u = 0; u < U1; ++u) ok = ok & ((!need[u]) | (tag_ok(whi[u], tag) & tag_ok(wlo[u], tag)));
-        const bool wok = __ballot(!ok) == 0;
-        const bool expired = wall_clock64() - t0 > kCoopWaitTicks;
-        if constexpr (XW == 1) {
-          if (wok) {
-            done = true;
-            break;
-          }
-          if (expired) break;
-        } else {
-          if (lane == 0) s_xok[it & 1][wid] = (wok ? 1 : 0) | (expired ? 2 : 0);
-          __syncthreads();
-          int all = 1, any_exp = 0;
-#pragma unroll
-          for (int q = 0; q < XW; ++q) {
-            const int v = s_xok[it & 1][q];
-            all &= v;
-            any_exp |= v >> 1;
-          }
-          if (all & 1) {
-            done = true;
-            break;
-          }
-          if (any_exp) break;
+        for (int u = 0; u < 6; ++u) ok = ok & ((!hon) | tag_ok(h[u], tag));
+        ok = ok & ((!aon) | (tag_ok(ah, tag) & tag_ok(al, tag)));
+        if (__ballot(!ok) == 0) break;
+        if (wall_clock64() - t0 > kCoopWaitTicks) {
+          expire();
+          break;
         }
       }
-      if (!done) {
-        if (tid == 0) {
-          __hip_atomic_store(&st->xerr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          s_abort = 1;
-        }
-      } else {
-#pragma unroll
-        for (int u = 0; u < U1; ++u) {
-          const int p = lane + 64 * (wid + XW * u), rec = p / NR, w = p % NR;
-          if (rec < P + 3) s_xb[rec][w] = need[u] ? as_f64(whi[u], wlo[u]) : 0.0;
-        }
+      if (hon) {
+        s_hi[tid] = (int)(uint32_t)h[0];
+        s_hv[tid] = as_f64(h[1], h[2]);
+        s_hp[tid] = (int)(uint32_t)h[3];
+        s_hx[tid] = as_f64(h[4], h[5]);
       }
-      if constexpr (XW == 1) {
-        lds_wave_sync();
-      } else {
-        __syncthreads();
-      }
-      if (!s_abort && wid == 0) {
-        double gv = -1.0;
-        int gi = INT_MAX, gw = 0;
-        if (lane < P) {
-          gv = as_f64(h1, h2);
-          gi = (int)(uint32_t)h0;
-          gw = lane;
-        }
-        wave::amax(gv, gi, gw);
-        if (gv < 0.0) {
-          gv = 0.0;
-          gi = k;
-        }
-        // W row of imax from its L row (used when the first test fails)
-        if (lane < NB)
-          s_wi[lane] = w_lane<NB>(&s_xb[gw][1], s_cA, s_cB, s_cC, lane, 0, false, false, 0.0,
-                                  0.0, 0.0);
-        if (lane == 0) {
-          s_colmax = gv;
-          s_imax = gi;
-          s_gw = gw;
-        }
-      }
+      if (aon) s_akk = as_f64(ah, al);
+      __syncthreads();
+      if (s_abort) return;
+      colmax = -1.0;
+      imax = INT_MAX;
+      if (lane < P) wave::amax3(colmax, imax, gw, s_hv[lane], s_hi[lane], lane);
+      if (lane + 64 < P) wave::amax3(colmax, imax, gw, s_hv[lane + 64], s_hi[lane + 64], lane + 64);
+      wave::amax(colmax, imax, gw);
+      akk = s_akk;
+      wki = s_hx[gw];
+      iphys = s_hp[gw];
     }
-    __syncthreads();
-    if (s_abort) return;
-    ++c;
-    const double colmax = s_colmax;
-    const int imax = s_imax;
-    const double akk = s_xb[P][0], absakk = fabs(akk);
+    if (colmax < 0.0) {
+      colmax = 0.0;
+      imax = k;
+    }
+    const double absakk = fabs(akk);
 
     // ---- Bunch-Kaufman decision ----------------------------------------------
     int kind;  // 0 zero, 1 1x1, 2 1x1 (second test), 3 1x1 swap, 4 2x2
     int kstep = 1, q = k;
-    double aii = 0.0, wki = 0.0;
+    double aii = 0.0, y = 0.0;
     if (fmax(absakk, colmax) == 0.0 || isnan(absakk)) {
       kind = 0;
     } else if (absakk >= alpha * colmax) {
       kind = 1;
     } else {
-      const int src_i = s_map[imax - k0];
-      const int src_k2 = (k + 2 < N) ? s_map[k + 2 - k0] : 0;
+      ++nsec;
       // look-ahead with the candidate past the strip: its entries in rows
-      // past the strip still lack the previous panel's update (the column of
-      // position k + 2 lies in the strip: every position up to k0 + nb holds
-      // a physical row of the strip)
-      const bool fly = la && src_i >= kstrip;
-      // the previous panel's multipliers from column 0 (computed here, not
-      // kept live through the pivot loop)
+      // past the strip still lack the previous panel's update
+      const bool fly = la && iphys >= kstrip;
+      if (pos >= k && (!fly || rho < kstrip)) y = (double)sym_at(X, rho, iphys, ld);
       const double *pL = pv.L + (pv.labs ? (size_t)s_kprev * (size_t)N : 0);
       if constexpr (LA) if (fly) {
-        if (tid < 40) s_pw[tid] = (tid < jwp) ? pv.W[src_i + tid * ld] : 0.0;
-        else if (tid >= 64 && tid < 104)
-          s_pl[tid - 64] = (tid - 64 < jwp) ? pL[src_i + (tid - 64) * ld] : 0.0;
-        __syncthreads();
-      }
-      double wic[R];
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int rho = gbase + tid + T * r;
-        wic[r] = 0.0;
-        if (pos[r] >= k) {
-          if (!fly || rho < kstrip) wic[r] = (double)sym_at(X, rho, src_i, ld);
-          if (k + 2 < N) pre2[r] = sym_at(X, rho, src_k2, ld);
+        if (tid >= 128 && tid < 128 + CPW)
+          s_pw[tid - 128] = (tid - 128 < jwp) ? pv.W[iphys + (tid - 128) * ld] : 0.0;
+        if (tid >= 64 && tid < 128) {
+          for (int t = tid - 64; t < CPW; t += 64) s_pl[t] = (t < jwp) ? pL[iphys + t * ld] : 0.0;
         }
       }
-      if constexpr (LA) if (fly) {
-        keep_branch();
-        static_assert(R == 2, "two rows per call");
-        const int rho0 = gbase + tid, rho1 = gbase + tid + T;
-        const bool on0 = pos[0] >= k && rho0 >= kstrip, on1 = pos[1] >= k && rho1 >= kstrip;
-        const TX *pX;
-        if constexpr (sizeof(TX) == 8) pX = pv.X;
-        else pX = pv.Xf;
-        const double2 e = pending_entries<TX>(pX, pv.src, pv.W, pL, rho0, rho1, on0, on1, src_i,
-                                              jwp, ld, s_pw, s_pl);
-        if (on0) wic[0] = e.x;
-        if (on1) wic[1] = e.y;
-      }
-#pragma unroll
-      for (int t0 = 0; t0 < NB; t0 += 8) {
-        if (t0 < j) {
-          keep_branch();
-          // columns t >= j: L = 0 and the W entries are zeros too, so
-          // their products add an exact zero (no per-column select)
-          double wv[8];
-#pragma unroll
-          for (int u = 0; u < 8; ++u) wv[u] = s_wi[t0 + u];
-#pragma unroll
-          for (int u = 0; u < 8; ++u) {
-#pragma unroll
-            for (int r = 0; r < R; ++r) wic[r] = fma(-Lr[r][t0 + u], wv[u], wic[r]);
-          }
-        }
-      }
-      // ---- X3: partial maxima of the updated column imax -----------------------
-      const int par = c & 1;
-      const uint32_t tag = tagb + (uint32_t)c;
-      uint64_t *mine = slot(par, g);
-      double rv = 0.0;
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        if (pos[r] >= k) {
-          s_wic[r * T + tid] = wic[r];
-          if (pos[r] == imax) put_f64(mine + X3_AII, wic[r], tag);
-          else rv = fmax(rv, fabs(wic[r]));
-          const int po = pos[r] - k;
-          if (po <= 2) put_f64(mine + X3_POS + 2 * po, wic[r], tag);
-        }
-      }
-      rv = wave::max(rv);
-      if (lane == 0) put_f64(mine + 2 * wid, rv, tag);
       if (wid == 0) {
-        const int oi = owner(src_i);
-        // lane 1 + i < 4 reads the column-imax value at position k + i
-        const int ol = (lane >= 1 && lane <= 3 && k + lane - 1 < N)
-                           ? owner(s_map[k + lane - 1 - k0]) : -1;
-        // unconditional loads (see X1): partial maxima, then lane 0: a_ii,
-        // lanes 1..3: the column-imax values at positions k..k+2
-        const uint64_t *pp[U3];
-#pragma unroll
-        for (int u = 0; u < U3; ++u) {
-          const int p = lane + 64 * u;
-          pp[u] = (p < P * NWV) ? slot(par, p / NWV) + 2 * (p % NWV) : slot(par, g);
+        if (P > 1) {
+          // the candidate's L row from its owner's slot of X1
+          const int par = (c - 1) & 1;
+          const uint32_t tag = tagb + (uint32_t)(c - 1);
+          const uint64_t *rp = slot(par, gw) + (lane < j ? 8 + 2 * lane : 0);
+          uint64_t hi, lo;
+          const uint64_t t0 = wall_clock64();
+          for (;;) {
+            hi = get_w(rp);
+            lo = get_w(lane < j ? rp + 1 : rp);
+            if (__ballot(!(tag_ok(hi, tag) & tag_ok(lo, tag))) == 0) break;
+            if (wall_clock64() - t0 > kCoopWaitTicks) {
+              expire();
+              break;
+            }
+          }
+          if (lane < j) s_irow[lane] = as_f64(hi, lo);
+          lds_wave_sync();
         }
-        const bool needa = (lane == 0) || (lane <= 3 && ol >= 0);
-        const uint64_t *aq = (lane == 0) ? slot(par, oi) + X3_AII
-                             : (lane <= 3 && ol >= 0) ? slot(par, ol) + X3_POS + 2 * (lane - 1)
-                             : slot(par, g);
-        uint64_t phi[U3], plo[U3], ahi, alo;
-        const uint64_t t0 = wall_clock64();
-        bool done = false;
-        for (;;) {
-#pragma unroll
-          for (int u = 0; u < U3; ++u) {
-            phi[u] = get_w(pp[u]);
-            plo[u] = get_w(pp[u] + 1);
-          }
-          ahi = get_w(aq);
-          alo = get_w(aq + 1);
-          bool ok = (!needa) | (tag_ok(ahi, tag) & tag_ok(alo, tag));
-#pragma unroll
-          for (int u = 0; u < U3; ++u)
-            ok = ok & ((lane + 64 * u >= P * NWV) | (tag_ok(phi[u], tag) & tag_ok(plo[u], tag)));
-          if (__ballot(!ok) == 0) {
-            done = true;
-            break;
-          }
-          if (wall_clock64() - t0 > kCoopWaitTicks) break;
-        }
-        if (!done) {
-          if (lane == 0) {
-            __hip_atomic_store(&st->xerr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            s_abort = 1;
-          }
-        } else {
-          double m = 0.0;
-#pragma unroll
-          for (int u = 0; u < U3; ++u)
-            if (lane + 64 * u < P * NWV) m = fmax(m, as_f64(phi[u], plo[u]));
-          m = wave::max(m);
-          if (lane == 0) {
-            s_rowmax = m;
-            s_aii = as_f64(ahi, alo);
-          } else if (lane <= 3) {
-            s_xwic[lane - 1] = needa ? as_f64(ahi, alo) : 0.0;
-          }
-        }
+        s_wi[lane] = (lane < j) ? wrow(s_irow, lane) : 0.0;
       }
       __syncthreads();
       if (s_abort) return;
-      ++c;
-      const double rowmax = s_rowmax;
+      if constexpr (LA) if (fly) {
+        const TX *pX;
+        if constexpr (sizeof(TX) == 8) pX = pv.X;
+        else pX = pv.Xf;
+        const bool on = pos >= k && rho >= kstrip;
+        if (on) y = pending_entry<TX>(pX, pv.src, pv.W, pL, rho, iphys, jwp, ld, s_pw, s_pl);
+      }
+#pragma unroll 4
+      for (int t = 0; t < j; ++t) y = fma(-s_L[t * CLD + tid], s_wi[t], y);
+      // ---- X3: maximum of the updated column imax, and a_ii --------------------
+      double rv = (pos >= k && pos != imax) ? fabs(y) : 0.0;
+      rv = wave::max(rv);
+      if (lane == 0) s_cv[wid] = rv;
+      if (pos == imax) s_aii = y;
+      __syncthreads();
+      double rowmax = fmax(fmax(s_cv[0], s_cv[1]), fmax(s_cv[2], s_cv[3]));
+      static_assert(NWV == 4, "four waves");
+      if (P > 1) {
+        const int par = c & 1;
+        const uint32_t tag = tagb + (uint32_t)c;
+        ++c;
+        uint64_t *mine = slot(par, g);
+        if (tid == 0) put_f64(mine, rowmax, tag);
+        if (pos == imax) put_f64(mine + 2, y, tag);
+        const bool hon = tid < P, aon = tid == 128;
+        const uint64_t *hp = slot(par, hon ? tid : g), *ap = slot(par, gw) + 2;
+        uint64_t h0, h1, ah, al;
+        const uint64_t t0 = wall_clock64();
+        for (;;) {
+          h0 = get_w(hp);
+          h1 = get_w(hp + 1);
+          ah = get_w(ap);
+          al = get_w(ap + 1);
+          const bool ok = ((!hon) | (tag_ok(h0, tag) & tag_ok(h1, tag))) &
+                          ((!aon) | (tag_ok(ah, tag) & tag_ok(al, tag)));
+          if (__ballot(!ok) == 0) break;
+          if (wall_clock64() - t0 > kCoopWaitTicks) {
+            expire();
+            break;
+          }
+        }
+        if (hon) s_hv[tid] = as_f64(h0, h1);
+        if (aon) s_aii = as_f64(ah, al);
+        __syncthreads();
+        if (s_abort) return;
+        rowmax = 0.0;
+        if (lane < P) rowmax = s_hv[lane];
+        if (lane + 64 < P) rowmax = fmax(rowmax, s_hv[lane + 64]);
+        rowmax = wave::max(rowmax);
+      }
       aii = s_aii;
-      wki = s_xb[s_gw][0];
       if (absakk >= alpha * colmax * (colmax / rowmax)) {
         kind = 2;
       } else if (fabs(aii) >= alpha * rowmax) {
@@ -601,9 +703,9 @@ __global__ __launch_bounds__(T) void k_bk_panel_coop(int N, int nb, double alpha
     }
     const int p = k + kstep - 1;
     const bool sw = (q != p);
-    const int kn = k + kstep;
     double Da = akk, Dc = 0.0, Db = 0.0, det = 1.0;
     if (kind == 3) Da = aii;
+    // a zero (or NaN) pivot eliminates nothing: its W column is zero
     const double Dw = (kind == 0) ? 0.0 : Da;
     if (kind == 4) {
       Db = wki;
@@ -611,111 +713,53 @@ __global__ __launch_bounds__(T) void k_bk_panel_coop(int N, int nb, double alpha
       det = Da * Dc - Db * Db;
     }
     const double rD = (kind == 4) ? 1.0 / det : (kind == 3) ? 1.0 / aii : 1.0 / akk;
-
-    // ---- multipliers, new positions, next column ------------------------------
-    double l0[R], l1[R];
-    bool act[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int pr = pos[r];
-      l1[r] = 0.0;
+    // ---- multipliers and new positions ------------------------------------------
+    {
+      bool act;
+      double l0, l1 = 0.0;
       if (kind == 4) {
-        act[r] = pr >= k + 1 && pr != q;
-        const double x0 = s_wkc[r * T + tid], y0 = s_wic[r * T + tid];
-        l0[r] = (x0 * Dc - y0 * Db) * rD;
-        l1[r] = (y0 * Da - x0 * Db) * rD;
+        act = pos >= k + 1 && pos != q;
+        l0 = (x * Dc - y * Db) * rD;
+        l1 = (y * Da - x * Db) * rD;
       } else if (kind == 3) {
-        act[r] = pr >= k && pr != q;
-        l0[r] = s_wic[r * T + tid] * rD;
+        act = pos >= k && pos != q;
+        l0 = y * rD;
       } else {
-        act[r] = pr > k;
-        l0[r] = (kind == 0) ? 0.0 : s_wkc[r * T + tid] * rD;
+        act = pos > k;
+        l0 = (kind == 0) ? 0.0 : x * rD;
       }
-      int np = pr;
+      s_L[j * CLD + tid] = act ? l0 : 0.0;
+      if (kind == 4) s_L[(j + 1) * CLD + tid] = act ? l1 : 0.0;
       if (sw) {
-        if (pr == p) np = q;
-        else if (pr == q) np = p;
-      }
-      pos[r] = np;
-      double an = (double)pre1[r];
-      if (kind == 3 && q == k + 1) an = s_acur[r * T + tid];
-      if (kind == 4 && q != k + 2) an = (double)pre2[r];
-      s_acur[r * T + tid] = an;
-    }
-    // the step's column(s) of the register tile (j is uniform: one scalar
-    // compare per column, which every wave runs on the compute unit's shared
-    // scalar unit; the 2x2 pivot's second column only on 2x2 steps)
-#pragma unroll
-    for (int t = 0; t < NB; ++t) {
-      if (t == j) {
-        keep_branch();
-#pragma unroll
-        for (int r = 0; r < R; ++r) Lr[r][t] = act[r] ? l0[r] : Lr[r][t];
+        if (pos == p) pos = q;
+        else if (pos == q) pos = p;
+        s_pos[tid] = pos;
       }
     }
-    if (kind == 4) {
-      keep_branch();
-#pragma unroll
-      for (int t = 1; t < NB; ++t) {
-        if (t == j + 1) {
-          keep_branch();
-#pragma unroll
-          for (int r = 0; r < R; ++r) Lr[r][t] = act[r] ? l1[r] : Lr[r][t];
-        }
-      }
-    }
-
-    // ---- W row of the next pivot, from the exchanged rows (wave 0) -------------
-    if (wid == 0 && kn < N) {
-      // the row at position kn came from position k + inx before the interchange
-      const int inx = (kind == 4) ? ((q == k + 2) ? 1 : 2) : (kind == 3 && q == k + 1) ? 0 : 1;
-      const double x0 = s_xb[P + inx][0], y0 = s_xwic[inx];
-      double n0, n1 = 0.0;
-      if (kind == 4) {
-        n0 = (x0 * Dc - y0 * Db) * rD;
-        n1 = (y0 * Da - x0 * Db) * rD;
-      } else if (kind == 3) {
-        n0 = y0 * rD;
-      } else {
-        n0 = (kind == 0) ? 0.0 : x0 * rD;
-      }
-      if (lane < NB) {
-        double v = s_xb[P + inx][1 + lane];
-        if (lane == j) v = n0;
-        if (kind == 4 && lane == j + 1) v = n1;
-        s_nrow[lane] = v;
-      }
-      lds_wave_sync();
-      if (lane < NB)
-        s_wk[lane] = w_lane<NB>(s_nrow, s_cA, s_cB, s_cC, lane, j, true, kind == 4,
-                                (kind == 4) ? Da : Dw, Dc, Db);
-    }
-
-    // ---- pivot records and map -------------------------------------------------
     if (tid == 0) {
       if (sw) {
         const int t0 = s_map[p - k0];
-        s_map[p - k0] = s_map[q - k0];
-        s_map[q - k0] = t0;
+        s_map[p - k0] = iphys;
+        if (q - k0 < CNB + 2) s_map[q - k0] = t0;
       }
-      // the pivot records go to global memory at the end of the panel: a
-      // store here would make this wave wait for its prefetch of the next
-      // column at the next write of the store's source registers
+      s_cA[j] = (kind == 4) ? Da : Dw;
+      s_cB[j] = Db;
+      s_cC[j] = 0.0;
+      s_pdd[j] = Da;
+      s_pds[j] = Db;
       if (kind == 4) {
-        s_pdd[j] = Da;
+        s_cA[j + 1] = Dc;
+        s_cB[j + 1] = 0.0;
+        s_cC[j + 1] = Db;
         s_pdd[j + 1] = Dc;
-        s_pds[j] = Db;
         s_pds[j + 1] = 0.0;
-        s_pip[j] = -(q + 1);
-        s_pip[j + 1] = -(q + 1);
+        s_pip[j] = s_pip[j + 1] = -(q + 1);
         s_pbk[j] = 2;
         s_pbk[j + 1] = 3;
         c_pos++;
         c_neg++;
         c_2x2++;
       } else {
-        s_pdd[j] = Da;
-        s_pds[j] = 0.0;
         s_pip[j] = q + 1;
         s_pbk[j] = 1;
         if (Da > 0.0) c_pos++;
@@ -726,55 +770,41 @@ __global__ __launch_bounds__(T) void k_bk_panel_coop(int N, int nb, double alpha
         }
       }
     }
-    pj = j;
-    p2 = (kind == 4);
-    pA0 = (kind == 4) ? Da : Dw;
-    pB0 = Db;
-    pA1 = Dc;
+    any2 = any2 || kind == 4;
     j += kstep;
-    k = kn;
-    __syncthreads();
+    k += kstep;
+    if (j < nb && k < N) {
+      // the window rows with the new column, the next block's entries
+      const bool spec = slow == 0;
+      const int m = xb(CB, true, j & ~(CB - 1), j, 0, spec ? j : -1);
+      if (m < 0) return;
+      loaded = spec;
+    }
   }
 
   // ---- write the panel's multipliers and W = L D for the trailing rows ---------
   const int kend = k, jend = j;
   const int lcol = lstage ? 0 : k0;  // staged multipliers: column t at t N
-  if (tid == 0 && pj >= 0) {
-    s_cA[pj] = pA0;
-    s_cB[pj] = pB0;
-    if (p2) {
-      s_cA[pj + 1] = pA1;
-      s_cC[pj + 1] = pB0;
-    }
-  }
   __syncthreads();
-  if (g == 0) {
-    for (int t = tid; t < jend; t += T) {
-      dd[k0 + t] = s_pdd[t];
-      ds[k0 + t] = s_pds[t];
-      ipiv[k0 + t] = s_pip[t];
-      blk[k0 + t] = s_pbk[t];
-    }
+  if (g == 0 && tid < jend) {
+    dd[k0 + tid] = s_pdd[tid];
+    ds[k0 + tid] = s_pds[tid];
+    ipiv[k0 + tid] = s_pip[tid];
+    blk[k0 + tid] = s_pbk[tid];
   }
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int pr = pos[r];
-    if (pr < 0) continue;
-    const int rho = gbase + tid + T * r;
-#pragma unroll
-    for (int t = 0; t < NB; ++t)
-      if (t < jend && pr > k0 + t) Lout[pr + (lcol + t) * ld] = Lr[r][t];
-    if (pr >= kend) {
-#pragma unroll
-      for (int t = 0; t < NB; ++t) {
-        if (t < jend) {
-          double v = Lr[r][t] * s_cA[t];
-          if (t + 1 < NB) v = v + Lr[r][t + 1 < NB ? t + 1 : t] * s_cB[t];
-          if (t >= 1) v = v + Lr[r][t >= 1 ? t - 1 : 0] * s_cC[t];
-          W[pr + t * ld] = v;
+  if (pos >= 0) {
+    const int below = min(jend, pos - k0);  // columns t with pos > k0 + t
+    for (int t = 0; t < below; ++t) Lout[pos + (lcol + t) * ld] = s_L[t * CLD + tid];
+    if (pos >= kend) {
+      for (int t = 0; t < jend; ++t) {
+        double v = s_L[t * CLD + tid] * s_cA[t];
+        if (any2) {
+          if (t + 1 < jend) v = v + s_L[(t + 1) * CLD + tid] * s_cB[t];
+          if (t >= 1) v = v + s_L[(t - 1) * CLD + tid] * s_cC[t];
         }
+        W[pos + t * ld] = v;
       }
-      src_out[pr] = rho;
+      src_out[pos] = rho;
     }
   }
   if (g == 0 && tid == 0) {
@@ -788,9 +818,8 @@ __global__ __launch_bounds__(T) void k_bk_panel_coop(int N, int nb, double alpha
     st->n2x2 += c_2x2;
     if (st->info == 0 && first_zero != 0) st->info = first_zero;
     st->xtag = s_tag0 + 1u;
-    // every step takes the first exchange; c counts both
     st->csteps += nsteps;
-    st->cx3 += c - nsteps;
+    st->cx3 += nsec;
   }
 }
 
@@ -867,74 +896,47 @@ __global__ __launch_bounds__(T) void k_xch_probe(int P, int rounds, int words,
   if (g == 0 && tid == 0) out[0] = wall_clock64() - t_start;
 }
 
-// Variants: (threads, rows per thread, register tile, most workgroups)
-constexpr int kCoopT = 512, kCoopR = 2, kCoopNB = 32;
-constexpr int kCoopP = (kCoopMaxN + kCoopT * kCoopR - 1) / (kCoopT * kCoopR);
-
 }  // namespace
 
-int bk_coop_rows_per_wg() { return kCoopT * kCoopR; }
-
-// Occupancy of the instantiation used at order N times the compute units must
-// cover its workgroups: they spin on each other's exchange words.
+// Occupancy times the compute units must cover the workgroups of order N:
+// they spin on each other's exchange words.
 bool bk_coop_resident(int N) {
-  const int P = (N + kCoopT * kCoopR - 1) / (kCoopT * kCoopR);
+  const int P = bk_coop_wgs(N);
   int dev = 0, cus = 0, per = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
-  hipError_t e;
-  if (P <= 4)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &per, k_bk_panel_coop<kCoopT, kCoopR, kCoopNB, 4, double, false>, kCoopT, 0);
-  else if (P <= 8)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &per, k_bk_panel_coop<kCoopT, kCoopR, kCoopNB, 8, double, false>, kCoopT, 0);
-  else if (P <= 12)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &per, k_bk_panel_coop<kCoopT, kCoopR, kCoopNB, 12, double, false>, kCoopT, 0);
-  else
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &per, k_bk_panel_coop<kCoopT, kCoopR, kCoopNB, kCoopP, double, false>, kCoopT, 0);
-  if (e != hipSuccess) {
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_bk_panel_coop<double, false>, CT, 0) !=
+      hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
   return (long)per * cus >= P;
 }
-int bk_coop_nb() { return kCoopNB; }
-int bk_coop_wgs(int N) { return (N + kCoopT * kCoopR - 1) / (kCoopT * kCoopR); }
+int bk_coop_nb() { return CNB; }
+int bk_coop_wgs(int N) { return (N + CT - 1) / CT; }
 
-// The exchange reads of X1 hold (PMAX + 3) (NB + 1) / 64 word pairs per lane
-// in registers (every lane issues all of them on every poll), so the grid
-// picks the smallest instantiation that covers the panel: `rows` bounds the
-// rows left at the panel's start (every earlier panel factored at least
-// nb - 1 columns), and with them its workgroups.
+// `rows` bounds the rows left at the panel's start (every earlier panel
+// factored at least nb - 1 columns), and with them its workgroups.
 template <typename TX, bool LA>
 static void panel_coop(hipStream_t s, int rows, int N, int nb, double alpha, const TX *X,
                        const PanelPrev &pv, double *Lout, int lstage, int32_t *src_out, double *W,
                        double *dd, double *ds, int32_t *ipiv, int32_t *blk, FacState *st,
                        int32_t *panel_k0, uint64_t *xch) {
   const int P = std::max(1, std::min(bk_coop_wgs(N), bk_coop_wgs(rows)));
-#define MDS_COOP(PM_)                                                                  \
-  k_bk_panel_coop<kCoopT, kCoopR, kCoopNB, PM_, TX, LA><<<P, kCoopT, 0, s>>>(          \
-      N, nb, alpha, P, X, pv, Lout, src_out, W, dd, ds, ipiv, blk, st, panel_k0, xch, lstage)
-  if (P <= 4) MDS_COOP(4);
-  else if (P <= 8) MDS_COOP(8);
-  else if (P <= 12) MDS_COOP(12);
-  else MDS_COOP(kCoopP);
-#undef MDS_COOP
+  k_bk_panel_coop<TX, LA><<<P, CT, 0, s>>>(N, std::min(nb, CNB), alpha, X, pv, Lout, src_out, W, dd,
+                                           ds, ipiv, blk, st, panel_k0, xch, lstage);
 }
 
 int bk_xch_probe(hipStream_t s, int P, int rounds, int words, uint64_t *xch, int32_t *err,
                  uint64_t *out) {
-  constexpr int U = 4;  // words read per thread: P * words <= 4 * 512
-  if (P < 1 || P > kCoopMaxP || words < 1 || words > kCoopSlotWords || P * words > U * kCoopT ||
+  constexpr int T = 512, U = 4;  // words read per thread: P * words <= 4 * 512
+  if (P < 1 || P > kProbeMaxP || words < 1 || words > kCoopSlotWords || P * words > U * T ||
       rounds < 1)
     return -1;
-  k_xch_probe<kCoopT, U><<<P, kCoopT, 0, s>>>(P, rounds, words, xch, err, out);
+  k_xch_probe<T, U><<<P, T, 0, s>>>(P, rounds, words, xch, err, out);
   return 0;
 }
 

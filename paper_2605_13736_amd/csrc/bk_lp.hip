@@ -28,7 +28,7 @@ constexpr int TSL1 = TSL + 1;  // odd row stride of the staged panels
 constexpr int TSTL = TT * TSL / 256;  // staged entries per thread and panel
 constexpr int kTrailingLpGrid = kTileGrid;  // persistent form: 512 workgroups (2 per CU at <= 196 VGPRs)
 static_assert(TT * TSL % 256 == 0, "staging");
-static_assert(TT == kNearCols, "the near strip is one tile column");
+static_assert(TT * kNearTiles == kNearCols, "near strip");
 
 // round-to-nearest-even FP32 -> BF16 (finite inputs)
 __device__ inline short to_bf16(float x) {
@@ -469,7 +469,8 @@ void launch_trailing_lp_part(hipStream_t s, int mode, int N, int nb, long rem, i
                              const int32_t *panel_k0) {
   if (rem <= 0 || nb + 1 > TSL) return;
   const long nt = (rem + TT - 1) / TT;
-  const long tiles = (part == 1) ? nt : (nt - 1) * nt / 2;
+  const long tiles = (part == 1) ? kNearTiles * nt
+                     : (nt > kNearTiles) ? (nt - kNearTiles) * (nt - kNearTiles + 1) / 2 : 0;
   if (tiles <= 0) return;
   const unsigned g = (unsigned)std::min(tiles, (long)std::max(grid, 1));
   if (mode == 2)

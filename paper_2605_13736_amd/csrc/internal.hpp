@@ -17,8 +17,11 @@ constexpr int kMaxNb = 64;           // largest supported panel width
 constexpr int kRedBlocks = 1024;     // partial-reduction slots
 constexpr int kDotBlocks = 64;       // blocks per column of a Krylov dot product
 constexpr int kGmresRestart = 20;    // GMRES restart length of the mixed-precision refinement
-constexpr int kCoopMaxP = 32;        // cooperative panel: most workgroups
+constexpr int kCoopMaxP = 80;        // cooperative panel: most workgroups
+constexpr int kProbeMaxP = 32;       // exchange probe: most workgroups
 constexpr int kCoopSlotWords = 512;  // cooperative panel: 64-bit exchange words per workgroup and parity
+constexpr int kCoopRowWords = 2048;  // ... and of the window rows, per parity
+constexpr size_t kCoopXchBytes = 8 * 2 * ((size_t)kCoopMaxP * kCoopSlotWords + kCoopRowWords);
 constexpr int kSBlkMax = 16;         // largest coupling block of the sparse Hessian
 
 // Coupling blocks of the sparse Hessian (sblock.hip) and the transformed
@@ -54,12 +57,13 @@ struct FacState {
 
 // Look-ahead of the cooperative factorization: while the trailing update of
 // panel b runs on part of the device, panel b + 1 factors its columns, which
-// a near update (the 64-column strip at the trailing matrix's start) has
+// a near update (the kNearCols-column strip at the trailing matrix's start) has
 // already brought up to date.  Entries it reads outside that strip (the
 // candidate column of a failed first Bunch-Kaufman test) it computes itself
 // from panel b's input and multipliers: entry (i, c), i >= c, of its input is
 // X[src(i), src(c)] - sum_t W[c, t] L[i, t] (lower triangle of X).
-constexpr int kNearCols = 64;  // columns of the near update past its start
+constexpr int kNearTiles = 2;   // 64-column tile columns of the near update
+constexpr int kNearCols = 64 * kNearTiles;  // its columns past its start
 struct PanelPrev {
   const double *X;      // panel b's input, physical indices (FP64 storage), or
   const float *Xf;      // ... in FP32 storage (null both: no look-ahead)
@@ -260,7 +264,8 @@ void launch_bk_panel(hipStream_t s, int N, int nb, double alpha, double *M, doub
                      int32_t *panel_k0);
 // rem: an upper bound of the rows of the trailing matrix after the panel of
 // slot `slot` (sizes the grid; 0 or less: nothing to update)
-void launch_bk_trailing(hipStream_t s, int N, int nb, long rem, int slot, const double *W,
+// wmax: the widest panel possible (at most nb + 1)
+void launch_bk_trailing(hipStream_t s, int N, int nb, int wmax, long rem, int slot, const double *W,
                         const double *X, double *Y, const double *Lsrc, const int32_t *src,
                         const FacState *st, const int32_t *panel_k0);
 // look-ahead parts of the trailing update of slot `slot` (nb + 1 <= 36):
@@ -300,15 +305,14 @@ void launch_bk_panel_reg(hipStream_t s, int threads, int N, int nb, double alpha
                          int32_t *ipiv, int32_t *blk, FacState *st, int32_t *panel_k0);
 
 // bk_coop.hip: cooperative register panel over several workgroups (any N up
-// to the solver limit; X in FP64 or FP32); xch: 2 * kCoopMaxP * kCoopSlotWords
-// exchange words, zeroed once
-int bk_coop_rows_per_wg();
+// to the solver limit; X in FP64 or FP32); xch: kCoopXchBytes of exchange
+// words, zeroed once
 // whether the device can hold every workgroup of the panel for order N at once
 bool bk_coop_resident(int N);
 int bk_coop_nb();
 int bk_coop_wgs(int N);
 // rows: at least the rows left at the panel's start (sizes the grid)
-// Exchange round-trip probe of the cooperative panel (P <= kCoopMaxP workgroups,
+// Exchange round-trip probe of the cooperative panel (P <= kProbeMaxP workgroups,
 // words <= kCoopSlotWords per workgroup, P * words <= 2048); -1: bad sizes.
 int bk_xch_probe(hipStream_t s, int P, int rounds, int words, uint64_t *xch, int32_t *err,
                  uint64_t *out);

@@ -13,7 +13,7 @@
 // Any other grid size walks the tiles in plain row-major triangular order.
 #pragma once
 
-#include <hip/hip_runtime.h>
+#include "internal.hpp"
 
 namespace mds {
 
@@ -59,25 +59,24 @@ __device__ inline bool tile_of(long x, int nt, bool xcd, int &ti, int &tj) {
 }
 
 // Tiles of one launch: part 0 every lower tile (in the order above),
-// part 1 the first tile column (the near strip of the look-ahead), part 2
-// the tiles right of it (ti >= tj >= 1, row-major).
-// the rest (part 2) walks the triangle of the tiles from (1, 1) on, in the
-// order above.
+// part 1 the first kNearTiles tile columns (the near strip of the
+// look-ahead), part 2 the tiles right of them: the triangle from tile
+// (kNearTiles, kNearTiles) on, in the order above.
 __device__ inline long part_slots(int part, int nt, bool xcd) {
-  if (part == 1) return nt;
-  if (part == 2) return tile_slots(nt - 1, xcd);
+  if (part == 1) return (long)kNearTiles * nt;
+  if (part == 2) return tile_slots(max(nt - kNearTiles, 0), xcd);
   return tile_slots(nt, xcd);
 }
 __device__ inline bool part_tile(int part, long x, int nt, bool xcd, int &ti, int &tj) {
   if (part == 1) {
-    ti = (int)x;
-    tj = 0;
-    return ti < nt;
+    tj = (int)(x / nt);
+    ti = (int)(x % nt);
+    return ti >= tj;
   }
   if (part == 2) {
-    const bool ok = tile_of(x, nt - 1, xcd, ti, tj);
-    ++ti;
-    ++tj;
+    const bool ok = tile_of(x, nt - kNearTiles, xcd, ti, tj);
+    ti += kNearTiles;
+    tj += kNearTiles;
     return ok;
   }
   return tile_of(x, nt, xcd, ti, tj);

@@ -111,6 +111,15 @@ __device__ inline double max(double v) {
   return fmax(r, fmax(lane_read(v, 32), lane_read(v, 48)));
 }
 
+// minimum over the wave, every lane
+__device__ inline int imin(int v) {
+  v = min(v, dpp<kXor1>(v));
+  v = min(v, dpp<kXor2>(v));
+  v = min(v, dpp<kRor4>(v));
+  v = min(v, dpp<kRor8>(v));
+  return min(min(lane_read(v, 0), lane_read(v, 16)), min(lane_read(v, 32), lane_read(v, 48)));
+}
+
 // sum over the wave, every lane (association: quads, rows, then rows 0..3)
 __device__ inline double sum(double v) {
   v = v + dpp<kXor1>(v);
