@@ -101,16 +101,14 @@ enum { MDS_FP64 = 0, MDS_FP32 = 1, MDS_BF16 = 2, MDS_BF16X3 = 3 };
 
 typedef struct {
   int32_t nb;          /* panel width of the blocked factorization (0: default) */
-  int32_t panel;       /* 0: automatic (register-resident panel when its tile
-                          allows nb >= 16, i.e. N <= 2048; above that the
-                          cooperative panel, which hands over to the
-                          one-workgroup register panel once at most 1024
-                          rows remain),
+  int32_t panel;       /* 0: automatic (the cooperative panel; the register
+                          panel when panel_threads is set and its tile
+                          allows nb >= 16, i.e. N <= 2048),
                           1: panel kept in device memory (FP64 only),
                           2: register-resident panel, one workgroup (N <= 4096),
-                          3: register-resident panel over ceil(N / 1024)
-                             cooperating workgroups, nb <= 32 (any N); its
-                             workgroups exchange pivot data through the
+                          3: cooperative panel over ceil(N / 256)
+                             workgroups, nb <= 32 (64 above N = 2048; any N);
+                             its workgroups exchange pivot data through the
                              workspace and must run concurrently: when an
                              exchange wait expires (~0.7 s) the matrix is
                              condensed again and factored by the memory
@@ -124,7 +122,7 @@ typedef struct {
   int32_t precision;   /* MDS_FP64 (default), MDS_FP32, MDS_BF16, MDS_BF16X3   */
   int32_t panel_threads; /* register panel workgroup: 64, 128, 256, 512 or
                             1024 (0: 128 up to N = 128, 256 up to N = 256,
-                            else 512); the cooperative panel uses 512; the
+                            else 512); the cooperative panel uses 256; the
                             LDS factorization 256 or 512 (0: 512)           */
   int32_t nlp;         /* 1: the workspace also holds the model objects of a
                           general NLP (mds_set_nlp)                         */
@@ -133,11 +131,12 @@ typedef struct {
                           this many sparse variables (mds_set_sparse_blocks)
                           and the transformed Jacobian they induce (up to
                           sblk_max * nnz_s entries)                          */
-  int32_t lookahead;   /* cooperative factorization: 0 automatic (on for
-                          N >= 8192), 1 on, 2 off.  With look-ahead, panel
-                          b + 1 and the update of the 64-column strip ahead
-                          of it run on a few reserved compute units (4 per
-                          XCD, at least the panel's workgroups) while the
+  int32_t lookahead;   /* cooperative factorization: 0 automatic (off: it
+                          does not pay), 1 on, 2 off.  With look-ahead, panel
+                          b + 1 and the update of the 128-column strip ahead
+                          of it run on a few reserved compute units (4 or 8
+                          per XCD, at least the panel's workgroups: N <=
+                          16384 on 256 units) while the
                           rest of panel b's trailing update runs on the
                           others (two CU-masked streams the handle creates;
                           the handle's stream waits for both).  Panel b + 1
@@ -243,8 +242,7 @@ typedef struct {       /* one IPM iteration (host) */
  * (hipEvents recorded around each launch on the stream it runs on).  PERMUTE
  * is the conversion of a new factor to standard form before its first solve;
  * SOLVE is one triangular-solve sequence (permute, L, D, L', permute);
- * PANEL_TAIL holds the register-panel launches that finish a cooperative
- * factorization (PANEL then holds only the cooperative ones).  FACTOR is
+ * PANEL_TAIL is unused (zero).  FACTOR is
  * each whole factorization on the handle's stream (with look-ahead its
  * classes overlap, so their sum exceeds it); NEAR the look-ahead's strip
  * updates (TRAILING then holds the rest of each trailing update). */

@@ -118,9 +118,8 @@ Layout make_layout(const mds_dims &d, int nb, bool pingpong, int precision, int 
   const size_t nd = d.n_d, ns = d.n_s, m = d.m, N = nd + m, n = nd + ns;
   const size_t nx = n + (size_t)d.m_I;
   const size_t nnz = (size_t)d.nnz_s;
-  // panels: at least nb - 1 columns each, the register tail's 16-column
-  // tile over the last 2048 rows adds at most 40 (see make_plan)
-  const size_t maxp = N / (size_t)std::max(nb - 1, 1) + 42;
+  // panels: at least nb - 1 columns each
+  const size_t maxp = N / (size_t)std::max(nb - 1, 1) + 2;
   size_t bytes[S_COUNT] = {};
   bytes[S_M] = 8 * N * N;
   const bool mixed = precision != MDS_FP64;
@@ -214,7 +213,6 @@ struct PanelChoice {
   bool coop;  // cooperative panel over several workgroups
   int nb, adv, threads;
   bool lds;   // unblocked factorization of the whole M in one workgroup's LDS
-  bool tail = false;  // cooperative: the register panel once the rows left fit one workgroup
 };
 
 // workgroup size of the single-workgroup register panel: the option
@@ -230,14 +228,12 @@ int panel_threads_of(const mds_options *o, int N) {
 // Panel choice.  panel option 1: memory panel; 2: register panel (N <= 4096);
 // 3: cooperative panel over ceil(N / 256) workgroups (any N); 4: the whole M
 // in one workgroup's LDS (FP64, N <= bk_lds_max_n()).
-// 0 (automatic): the cooperative panel, except in mixed precision while the
-// register panel's tile keeps nb >= 16 (N <= 2048) or when panel_threads
-// asks for the register panel.  Newton step, register / cooperative panel:
-// N = 101 0.55 / 0.42 ms, 771 2.9 / 1.5, 2051 8.6 (former cooperative panel
-// and register tail) / 3.4.
-// Cooperative nb: 64 in FP64 above N = 2048, where the trailing update's
-// traffic (inverse to the width) counts; 32 below and in mixed precision,
-// whose trailing update stages at most 48 columns.
+// 0 (automatic): the cooperative panel, unless panel_threads asks for the
+// register panel (its tile must keep nb >= 16: N <= 2048).  Newton step,
+// register / cooperative panel: N = 101 0.55 / 0.42 ms, 771 2.9 / 1.5, 2051
+// 8.6 (former cooperative panel and register tail) / 3.4.
+// Cooperative nb: 64 above N = 2048, where the trailing update's traffic
+// (inverse to the width) counts; 32 below, where it does not.
 PanelChoice panel_of(const mds_dims &d, const mds_options *o) {
   const int N = d.n_d + d.m;
   const int popt = o ? o->panel : 0;
@@ -257,18 +253,17 @@ PanelChoice panel_of(const mds_dims &d, const mds_options *o) {
   }
   if (popt == 2 && rnb == 0) return c;
   const bool use_reg =
-      rnb > 0 && (popt == 2 || (popt == 0 && rnb >= 16 && (prec != MDS_FP64 || (o && o->panel_threads != 0))));
+      rnb > 0 && (popt == 2 || (popt == 0 && rnb >= 16 && o && o->panel_threads != 0));
   const bool use_coop = !use_reg && (popt == 3 || popt == 0);
   if (use_reg) {
     int nb = (o && o->nb > 0) ? o->nb : rnb;
     nb = std::min(std::max(nb, 2), rnb);
     c = {true, false, nb, std::max(nb - 1, 1), thr, false};
   } else if (use_coop) {
-    const int cnb = (prec == MDS_FP64 && N > 2048) ? bk_coop_nb() : 32;
+    const int cnb = (N > 2048) ? bk_coop_nb() : 32;
     int nb = (o && o->nb > 0) ? o->nb : cnb;
     nb = std::min(std::max(nb, 2), cnb);
-    c = {true, true, nb, std::max(nb - 1, 1), 512, false};
-    c.tail = (popt == 0 && prec != MDS_FP64);
+    c = {true, true, nb, std::max(nb - 1, 1), bk_coop_rows(), false};
   } else {
     int nb = (o && o->nb > 0) ? o->nb : default_nb(N);
     nb = std::min(std::max(nb, 2), kMaxNb);
@@ -321,37 +316,22 @@ int condense_impl(mds_handle *h, double dw, double dc) {
   return MDS_OK;
 }
 
-// Slot plan of a factorization (fixed per handle): the handle's panel until
-// at most bk_reg_tail_rows() rows can remain (cooperative panel with the
-// automatic tail), then the register tail, whose tile is 16 columns wide
-// above 1024 rows and 32 below.
+// Slot plan of a factorization (fixed per handle): the rows that can remain
+// at each panel's start.
 void make_plan(mds_handle *h) {
   h->plan.clear();
-  long rows = h->N;
-  while (rows > 0) {
-    SlotPlan sp{0, rows, 0};
-    if (h->panel_coop && h->panel_tail && rows <= bk_reg_tail_rows())
-      sp.tail_nb = std::min(bk_reg_tail_nb((int)rows), h->nb);
-    sp.rows_after = rows - (sp.tail_nb ? std::max(sp.tail_nb - 1, 1) : h->adv);
-    h->plan.push_back(sp);
-    rows = sp.rows_after;
-  }
+  for (long rows = h->N; rows > 0; rows -= h->adv)
+    h->plan.push_back(SlotPlan{rows, rows - h->adv});
 }
 
-bool is_tail_slot(const mds_handle *h, int b) { return h->plan[b].tail_nb != 0; }
-
-// Panel of slot b on the ping-pong layout: the cooperative panel, the
-// register tail over its last rows, or the one-workgroup register panel.
+// Panel of slot b on the ping-pong layout: the cooperative panel or the
+// one-workgroup register panel.
 template <typename TX>
 void launch_reg_panel(mds_handle *h, hipStream_t s, int b, const TX *X, double *Y) {
   const int N = h->N;
-  const SlotPlan &sp = h->plan[b];
-  if (h->panel_coop && !sp.tail_nb)
-    launch_bk_panel_coop(s, (int)sp.rows, N, h->nb, h->alpha_bk, X, Y, h->w.src, h->w.W, h->w.dd,
-                         h->w.ds, h->w.ipiv, h->w.blk, h->w.fst, h->w.panel_k0, h->w.xch);
-  else if (h->panel_coop)
-    launch_bk_panel_reg_tail(s, (int)sp.rows, N, h->nb, h->alpha_bk, X, Y, h->w.src, h->w.W,
-                             h->w.dd, h->w.ds, h->w.ipiv, h->w.blk, h->w.fst, h->w.panel_k0);
+  if (h->panel_coop)
+    launch_bk_panel_coop(s, (int)h->plan[b].rows, N, h->nb, h->alpha_bk, X, Y, h->w.src, h->w.W,
+                         h->w.dd, h->w.ds, h->w.ipiv, h->w.blk, h->w.fst, h->w.panel_k0, h->w.xch);
   else
     launch_bk_panel_reg(s, h->panel_threads, N, h->nb, h->alpha_bk, X, Y, h->w.src, h->w.W,
                         h->w.dd, h->w.ds, h->w.ipiv, h->w.blk, h->w.fst, h->w.panel_k0);
@@ -368,6 +348,8 @@ void factor_launches(mds_handle *h, hipStream_t s) {
     factor_launches_la(h, s);
     return;
   }
+  // the cooperative panel never passes nb columns, the others end on a 2x2
+  const int wmax = h->panel_coop ? h->nb : h->nb + 1;
   launch_fac_reset(s, h->w.fst, h->w.panel_k0);
   const int slots = (int)h->plan.size();
   if (h->panel_lds) {
@@ -385,19 +367,17 @@ void factor_launches(mds_handle *h, hipStream_t s) {
       const float *X = h->w.X32[b & 1];
       float *Y = h->w.X32[(b + 1) & 1];
       {
-        TimedLaunch t(h, is_tail_slot(h, b) ? MDS_T_PANEL_TAIL : MDS_T_PANEL);
+        TimedLaunch t(h, MDS_T_PANEL);
         launch_reg_panel(h, s, b, X, h->w.M);
       }
       if (h->plan[b].rows_after > 0) {
         TimedLaunch t(h, MDS_T_TRAILING);
-        launch_trailing_lp(s, h->precision, N, h->nb, h->plan[b].rows_after, b, h->w.W, X, Y,
+        launch_trailing_lp(s, h->precision, N, h->nb, wmax, h->plan[b].rows_after, b, h->w.W, X, Y,
                            h->w.M, h->w.src, h->w.fst, h->w.panel_k0);
       }
     }
   }
   const bool fp64 = h->precision == MDS_FP64 || h->force64;
-  // the cooperative panel never passes nb columns, the others end on a 2x2
-  const int wmax = h->panel_coop ? h->nb : h->nb + 1;
   for (int b = 0; b < (fp64 && !h->panel_lds ? slots : 0); ++b) {
     // register panel: slot b reads buffer b%2 and writes its L and the
     // updated trailing matrix into the other buffer
@@ -405,7 +385,7 @@ void factor_launches(mds_handle *h, hipStream_t s) {
     if (h->panel_reg && (b & 1)) X = h->w.M2;
     if (h->panel_reg && !(b & 1)) Y = h->w.M2;
     {
-      TimedLaunch t(h, is_tail_slot(h, b) ? MDS_T_PANEL_TAIL : MDS_T_PANEL);
+      TimedLaunch t(h, MDS_T_PANEL);
       if (h->panel_reg)
         launch_reg_panel(h, s, b, (const double *)X, Y);
       else
@@ -432,7 +412,6 @@ void factor_launches(mds_handle *h, hipStream_t s) {
 // buffer of parity b % 2, which B copies into place before the rest of the
 // update (the next panel's output buffer is the one that update reads).
 // FP32 storage: they go straight to M, which no trailing update writes.
-// Register-panel tail slots run in order on A.
 void factor_launches_la(mds_handle *h, hipStream_t s) {
   const int N = h->N, nb = h->nb;
   const bool lowp = h->precision != MDS_FP64 && !h->force64;
@@ -465,70 +444,49 @@ void factor_launches_la(mds_handle *h, hipStream_t s) {
     float *X32 = buf32[p], *Y32 = buf32[q];
     const long left = h->plan[b].rows, rem = h->plan[b].rows_after;
     const bool more = rem > 0;
-    if (!is_tail_slot(h, b)) {
+    {
+      TimedLaunch t(h, MDS_T_PANEL, A);
+      if (lowp) {
+        PanelPrev pv{};
+        if (b > 0) pv = PanelPrev{nullptr, buf32[q], src[q], Wb[q], w.M, 1, -1};
+        launch_bk_panel_coop_la(A, (int)left, N, nb, h->alpha_bk, (const float *)X32, pv, w.M,
+                                src[p], Wb[p], w.dd, w.ds, w.ipiv, w.blk, w.fst, w.panel_k0,
+                                w.xch);
+      } else {
+        PanelPrev pv{};
+        if (b > 0) pv = PanelPrev{buf[q], nullptr, src[q], Wb[q], w.lst[q], 0, ~15};
+        launch_bk_panel_coop_la(A, (int)left, N, nb, h->alpha_bk, (const double *)X, pv,
+                                w.lst[p], src[p], Wb[p], w.dd, w.ds, w.ipiv, w.blk, w.fst,
+                                w.panel_k0, w.xch);
+      }
+    }
+    wait_far();
+    if (more) {
       {
-        TimedLaunch t(h, MDS_T_PANEL, A);
-        if (lowp) {
-          PanelPrev pv{};
-          if (b > 0) pv = PanelPrev{nullptr, buf32[q], src[q], Wb[q], w.M, 1, -1};
-          launch_bk_panel_coop_la(A, (int)left, N, nb, h->alpha_bk, (const float *)X32, pv, w.M,
-                                  src[p], Wb[p], w.dd, w.ds, w.ipiv, w.blk, w.fst, w.panel_k0,
-                                  w.xch);
-        } else {
-          PanelPrev pv{};
-          if (b > 0) pv = PanelPrev{buf[q], nullptr, src[q], Wb[q], w.lst[q], 0, ~15};
-          launch_bk_panel_coop_la(A, (int)left, N, nb, h->alpha_bk, (const double *)X, pv,
-                                  w.lst[p], src[p], Wb[p], w.dd, w.ds, w.ipiv, w.blk, w.fst,
-                                  w.panel_k0, w.xch);
-        }
+        TimedLaunch t(h, MDS_T_NEAR, A);
+        if (lowp)
+          launch_trailing_lp_part(A, h->precision, N, nb, rem, b, 1, 2 * h->la_cus, Wb[p], X32,
+                                  Y32, w.M, src[p], w.fst, w.panel_k0);
+        else
+          launch_bk_trailing_part(A, N, nb, rem, b, 1, 2 * h->la_cus, Wb[p], X, Y, w.lst[p],
+                                  src[p], w.fst, w.panel_k0);
       }
-      wait_far();
-      if (more) {
-        {
-          TimedLaunch t(h, MDS_T_NEAR, A);
-          if (lowp)
-            launch_trailing_lp_part(A, h->precision, N, nb, rem, b, 1, 2 * h->la_cus, Wb[p], X32,
-                                    Y32, w.M, src[p], w.fst, w.panel_k0);
-          else
-            launch_bk_trailing_part(A, N, nb, rem, b, 1, 2 * h->la_cus, Wb[p], X, Y, w.lst[p],
-                                    src[p], w.fst, w.panel_k0);
-        }
-        (void)hipEventRecord(ev_near, A);
-        (void)hipStreamWaitEvent(B, ev_near, 0);
-        if (!lowp) launch_lstage_copy(B, N, left, b, w.lst[p], Y, w.fst, w.panel_k0);
-        {
-          TimedLaunch t(h, MDS_T_TRAILING, B);
-          if (lowp)
-            launch_trailing_lp_part(B, h->precision, N, nb, rem, b, 2, h->la_grid, Wb[p], X32,
-                                    Y32, w.M, src[p], w.fst, w.panel_k0);
-          else
-            launch_bk_trailing_part(B, N, nb, rem, b, 2, h->la_grid, Wb[p], X, Y, w.lst[p],
-                                    src[p], w.fst, w.panel_k0);
-        }
-        (void)hipEventRecord(ev_far, B);
-        far_pending = true;
-      } else if (!lowp) {
-        launch_lstage_copy(A, N, left, b, w.lst[p], Y, w.fst, w.panel_k0);
-      }
-    } else {
-      wait_far();
+      (void)hipEventRecord(ev_near, A);
+      (void)hipStreamWaitEvent(B, ev_near, 0);
+      if (!lowp) launch_lstage_copy(B, N, left, b, w.lst[p], Y, w.fst, w.panel_k0);
       {
-        TimedLaunch t(h, MDS_T_PANEL_TAIL, A);
+        TimedLaunch t(h, MDS_T_TRAILING, B);
         if (lowp)
-          launch_bk_panel_reg_tail(A, (int)left, N, nb, h->alpha_bk, (const float *)X32, w.M,
-                                   w.src, w.W, w.dd, w.ds, w.ipiv, w.blk, w.fst, w.panel_k0);
+          launch_trailing_lp_part(B, h->precision, N, nb, rem, b, 2, h->la_grid, Wb[p], X32,
+                                  Y32, w.M, src[p], w.fst, w.panel_k0);
         else
-          launch_bk_panel_reg_tail(A, (int)left, N, nb, h->alpha_bk, (const double *)X, Y, w.src,
-                                   w.W, w.dd, w.ds, w.ipiv, w.blk, w.fst, w.panel_k0);
+          launch_bk_trailing_part(B, N, nb, rem, b, 2, h->la_grid, Wb[p], X, Y, w.lst[p],
+                                  src[p], w.fst, w.panel_k0);
       }
-      if (more) {
-        TimedLaunch t(h, MDS_T_TRAILING, A);
-        if (lowp)
-          launch_trailing_lp(A, h->precision, N, nb, rem, b, w.W, X32, Y32, w.M, w.src, w.fst,
-                             w.panel_k0);
-        else
-          launch_bk_trailing(A, N, nb, nb + 1, rem, b, w.W, X, Y, Y, w.src, w.fst, w.panel_k0);
-      }
+      (void)hipEventRecord(ev_far, B);
+      far_pending = true;
+    } else if (!lowp) {
+      launch_lstage_copy(A, N, left, b, w.lst[p], Y, w.fst, w.panel_k0);
     }
   }
   wait_far();
@@ -537,8 +495,8 @@ void factor_launches_la(mds_handle *h, hipStream_t s) {
 }
 
 // CU-masked streams of the look-ahead: A on `reserve` compute units (the same
-// count on every XCD: unit x + 8 j of XCD x, which is also XCD x when the
-// mask's bits are dealt to the XCDs in turn), B on the others.  Leaves the
+// count on every XCD, also when the mask's bits are dealt to the XCDs in
+// turn: m units of XCD x, a stride apart from unit x % stride on), B on the others.  Leaves the
 // look-ahead off when the device does not have 8 equal XCDs or a stream
 // cannot be made.
 void setup_lookahead(mds_handle *h) {
@@ -550,11 +508,12 @@ void setup_lookahead(mds_handle *h) {
   if (cus < 64 || cus % 8 != 0) return;
   const int r = bk_coop_la_reserve(h->N, cus);
   const int per = cus / 8, m = r / 8;
-  if (r == 0 || r % 8 != 0 || 7 + 8 * (m - 1) >= per) return;
+  if (r == 0 || per % m != 0) return;
+  const int stride = per / m;
   std::vector<uint32_t> ma((cus + 31) / 32, 0u), mb((cus + 31) / 32, 0u);
   for (int x = 0; x < 8; ++x)
     for (int j = 0; j < m; ++j) {
-      const int bit = per * x + x + 8 * j;
+      const int bit = per * x + x % stride + stride * j;
       ma[bit / 32] |= 1u << (bit % 32);
     }
   for (int bit = 0; bit < cus; ++bit)
@@ -1262,7 +1221,6 @@ int mds_create(mds_handle **out, const mds_dims *dims, const mds_options *opts, 
   h->nb = nb;
   h->panel_reg = pc.reg;
   h->panel_coop = pc.coop;
-  h->panel_tail = pc.tail;
   h->panel_lds = pc.lds;
   h->panel_threads = pc.threads;
   h->precision = prec;
@@ -1383,9 +1341,12 @@ int mds_create(mds_handle **out, const mds_dims *dims, const mds_options *opts, 
     delete h;
     return MDS_EHIP;
   }
-  // look-ahead: automatic from N = 8192 (below, the candidate columns it
-  // computes on the fly cost about what the overlap saves)
-  if (pc.coop && !coop_off && la_opt != 2 && (la_opt == 1 || h->N >= 8192)) setup_lookahead(h);
+  // look-ahead: only on request.  With speculative panels the panel is a
+  // quarter to half of the factorization and the trailing update, which uses
+  // every compute unit, loses more on the units the look-ahead reserves than
+  // the overlap saves (off / on: N = 4096 7.3 / 8.1 ms per Newton step, 9001
+  // 26.0 / 27.3, 16384 86 / 96; FP32 storage 10.8 / 11.7, 32.9 / 33.1, 88 / 93)
+  if (pc.coop && !coop_off && la_opt == 1) setup_lookahead(h);
   *out = h;
   return MDS_OK;
 }
@@ -2280,12 +2241,7 @@ int mds_get_inv_ds(mds_handle *h, double *inv_d_host) {
 int mds_get_info(const mds_handle *h, mds_info *out) {
   if (!h || !out) return MDS_ENULL;
   out->nb = h->nb;
-  // fewest columns a panel factors, the last panel aside (the register
-  // tail's 16-column tile factors 15)
-  int mw = h->adv;
-  for (size_t b = 0; b + 1 < h->plan.size(); ++b)
-    mw = (int)std::min<long>(mw, h->plan[b].rows - h->plan[b].rows_after);
-  out->min_width = mw;
+  out->min_width = h->adv;  // fewest columns a panel factors, the last panel aside
   out->panel = h->panel_lds ? 3 : h->panel_coop ? 2 : h->panel_reg ? 0 : 1;
   out->precision = h->precision;
   out->panel_threads = (h->panel_reg || h->panel_lds) ? h->panel_threads : 1024;

@@ -916,6 +916,7 @@ bool bk_coop_resident(int N) {
   return (long)per * cus >= P;
 }
 int bk_coop_nb() { return CNB; }
+int bk_coop_rows() { return CT; }
 int bk_coop_wgs(int N) { return (N + CT - 1) / CT; }
 
 // `rows` bounds the rows left at the panel's start (every earlier panel
@@ -972,14 +973,14 @@ void launch_bk_panel_coop_la(hipStream_t s, int rows, int N, int nb, double alph
                           panel_k0, xch);
 }
 
-// One panel workgroup per compute unit (each takes the whole register file),
-// so the reserved units must number at least the first panel's workgroups;
-// at least 32 (4 per XCD), since the near update runs on them too, and a
-// multiple of the XCD count so that every XCD keeps the same share.
+// One panel workgroup per compute unit (its LDS holds one), so the reserved
+// units must number at least the first panel's workgroups: 4 or 8 per XCD
+// (the near update runs on them too), so that every XCD keeps the same
+// share; no look-ahead when that is not enough (N > 16384 on 256 units).
 int bk_coop_la_reserve(int N, int cus) {
   const int P = bk_coop_wgs(N);
-  const int r = std::max(32, (P + 7) / 8 * 8);
-  return (r <= cus / 4) ? r : 0;
+  const int r = (P <= 32) ? 32 : 64;
+  return (P <= r && r <= cus / 4) ? r : 0;
 }
 
 }  // namespace mds

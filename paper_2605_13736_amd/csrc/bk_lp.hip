@@ -23,7 +23,7 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 typedef short s4 __attribute__((ext_vector_type(4)));
 
 constexpr int TT = 64;
-constexpr int TSL = 48;        // panel columns staged in LDS per chunk (multiple of 16)
+constexpr int TSL = 64;        // panel columns staged in LDS per chunk (multiple of 16)
 constexpr int TSL1 = TSL + 1;  // odd row stride of the staged panels
 constexpr int TSTL = TT * TSL / 256;  // staged entries per thread and panel
 constexpr int kTrailingLpGrid = kTileGrid;  // persistent form: 512 workgroups (2 per CU at <= 196 VGPRs)
@@ -211,7 +211,7 @@ __global__ __launch_bounds__(256) void k_trailing_lp(int N, int nb, const double
       }
 }
 
-// Persistent form of k_trailing_lp for panels of at most TSL - 1 columns
+// Persistent form of k_trailing_lp for panels of at most TSL columns
 // (one staging chunk): a grid of a few workgroups per compute unit walks the
 // tiles, loading the next tile's entries and panel rows while it computes
 // the current one.  Per entry the arithmetic is the one of k_trailing_lp.
@@ -259,7 +259,7 @@ __device__ inline void lp_load(int i0, int c0, bool diag, int N, int kend, int k
 }
 
 template <int MODE>
-__global__ __launch_bounds__(256) void k_trailing_lp_ps(int N, int nb,
+__global__ __launch_bounds__(256, 2) void k_trailing_lp_ps(int N, int nb,
                                                         const double *__restrict__ W,
                                                         const float *X, float *Y,
                                                         const double *__restrict__ Lsrc,
@@ -438,13 +438,13 @@ __global__ void k_vscale(int n, const double *__restrict__ s, double *__restrict
 
 }  // namespace
 
-void launch_trailing_lp(hipStream_t s, int mode, int N, int nb, long rem, int slot,
+void launch_trailing_lp(hipStream_t s, int mode, int N, int nb, int wmax, long rem, int slot,
                         const double *W, const float *X, float *Y, const double *Lsrc,
                         const int32_t *src, const FacState *st, const int32_t *panel_k0) {
   if (rem <= 0) return;
   const long nt = (rem + TT - 1) / TT;
   const long tiles = nt * (nt + 1) / 2;
-  if (nb + 1 <= TSL) {
+  if (wmax <= TSL) {
     // persistent: a few workgroups per compute unit walk the tiles
     const unsigned g = (unsigned)std::min(tiles, (long)kTrailingLpGrid);
     if (mode == 2)
@@ -467,7 +467,7 @@ void launch_trailing_lp_part(hipStream_t s, int mode, int N, int nb, long rem, i
                              int grid, const double *W, const float *X, float *Y,
                              const double *Lsrc, const int32_t *src, const FacState *st,
                              const int32_t *panel_k0) {
-  if (rem <= 0 || nb + 1 > TSL) return;
+  if (rem <= 0 || nb > TSL) return;
   const long nt = (rem + TT - 1) / TT;
   const long tiles = (part == 1) ? kNearTiles * nt
                      : (nt > kNearTiles) ? (nt - kNearTiles) * (nt - kNearTiles + 1) / 2 : 0;

@@ -75,13 +75,11 @@ struct PanelPrev {
 };
 
 // One slot of a factorization's launch sequence (one panel launch and its
-// trailing update): tail_nb 0 for the handle's panel kernel, else the tile
-// width of the register tail; rows bounds the rows left at the slot's start
-// and rows_after those left for its trailing update (the device's progress
-// is not known to the host; every panel factors at least its tile width - 1
-// columns unless the matrix ends).
+// trailing update): rows bounds the rows left at the slot's start and
+// rows_after those left for its trailing update (the device's progress is
+// not known to the host; every panel factors at least adv columns unless the
+// matrix ends).
 struct SlotPlan {
-  int tail_nb;
   long rows, rows_after;
 };
 
@@ -144,7 +142,6 @@ struct mds_handle {
   int mI = 0, mE = 0, nx = 0;  // inequality rows, equality rows, n + mI
   bool panel_reg = false;  // register-resident panel kernel (ping-pong layout)
   bool panel_coop = false; // ... spread over several workgroups
-  bool panel_tail = false; // ... with the register panel once its rows fit one workgroup
   bool panel_lds = false;  // whole M in one workgroup's LDS, unblocked
   const double *dcv_user = nullptr;  // caller's per-row diagonal subtracted from M22 (m)
   // general-NLP mode (mds_set_nlp): the model, the quadratic problem it
@@ -284,19 +281,6 @@ void launch_lstage_copy(hipStream_t s, int N, long rows, int slot, const double 
 // workgroup of `threads` = 512 or 1024
 int bk_reg_rows(int N, int threads);
 int bk_reg_nb(int N, int threads);
-// register panel over the last rows of a cooperative factorization (rows >=
-// N - k0, rows <= bk_reg_tail_rows(), nb <= 32); it factors at least
-// bk_reg_tail_nb(rows) - 1 columns per launch (unless the matrix ends)
-int bk_reg_tail_rows();
-int bk_reg_tail_nb(int rows);
-void launch_bk_panel_reg_tail(hipStream_t s, int rows, int N, int nb, double alpha,
-                              const double *X, double *Lout, int32_t *src_out, double *W,
-                              double *dd, double *ds, int32_t *ipiv, int32_t *blk, FacState *st,
-                              int32_t *panel_k0);
-void launch_bk_panel_reg_tail(hipStream_t s, int rows, int N, int nb, double alpha,
-                              const float *X, double *Lout, int32_t *src_out, double *W,
-                              double *dd, double *ds, int32_t *ipiv, int32_t *blk, FacState *st,
-                              int32_t *panel_k0);
 void launch_bk_panel_reg(hipStream_t s, int threads, int N, int nb, double alpha, const double *X,
                          double *Lout, int32_t *src_out, double *W, double *dd, double *ds,
                          int32_t *ipiv, int32_t *blk, FacState *st, int32_t *panel_k0);
@@ -310,6 +294,7 @@ void launch_bk_panel_reg(hipStream_t s, int threads, int N, int nb, double alpha
 // whether the device can hold every workgroup of the panel for order N at once
 bool bk_coop_resident(int N);
 int bk_coop_nb();
+int bk_coop_rows();  // rows (threads) of a workgroup
 int bk_coop_wgs(int N);
 // rows: at least the rows left at the panel's start (sizes the grid)
 // Exchange round-trip probe of the cooperative panel (P <= kProbeMaxP workgroups,
@@ -352,7 +337,7 @@ void launch_bk_lds(hipStream_t s, int threads, int N, double alpha, double *M, d
                    double *ds, int32_t *ipiv, int32_t *blk, int32_t *perm, FacState *st);
 
 // bk_lp.hip: FP32-storage trailing update (mode MDS_FP32 or MDS_BF16 products)
-void launch_trailing_lp(hipStream_t s, int mode, int N, int nb, long rem, int slot,
+void launch_trailing_lp(hipStream_t s, int mode, int N, int nb, int wmax, long rem, int slot,
                         const double *W, const float *X, float *Y, const double *Lsrc,
                         const int32_t *src, const FacState *st, const int32_t *panel_k0);
 // look-ahead parts (as launch_bk_trailing_part; Lsrc in place, not staged)

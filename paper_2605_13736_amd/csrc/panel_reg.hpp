@@ -126,7 +126,7 @@ __device__ inline void panel_reg_dev(int N, int nb, double alpha,
     if (tid == 0) st->xerr = 1;
     return;
   }
-  const int ld = N;  // N <= 20480 (a cooperative factorization's tail): offsets fit in 32 bits
+  const int ld = N;  // offsets fit in 32 bits
 
   double Lr[R][NB];
   // prefetched un-updated column values, kept in the storage type and
