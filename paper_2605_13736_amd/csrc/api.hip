@@ -394,8 +394,12 @@ void factor_launches(mds_handle *h, hipStream_t s) {
     }
     if (h->plan[b].rows_after > 0) {
       TimedLaunch t(h, MDS_T_TRAILING);
-      launch_bk_trailing(s, N, h->nb, wmax, h->plan[b].rows_after, b, h->w.W, X, Y, Y,
-                         h->panel_reg ? h->w.src : nullptr, h->w.fst, h->w.panel_k0);
+      if (h->panel_coop)
+        launch_bk_trailing_coop(s, N, h->plan[b].rows_after, b, 0, h->w.W, X, Y, Y, h->w.src,
+                                h->w.fst, h->w.panel_k0);
+      else
+        launch_bk_trailing(s, N, h->nb, h->plan[b].rows_after, b, h->w.W, X, Y, Y,
+                           h->panel_reg ? h->w.src : nullptr, h->w.fst, h->w.panel_k0);
     }
   }
 }
@@ -468,8 +472,8 @@ void factor_launches_la(mds_handle *h, hipStream_t s) {
           launch_trailing_lp_part(A, h->precision, N, nb, rem, b, 1, 2 * h->la_cus, Wb[p], X32,
                                   Y32, w.M, src[p], w.fst, w.panel_k0);
         else
-          launch_bk_trailing_part(A, N, nb, rem, b, 1, 2 * h->la_cus, Wb[p], X, Y, w.lst[p],
-                                  src[p], w.fst, w.panel_k0);
+          launch_bk_trailing_coop(A, N, rem, b, 1, Wb[p], X, Y, w.lst[p], src[p], w.fst,
+                                  w.panel_k0);
       }
       (void)hipEventRecord(ev_near, A);
       (void)hipStreamWaitEvent(B, ev_near, 0);
@@ -480,8 +484,8 @@ void factor_launches_la(mds_handle *h, hipStream_t s) {
           launch_trailing_lp_part(B, h->precision, N, nb, rem, b, 2, h->la_grid, Wb[p], X32,
                                   Y32, w.M, src[p], w.fst, w.panel_k0);
         else
-          launch_bk_trailing_part(B, N, nb, rem, b, 2, h->la_grid, Wb[p], X, Y, w.lst[p],
-                                  src[p], w.fst, w.panel_k0);
+          launch_bk_trailing_coop(B, N, rem, b, 2, Wb[p], X, Y, w.lst[p], src[p], w.fst,
+                                  w.panel_k0);
       }
       (void)hipEventRecord(ev_far, B);
       far_pending = true;
@@ -578,7 +582,7 @@ void factor_launches_mem(mds_handle *h, hipStream_t s) {
     }
     if ((long)N - (long)(b + 1) * nb > 0) {
       TimedLaunch t(h, MDS_T_TRAILING);
-      launch_bk_trailing(s, N, nb, nb + 1, (long)N - (long)(b + 1) * nb, b, h->w.W, h->w.M, h->w.M,
+      launch_bk_trailing(s, N, nb, (long)N - (long)(b + 1) * nb, b, h->w.W, h->w.M, h->w.M,
                          h->w.M, nullptr, h->w.fst, h->w.panel_k0);
     }
   }

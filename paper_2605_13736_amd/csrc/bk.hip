@@ -314,7 +314,6 @@ constexpr int TT = 64;
 static_assert(TT * kNearTiles == kNearCols, "near strip");
 constexpr int TS = 36;        // panel columns staged in LDS per chunk (multiple of 4)
 constexpr int TS1 = TS + 1;   // odd row stride of the staged panels
-constexpr int TSB = 64;       // ... of the persistent form for wide panels
 constexpr int TSTAGE = TT * TS / 256;  // staged entries per thread and panel
 constexpr int kTrailingGrid = kTileGrid;  // persistent trailing update: 512 workgroups (2 per CU at 194 VGPRs)
 static_assert(TT * TS % 256 == 0, "staging");
@@ -327,7 +326,7 @@ __global__ __launch_bounds__(256) void k_bk_trailing(int N, int nb, const double
                                                      const int32_t *__restrict__ src,
                                                      const FacState *__restrict__ st,
                                                      const int32_t *__restrict__ panel_k0,
-                                                     int slot, int part) {
+                                                     int slot) {
   // the staged panels: W rows c0.., L rows i0..
   __shared__ double s_buf[2 * TT * TS1];
   double *s_w = s_buf, *s_l = s_buf + TT * TS1;
@@ -341,19 +340,12 @@ __global__ __launch_bounds__(256) void k_bk_trailing(int N, int nb, const double
   // N is a multiple of 16); rows and columns below kend are masked
   const int a0 = kend & ~15;
   const int nt = (N - a0 + TT - 1) / TT;
-  // look-ahead's near strip (part 1): the first kNearTiles tile columns, the
-  // multipliers staged; otherwise triangular tile index -> (ti >= tj)
-  const int lk0 = (part == 1) ? 0 : k0;
+  // triangular tile index -> (ti >= tj)
   const int x = blockIdx.x;
   int ti = (int)((sqrt(8.0 * (double)x + 1.0) - 1.0) * 0.5);
   while ((ti + 1) * (ti + 2) / 2 <= x) ++ti;
   while (ti * (ti + 1) / 2 > x) --ti;
   int tj = x - ti * (ti + 1) / 2;
-  if (part == 1) {
-    tj = x / nt;
-    ti = x % nt;
-    if (tj >= kNearTiles || ti < tj) return;
-  }
   if (ti >= nt) return;
   const int i0 = a0 + ti * TT, c0 = a0 + tj * TT;
   const size_t ld = (size_t)N;
@@ -409,7 +401,7 @@ __global__ __launch_bounds__(256) void k_bk_trailing(int N, int nb, const double
       const int e = tid + 256 * u, r = e & (TT - 1), t = e >> 6;
       const int c = c0 + r, i = i0 + r;
       vw[u] = (t < tw && c >= kend && c < N) ? W[(size_t)c + (size_t)(tb + t) * ld] : 0.0;
-      vl[u] = (t < tw && i >= kend && i < N) ? Lsrc[(size_t)i + (size_t)(lk0 + tb + t) * ld] : 0.0;
+      vl[u] = (t < tw && i >= kend && i < N) ? Lsrc[(size_t)i + (size_t)(k0 + tb + t) * ld] : 0.0;
     }
 #pragma unroll
     for (int u = 0; u < TSTAGE; ++u) {
@@ -445,18 +437,163 @@ __global__ __launch_bounds__(256) void k_bk_trailing(int N, int nb, const double
       }
 }
 
+// 32-bit byte offsets from a uniform base
+__device__ inline double ldb(const double *p, unsigned off) {
+  return *(const double *)((const char *)p + off);
+}
+template <int TSC, bool IN>
+__device__ __forceinline__ void trailing_tile(int N, int kend, int jw, int lk0, int i0, int c0, bool diag,
+                                     const double *__restrict__ W, const double *X, double *Y,
+                                     const double *Lsrc, const int32_t *__restrict__ src,
+                                     double *s_w, double *s_l) {
+  constexpr int TS1 = TSC + 1, U = TT * TSC / 256;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int l16 = lane & 15, l4 = lane >> 4;
+  const int wc = c0 + (wv & 1) * 32, wi = i0 + (wv >> 1) * 32;
+  const unsigned st8 = (unsigned)N * 8u;
+  unsigned si[2], sc[2][4];
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    const int i = wi + b * 16 + l16;
+    si[b] = (IN || (i >= kend && i < N)) ? (unsigned)src[i] : 0u;
+  }
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int c = wc + a * 16 + l4 + 4 * r;
+      sc[a][r] = (IN || (c >= kend && c < N)) ? (unsigned)src[c] : 0u;
+    }
+  const int sr = tid & 63, stt = tid >> 6;
+  const bool won = IN || (c0 + sr >= kend && c0 + sr < N), lon = IN || (i0 + sr >= kend && i0 + sr < N);
+  const unsigned wof = (unsigned)(c0 + sr) * 8u + (unsigned)stt * st8;
+  const unsigned lof = (unsigned)(i0 + sr) * 8u + (unsigned)stt * st8;
+  const double *Lb = Lsrc + (size_t)lk0 * N;
+  double vw[U], vl[U];
+  auto stage_load = [&](int tb) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const double *Wu = W + (size_t)(tb + 4 * u) * N, *Lu = Lb + (size_t)(tb + 4 * u) * N;
+      const bool ton = tb + 4 * u + stt < jw;
+      vw[u] = (won && ton) ? ldb(Wu, wof) : 0.0;
+      vl[u] = (lon && ton) ? ldb(Lu, lof) : 0.0;
+    }
+  };
+  stage_load(0);
+  double xv[2][2][4];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const unsigned hi = max(si[b], sc[a][r]), lo = min(si[b], sc[a][r]);
+        const int c = wc + a * 16 + l4 + 4 * r, i = wi + b * 16 + l16;
+        const bool on = IN || (c >= kend && c < N && i < N && (!diag || i >= c));
+        xv[a][b][r] = on ? ldb(X, hi * 8u + __umul24(lo, st8)) : 0.0;
+      }
+  d4 acc[2][2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) acc[a][b] = d4{0.0, 0.0, 0.0, 0.0};
+  const double *wr[2], *lr[2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a) wr[a] = s_w + (wc - c0 + a * 16 + l16) * TS1 + l4;
+#pragma unroll
+  for (int b = 0; b < 2; ++b) lr[b] = s_l + (wi - i0 + b * 16 + l16) * TS1 + l4;
+  double *dw = s_w + sr * TS1 + stt, *dl = s_l + sr * TS1 + stt;
+  for (int tb = 0; tb < jw; tb += TSC) {
+    if (tb > 0) __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      dw[4 * u] = vw[u];
+      dl[4 * u] = vl[u];
+    }
+    __syncthreads();
+    if (tb + TSC < jw) stage_load(tb + TSC);
+#pragma unroll
+    for (int t0 = 0; t0 < TSC; t0 += 4) {
+      if (tb + t0 < jw) {
+        double av[2], bv[2];
+#pragma unroll
+        for (int a = 0; a < 2; ++a) av[a] = wr[a][t0];
+#pragma unroll
+        for (int b = 0; b < 2; ++b) bv[b] = lr[b][t0];
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+          for (int b = 0; b < 2; ++b)
+            acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], acc[a][b], 0, 0, 0);
+      }
+    }
+  }
+  const unsigned yof = (unsigned)(wi + l16) * 8u + (unsigned)(wc + l4) * st8;
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int c = wc + a * 16 + l4 + 4 * r, i = wi + b * 16 + l16;
+        if (IN || (c >= kend && c < N && i < N && (!diag || i >= c))) {
+          double *Yu = Y + (size_t)(a * 16 + 4 * r) * N + b * 16;
+          *(double *)((char *)Yu + yof) = xv[a][b][r] - acc[a][b][r];
+        }
+      }
+}
+
+// Trailing update after a cooperative panel (at most 64 columns): one 64 x 64
+// lower tile per workgroup.  At K = 64 a tile moves 64 KB of X and Y, and the
+// copy rate of the device (4.9 TB/s) allows a compute unit 3.4 us for that, its
+// matrix cores 1.7 us, so what counts is that nothing else takes longer: four
+// workgroups per compute unit overlap each other's latencies (LDS staging in
+// 16-column chunks, 128 VGPRs), interior tiles have no guards, and every
+// address is a uniform base plus a 32-bit byte offset (8 N^2 < 2^32).  The
+// persistent form spent as long on 64-bit addresses and guards as on its
+// memory traffic: N = 16384, 51 against 60 ms per factorization (3.65 TB/s);
+// 32-column chunks (4 workgroups, spills) 67 ms, the XCD super-tile order 52 ms.
+// part: 0 every tile, 1 and 2 the look-ahead's parts (multipliers staged).
+constexpr int TSC = 16;
+__global__ __launch_bounds__(256, 4) void k_bk_trailing_coop(int N, const double *__restrict__ W,
+                                                             const double *X, double *Y,
+                                                             const double *Lsrc,
+                                                             const int32_t *__restrict__ src,
+                                                             const FacState *__restrict__ st,
+                                                             const int32_t *__restrict__ panel_k0,
+                                                             int slot, int part) {
+  __shared__ double s_buf[2 * TT * (TSC + 1)];
+  double *s_w = s_buf, *s_l = s_buf + TT * (TSC + 1);
+  if (slot >= st->npanel) return;
+  const int k0 = panel_k0[slot], kend = panel_k0[slot + 1];
+  if (kend >= N || kend <= k0) return;
+  // tiles start at the 16-row (128-byte) boundary at or below kend; rows and
+  // columns below kend are masked
+  const int a0 = kend & ~15;
+  const int nt = (N - a0 + TT - 1) / TT;
+  int ti, tj;
+  if ((long)blockIdx.x >= part_slots(part, nt, false)) return;
+  if (!part_tile(part, blockIdx.x, nt, false, ti, tj)) return;
+  const int lk0 = (part == 0) ? k0 : 0;
+  const int i0 = a0 + ti * TT, c0 = a0 + tj * TT;
+  if (ti != tj && c0 >= kend && i0 + TT <= N)
+    trailing_tile<TSC, true>(N, kend, kend - k0, lk0, i0, c0, false, W, X, Y, Lsrc, src, s_w, s_l);
+  else
+    trailing_tile<TSC, false>(N, kend, kend - k0, lk0, i0, c0, ti == tj, W, X, Y, Lsrc, src, s_w,
+                              s_l);
+}
+
 // Persistent form of k_bk_trailing for panels of at most TS - 1 columns
 // (one staging chunk): a grid of a few workgroups per compute unit walks the
 // tiles in row-major triangular order, and while it computes one tile the
 // loads of its next tile (the entries it updates and the panel rows it
 // stages) are already in flight.  Per entry the arithmetic is the one of
 // k_bk_trailing, in the same order.
-template <int TSW>
 __device__ inline void tr_load(int i0, int c0, bool diag, int N, int kend, int lk0, int jw,
                                const double *__restrict__ W, const double *X,
                                const double *Lsrc, const int32_t *__restrict__ src,
-                               double (&xv)[2][2][4], double (&vw)[TT * TSW / 256],
-                               double (&vl)[TT * TSW / 256]) {
+                               double (&xv)[2][2][4], double (&vw)[TSTAGE],
+                               double (&vl)[TSTAGE]) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int l16 = lane & 15, l4 = lane >> 4;
   const size_t ld = (size_t)N;
@@ -488,7 +625,7 @@ __device__ inline void tr_load(int i0, int c0, bool diag, int N, int kend, int l
                           : 0.0;
       }
 #pragma unroll
-  for (int u = 0; u < TT * TSW / 256; ++u) {
+  for (int u = 0; u < TSTAGE; ++u) {
     const int e = tid + 256 * u, r = e & (TT - 1), t = e >> 6;
     const int c = c0 + r, i = i0 + r;
     vw[u] = (t < jw && c >= kend && c < N) ? W[(size_t)c + (size_t)t * ld] : 0.0;
@@ -497,43 +634,37 @@ __device__ inline void tr_load(int i0, int c0, bool diag, int N, int kend, int l
 }
 
 
-template <int TSW>
-__global__ __launch_bounds__(256, 2) void k_bk_trailing_ps(int N, int nb,
+__global__ __launch_bounds__(256) void k_bk_trailing_ps(int N, int nb,
                                                         const double *__restrict__ W,
                                                         const double *X, double *Y,
                                                         const double *Lsrc,
                                                         const int32_t *__restrict__ src,
                                                         const FacState *__restrict__ st,
                                                         const int32_t *__restrict__ panel_k0,
-                                                        int slot, int part) {
-  constexpr int TS1 = TSW + 1, TSTAGE = TT * TSW / 256;
+                                                        int slot) {
   __shared__ double s_buf[2 * TT * TS1];
   double *s_w = s_buf, *s_l = s_buf + TT * TS1;
   if (slot >= st->npanel) return;
   const int k0 = panel_k0[slot], kend = panel_k0[slot + 1];
-  if (kend >= N || kend <= k0 || kend - k0 > nb + 1 || kend - k0 > TSW) return;
+  if (kend >= N || kend <= k0 || kend - k0 > nb + 1 || kend - k0 > TS) return;
   const int jw = kend - k0;
-  // the look-ahead parts read the panel's multipliers from its staging buffer
-  const int lk0 = (part == 0) ? k0 : 0;
   const int a0 = kend & ~15;
   const int nt = (N - a0 + TT - 1) / TT;
   // plain row-major order: measured at N = 16384, the super-tile order of
   // tile_order.hpp cut this kernel's fetched bytes by 17% but made it 3.5%
-  // slower (188.8 against 182.4 us per launch), and as the look-ahead's rest
-  // of the update 4% slower (113.0 against 108.5 ms per factorization); the
-  // FP32 update keeps it
+  // slower (188.8 against 182.4 us per launch); the FP32 update keeps it
   const bool xcd = false;
-  const long nslots = part_slots(part, nt, xcd);
+  const long nslots = tile_slots(nt, xcd);
   const size_t ld = (size_t)N;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int l16 = lane & 15, l4 = lane >> 4;
   // first slot of this workgroup that holds a tile
   long x = blockIdx.x;
   int ti = 0, tj = 0;
-  while (x < nslots && !part_tile(part, x, nt, xcd, ti, tj)) x += gridDim.x;
+  while (x < nslots && !tile_of(x, nt, xcd, ti, tj)) x += gridDim.x;
   if (x >= nslots) return;
   double xn[2][2][4], vwn[TSTAGE], vln[TSTAGE];
-  tr_load<TSW>(a0 + ti * TT, a0 + tj * TT, ti == tj, N, kend, lk0, jw, W, X, Lsrc, src, xn, vwn, vln);
+  tr_load(a0 + ti * TT, a0 + tj * TT, ti == tj, N, kend, k0, jw, W, X, Lsrc, src, xn, vwn, vln);
   while (x < nslots) {
     const int i0 = a0 + ti * TT, c0 = a0 + tj * TT;
     const bool diag = (ti == tj);
@@ -547,7 +678,7 @@ __global__ __launch_bounds__(256, 2) void k_bk_trailing_ps(int N, int nb,
         for (int r = 0; r < 4; ++r) xv[a][b][r] = xn[a][b][r];
     __syncthreads();  // the previous tile is done with the staging buffer
 #pragma unroll
-    for (int u = 0; u < TT * TSW / 256; ++u) {
+    for (int u = 0; u < TSTAGE; ++u) {
       const int e = tid + 256 * u, r = e & (TT - 1), t = e >> 6;
       s_w[r * TS1 + t] = vwn[u];
       s_l[r * TS1 + t] = vln[u];
@@ -556,9 +687,9 @@ __global__ __launch_bounds__(256, 2) void k_bk_trailing_ps(int N, int nb,
     // the next slot that holds a tile, its loads in flight during this one
     long xnext = x + gridDim.x;
     int tin = 0, tjn = 0;
-    while (xnext < nslots && !part_tile(part, xnext, nt, xcd, tin, tjn)) xnext += gridDim.x;
+    while (xnext < nslots && !tile_of(xnext, nt, xcd, tin, tjn)) xnext += gridDim.x;
     if (xnext < nslots)
-      tr_load<TSW>(a0 + tin * TT, a0 + tjn * TT, tin == tjn, N, kend, lk0, jw, W, X, Lsrc, src, xn, vwn,
+      tr_load(a0 + tin * TT, a0 + tjn * TT, tin == tjn, N, kend, k0, jw, W, X, Lsrc, src, xn, vwn,
               vln);
     d4 acc[2][2];
 #pragma unroll
@@ -623,7 +754,7 @@ void launch_bk_panel(hipStream_t s, int N, int nb, double alpha, double *M, doub
   k_bk_panel<<<1, NT, 0, s>>>(N, nb, alpha, M, W, dd, ds, ipiv, blk, st, panel_k0);
 }
 
-void launch_bk_trailing(hipStream_t s, int N, int nb, int wmax, long rem, int slot, const double *W,
+void launch_bk_trailing(hipStream_t s, int N, int nb, long rem, int slot, const double *W,
                         const double *X, double *Y, const double *Lsrc, const int32_t *src,
                         const FacState *st, const int32_t *panel_k0) {
   // rem bounds the rows of the trailing matrix after slot `slot`; the
@@ -631,39 +762,27 @@ void launch_bk_trailing(hipStream_t s, int N, int nb, int wmax, long rem, int sl
   if (rem <= 0) return;
   const long nt = (rem + 15 + TT - 1) / TT;
   const long tiles = nt * (nt + 1) / 2;
-  // persistent: a few workgroups per compute unit walk the tiles
-  const unsigned grid = (unsigned)std::min(tiles, (long)kTrailingGrid);
-  if (wmax <= TS) {
-    k_bk_trailing_ps<TS><<<grid, 256, 0, s>>>(N, nb, W, X, Y, Lsrc, src, st, panel_k0, slot, 0);
-  } else if (wmax <= TSB) {
-    k_bk_trailing_ps<TSB><<<grid, 256, 0, s>>>(N, nb, W, X, Y, Lsrc, src, st, panel_k0, slot, 0);
+  if (nb + 1 <= TS) {
+    // persistent: a few workgroups per compute unit walk the tiles
+    const long grid = std::min(tiles, (long)kTrailingGrid);
+    k_bk_trailing_ps<<<(unsigned)grid, 256, 0, s>>>(N, nb, W, X, Y, Lsrc, src, st, panel_k0, slot);
   } else {
-    k_bk_trailing<<<(unsigned)tiles, 256, 0, s>>>(N, nb, W, X, Y, Lsrc, src, st, panel_k0, slot,
-                                                  0);
+    k_bk_trailing<<<(unsigned)tiles, 256, 0, s>>>(N, nb, W, X, Y, Lsrc, src, st, panel_k0, slot);
   }
 }
 
-void launch_bk_trailing_part(hipStream_t s, int N, int nb, long rem, int slot, int part, int grid,
-                             const double *W, const double *X, double *Y, const double *Lsrc,
-                             const int32_t *src, const FacState *st, const int32_t *panel_k0) {
-  if (rem <= 0 || nb > TSB) return;
+void launch_bk_trailing_coop(hipStream_t s, int N, long rem, int slot, int part, const double *W,
+                             const double *X, double *Y, const double *Lsrc, const int32_t *src,
+                             const FacState *st, const int32_t *panel_k0) {
+  if (rem <= 0) return;
   const long nt = (rem + 15 + TT - 1) / TT;
-  const long tiles = (part == 1) ? kNearTiles * nt
-                     : (nt > kNearTiles) ? (nt - kNearTiles) * (nt - kNearTiles + 1) / 2 : 0;
+  const long tiles = (part == 1)          ? kNearTiles * nt
+                     : (part == 0)        ? nt * (nt + 1) / 2
+                     : (nt > kNearTiles) ? (nt - kNearTiles) * (nt - kNearTiles + 1) / 2
+                                          : 0;
   if (tiles <= 0) return;
-  if (part == 1) {
-    // one tile per workgroup (104 VGPRs: more workgroups per compute unit
-    // than the persistent form's two)
-    k_bk_trailing<<<(unsigned)tiles, 256, 0, s>>>(N, nb, W, X, Y, Lsrc, src, st, panel_k0, slot, 1);
-    return;
-  }
-  const long g = std::min(tiles, (long)std::max(grid, 1));
-  if (nb <= TS)
-    k_bk_trailing_ps<TS><<<(unsigned)g, 256, 0, s>>>(N, nb, W, X, Y, Lsrc, src, st, panel_k0, slot,
+  k_bk_trailing_coop<<<(unsigned)tiles, 256, 0, s>>>(N, W, X, Y, Lsrc, src, st, panel_k0, slot,
                                                      part);
-  else
-    k_bk_trailing_ps<TSB><<<(unsigned)g, 256, 0, s>>>(N, nb, W, X, Y, Lsrc, src, st, panel_k0,
-                                                      slot, part);
 }
 
 void launch_lstage_copy(hipStream_t s, int N, long rows, int slot, const double *Lst, double *Lout,
@@ -671,7 +790,7 @@ void launch_lstage_copy(hipStream_t s, int N, long rows, int slot, const double 
   // rows: the rows at the panel's start, at most
   if (rows <= 0) return;
   const unsigned gx = (unsigned)std::min<long>((rows + 1023) / 1024, 64);
-  k_lstage_copy<<<dim3(gx, (unsigned)TSB), 256, 0, s>>>(N, Lst, Lout, st, panel_k0, slot);
+  k_lstage_copy<<<dim3(gx, 64u), 256, 0, s>>>(N, Lst, Lout, st, panel_k0, slot);
 }
 
 }  // namespace mds

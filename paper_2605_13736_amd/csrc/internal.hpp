@@ -261,17 +261,16 @@ void launch_bk_panel(hipStream_t s, int N, int nb, double alpha, double *M, doub
                      int32_t *panel_k0);
 // rem: an upper bound of the rows of the trailing matrix after the panel of
 // slot `slot` (sizes the grid; 0 or less: nothing to update)
-// wmax: the widest panel possible (at most nb + 1)
-void launch_bk_trailing(hipStream_t s, int N, int nb, int wmax, long rem, int slot, const double *W,
+void launch_bk_trailing(hipStream_t s, int N, int nb, long rem, int slot, const double *W,
                         const double *X, double *Y, const double *Lsrc, const int32_t *src,
                         const FacState *st, const int32_t *panel_k0);
-// look-ahead parts of the trailing update of slot `slot` (nb + 1 <= 36):
-// part 1 the near strip (the first 64-column tile column), part 2 the rest;
-// both persistent over at most `grid` workgroups; Lsrc holds the
-// panel's multipliers staged (row i, column t at Lsrc[i + t N])
-void launch_bk_trailing_part(hipStream_t s, int N, int nb, long rem, int slot, int part, int grid,
-                             const double *W, const double *X, double *Y, const double *Lsrc,
-                             const int32_t *src, const FacState *st, const int32_t *panel_k0);
+// ... after a cooperative panel (at most 64 columns, src not null); part 0
+// the whole update, 1 and 2 the look-ahead's: the near strip (the first
+// kNearTiles tile columns) and the rest, with Lsrc the panel's staged
+// multipliers (row i, column t at Lsrc[i + t N])
+void launch_bk_trailing_coop(hipStream_t s, int N, long rem, int slot, int part, const double *W,
+                             const double *X, double *Y, const double *Lsrc, const int32_t *src,
+                             const FacState *st, const int32_t *panel_k0);
 // staged multipliers of slot `slot` into their place in Lout (columns
 // k0 .. kend - 1, rows below the diagonal)
 void launch_lstage_copy(hipStream_t s, int N, long rows, int slot, const double *Lst, double *Lout,
