@@ -600,7 +600,7 @@ typedef struct {
 } mds_batch_result;
 
 typedef struct {
-  int32_t nb;         /* panel width, 2..16 (0: 16)                              */
+  int32_t nb;         /* panel width, 2..16 (0: 16); FP64 panels hold 4 nb columns */
   int32_t grid;       /* persistent workgroups = scratch slots (0: min(count, 256)) */
   int32_t use_graph;  /* 0: plain launches; otherwise replay a captured hipGraph */
   int32_t precision;  /* MDS_FP64 (0, default) or MDS_FP32: equilibrated S M S

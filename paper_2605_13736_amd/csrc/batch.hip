@@ -3,8 +3,10 @@
 // problems from an atomic queue (largest first) and runs the whole Newton
 // system for each inside the workgroup:
 //   condense (same IEEE sequence as condense.hip, so M is bit-identical),
-//   blocked Bunch-Kaufman (panel::panel_reg_dev + per-wave trailing tiles on
-//   FP64 MFMA, ping-pong buffers), inertia correction (Algorithm IC),
+//   blocked Bunch-Kaufman (FP64: speculative panels of 4 nb <= 64 columns,
+//   per-wave 64 x 64 trailing tiles on FP64 MFMA; mixed precision:
+//   panel::panel_reg_dev of nb columns; ping-pong buffers), inertia
+//   correction (Algorithm IC),
 //   LDL' solve in the panels' own row frames, back-substitution of dx_s.
 // Each workgroup owns one slot of scratch buffers sized for the largest
 // problem.  The host captures the queue reset and the kernel in a hipGraph and
@@ -96,11 +98,12 @@ struct ResultDev {
 };
 
 // ---- condensation (bit-identical to k_condense_dense / k_condense_schur) ----
-__device__ __attribute__((noinline)) void condense_wg(const ProbDev &P, double *inv_d, double dw, double dc, double *M) {
+__device__ __attribute__((noinline)) void condense_wg(const ProbDev &P, double *inv_d, double dw, double dc, double *M, bool full) {
   const int tid = threadIdx.x, nd = P.nd, m = P.m, N = nd + m;
   for (int k = tid; k < P.ns; k += BT) inv_d[k] = 1.0 / (P.dsbase[k] + dw);
+  // the FP64 factorization reads the lower triangle only
   for (int j = 0; j < N; ++j)
-  for (int i = tid; i < N; i += BT) {
+  for (int i = (full ? 0 : j & ~63) + tid; i < N; i += BT) {
     double v;
     if (i < nd && j < nd) {
       v = P.H[(size_t)i + (size_t)j * nd];
@@ -127,7 +130,7 @@ __device__ __attribute__((noinline)) void condense_wg(const ProbDev &P, double *
         double acc = M[pos];
         acc = acc - (P.cval[e] * dk) * jrk;
         M[pos] = acc;
-        if (i != r) M[(size_t)(nd + r) + (size_t)(nd + i) * N] = acc;
+        if (full && i != r) M[(size_t)(nd + r) + (size_t)(nd + i) * N] = acc;
       }
     }
     const size_t dpos = (size_t)(nd + r) + col;
@@ -136,10 +139,7 @@ __device__ __attribute__((noinline)) void condense_wg(const ProbDev &P, double *
   __syncthreads();
 }
 
-// ---- trailing update: every wave takes 32 x 32 lower tiles on its own --------
-// D[c][i] = sum_t W[c, t] L[i, t]; Y(i, c) = X(src i, src c) - D[c][i] for the
-// lower tile only (every reader takes entries above the diagonal from the
-// lower triangle).
+// ---- global-memory pointers of the workgroup phases ----------------------------
 typedef __attribute__((address_space(1))) const double gdouble;
 typedef __attribute__((address_space(1))) const float gfloat;
 typedef __attribute__((address_space(1))) const int32_t gint;
@@ -153,91 +153,564 @@ __device__ inline unsigned long long ubase(const void *p) {
   const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32));
   return ((unsigned long long)hi << 32) | lo;
 }
-__device__ __attribute__((noinline)) void trailing_wg(int N, int k0, int kend, const double *W, const double *X, double *Y,
-                            const int32_t *src, const double *zero, double (*s_t)[TW + 1]) {
-  // The FP64 tiles keep guarded loads: with the zero-block loads of the FP32
-  // tiles below, the FP64 batch measured 7% slower (its traffic is twice the
-  // FP32 tiles' and the extra loads in flight did not pay).
-  (void)zero;
+
+// ---- FP64: speculative panel of up to 64 columns, multipliers in memory ----------
+// The workgroup's panel as in the cooperative panel (bk_coop.hip): 16-column
+// blocks factored as if every pivot passed the first Bunch-Kaufman test, each
+// row checking its own entries; the columns before the first failure stand
+// and the failing pivot is taken by a full step.  One workgroup holds all
+// rows, so nothing is exchanged, and at up to 2048 rows neither registers nor
+// LDS hold 64 columns: L and W = L D live in memory (L in Y, column t at
+// (k0 + t) N, W at t N), in logical row order (an interchange swaps their
+// rows), and every block reads the ones before it once, as MFMA operands.
+// X keeps its physical order, s.map takes a logical position (less k0) to it.
+// Wave 0 factors the 16 x 16 diagonal block while the others bring their
+// first 64 rows up to date.
+constexpr int SB = 16;        // columns of a block
+constexpr int SNB = 64;       // most columns of a panel
+constexpr int SWL = SNB + 2;  // stride of a window row
+struct PanelLds {
+  double lw[SB * SWL], ww[SB * SWL];  // L and W rows of the block's positions
+  double u[4][10];                    // pivots' reciprocals and W entries, per four columns
+  double aw[4][64];                   // -W of the diagonal block, MFMA operand
+  double dn[SB];                      // its D
+  double wk[SNB], wi[SNB];
+  double cv[NWAVE], akk, aii, wki;
+  int ci[NWAVE], fail;
+  int map[BMAX_N];
+};
+
+// one per workgroup; a function so that its accesses stay LDS accesses in the
+// out-of-line phases (a reference passed to them would make them flat)
+__device__ __forceinline__ PanelLds &panel_lds() {
+  __shared__ PanelLds l;
+  return l;
+}
+
+__device__ inline void spec_load(gdouble *gX, const PanelLds &s, int N, int k0, int jb, int r0,
+                                 int ce, int gi, d4 (&acc)[4]) {
+  const int lane = threadIdx.x & 63, l16 = lane & 15, l4 = lane >> 4;
+  int pr[4], pc[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) pr[q] = s.map[min(64 * gi + 16 * q + l16, N - 1 - k0)];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int c = l4 + 4 * r;
+    pc[r] = s.map[jb + min(max(c, r0), ce - 1)];
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      acc[q][r] = gX[(unsigned)(max(pr[q], pc[r]) + min(pr[q], pc[r]) * N)];
+}
+
+// acc -= W(block, :) L(rows, :)' over the panel's first j columns
+__device__ inline void spec_update(gdouble *gY, const PanelLds &s, int N, int k0, int j, int r0,
+                                   int ce, int gi, d4 (&acc)[4]) {
+  const int lane = threadIdx.x & 63, l16 = lane & 15, l4 = lane >> 4;
+  const bool wc = l16 >= r0 && l16 < ce;
+  unsigned row[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) row[q] = (unsigned)min(k0 + 64 * gi + 16 * q + l16, N - 1);
+  for (int t0 = 0; t0 < j; t0 += 16) {
+    double bl[4][4];
+#pragma unroll
+    for (int z = 0; z < 4; ++z) {
+      const int t = min(t0 + 4 * z + l4, j - 1);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) bl[z][q] = gY[row[q] + (unsigned)((k0 + t) * N)];
+    }
+#pragma unroll
+    for (int z = 0; z < 4; ++z) {
+      if (t0 + 4 * z < j) {
+        const int t = t0 + 4 * z + l4;
+        const bool on = t < j;
+        const double aw = (on && wc) ? -s.ww[l16 * SWL + t] : 0.0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(aw, on ? bl[z][q] : 0.0, acc[q], 0, 0, 0);
+      }
+    }
+  }
+}
+
+// Diagonal block (one wave): L D L' of the block's 16 x 16 window, four
+// columns at a time; its scalars and MFMA operands go to LDS.
+__device__ inline void spec_diag(gdouble *gX, PanelLds &s, int N, int k0, int jb, int j, int r0,
+                                 int ce) {
+  const int lane = threadIdx.x & 63, l16 = lane & 15, l4 = lane >> 4;
+  const bool wc = l16 >= r0 && l16 < ce;
+  d4 dacc;
+  const int pi = s.map[jb + min(max(l16, r0), ce - 1)];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int c = l4 + 4 * r;
+    const int pc = s.map[jb + min(max(c, r0), ce - 1)];
+    const double v = gX[(unsigned)(max(pi, pc) + min(pi, pc) * N)];
+    dacc[r] = (wc && c >= r0 && c < ce && l16 >= c) ? v : 0.0;
+  }
+  for (int t0 = 0; t0 < j; t0 += 4) {
+    const int t = t0 + l4;
+    const bool on = t < j && wc;
+    const double aw = on ? -s.ww[l16 * SWL + t] : 0.0, dl = on ? s.lw[l16 * SWL + t] : 0.0;
+    dacc = __builtin_amdgcn_mfma_f64_16x16x4f64(aw, dl, dacc, 0, 0, 0);
+  }
+  int ff = ce;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    if (4 * u + 3 >= r0 && 4 * u < ce && ff == ce) {
+      bool on[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) on[q] = 4 * u + q >= r0 && 4 * u + q < ce;
+      const double m00 = wave::lane_read(dacc[u], 4 * u);
+      const double m10 = wave::lane_read(dacc[u], 4 * u + 1);
+      const double m20 = wave::lane_read(dacc[u], 4 * u + 2);
+      const double m30 = wave::lane_read(dacc[u], 4 * u + 3);
+      double m11 = wave::lane_read(dacc[u], 4 * u + 17);
+      double m21 = wave::lane_read(dacc[u], 4 * u + 18);
+      double m31 = wave::lane_read(dacc[u], 4 * u + 19);
+      double m22 = wave::lane_read(dacc[u], 4 * u + 34);
+      double m32 = wave::lane_read(dacc[u], 4 * u + 35);
+      double m33 = wave::lane_read(dacc[u], 4 * u + 51);
+      const double rd0 = on[0] ? 1.0 / m00 : 0.0;
+      const double l10 = m10 * rd0, l20 = m20 * rd0, l30 = m30 * rd0;
+      const double w10 = l10 * m00, w20 = l20 * m00, w30 = l30 * m00;
+      m11 = fma(-l10, w10, m11);
+      m21 = fma(-l20, w10, m21);
+      m31 = fma(-l30, w10, m31);
+      m22 = fma(-l20, w20, m22);
+      m32 = fma(-l30, w20, m32);
+      m33 = fma(-l30, w30, m33);
+      const double rd1 = on[1] ? 1.0 / m11 : 0.0;
+      const double l21 = m21 * rd1, l31 = m31 * rd1;
+      const double w21 = l21 * m11, w31 = l31 * m11;
+      m22 = fma(-l21, w21, m22);
+      m32 = fma(-l31, w21, m32);
+      m33 = fma(-l31, w31, m33);
+      const double rd2 = on[2] ? 1.0 / m22 : 0.0;
+      const double l32 = m32 * rd2, w32 = l32 * m22;
+      m33 = fma(-l32, w32, m33);
+      const double rd3 = on[3] ? 1.0 / m33 : 0.0;
+      const double down = wave::sel4(l4, m00, m11, m22, m33);
+      const bool onw = 4 * u + l4 >= r0 && 4 * u + l4 < ce;
+      double o[4];
+      wave::rows4(dacc[u], o);
+      const double l0 = o[0] * rd0;
+      const double l1 = fma(-l0, w10, o[1]) * rd1;
+      const double l2 = fma(-l1, w21, fma(-l0, w20, o[2])) * rd2;
+      const double l3 = fma(-l2, w32, fma(-l1, w31, fma(-l0, w30, o[3]))) * rd3;
+      const double lo = (l16 > 4 * u + l4 && l16 < ce && onw) ? wave::sel4(l4, l0, l1, l2, l3) : 0.0;
+      const double aw = -(lo * (onw ? down : 0.0));
+      if (4 * u + 4 < ce) dacc = __builtin_amdgcn_mfma_f64_16x16x4f64(aw, lo, dacc, 0, 0, 0);
+      s.aw[u][lane] = aw;
+      if (l16 == 0) s.dn[4 * u + l4] = down;
+      if (lane == 0) {
+        const double v[10] = {rd0, rd1, rd2, rd3, w10, w20, w30, w21, w31, w32};
+#pragma unroll
+        for (int z = 0; z < 10; ++z) s.u[u][z] = v[z];
+      }
+      const unsigned long long bad = __ballot(onw && !(fabs(down) > 0.0));
+      if (bad != 0)
+        ff = 4 * u + ((bad & 0xffffull) ? 0 : (bad & 0xffff0000ull) ? 1
+                      : (bad & 0xffff00000000ull) ? 2 : 3);
+    }
+  }
+  if (lane == 0 && ff < ce) atomicMin(&s.fail, ff);
+}
+
+// Forward substitution of 64 rows over the block: L and W written, first
+// failing column in ff.
+__device__ inline void spec_rows(gdouble_out *oY, gdouble_out *oW, const PanelLds &s, int N, int k0,
+                                 int jb, int r0, int ce, double alpha, int gi, d4 (&acc)[4],
+                                 int &ff) {
+  const int lane = threadIdx.x & 63, l16 = lane & 15, l4 = lane >> 4;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    if (4 * u + 3 >= r0 && 4 * u < ff) {
+      const double rd0 = s.u[u][0], rd1 = s.u[u][1], rd2 = s.u[u][2], rd3 = s.u[u][3];
+      const double w10 = s.u[u][4], w20 = s.u[u][5], w30 = s.u[u][6], w21 = s.u[u][7],
+                   w31 = s.u[u][8], w32 = s.u[u][9];
+      const double aw = s.aw[u][lane], down = s.dn[4 * u + l4], dabs = fabs(down);
+      const bool onw = 4 * u + l4 >= r0 && 4 * u + l4 < ce;
+      const int col = k0 + jb + 4 * u + l4;
+      const bool more = 4 * u + 4 < ce;
+      unsigned long long bad = 0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        double o[4];
+        wave::rows4(acc[q][u], o);
+        const double l0 = o[0] * rd0;
+        const double x1 = fma(-l0, w10, o[1]);
+        const double l1 = x1 * rd1;
+        const double x2 = fma(-l1, w21, fma(-l0, w20, o[2]));
+        const double l2 = x2 * rd2;
+        const double x3 = fma(-l2, w32, fma(-l1, w31, fma(-l0, w30, o[3])));
+        const double l3 = x3 * rd3;
+        const double wr = wave::sel4(l4, o[0], x1, x2, x3);
+        const double lr = wave::sel4(l4, l0, l1, l2, l3);
+        const int row = k0 + 64 * gi + 16 * q + l16;
+        const bool act = onw && row < N && row > col;
+        bad |= __ballot(act && !(dabs >= alpha * fabs(wr)));
+        if (act) {
+          oY[(unsigned)(row + col * N)] = lr;
+          oW[(unsigned)(row + (jb + 4 * u + l4) * N)] = lr * down;
+        }
+        if (more)
+          acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(aw, onw ? lr : 0.0, acc[q], 0, 0, 0);
+      }
+      if (bad != 0)
+        ff = min(ff, 4 * u + ((bad & 0xffffull) ? 0 : (bad & 0xffff0000ull) ? 1
+                              : (bad & 0xffff00000000ull) ? 2 : 3));
+    }
+  }
+}
+
+// One panel of at most nbw columns from k0 on; returns its end (in every
+// thread) and records it in S.st and S.pk0.
+__device__ __attribute__((noinline)) int panel_spec_wg(int N, int k0, int nbw, double alpha,
+                                                       const double *X, double *Y,
+                                                       const SlotDev &S) {
+  PanelLds &s = panel_lds();
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  gdouble *gX = (gdouble *)ubase(X), *gY = (gdouble *)ubase(Y), *gW = (gdouble *)ubase(S.W);
+  gdouble_out *oY = (gdouble_out *)ubase(Y), *oW = (gdouble_out *)ubase(S.W);
+  for (int x = tid; x < N - k0; x += BT) s.map[x] = k0 + x;
+  __syncthreads();
+  int k = k0, j = 0, slow = 0, cool = 0;
+  int c_pos = 0, c_zero = 0, c_neg = 0, c_2x2 = 0, first_zero = 0;
+  while (j < nbw && k < N) {
+    if (slow == 0) {
+      const int jb = j & ~(SB - 1), r0 = j - jb;
+      const int len = min(min(SB - r0, nbw - j), N - k), ce = r0 + len;
+      for (int e = tid; e < SB * j; e += BT) {
+        const int q = e & (SB - 1), t = e >> 4, row = k0 + jb + q;
+        if (row < N) {
+          s.lw[q * SWL + t] = gY[(unsigned)(row + (k0 + t) * N)];
+          s.ww[q * SWL + t] = gW[(unsigned)(row + t * N)];
+        }
+      }
+      if (tid == 0) s.fail = ce;
+      __syncthreads();
+      const int ng = (N - k0 + 63) >> 6;
+      int gi = ((k - k0) >> 6) + ((wv + NWAVE - 1) & (NWAVE - 1));
+      d4 acc[4];
+      if (wv == 0) {
+        spec_diag(gX, s, N, k0, jb, j, r0, ce);
+      } else if (gi < ng) {
+        spec_load(gX, s, N, k0, jb, r0, ce, gi, acc);
+        spec_update(gY, s, N, k0, j, r0, ce, gi, acc);
+      }
+      __syncthreads();
+      int ff = s.fail;
+      for (bool pre = wv != 0; gi < ng; gi += NWAVE, pre = false) {
+        if (!pre) {
+          spec_load(gX, s, N, k0, jb, r0, ce, gi, acc);
+          spec_update(gY, s, N, k0, j, r0, ce, gi, acc);
+        }
+        spec_rows(oY, oW, s, N, k0, jb, r0, ce, alpha, gi, acc, ff);
+      }
+      if (lane == 0 && ff < ce) atomicMin(&s.fail, ff);
+      __syncthreads();
+      const int a = s.fail - r0;
+      if (wv == 0) {
+        double d = 0.0;
+        if (lane < a) {
+          d = s.dn[r0 + lane];
+          S.dd[k + lane] = d;
+          S.ds[k + lane] = 0.0;
+          S.ipiv[k + lane] = k + lane + 1;
+          S.blk[k + lane] = 1;
+        }
+        c_pos += __popcll(__ballot(lane < a && d > 0.0));
+        c_neg += __popcll(__ballot(lane < a && d < 0.0));
+      }
+      j += a;
+      k += a;
+      if (a < len) {
+        cool = (a == 0) ? min(2 * cool + 1, 15) : 0;
+        slow = 1 + (cool >> 1);
+      } else {
+        cool = 0;
+      }
+      __syncthreads();
+      continue;
+    }
+    // ---- full pivot step -------------------------------------------------------
+    if (j >= nbw - 1) break;  // no room for a 2x2
+    --slow;
+    const int nr = (N - k + BT - 1) / BT;  // rows of this thread: k + tid + BT r
+    // updated column of logical position c, whose W row is in w
+    auto column = [&](int c, const double *w, double (&v)[BR]) {
+      const int pc = s.map[c - k0];
+#pragma unroll
+      for (int r = 0; r < BR; ++r) {
+        const int x = k + tid + BT * r;
+        v[r] = 0.0;
+        if (r < nr && x < N) {
+          const int px = s.map[x - k0];
+          v[r] = gX[(unsigned)(max(px, pc) + min(px, pc) * N)];
+        }
+      }
+      for (int t0 = 0; t0 < j; t0 += 8) {
+#pragma unroll
+        for (int r = 0; r < BR; ++r) {
+          if (r < nr) {
+            const unsigned x = (unsigned)min(k + tid + BT * r, N - 1);
+            double l[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) l[u] = gY[x + (unsigned)((k0 + min(t0 + u, j - 1)) * N)];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[r] = fma(-l[u], (t0 + u < j) ? w[t0 + u] : 0.0, v[r]);
+          }
+        }
+      }
+    };
+    if (tid < j) s.wk[tid] = gW[(unsigned)(k + tid * N)];
+    __syncthreads();
+    double x0[BR], y0[BR];
+    column(k, s.wk, x0);
+    double bv = -1.0;
+    int bi = INT_MAX;
+#pragma unroll
+    for (int r = 0; r < BR; ++r) {
+      const int x = k + tid + BT * r;
+      y0[r] = 0.0;
+      if (x == k) s.akk = x0[r];
+      else if (r < nr && x < N) panel::amax_combine(bv, bi, fabs(x0[r]), x);
+    }
+    wave::amax(bv, bi);
+    if (lane == 0) {
+      s.cv[wv] = bv;
+      s.ci[wv] = bi;
+    }
+    __syncthreads();
+    double colmax = -1.0;
+    int imax = INT_MAX;
+#pragma unroll
+    for (int w = 0; w < NWAVE; ++w) panel::amax_combine(colmax, imax, s.cv[w], s.ci[w]);
+    if (colmax < 0.0) {
+      colmax = 0.0;
+      imax = k;
+    }
+    const double akk = s.akk, absakk = fabs(akk);
+    int kind;  // 0 zero, 1 1x1, 2 1x1 (second test), 3 1x1 swap, 4 2x2
+    int kstep = 1, q = k;
+    double aii = 0.0, wki = 0.0;
+    if (fmax(absakk, colmax) == 0.0 || isnan(absakk)) {
+      kind = 0;
+    } else if (absakk >= alpha * colmax) {
+      kind = 1;
+    } else {
+      if (tid < j) s.wi[tid] = gW[(unsigned)(imax + tid * N)];
+#pragma unroll
+      for (int r = 0; r < BR; ++r)
+        if (k + tid + BT * r == imax) s.wki = x0[r];
+      __syncthreads();
+      column(imax, s.wi, y0);
+      double rv = 0.0;
+#pragma unroll
+      for (int r = 0; r < BR; ++r) {
+        const int x = k + tid + BT * r;
+        if (x == imax) s.aii = y0[r];
+        else if (r < nr && x < N) rv = fmax(rv, fabs(y0[r]));
+      }
+      rv = wave::max(rv);
+      if (lane == 0) s.cv[wv] = rv;
+      __syncthreads();
+      double rowmax = 0.0;
+#pragma unroll
+      for (int w = 0; w < NWAVE; ++w) rowmax = fmax(rowmax, s.cv[w]);
+      aii = s.aii;
+      wki = s.wki;
+      if (absakk >= alpha * colmax * (colmax / rowmax)) {
+        kind = 2;
+      } else if (fabs(aii) >= alpha * rowmax) {
+        kind = 3;
+        q = imax;
+      } else {
+        kind = 4;
+        q = imax;
+        kstep = 2;
+      }
+    }
+    const int p = k + kstep - 1;
+    const bool sw = (q != p);
+    double Da = akk, Dc = 0.0, Db = 0.0, det = 1.0;
+    if (kind == 3) Da = aii;
+    const double Dw = (kind == 0) ? 0.0 : Da;  // a zero pivot eliminates nothing
+    if (kind == 4) {
+      Db = wki;
+      Dc = aii;
+      det = Da * Dc - Db * Db;
+    }
+    const double rD = (kind == 4) ? 1.0 / det : (kind == 3) ? 1.0 / aii : 1.0 / akk;
+#pragma unroll
+    for (int r = 0; r < BR; ++r) {
+      const int x = k + tid + BT * r;
+      if (r < nr && x < N) {
+        const unsigned nx = (unsigned)((sw && x == p) ? q : x);  // its row after the interchange
+        const unsigned cj = (unsigned)((k0 + j) * N), wj = (unsigned)(j * N);
+        if (kind == 4) {
+          if (x >= k + 1 && x != q) {
+            const double l0 = (x0[r] * Dc - y0[r] * Db) * rD, l1 = (y0[r] * Da - x0[r] * Db) * rD;
+            oY[nx + cj] = l0;
+            oY[nx + cj + (unsigned)N] = l1;
+            oW[nx + wj] = l0 * Da + l1 * Db;
+            oW[nx + wj + (unsigned)N] = l1 * Dc + l0 * Db;
+          }
+        } else if (kind == 3) {
+          if (x != q) {
+            const double l0 = y0[r] * rD;
+            oY[nx + cj] = l0;
+            oW[nx + wj] = l0 * Da;
+          }
+        } else if (x > k) {
+          const double l0 = (kind == 0) ? 0.0 : x0[r] * rD;
+          oY[nx + cj] = l0;
+          oW[nx + wj] = l0 * Dw;
+        }
+      }
+    }
+    if (sw && lane < j && wv < 2) {
+      // the interchanged rows of the earlier columns
+      const unsigned cl = (unsigned)((wv == 0) ? (k0 + lane) * N : lane * N);
+      gdouble_out *o = (wv == 0) ? oY : oW;
+      const double a = o[cl + (unsigned)p], b = o[cl + (unsigned)q];
+      o[cl + (unsigned)p] = b;
+      o[cl + (unsigned)q] = a;
+    }
+    if (tid == 0) {
+      if (sw) {
+        const int t0 = s.map[p - k0];
+        s.map[p - k0] = s.map[q - k0];
+        s.map[q - k0] = t0;
+      }
+      S.dd[k] = Da;
+      S.ds[k] = Db;
+      if (kind == 4) {
+        oY[(unsigned)(k + 1 + (k0 + j) * N)] = 0.0;
+        S.dd[k + 1] = Dc;
+        S.ds[k + 1] = 0.0;
+        S.ipiv[k] = S.ipiv[k + 1] = -(q + 1);
+        S.blk[k] = 2;
+        S.blk[k + 1] = 3;
+        c_pos++;
+        c_neg++;
+        c_2x2++;
+      } else {
+        S.ipiv[k] = q + 1;
+        S.blk[k] = 1;
+        if (Da > 0.0) c_pos++;
+        else if (Da < 0.0) c_neg++;
+        else {
+          c_zero++;
+          if (first_zero == 0) first_zero = k + 1;
+        }
+      }
+    }
+    j += kstep;
+    k += kstep;
+    __syncthreads();
+  }
+  if (tid == 0) {
+    FacState *st = S.st;
+    const int b = st->npanel;
+    S.pk0[b + 1] = k;
+    st->npanel = b + 1;
+    st->k = k;
+    st->npos += c_pos;
+    st->nzero += c_zero;
+    st->nneg += c_neg;
+    st->n2x2 += c_2x2;
+    if (st->info == 0 && first_zero != 0) st->info = first_zero;
+  }
+  return k;
+}
+
+// FP64 trailing update, lower triangle: every wave takes 64 x 64 tiles on its
+// own (4 x 4 MFMA blocks), Y(i, c) = X(map i, map c) - sum_t W[c, t] L[i, t].
+// The operands come straight from memory, each used four times: per tile as
+// many operand bytes as X and Y bytes at 64 columns, against three times as
+// many for 32 x 32 tiles at 16 columns, whose launches moved 509 GB per 512
+// problems.  Rows past N are read clamped and not stored.
+__device__ __attribute__((noinline)) void trailing_wg(int N, int k0, int kend, const double *W,
+                                                      const double *X, double *Y) {
+  const PanelLds &s = panel_lds();
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int l16 = lane & 15, l4 = lane >> 4;
+  gdouble *gX = (gdouble *)ubase(X), *gL = (gdouble *)ubase(Y), *gW = (gdouble *)ubase(W);
+  gdouble_out *oY = (gdouble_out *)ubase(Y);
   const int jw = kend - k0, n = N - kend;
-  const int nt = (n + TW - 1) / TW;
-  const int ntiles = nt * (nt + 1) / 2;
-  const size_t ld = (size_t)N;
-  (void)s_t;
+  const int nt = (n + 63) >> 6, ntiles = nt * (nt + 1) / 2;
   for (int x = wv; x < ntiles; x += NWAVE) {
     int ti = (int)((sqrt(8.0 * (double)x + 1.0) - 1.0) * 0.5);
     while ((ti + 1) * (ti + 2) / 2 <= x) ++ti;
     while (ti * (ti + 1) / 2 > x) --ti;
     const int tj = x - ti * (ti + 1) / 2;
-    const int i0 = kend + ti * TW, c0 = kend + tj * TW;
-    // Every load of the tile is issued before the first use: the panel's map
-    // for the tile's rows (lanes 0-31) and columns (lanes 32-63), the W and L
-    // operands of every k-step, then the un-updated entries.
-    const int li = (lane < 32) ? i0 + lane : c0 + (lane - 32);
-    const int sidx = (li < N) ? src[li] : 0;
-    constexpr int KS = (BNB + 1 + 3) / 4;  // a panel has at most nb + 1 columns
-    double av[KS][2], bv[KS][2];
+    const int i0 = kend + 64 * ti, c0 = kend + 64 * tj;
+    int pr[4];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      const int tt = 4 * ks + l4;
+    for (int b = 0; b < 4; ++b) pr[b] = s.map[min(i0 + 16 * b + l16, N - 1) - k0];
+    d4 acc[4][4];
 #pragma unroll
-      for (int a = 0; a < 2; ++a) {
-        const int c = c0 + a * 16 + l16;
-        av[ks][a] = (tt < jw && c < N) ? W[(size_t)c + (size_t)tt * ld] : 0.0;
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int pc = s.map[min(c0 + 16 * a + l4 + 4 * r, N - 1) - k0];
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+          acc[a][b][r] = gX[(unsigned)(max(pr[b], pc) + min(pr[b], pc) * N)];
       }
+    unsigned wi[4], li[4];
 #pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        const int i = i0 + b * 16 + l16;
-        bv[ks][b] = (tt < jw && i < N) ? Y[(size_t)i + (size_t)(k0 + tt) * ld] : 0.0;
-      }
+    for (int a = 0; a < 4; ++a) {
+      wi[a] = (unsigned)min(c0 + 16 * a + l16, N - 1);
+      li[a] = (unsigned)min(i0 + 16 * a + l16, N - 1);
     }
-    const bool diag = (ti == tj);
-    double xv[2][2][4];
+    double av[4], bv[4];
+    auto operands = [&](int t0, double (&oa)[4], double (&ob)[4]) {
+      const int t = min(t0 + l4, jw - 1);
+      const unsigned wo = (unsigned)(t * N), lo = (unsigned)((k0 + t) * N);
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+      for (int a = 0; a < 4; ++a) oa[a] = gW[wi[a] + wo];
 #pragma unroll
-      for (int b = 0; b < 2; ++b)
+      for (int b = 0; b < 4; ++b) ob[b] = gL[li[b] + lo];
+    };
+    operands(0, av, bv);
+    for (int t0 = 0; t0 < jw; t0 += 4) {
+      double an[4], bn[4];
+      operands(t0 + 4, an, bn);  // clamped to the panel: the last one is not used
+      const bool on = t0 + l4 < jw;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int cl = a * 16 + l4 + 4 * r, il = b * 16 + l16;
-          const int si = __shfl(sidx, il), sc = __shfl(sidx, 32 + cl);
-          const int c = c0 + cl, i = i0 + il;
-          const bool ok = c < N && i < N && (!diag || i >= c);
-          // lower triangle only: entry (max, min) of the physical indices
-          xv[a][b][r] = ok ? X[(si >= sc) ? (size_t)si + (size_t)sc * ld : (size_t)sc + (size_t)si * ld] : 0.0;
-        }
-    d4 acc[2][2];
+      for (int a = 0; a < 4; ++a) {
+        const double w = on ? -av[a] : 0.0;
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+        for (int b = 0; b < 4; ++b)
+          acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(w, on ? bv[b] : 0.0, acc[a][b], 0, 0, 0);
+      }
 #pragma unroll
-      for (int b = 0; b < 2; ++b) acc[a][b] = d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      if (4 * ks < jw) {
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-          for (int b = 0; b < 2; ++b)
-            acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[ks][a], bv[ks][b], acc[a][b], 0, 0, 0);
+      for (int a = 0; a < 4; ++a) {
+        av[a] = an[a];
+        bv[a] = bn[a];
       }
     }
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < 4; ++a)
 #pragma unroll
-      for (int b = 0; b < 2; ++b)
+      for (int b = 0; b < 4; ++b)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          // FP64 16 x 16 MFMA result: lane l, register r holds row l/16 + 4 r
-          const int c = c0 + a * 16 + l4 + 4 * r;
-          const int i = i0 + b * 16 + l16;
-          if (c < N && i < N && (!diag || i >= c)) Y[(size_t)i + (size_t)c * ld] = xv[a][b][r] - acc[a][b][r];
+          const int c = c0 + 16 * a + l4 + 4 * r, i = i0 + 16 * b + l16;
+          if (i < N && i >= c) oY[(unsigned)(i + c * N)] = acc[a][b][r];
         }
   }
 }
 
-// Mixed precision: the same tiles with FP32 storage of the trailing matrix.
+// ---- mixed precision: trailing update, every wave takes 32 x 32 lower tiles ------
+// D[c][i] = sum_t W[c, t] L[i, t]; Y(i, c) = X(src i, src c) - D[c][i] for the
+// lower tile only (every reader takes entries above the diagonal from the
+// lower triangle), with FP32 storage of the trailing matrix.
 // Every load of a tile is issued before the first use: an operand outside
 // the tile (past N, or a panel column past the panel's width) is read from
 // the slot's zero block instead, each load is unconditional from a
@@ -250,8 +723,7 @@ __device__ __attribute__((noinline)) void trailing_wg(int N, int k0, int kend, c
 __device__ __attribute__((noinline)) void trailing_wg_lp(int N, int k0, int kend, const double *W,
                                                          const double *Lsrc, const float *X,
                                                          float *Y, const int32_t *src,
-                                                         const double *zero,
-                                                         double (*s_t)[TW + 1]) {
+                                                         const double *zero) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   gdouble *gW = (gdouble *)ubase(W), *gL = (gdouble *)ubase(Lsrc), *gZ = (gdouble *)ubase(zero);
   gfloat *gX = (gfloat *)ubase(X), *gZf = (gfloat *)ubase(zero);
@@ -261,7 +733,6 @@ __device__ __attribute__((noinline)) void trailing_wg_lp(int N, int k0, int kend
   const int l16 = lane & 15, l4 = lane >> 4;
   const int jw = kend - k0, n = N - kend;
   const int nt = (n + TW - 1) / TW;
-  (void)s_t;
   constexpr int KS = (BNB + 1 + 3) / 4;
   // Each wave walks whole tile columns, top to bottom: the W operands and
   // the columns' map stay in registers for all the column's tiles (5% more
@@ -371,12 +842,6 @@ __device__ __attribute__((noinline)) void equilibrate_wg(int N, const double *M,
 
 // The phases are kept out of line so that each gets its own register
 // allocation (the panel needs most of the register file for L).
-__device__ __attribute__((noinline)) void panel_call(int N, int nb, double alpha, const double *X,
-                                                     double *Y, const SlotDev &S) {
-  panel::panel_reg_dev<BT, BR, BNB, double>(N, nb, alpha, X, Y, S.src, S.W, S.dd, S.ds, S.ipiv,
-                                            S.blk, S.st, S.pk0);
-}
-
 __device__ __attribute__((noinline)) void panel_call_lp(int N, int nb, double alpha,
                                                         const float *X, const SlotDev &S) {
   panel::panel_reg_dev<BT, BR, BNB, float>(N, nb, alpha, X, S.buf[0], S.src, S.W, S.dd, S.ds,
@@ -385,8 +850,7 @@ __device__ __attribute__((noinline)) void panel_call_lp(int N, int nb, double al
 
 // Mixed precision: blocked factorization of X32[0] = FP32(S M S); L (FP64)
 // of every panel lands in buf[0].
-__device__ void factor_wg_lp(int N, int nb, double alpha, const SlotDev &S,
-                             double (*s_t)[TW + 1]) {
+__device__ void factor_wg_lp(int N, int nb, double alpha, const SlotDev &S) {
   const int tid = threadIdx.x;
   if (tid == 0) {
     FacState z{};
@@ -402,14 +866,13 @@ __device__ void factor_wg_lp(int N, int nb, double alpha, const SlotDev &S,
     panel_call_lp(N, nb, alpha, X, S);
     __syncthreads();
     const int kend = S.st->k;
-    if (kend < N) trailing_wg_lp(N, k0, kend, S.W, S.buf[0], X, Y, S.src, S.zero, s_t);
+    if (kend < N) trailing_wg_lp(N, k0, kend, S.W, S.buf[0], X, Y, S.src, S.zero);
     __syncthreads();
   }
 }
 
 // ---- blocked factorization of the slot's buf[0] --------------------------------
-__device__ void factor_wg(int N, int nb, double alpha, const SlotDev &S,
-                          double (*s_t)[TW + 1]) {
+__device__ void factor_wg(int N, int nb, double alpha, const SlotDev &S) {
   const int tid = threadIdx.x;
   if (tid == 0) {
     FacState z{};
@@ -417,15 +880,14 @@ __device__ void factor_wg(int N, int nb, double alpha, const SlotDev &S,
     S.pk0[0] = 0;
   }
   __syncthreads();
-  for (int b = 0;; ++b) {
-    const int k0 = S.st->k;
-    if (k0 >= N) break;
+  const int nbw = min(4 * nb, SNB);
+  int k0 = 0;
+  for (int b = 0; k0 < N; ++b) {
     const double *X = S.buf[b & 1];
     double *Y = S.buf[(b + 1) & 1];
-    panel_call(N, nb, alpha, X, Y, S);
-    __syncthreads();
-    const int kend = S.st->k;
-    if (kend < N) trailing_wg(N, k0, kend, S.W, X, Y, S.src, S.zero, s_t);
+    const int kend = panel_spec_wg(N, k0, nbw, alpha, X, Y, S);
+    if (kend < N) trailing_wg(N, k0, kend, S.W, X, Y);
+    k0 = kend;
     __syncthreads();
   }
 }
@@ -437,7 +899,7 @@ __device__ void factor_wg(int N, int nb, double alpha, const SlotDev &S,
 // one, p = -1 for its second row) and the panel's diagonal block of L into
 // s_db (w x w, one load per entry, all in flight at once); the sequential
 // steps then touch only LDS and broadcast a lane's value with readlane.
-constexpr int BDB = BNB + 1;  // widest panel (a final 2x2 pivot)
+constexpr int BDB = SNB + 1;  // row stride of the diagonal block (panels of at most SNB columns)
 
 __device__ inline void panel_records(const SlotDev &S, int k0, int w, int *s_pq) {
   const int tid = threadIdx.x;
@@ -449,10 +911,9 @@ __device__ inline void panel_records(const SlotDev &S, int k0, int w, int *s_pq)
 }
 
 __device__ inline void diag_block(const double *Lb, size_t ld, int k0, int w, double *s_db) {
-  const int tid = threadIdx.x;
-  if (tid < BDB * BDB) {
-    const int r = tid % BDB, c = tid / BDB;
-    if (r < w && c < w) s_db[r * BDB + c] = Lb[(size_t)(k0 + r) + (size_t)(k0 + c) * ld];
+  for (int e = threadIdx.x; e < w * SNB; e += BT) {
+    const int r = e % SNB, c = e / SNB;
+    if (r < w && r > c) s_db[r * BDB + c] = Lb[(size_t)(k0 + r) + (size_t)(k0 + c) * ld];
   }
 }
 
@@ -491,7 +952,13 @@ __device__ __attribute__((noinline)) void solve_wg(int N, const SlotDev &S, doub
     __syncthreads();
     for (int x = k1 + tid; x < N; x += BT) {
       double v = z[x];
-      for (int c = k0; c < k1; ++c) v = fma(-Lb[(size_t)x + (size_t)c * ld], z[c], v);
+      for (int c0 = k0; c0 < k1; c0 += 8) {
+        double l[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) l[u] = Lb[(size_t)x + (size_t)min(c0 + u, k1 - 1) * ld];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v = fma(-l[u], (c0 + u < k1) ? z[c0 + u] : 0.0, v);
+      }
       z[x] = v;
     }
     __syncthreads();
@@ -516,26 +983,28 @@ __device__ __attribute__((noinline)) void solve_wg(int N, const SlotDev &S, doub
     const double *Lb = mixed ? S.buf[0] : S.buf[(b + 1) & 1];
     panel_records(S, k0, w, s_pq);
     diag_block(Lb, ld, k0, w, s_db);
-    double acc[BNB + 1];
+    for (int cb = 0; cb < w; cb += 16) {
+      double acc[16];
 #pragma unroll
-    for (int c = 0; c <= BNB; ++c) acc[c] = 0.0;
-    for (int x = k1 + tid; x < N; x += BT) {
-      const double zx = z[x];
+      for (int c = 0; c < 16; ++c) acc[c] = 0.0;
+      for (int x = k1 + tid; x < N; x += BT) {
+        const double zx = z[x];
 #pragma unroll
-      for (int c = 0; c <= BNB; ++c)
-        if (c < w) acc[c] = fma(Lb[(size_t)x + (size_t)(k0 + c) * ld], zx, acc[c]);
-    }
+        for (int c = 0; c < 16; ++c)
+          acc[c] = fma(Lb[(size_t)x + (size_t)(k0 + min(cb + c, w - 1)) * ld], zx, acc[c]);
+      }
 #pragma unroll
-    for (int c = 0; c <= BNB; ++c) {
-      const double v = wave::sum(acc[c]);
-      if (lane == 0) s_part[wv * (BNB + 1) + c] = v;
+      for (int c = 0; c < 16; ++c) {
+        const double v = wave::sum(acc[c]);
+        if (lane == 0) s_part[wv * SNB + cb + c] = v;
+      }
     }
     __syncthreads();
     if (wv == 0) {
       double v = 0.0;
       if (lane < w) {
         double s = 0.0;
-        for (int q = 0; q < NWAVE; ++q) s += s_part[q * (BNB + 1) + lane];
+        for (int q = 0; q < NWAVE; ++q) s += s_part[q * SNB + lane];
         v = z[k0 + lane] - s;
       }
       for (int c = w - 1; c > 0; --c) {
@@ -687,14 +1156,10 @@ __global__ __launch_bounds__(BT) void k_batch(int count, const int32_t *__restri
                                               ResultDev *results, int refine_max) {
   constexpr bool mixed = MIXED;
   const double dc_sing = *dc_sing_p;
-  __shared__ double s_t[NWAVE * TW][TW + 1];
+  __shared__ double s_db[SNB * BDB];
+  __shared__ int s_pq[2 * SNB];
   __shared__ double s_z[BMAX_N];
-  __shared__ double s_part[NWAVE * (BNB + 1)];
-  // the solves' diagonal block and pivot records live in the trailing
-  // update's transpose tiles, which no solve uses
-  double *s_db = &s_t[0][0];
-  int *s_pq = (int *)(s_db + BDB * BDB);
-  static_assert(BDB * BDB * 8 + 2 * BDB * 4 <= NWAVE * TW * (TW + 1) * 8, "solve staging");
+  __shared__ double s_part[NWAVE * SNB];
   __shared__ int s_p;
   const int tid = threadIdx.x;
   const SlotDev S = slots[blockIdx.x];
@@ -713,12 +1178,12 @@ __global__ __launch_bounds__(BT) void k_batch(int count, const int32_t *__restri
     const double dw0 = 1e-4, kw_plus_bar = 100.0, dw_max = 1e20;
     int trials = 1, status = 0;
     double dw = 0.0, dc = 0.0;
-    condense_wg(P, S.inv_d, 0.0, 0.0, S.buf[0]);
+    condense_wg(P, S.inv_d, 0.0, 0.0, S.buf[0], MIXED);
     if constexpr (MIXED) {
       equilibrate_wg(N, S.buf[0], S.eq, S.x32[0]);
-      factor_wg_lp(N, nb, alpha, S, s_t);
+      factor_wg_lp(N, nb, alpha, S);
     } else {
-      factor_wg(N, nb, alpha, S, s_t);
+      factor_wg(N, nb, alpha, S);
     }
     bool ok = S.st->npos == P.nd && S.st->nzero == 0 && S.st->nneg == P.m;
     if (!ok) {
@@ -726,12 +1191,12 @@ __global__ __launch_bounds__(BT) void k_batch(int count, const int32_t *__restri
       dw = dw0;
       for (;;) {
         trials++;
-        condense_wg(P, S.inv_d, dw, dc, S.buf[0]);
+        condense_wg(P, S.inv_d, dw, dc, S.buf[0], MIXED);
         if constexpr (MIXED) {
           equilibrate_wg(N, S.buf[0], S.eq, S.x32[0]);
-          factor_wg_lp(N, nb, alpha, S, s_t);
+          factor_wg_lp(N, nb, alpha, S);
         } else {
-          factor_wg(N, nb, alpha, S, s_t);
+          factor_wg(N, nb, alpha, S);
         }
         ok = S.st->npos == P.nd && S.st->nzero == 0 && S.st->nneg == P.m;
         if (ok) break;
@@ -1055,9 +1520,9 @@ __device__ __attribute__((noinline)) void ipm_refine_wg(const ProbDev &P, const 
 
 // Condense + factor with the shifts, and whether In(M) = (n_d, 0, m)
 __device__ inline bool ipm_factor_wg(const ProbDev &P, const SlotDev &S, int nb, double alpha,
-                                     double dw, double dc, double (*s_t)[TW + 1]) {
-  condense_wg(P, S.inv_d, dw, dc, S.buf[0]);
-  factor_wg(P.nd + P.m, nb, alpha, S, s_t);
+                                     double dw, double dc) {
+  condense_wg(P, S.inv_d, dw, dc, S.buf[0], false);
+  factor_wg(P.nd + P.m, nb, alpha, S);
   return S.st->npos == P.nd && S.st->nzero == 0 && S.st->nneg == P.m;
 }
 
@@ -1068,11 +1533,10 @@ __global__ __launch_bounds__(BT) void k_batch_ipm(int count, const int32_t *__re
                                                   double alpha, IpmParams prm, int32_t *queue,
                                                   unsigned long long *t0, IpmResDev *results,
                                                   IpmIterDev *trace) {
-  __shared__ double s_t[NWAVE * TW][TW + 1];
+  __shared__ double s_db[SNB * BDB];
+  __shared__ int s_pq[2 * SNB];
   __shared__ double s_z[BMAX_N];
-  __shared__ double s_part[NWAVE * (BNB + 1)];
-  double *s_db = &s_t[0][0];
-  int *s_pq = (int *)(s_db + BDB * BDB);
+  __shared__ double s_part[NWAVE * SNB];
   __shared__ int s_p;
   const int tid = threadIdx.x;
   const SlotDev S = slots[blockIdx.x];
@@ -1173,13 +1637,13 @@ __global__ __launch_bounds__(BT) void k_batch_ipm(int count, const int32_t *__re
       // inertia correction (Algorithm IC)
       int trials = 1;
       double dw = 0.0, dc = 0.0;
-      bool ok = ipm_factor_wg(P, S, nb, alpha, 0.0, 0.0, s_t);
+      bool ok = ipm_factor_wg(P, S, nb, alpha, 0.0, 0.0);
       if (!ok) {
         dc = (S.st->nzero > 0) ? dc_bar * pow(mu, kappa_c) : 0.0;
         dw = (dw_last == 0.0) ? dw0 : fmax(dw_min, kw_minus * dw_last);
         for (;;) {
           trials++;
-          ok = ipm_factor_wg(P, S, nb, alpha, dw, dc, s_t);
+          ok = ipm_factor_wg(P, S, nb, alpha, dw, dc);
           if (ok) {
             dw_last = dw;
             break;

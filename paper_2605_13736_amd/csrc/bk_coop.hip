@@ -39,6 +39,8 @@ namespace {
 
 using panel::lds_wave_sync;
 using panel::sym_at;
+using wave::rows4;
+using wave::sel4;
 
 constexpr unsigned long long kCoopWaitTicks = 1ull << 26;  // ~0.67 s of the 100 MHz clock
 
@@ -126,31 +128,6 @@ static_assert(CNB <= kMaxNb && CNB % CB == 0 && CLD % 32 == 17, "tile");
 static_assert(8 + 2 * CNB <= kCoopSlotWords && CB * CNB * 2 <= kCoopRowWords, "exchange slot");
 
 typedef double d4 __attribute__((ext_vector_type(4)));
-
-// o[q] = x of lane (l & 15) + 16 q
-__device__ inline void rows4(double x, double (&o)[4]) {
-  const unsigned long long b = (unsigned long long)__double_as_longlong(x);
-  unsigned r[2][4];
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const unsigned v = (unsigned)(b >> (32 * h));
-    // [r0 r1 r0 r1], [r2 r3 r2 r3]; then one row of each pair everywhere
-    const auto a = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-    const auto lo = __builtin_amdgcn_permlane16_swap(a[0], a[0], false, false);
-    const auto hi = __builtin_amdgcn_permlane16_swap(a[1], a[1], false, false);
-    r[h][0] = lo[0];
-    r[h][1] = lo[1];
-    r[h][2] = hi[0];
-    r[h][3] = hi[1];
-  }
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-    o[q] = __longlong_as_double((long long)(((unsigned long long)r[1][q] << 32) | r[0][q]));
-}
-
-__device__ inline double sel4(int q, double a, double b, double c, double d) {
-  return (q < 2) ? (q == 0 ? a : b) : (q == 2 ? c : d);
-}
 
 template <typename TX, bool LA>
 __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alpha,

@@ -129,5 +129,30 @@ __device__ inline double sum(double v) {
   return (lane_read(v, 0) + lane_read(v, 16)) + (lane_read(v, 32) + lane_read(v, 48));
 }
 
+// o[q] = x of lane (l & 15) + 16 q
+__device__ inline void rows4(double x, double (&o)[4]) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+  unsigned r[2][4];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const unsigned v = (unsigned)(b >> (32 * h));
+    // [r0 r1 r0 r1], [r2 r3 r2 r3]; then one row of each pair everywhere
+    const auto a = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    const auto lo = __builtin_amdgcn_permlane16_swap(a[0], a[0], false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(a[1], a[1], false, false);
+    r[h][0] = lo[0];
+    r[h][1] = lo[1];
+    r[h][2] = hi[0];
+    r[h][3] = hi[1];
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    o[q] = __longlong_as_double((long long)(((unsigned long long)r[1][q] << 32) | r[0][q]));
+}
+
+__device__ inline double sel4(int q, double a, double b, double c, double d) {
+  return (q < 2) ? (q == 0 ? a : b) : (q == 2 ? c : d);
+}
+
 }  // namespace wave
 }  // namespace mds
