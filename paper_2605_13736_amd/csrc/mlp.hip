@@ -18,8 +18,6 @@ namespace {
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef short s4 __attribute__((ext_vector_type(4)));
 
-constexpr int GT = 64;  // output tile (rows x cols) per workgroup of 256 threads
-
 __device__ inline short bf16_rne(float x) {
   const uint32_t u = __float_as_uint(x);
   return (short)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
@@ -28,70 +26,105 @@ __device__ inline short bf16_rne(float x) {
 // C(i, j) = sum_k A(i, k) B(k, j) [+ bias(j)] [GELU], A(i,k) = A[i*sai + k*sak],
 // B(k,j) = B[k*sbk + j*sbj], C row-major with ldc.  Optionally stores the
 // pre-activation in Z.  MODE 0: FP32 MFMA; MODE 1: BF16 MFMA, FP32 accumulate.
-template <int MODE>
+// A product of these sizes is a few workgroups, bound by the latency of its
+// loads: KU k-steps of them leave together, unguarded (a guarded load waits
+// behind its own branch), at uniform offsets from the lane's address.  Mean
+// launch of a training step (128-256-256-193, batch 64): one guarded k-step
+// at a time 21 us, together 17, with 32 x 32 tiles 8.7.  The sums keep their
+// order.
+constexpr int KU = 16;
+template <int MODE, int WB>
 __global__ __launch_bounds__(256) void k_gemm(int M, int N, int K, const float *__restrict__ A,
                                               int64_t sai, int64_t sak,
                                               const float *__restrict__ B, int64_t sbk,
                                               int64_t sbj, const float *__restrict__ bias,
                                               float *__restrict__ Z, float *__restrict__ C,
                                               int64_t ldc, int gelu, int accumulate) {
-  const int i0 = blockIdx.y * GT, j0 = blockIdx.x * GT;
+  const int i0 = blockIdx.y * 32 * WB, j0 = blockIdx.x * 32 * WB;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int wi = i0 + (wv >> 1) * 32, wj = j0 + (wv & 1) * 32;
+  const int wi = i0 + (wv >> 1) * 16 * WB, wj = j0 + (wv & 1) * 16 * WB;
   const int l16 = lane & 15, l4 = lane >> 4;
-  f4 acc[2][2];
+  f4 acc[WB][WB];
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < WB; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = f4{0.f, 0.f, 0.f, 0.f};
+    for (int b = 0; b < WB; ++b) acc[a][b] = f4{0.f, 0.f, 0.f, 0.f};
+  // this lane's rows of A and columns of B (past the edge: the last one,
+  // loaded without a guard and replaced by zero)
+  int64_t ia[WB], jb[WB];
+#pragma unroll
+  for (int a = 0; a < WB; ++a) {
+    ia[a] = min(wi + a * 16 + l16, M - 1) * sai;
+    jb[a] = min(wj + a * 16 + l16, N - 1) * sbj;
+  }
+  const int64_t la = l4 * sak, lb = l4 * sbk;
   if (MODE == 0) {
-    for (int k0 = 0; k0 < K; k0 += 4) {
-      const int k = k0 + l4;
-      float av[2], bv[2];
+    for (int k0 = 0; k0 < K; k0 += 4 * KU) {
+      float av[KU][WB], bv[KU][WB];
+      const int rem = K - 1 - k0;  // steps past the end re-read the last one
+      const float *pa = A + (int64_t)k0 * sak, *pb = B + (int64_t)k0 * sbk;
+      if (rem >= 4 * KU - 1) {
 #pragma unroll
-      for (int a = 0; a < 2; ++a) {
-        const int i = wi + a * 16 + l16;
-        av[a] = (i < M && k < K) ? A[i * sai + k * sak] : 0.f;
+        for (int u = 0; u < KU; ++u) {
+#pragma unroll
+          for (int a = 0; a < WB; ++a) av[u][a] = (pa + 4 * u * sak)[ia[a] + la];
+#pragma unroll
+          for (int b = 0; b < WB; ++b) bv[u][b] = (pb + 4 * u * sbk)[jb[b] + lb];
+        }
+      } else {
+#pragma unroll
+        for (int u = 0; u < KU; ++u) {
+          const int k = min(4 * u + l4, rem);
+#pragma unroll
+          for (int a = 0; a < WB; ++a) av[u][a] = pa[ia[a] + k * sak];
+#pragma unroll
+          for (int b = 0; b < WB; ++b) bv[u][b] = pb[jb[b] + k * sbk];
+        }
       }
 #pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        const int j = wj + b * 16 + l16;
-        bv[b] = (j < N && k < K) ? B[k * sbk + j * sbj] : 0.f;
+      for (int u = 0; u < KU; ++u) {
+        if (k0 + 4 * u < K) {
+          const bool on = k0 + 4 * u + l4 < K;
+#pragma unroll
+          for (int a = 0; a < WB; ++a)
+#pragma unroll
+            for (int b = 0; b < WB; ++b)
+              acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                  on && wi + a * 16 + l16 < M ? av[u][a] : 0.f,
+                  on && wj + b * 16 + l16 < N ? bv[u][b] : 0.f, acc[a][b], 0, 0, 0);
+        }
       }
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[a], bv[b], acc[a][b], 0, 0, 0);
     }
   } else {
     for (int k0 = 0; k0 < K; k0 += 16) {
-      s4 av[2], bv[2];
+      s4 av[WB], bv[WB];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int k = k0 + 4 * l4 + e;
 #pragma unroll
-        for (int a = 0; a < 2; ++a) {
+        for (int a = 0; a < WB; ++a) {
           const int i = wi + a * 16 + l16;
-          av[a][e] = bf16_rne((i < M && k < K) ? A[i * sai + k * sak] : 0.f);
+          const float v = A[ia[a] + min(k, K - 1) * sak];
+          av[a][e] = bf16_rne((i < M && k < K) ? v : 0.f);
         }
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
+        for (int b = 0; b < WB; ++b) {
           const int j = wj + b * 16 + l16;
-          bv[b][e] = bf16_rne((j < N && k < K) ? B[k * sbk + j * sbj] : 0.f);
+          const float v = B[jb[b] + min(k, K - 1) * sbk];
+          bv[b][e] = bf16_rne((j < N && k < K) ? v : 0.f);
         }
       }
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
+      for (int a = 0; a < WB; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int b = 0; b < WB; ++b)
           acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av[a], bv[b], acc[a][b], 0, 0, 0);
     }
   }
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < WB; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < WB; ++b)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         // 16 x 16 FP32-accumulating MFMA result: lane l, register r holds
@@ -125,7 +158,14 @@ __global__ void k_colsum(int M, int N, const float *__restrict__ dZ, float *__re
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= N) return;
   float s = 0.f;
-  for (int i = 0; i < M; ++i) s += dZ[(int64_t)i * N + j];
+  for (int i0 = 0; i0 < M; i0 += 32) {
+    float v[32];  // loaded together, added in order
+#pragma unroll
+    for (int u = 0; u < 32; ++u) v[u] = dZ[(int64_t)min(i0 + u, M - 1) * N + j];
+#pragma unroll
+    for (int u = 0; u < 32; ++u)
+      if (i0 + u < M) s += v[u];
+  }
   db[j] = s;
 }
 
@@ -164,13 +204,22 @@ inline unsigned g256(int64_t n) { return (unsigned)((n + 255) / 256); }
 void gemm(hipStream_t s, int mode, int M, int N, int K, const float *A, int64_t sai, int64_t sak,
           const float *B, int64_t sbk, int64_t sbj, const float *bias, float *Z, float *C,
           int64_t ldc, int gelu, int accumulate) {
-  dim3 grid((unsigned)((N + GT - 1) / GT), (unsigned)((M + GT - 1) / GT));
-  if (mode == 1)
-    k_gemm<1><<<grid, 256, 0, s>>>(M, N, K, A, sai, sak, B, sbk, sbj, bias, Z, C, ldc, gelu,
-                                   accumulate);
-  else
-    k_gemm<0><<<grid, 256, 0, s>>>(M, N, K, A, sai, sak, B, sbk, sbj, bias, Z, C, ldc, gelu,
-                                   accumulate);
+  // 64 x 64 tiles, or 32 x 32 where those are too few to matter against 256
+  // compute units: a wave then waits on a quarter of the products
+  const int64_t big = (int64_t)((N + 63) / 64) * ((M + 63) / 64);
+  const int T = (big < 128) ? 32 : 64;
+  dim3 grid((unsigned)((N + T - 1) / T), (unsigned)((M + T - 1) / T));
+#define MDS_GEMM(MODE_, WB_)                                                                    \
+  k_gemm<MODE_, WB_><<<grid, 256, 0, s>>>(M, N, K, A, sai, sak, B, sbk, sbj, bias, Z, C, ldc, gelu, \
+                                          accumulate)
+  if (mode == 1) {
+    if (T == 32) MDS_GEMM(1, 1);
+    else MDS_GEMM(1, 2);
+  } else {
+    if (T == 32) MDS_GEMM(0, 1);
+    else MDS_GEMM(0, 2);
+  }
+#undef MDS_GEMM
 }
 
 }  // namespace
