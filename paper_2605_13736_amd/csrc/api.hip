@@ -95,7 +95,7 @@ enum Slot {
   S_GZ, S_GRHS, S_GX, S_GW, S_GPART, S_GCOEF, S_XCH, S_XLE, S_XUE, S_DCV, S_RY2,
   S_BBP, S_BOFF, S_BKB, S_BL, S_HRP, S_HCI, S_HSRC, S_HVAL, S_HCPTR, S_HCROW, S_HCMAP, S_HCVAL,
   S_BT1, S_BT2, S_NH, S_NJD, S_NV, S_NW, S_NZERO, S_NCX0, S_NCSOC, S_NYR, S_NXS, S_NDXS, S_NDYS,
-  S_NXR, S_NDR, S_NCMAP, S_SRC2, S_W2, S_LST, S_COUNT
+  S_NXR, S_NDR, S_NCMAP, S_SRC2, S_W2, S_LST, S_REC, S_RECN, S_COUNT
 };
 
 struct Layout {
@@ -155,6 +155,8 @@ Layout make_layout(const mds_dims &d, int nb, bool pingpong, int precision, int 
   bytes[S_FLAGS] = 4 * 16;
   bytes[S_RED] = 8 * (size_t)kRedBlocks * 8;
   bytes[S_SCAL] = 8 * 64;
+  bytes[S_REC] = 8 * (size_t)kRecStride * rec_blocks(d.n_d, d.n_s, d.m);
+  bytes[S_RECN] = 256;
   bytes[S_Z] = bytes[S_Z2] = 8 * N;
   bytes[S_HMAP] = 4 * maxp * N;
   bytes[S_PERM] = bytes[S_COLP] = 4 * N;
@@ -279,6 +281,13 @@ inline int ND(mds_handle *h) { return h->dims.n_d; }
 inline int NS(mds_handle *h) { return h->dims.n_s; }
 inline int MM(mds_handle *h) { return h->dims.m; }
 
+// Pinned host memory of a handle (doubles): the fused passes' combined record,
+// scalars read back, the factorization's state, the solves' error word.
+constexpr int kPinRec = 0, kPinScal = 16, kPinFac = 64, kPinErr = 96;
+constexpr size_t kPinBytes = 1024;
+static_assert(kRecVals < kPinScal && sizeof(FacState) <= 8 * (kPinErr - kPinFac), "pinned layout");
+inline FacState *pin_fac(mds_handle *h) { return reinterpret_cast<FacState *>(h->pin + kPinFac); }
+
 // ---- internal building blocks -------------------------------------------------
 
 int condense_impl(mds_handle *h, double dw, double dc) {
@@ -296,10 +305,9 @@ int condense_impl(mds_handle *h, double dw, double dc) {
       // blocks of Q_{x_s}: L Delta L', inv_d = 1/Delta, Jh = J_s L^{-T}
       sblk_factor(S(h), B, h->dsbase, dw, h->w.inv_d);
       sblk_transform(S(h), B, MM(h), h->P.Js_val);
-    } else {
-      launch_inv_d(S(h), NS(h), h->dsbase, dw, h->w.inv_d);
     }
-    launch_condense_dense(S(h), ND(h), MM(h), h->P.H, h->P.J_d, h->sigma_d, dw, h->w.M);
+    launch_condense_dense(S(h), ND(h), MM(h), h->P.H, h->P.J_d, h->sigma_d, dw, NS(h), h->dsbase,
+                          B.nblk > 0 ? nullptr : h->w.inv_d, h->w.M);
     if (B.nblk > 0)
       launch_condense_schur(S(h), ND(h), MM(h), h->N, B.hrp, B.hci, B.hval, B.hcptr, B.hcrow,
                             B.hcval, h->w.inv_d, dc, h->dcv_cur, h->w.M);
@@ -402,6 +410,7 @@ void factor_launches(mds_handle *h, hipStream_t s) {
                            h->panel_reg ? h->w.src : nullptr, h->w.fst, h->w.panel_k0);
     }
   }
+  launch_fac_publish(s, h->w.fst, pin_fac(h));
 }
 
 // Look-ahead form of the cooperative factorization.  Stream A (the
@@ -496,6 +505,7 @@ void factor_launches_la(mds_handle *h, hipStream_t s) {
   wait_far();
   (void)hipEventRecord(ev_join, A);
   (void)hipStreamWaitEvent(s, ev_join, 0);
+  launch_fac_publish(s, w.fst, pin_fac(h));
 }
 
 // CU-masked streams of the look-ahead: A on `reserve` compute units (the same
@@ -586,12 +596,14 @@ void factor_launches_mem(mds_handle *h, hipStream_t s) {
                          h->w.M, nullptr, h->w.fst, h->w.panel_k0);
     }
   }
+  launch_fac_publish(s, h->w.fst, pin_fac(h));
 }
 
+// The factorization's state, which its last launch left in pinned memory.
 int read_fac_state(mds_handle *h, FacState *st) {
   HIPCHK(hipGetLastError());
-  HIPCHK(hipMemcpyAsync(st, h->w.fst, sizeof(*st), hipMemcpyDeviceToHost, S(h)));
   HIPCHK(hipStreamSynchronize(S(h)));
+  *st = *pin_fac(h);
   return MDS_OK;
 }
 
@@ -653,10 +665,9 @@ void ensure_std(mds_handle *h) {
 
 // Error word of the triangular solves (a bounded wait that expired).
 int solve_status(mds_handle *h) {
-  int32_t e = 0;
-  HIPCHK(hipMemcpyAsync(&e, h->w.trsv + 1, 4, hipMemcpyDeviceToHost, S(h)));
+  HIPCHK(hipMemcpyAsync(h->pin + kPinErr, h->w.trsv + 1, 4, hipMemcpyDeviceToHost, S(h)));
   HIPCHK(hipStreamSynchronize(S(h)));
-  if (e) return set_err(h, MDS_EHIP, "triangular solve: dependency wait timed out");
+  if (*reinterpret_cast<const int32_t *>(h->pin + kPinErr)) return set_err(h, MDS_EHIP, "triangular solve: dependency wait timed out");
   return MDS_OK;
 }
 
@@ -701,39 +712,37 @@ int correct_impl(mds_handle *h, mds_reg *reg, double mu, mds_inertia *out) {
 
 int solve_impl(mds_handle *h, const double *r_d, const double *r_s, const double *r_y,
                double *dx_d, double *dx_s, double *dy) {
-  const int nd = ND(h), ns = NS(h), m = MM(h), N = h->N;
-  if (nd > 0) HIPCHK(hipMemcpyAsync(h->w.z, r_d, 8 * (size_t)nd, hipMemcpyDeviceToDevice, S(h)));
   const SBlk &B = h->sb;
-  if (B.nblk > 0) {
+  const bool blocks = B.nblk > 0;
+  if (blocks) {
     // r_y - Jh Delta^{-1} (L^{-1} r_s)
-    vec_copy(S(h), ns, r_s, B.tmp);
+    vec_copy(S(h), NS(h), r_s, B.tmp);
     sblk_solve(S(h), B, h->w.inv_d, 0, B.tmp);
-    launch_rhs_condense(S(h), m, B.hrp, B.hci, B.hval, h->w.inv_d, B.tmp, r_y, h->w.z + nd);
-  } else {
-    launch_rhs_condense(S(h), m, h->P.Js_rowptr, h->P.Js_col, h->P.Js_val, h->w.inv_d, r_s, r_y,
-                        h->w.z + nd);
   }
   ensure_std(h);
   {
     TimedLaunch t(h, MDS_T_SOLVE);
-    // mixed precision factors S M S: M^{-1} = S (S M S)^{-1} S
-    if (h->fac_lowprec) launch_vscale(S(h), N, h->w.eq, h->w.z);
-    launch_std_solve(S(h), N, h->w.M, h->w.dd, h->w.ds, h->w.blk, h->w.perm, h->w.z, h->w.z2,
-                     h->w.z, h->w.trsv);
-    if (h->fac_lowprec) launch_vscale(S(h), N, h->w.eq, h->w.z);
+    // mixed precision factors S M S: M^{-1} = S (S M S)^{-1} S.  With blocks
+    // dx_s = L^{-T} Delta^{-1} L^{-1} (r_s - J_s' dy): the unscaled
+    // back-substitution, then the block solves
+    const StdSolveArgs a{blocks ? B.hrp : h->P.Js_rowptr,
+                         blocks ? B.hci : h->P.Js_col,
+                         blocks ? B.hval : h->P.Js_val,
+                         h->w.inv_d,
+                         r_d,
+                         blocks ? B.tmp : r_s,
+                         r_y,
+                         h->fac_lowprec ? h->w.eq : nullptr,
+                         h->w.csc_ptr,
+                         h->w.csc_row,
+                         h->w.csc_val,
+                         blocks ? nullptr : h->w.inv_d,
+                         r_s};
+    launch_std_solve(S(h), h->N, ND(h), NS(h), h->w.M, h->w.dd, h->w.ds, h->w.blk, h->w.perm, a,
+                     h->w.z, h->w.z2, dx_d, dx_s, dy, h->w.trsv);
   }
   h->nsolves++;
-  if (nd > 0) HIPCHK(hipMemcpyAsync(dx_d, h->w.z, 8 * (size_t)nd, hipMemcpyDeviceToDevice, S(h)));
-  if (m > 0) HIPCHK(hipMemcpyAsync(dy, h->w.z + nd, 8 * (size_t)m, hipMemcpyDeviceToDevice, S(h)));
-  if (B.nblk > 0) {
-    // L^{-T} Delta^{-1} L^{-1} (r_s - J_s' dy): the unscaled back-substitution
-    // (inverse diagonal of ones), then the block solves
-    launch_backsub(S(h), ns, h->w.csc_ptr, h->w.csc_row, h->w.csc_val, nullptr, r_s, dy, dx_s);
-    sblk_solve(S(h), B, h->w.inv_d, 1, dx_s);
-  } else {
-    launch_backsub(S(h), ns, h->w.csc_ptr, h->w.csc_row, h->w.csc_val, h->w.inv_d, r_s, dy,
-                   dx_s);
-  }
+  if (blocks) sblk_solve(S(h), B, h->w.inv_d, 1, dx_s);
   HIPCHK(hipGetLastError());
   return MDS_OK;
 }
@@ -762,9 +771,72 @@ void kkt_matvec(mds_handle *h, const double *dxd, const double *dxs, const doubl
 }
 
 int read_scal(mds_handle *h, double *dst, int count) {
-  HIPCHK(hipMemcpyAsync(dst, h->w.scal, 8 * (size_t)count, hipMemcpyDeviceToHost, S(h)));
+  HIPCHK(hipMemcpyAsync(h->pin + kPinScal, h->w.scal, 8 * (size_t)count, hipMemcpyDeviceToHost,
+                        S(h)));
   HIPCHK(hipStreamSynchronize(S(h)));
+  memcpy(dst, h->pin + kPinScal, 8 * (size_t)count);
   return MDS_OK;
+}
+
+// The fused passes (fused.hip) serve the quadratic problem without coupling
+// blocks; models and blocks take the separate products below.
+bool use_fused(const mds_handle *h) { return !h->nlp_on && h->sb.nblk == 0; }
+
+// What every fused pass reads: the problem and the record buffers.
+RowArgs row_args(mds_handle *h) {
+  const mds_problem &P = h->P;
+  RowArgs a{};
+  a.nd = ND(h);
+  a.ns = NS(h);
+  a.m = MM(h);
+  a.mE = h->mE;
+  a.H = P.H;
+  a.Jd = P.J_d;
+  a.rp = P.Js_rowptr;
+  a.ci = P.Js_col;
+  a.v = P.Js_val;
+  a.cptr = h->w.csc_ptr;
+  a.crow = h->w.csc_row;
+  a.cval = h->w.csc_val;
+  a.c = P.c;
+  a.w = P.w;
+  a.g = P.g;
+  a.b = P.b;
+  a.xl = h->w.xl_e;
+  a.xu = h->w.xu_e;
+  a.rec = h->w.rec;
+  a.counter = h->w.rec_count;
+  a.out = h->pin + kPinRec;
+  return a;
+}
+
+// Combined record of the last fused pass.
+int read_rec(mds_handle *h, double (&v)[kRecVals + 1]) {
+  HIPCHK(hipGetLastError());
+  HIPCHK(hipStreamSynchronize(S(h)));
+  memcpy(v, h->pin + kPinRec, sizeof(v));
+  return MDS_OK;
+}
+
+// gf, jty, cx (and H x_d in w.xt, r_y = -c in ry when given) at x in one
+// pass; with zl the optimality error's record too.
+void eval_fused(mds_handle *h, const double *x, const double *y, const double *zl,
+                const double *zu, double mu, bool pair, double *ry) {
+  RowArgs a = row_args(h);
+  a.x = x;
+  a.xs = x + a.nd;
+  a.y = y;
+  a.zl = zl;
+  a.zu = zu;
+  a.mu = mu;
+  a.pair = pair ? 1 : 0;
+  a.hx = h->w.xt;
+  a.gf = h->w.tn;
+  a.jty = h->w.tn2;
+  a.cx = h->w.tm;
+  a.ryo = ry;
+  if (!zl) a.out = nullptr;
+  launch_rows(S(h), kRowEval, a);
 }
 
 int amax3(mds_handle *h, int64_t na, const double *a, int64_t nb, const double *b, int64_t nc,
@@ -914,11 +986,73 @@ int gmres_refine(mds_handle *h, const double *r_d, const double *r_s, const doub
   return (eta <= eta_tol) ? MDS_OK : MDS_REFINE_NOCONV;
 }
 
+// Refinement with the fused residual pass: one launch and one read-back per
+// residual, ||K||_inf and ||r||_inf in the first.
+int refine_fused(mds_handle *h, const double *r_d, const double *r_s, const double *r_y,
+                 double *dx_d, double *dx_s, double *dy, int max_steps, double eta_tol,
+                 mds_refine_info *info) {
+  const int nd = ND(h), ns = NS(h), m = MM(h);
+  double *res = h->w.res, *cor = h->w.cor, *prev = h->w.prev;
+  TRY(solve_impl(h, r_d, r_s, r_y, dx_d, dx_s, dy));
+  RowArgs a = row_args(h);
+  a.x = dx_d;
+  a.xs = dx_s;
+  a.y = dy;
+  a.rd = r_d;
+  a.rs = r_s;
+  a.ry = r_y;
+  a.sig = h->sigma_d;
+  a.dsb = h->dsbase;
+  a.dcv = h->dcv_cur;
+  a.dw = h->dw;
+  a.dc = h->dc;
+  a.res = res;
+  a.err = h->w.trsv + 1;
+  double nK = 0.0, nr = 0.0, eta_prev = INFINITY, eta = 0.0, rres = 0.0;
+  int steps = 0;
+  for (;;) {
+    a.norms = (steps == 0) ? 1 : 0;
+    double v[kRecVals + 1] = {};
+    launch_rows(S(h), kRowRes, a);
+    TRY(read_rec(h, v));
+    if (v[kRecVals] != 0.0)
+      return set_err(h, MDS_EHIP, "triangular solve: dependency wait timed out");
+    if (steps == 0) {
+      nK = v[2];
+      nr = v[3];
+    }
+    const double den = nK * v[1] + nr;
+    eta = (den > 0.0) ? v[0] / den : 0.0;
+    rres = (nr > 0.0) ? v[0] / nr : 0.0;
+    if (steps > 0 && !(eta < eta_prev)) {
+      // no decrease: keep the previous iterate
+      launch_step_update(S(h), nd, ns, m, cor, prev, dx_d, dx_s, dy, true);
+      eta = eta_prev;
+      HIPCHK(hipGetLastError());
+      HIPCHK(hipStreamSynchronize(S(h)));
+      break;
+    }
+    if (eta <= eta_tol || steps >= max_steps) break;
+    eta_prev = eta;
+    TRY(solve_impl(h, res, res + nd, res + nd + ns, cor, cor + nd, cor + nd + ns));
+    launch_step_update(S(h), nd, ns, m, cor, prev, dx_d, dx_s, dy, false);
+    steps++;
+  }
+  if (info) {
+    info->eta = eta;
+    info->rel_residual = rres;
+    info->steps = steps;
+  }
+  return (eta <= eta_tol) ? MDS_OK : MDS_REFINE_NOCONV;
+}
+
 int refine_impl(mds_handle *h, const double *r_d, const double *r_s, const double *r_y,
                 double *dx_d, double *dx_s, double *dy, int max_steps, double eta_tol,
                 mds_refine_info *info) {
   if (h->fac_lowprec)
     return gmres_refine(h, r_d, r_s, r_y, dx_d, dx_s, dy, max_steps, eta_tol, info);
+  if (use_fused(h))
+    return refine_fused(h, r_d, r_s, r_y, dx_d, dx_s, dy, max_steps, eta_tol, info);
   const int nd = ND(h), ns = NS(h), m = MM(h);
   const size_t nt = (size_t)nd + ns + m;
   double *res = h->w.res, *cor = h->w.cor, *prev = h->w.prev, *kx = h->w.kx;
@@ -1019,16 +1153,22 @@ void eval_grad_constr(mds_handle *h, const double *x, const double *y, double *r
   }
 }
 
+// have: gf, jty and cx of this point are in the scratch already
 int opt_error_impl(mds_handle *h, const double *x, const double *y, const double *zl,
-                   const double *zu, double mu, double *E, double *parts) {
+                   const double *zu, double mu, double *E, double *parts, bool have = false) {
   const int n = h->nx, m = MM(h);
   const double s_max = 100.0;
-  eval_grad_constr(h, x, y, nullptr);
-  ipm_red_opt(S(h), n, m, x, y, zl, zu, h->w.xl_e, h->w.xu_e, h->w.tn, h->w.tn2, h->w.tm, mu,
-              h->w.red, h->w.scal);
-  HIPCHK(hipGetLastError());
-  double s[8];
-  TRY(read_scal(h, s, 8));
+  double s[kRecVals + 1] = {};
+  if (use_fused(h) && !have) {
+    eval_fused(h, x, y, zl, zu, mu, false, nullptr);
+    TRY(read_rec(h, s));
+  } else {
+    if (!have) eval_grad_constr(h, x, y, nullptr);
+    ipm_red_opt(S(h), n, m, x, y, zl, zu, h->w.xl_e, h->w.xu_e, h->w.tn, h->w.tn2, h->w.tm, mu,
+                h->w.red, h->w.scal);
+    HIPCHK(hipGetLastError());
+    TRY(read_scal(h, s, 8));
+  }
   const double dual = s[0], prim = s[1], cl = s[2], cu = s[3], y1 = s[4], z1 = s[5];
   const double nz = s[6];
   const double sd = (m + nz > 0) ? std::max(s_max, (y1 + z1) / ((double)m + nz)) / s_max : 1.0;
@@ -1050,12 +1190,17 @@ int opt_error_pair(mds_handle *h, const double *x, const double *y, const double
                    const double *zu, double mu, double *E0, double *Emu) {
   const int n = h->nx, m = MM(h);
   const double s_max = 100.0;
-  eval_grad_constr(h, x, y, nullptr);
-  ipm_red_opt_pair(S(h), n, m, x, y, zl, zu, h->w.xl_e, h->w.xu_e, h->w.tn, h->w.tn2, h->w.tm,
-                   mu, h->w.red, h->w.scal);
-  HIPCHK(hipGetLastError());
-  double s[8];
-  TRY(read_scal(h, s, 8));
+  double s[kRecVals + 1] = {};
+  if (use_fused(h)) {
+    eval_fused(h, x, y, zl, zu, mu, true, nullptr);
+    TRY(read_rec(h, s));
+  } else {
+    eval_grad_constr(h, x, y, nullptr);
+    ipm_red_opt_pair(S(h), n, m, x, y, zl, zu, h->w.xl_e, h->w.xu_e, h->w.tn, h->w.tn2, h->w.tm,
+                     mu, h->w.red, h->w.scal);
+    HIPCHK(hipGetLastError());
+    TRY(read_scal(h, s, 8));
+  }
   const double dual = s[0], prim = s[1], cmu = s[2], c0 = s[3], y1 = s[4], z1 = s[5];
   const double nz = s[6];
   const double sd = (m + nz > 0) ? std::max(s_max, (y1 + z1) / ((double)m + nz)) / s_max : 1.0;
@@ -1148,12 +1293,31 @@ int nlp_jacobian(mds_handle *h, const double *x) {
   return MDS_OK;
 }
 
+// f, phi, theta at x, or at x + alpha p, which xt then holds
+int merit_at(mds_handle *h, const double *x, const double *p, double alpha, double *xt, double mu,
+             double (&s)[kRecVals + 1]) {
+  RowArgs a = row_args(h);
+  a.x = x;
+  a.xs = x + a.nd;
+  a.p = p;
+  a.alpha = alpha;
+  a.xt = xt;
+  a.mu = mu;
+  a.cx = h->w.tm;
+  launch_rows(S(h), kRowMerit, a);
+  return read_rec(h, s);
+}
+
 int merit_impl(mds_handle *h, const double *x, double mu, double *f, double *phi, double *theta) {
   if (h->nlp_on) return merit_nlp(h, x, mu, f, phi, theta, nullptr);
-  merit_launch(h, x, mu, h->w.scal);
-  HIPCHK(hipGetLastError());
-  double s[8];
-  TRY(read_scal(h, s, 8));
+  double s[kRecVals + 1] = {};
+  if (use_fused(h)) {
+    TRY(merit_at(h, x, nullptr, 0.0, nullptr, mu, s));
+  } else {
+    merit_launch(h, x, mu, h->w.scal);
+    HIPCHK(hipGetLastError());
+    TRY(read_scal(h, s, 8));
+  }
   if (f) *f = s[4];
   if (phi) *phi = s[4] - mu * s[5];
   if (theta) *theta = s[6];
@@ -1273,6 +1437,8 @@ int mds_create(mds_handle **out, const mds_dims *dims, const mds_options *opts, 
   w.flags = I(S_FLAGS);
   w.red = D(S_RED);
   w.scal = D(S_SCAL);
+  w.rec = D(S_REC);
+  w.rec_count = I(S_RECN);
   w.z = D(S_Z);
   w.z2 = D(S_Z2);
   w.hmap = I(S_HMAP);
@@ -1341,7 +1507,10 @@ int mds_create(mds_handle **out, const mds_dims *dims, const mds_options *opts, 
       hipMemsetAsync(w.xch, 0, kCoopXchBytes, h->stream) !=
           hipSuccess ||
       hipMemsetAsync(w.fst, 0, sizeof(FacState), h->stream) != hipSuccess ||
+      hipMemsetAsync(w.rec_count, 0, 256, h->stream) != hipSuccess ||
+      hipHostMalloc((void **)&h->pin, kPinBytes, hipHostMallocDefault) != hipSuccess ||
       hipStreamSynchronize(h->stream) != hipSuccess) {
+    if (h->pin) (void)hipHostFree(h->pin);
     delete h;
     return MDS_EHIP;
   }
@@ -1358,6 +1527,10 @@ int mds_create(mds_handle **out, const mds_dims *dims, const mds_options *opts, 
 void mds_destroy(mds_handle *h) {
   if (!h) return;
   for (hipEvent_t e : h->ev_pool) (void)hipEventDestroy(e);
+  if (h->pin) {
+    (void)hipStreamSynchronize(h->stream);  // its last writer
+    (void)hipHostFree(h->pin);
+  }
   if (h->fac_exec) (void)hipGraphExecDestroy(h->fac_exec);
   if (h->cap_stream) (void)hipStreamDestroy(h->cap_stream);
   if (h->la_a) (void)hipStreamDestroy(h->la_a);
@@ -1680,7 +1853,8 @@ int mds_sigma_rhs(mds_handle *h, const double *x, const double *y, const double 
   TRY(check_ready(h));
   if ((h->nx > 0 && (!x || !zl || !zu || !sigma || !r_x)) || (MM(h) > 0 && (!y || !r_y)))
     return set_err(h, MDS_ENULL, "vector missing");
-  eval_grad_constr(h, x, y, r_y);
+  if (use_fused(h)) eval_fused(h, x, y, nullptr, nullptr, mu, false, r_y);
+  else eval_grad_constr(h, x, y, r_y);
   ipm_sigma_rhs(S(h), h->nx, x, zl, zu, h->w.xl_e, h->w.xu_e, h->w.tn, h->w.tn2, mu, sigma, r_x);
   HIPCHK(hipGetLastError());
   return MDS_OK;
@@ -1941,7 +2115,7 @@ static int ipm_step_impl(mds_handle *h, mds_iterate *it, mds_step_info *info, bo
   // barrier update while the barrier subproblem is solved to kappa_eps * mu
   for (bool first = true;; first = false) {
     double Emu = Emu0;
-    if (!first) TRY(opt_error_impl(h, x, y, zl, zu, mu, &Emu, nullptr));
+    if (!first) TRY(opt_error_impl(h, x, y, zl, zu, mu, &Emu, nullptr, !nlp));
     if (!(Emu <= kappa_eps * mu)) break;
     const double mnew = std::max(h->ipm.tol / 10.0, std::min(kappa_mu * mu, std::pow(mu, theta_mu)));
     if (!(mnew < mu)) break;
@@ -1973,9 +2147,16 @@ static int ipm_step_impl(mds_handle *h, mds_iterate *it, mds_step_info *info, bo
   // and their rhs gains dcv .* r_d.
   double *sig = h->w.sig, *rx = h->w.rx, *ry = h->w.ry, *ry2 = h->w.ry2, *dsb = h->w.dsb;
   double *dx = h->w.dx, *dy = h->w.dy, *dzl = h->w.dzl, *dzu = h->w.dzu, *xt = h->w.xt;
-  TRY(mds_sigma_rhs(h, x, y, zl, zu, mu, sig, rx, ry));
-  if (nlp) TRY(nlp_model_ok(h));
-  ipm_dsbase(S(h), nd, ns, P.w, sig, dsb);
+  const bool fused = use_fused(h);
+  if (fused) {
+    // gf, jty and cx at x are those of the optimality error above
+    launch_newton_rhs(S(h), nd, ns, n, m, x, zl, zu, xl, xu, h->w.tn, h->w.tn2, h->w.tm, P.w, mu,
+                      sig, rx, dsb, ry);
+  } else {
+    TRY(mds_sigma_rhs(h, x, y, zl, zu, mu, sig, rx, ry));
+    if (nlp) TRY(nlp_model_ok(h));
+    ipm_dsbase(S(h), nd, ns, P.w, sig, dsb);
+  }
   h->sigma_d = sig;
   h->dsbase = dsb;
   h->sig_h = (h->mI > 0) ? sig + h->n : nullptr;
@@ -1997,9 +2178,9 @@ static int ipm_step_impl(mds_handle *h, mds_iterate *it, mds_step_info *info, bo
     I.inertia[2] = in.nneg;
     I.trials += reg.trials;
     if (fst == MDS_INERTIA_FAIL) return fst;
-    vec_copy(S(h), m, ry, ry2);
-    ipm_ineq_rhs(S(h), h->mI, h->mE, h->w.dcv, rx + h->n, ry2);
-    const int rst = refine_impl(h, rx, rx + nd, ry2, dx, dx + nd, dy, rsteps, 1e-14, ri);
+    if (h->mI > 0) launch_ineq_rhs2(S(h), m, h->mE, h->w.dcv, rx + h->n, ry, ry2);
+    const int rst = refine_impl(h, rx, rx + nd, h->mI > 0 ? ry2 : ry, dx, dx + nd, dy, rsteps,
+                                1e-14, ri);
     if (rst < 0) return rst;
     I.solves += 1 + ri->steps;
     return rst;
@@ -2023,27 +2204,43 @@ static int ipm_step_impl(mds_handle *h, mds_iterate *it, mds_step_info *info, bo
   if (rst < 0) return rst;
   if (rst == MDS_INERTIA_FAIL) return I.status = MDS_INERTIA_FAIL;
   I.eta = ri.eta;
-  // slack step from the multiplier step: dd = dcv .* (r_d + dy_h)
-  ipm_ineq_step(S(h), h->mI, h->mE, h->w.dcv, rx + h->n, dy, dx + h->n);
-  // fraction to the boundary, grad(phi_mu)' dx and the merit values at x:
-  // three reductions into separate records, read back together
-  ipm_dz(S(h), n, x, zl, zu, xl, xu, dx, mu, dzl, dzu);
-  ipm_red_ftb(S(h), n, x, xl, xu, dx, zl, zu, dzl, dzu, tau, h->w.red, h->w.scal);
-  // grad f at x (the refinement used the scratch), read by the gphi reduction
-  // before the merit products overwrite it
-  eval_grad_constr(h, x, nullptr, nullptr);
-  ipm_red_gphi(S(h), n, h->w.tn, x, xl, xu, dx, mu, h->w.red, h->w.scal + 8);
-  if (nlp) {
-    // the gradient pass left the rows' residual at x in w.tm: keep it for
-    // the second-order correction
-    vec_copy(S(h), m, h->w.tm, h->nlp_cx0);
-    nlp_merit_launch(h, x, mu, h->w.scal + 16);
+  double s24[24] = {};
+  if (fused) {
+    // slack step, multiplier directions, fraction to the boundary,
+    // grad(phi_mu)' dx and the merit values at x in one pass
+    const DirArgs a{nd,      ns,         n,          m,    h->mE,   x,    zl,   zu,   xl,
+                    xu,      h->w.tn,    h->w.xt,    h->w.tm, P.c, P.w,  P.g,  rx,   dy,
+                    h->w.dcv, mu,        tau,        dx,   dzl,     dzu,  h->w.rec,
+                    h->pin + kPinRec, h->w.rec_count};
+    launch_direction(S(h), a);
+    double v[kRecVals + 1];
+    TRY(read_rec(h, v));
+    s24[0] = v[0];
+    s24[1] = v[1];
+    s24[8 + 4] = v[4];
+    for (int q = 0; q < 4; ++q) s24[16 + 4 + q] = v[5 + q];
   } else {
-    merit_launch(h, x, mu, h->w.scal + 16);
+    // slack step from the multiplier step: dd = dcv .* (r_d + dy_h)
+    ipm_ineq_step(S(h), h->mI, h->mE, h->w.dcv, rx + h->n, dy, dx + h->n);
+    // fraction to the boundary, grad(phi_mu)' dx and the merit values at x:
+    // three reductions into separate records, read back together
+    ipm_dz(S(h), n, x, zl, zu, xl, xu, dx, mu, dzl, dzu);
+    ipm_red_ftb(S(h), n, x, xl, xu, dx, zl, zu, dzl, dzu, tau, h->w.red, h->w.scal);
+    // grad f at x (the refinement used the scratch), read by the gphi reduction
+    // before the merit products overwrite it
+    eval_grad_constr(h, x, nullptr, nullptr);
+    ipm_red_gphi(S(h), n, h->w.tn, x, xl, xu, dx, mu, h->w.red, h->w.scal + 8);
+    if (nlp) {
+      // the gradient pass left the rows' residual at x in w.tm: keep it for
+      // the second-order correction
+      vec_copy(S(h), m, h->w.tm, h->nlp_cx0);
+      nlp_merit_launch(h, x, mu, h->w.scal + 16);
+    } else {
+      merit_launch(h, x, mu, h->w.scal + 16);
+    }
+    HIPCHK(hipGetLastError());
+    TRY(read_scal(h, s24, 24));
   }
-  HIPCHK(hipGetLastError());
-  double s24[24];
-  TRY(read_scal(h, s24, 24));
   double fx = s24[16 + 4], fscale = 0.0;
   if (nlp) {
     TRY(nlp_model_ok(h));
@@ -2089,9 +2286,16 @@ static int ipm_step_impl(mds_handle *h, mds_iterate *it, mds_step_info *info, bo
   int nbt = 0;
   const double *xacc = xt;
   for (;;) {
-    ipm_axpy_to(S(h), n, x, dx, alpha, xt);
     double tht = 0.0, pht = 0.0;
-    TRY(merit_impl(h, xt, mu, nullptr, &pht, &tht));
+    if (fused) {
+      double v[kRecVals + 1];
+      TRY(merit_at(h, x, dx, alpha, xt, mu, v));
+      pht = v[4] - mu * v[5];
+      tht = v[6];
+    } else {
+      ipm_axpy_to(S(h), n, x, dx, alpha, xt);
+      TRY(merit_impl(h, xt, mu, nullptr, &pht, &tht));
+    }
     if (acceptable(alpha, tht, pht, &augment)) {
       accepted = true;
       break;

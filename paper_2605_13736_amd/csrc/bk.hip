@@ -74,6 +74,11 @@ __global__ void k_fac_reset(FacState *st, int32_t *panel_k0) {
   }
 }
 
+// the factorization's state to the host's pinned copy
+__global__ void k_fac_publish(const FacState *st, FacState *host) {
+  if (threadIdx.x == 0) *host = *st;
+}
+
 __global__ __launch_bounds__(NT) void k_bk_panel(int N, int nb, double alpha,
                                                  double *__restrict__ M,
                                                  double *__restrict__ W,
@@ -746,6 +751,10 @@ __global__ __launch_bounds__(256) void k_lstage_copy(int N, const double *__rest
 
 void launch_fac_reset(hipStream_t s, FacState *st, int32_t *panel_k0) {
   k_fac_reset<<<1, 64, 0, s>>>(st, panel_k0);
+}
+
+void launch_fac_publish(hipStream_t s, const FacState *st, FacState *host) {
+  k_fac_publish<<<1, 64, 0, s>>>(st, host);
 }
 
 void launch_bk_panel(hipStream_t s, int N, int nb, double alpha, double *M, double *W,

@@ -430,12 +430,6 @@ __global__ void k_to_f32_scaled(int N, const double *__restrict__ a, const doubl
   }
 }
 
-// v = s .* v
-__global__ void k_vscale(int n, const double *__restrict__ s, double *__restrict__ v) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) v[i] = s[i] * v[i];
-}
-
 }  // namespace
 
 void launch_trailing_lp(hipStream_t s, int mode, int N, int nb, int wmax, long rem, int slot,
@@ -487,10 +481,6 @@ void launch_equilibrate_f32(hipStream_t s, int N, const double *M, double *scale
   const int64_t n = (int64_t)N * N;
   const int64_t blocks = std::min<int64_t>((n + 255) / 256, 8192);
   k_to_f32_scaled<<<(unsigned)blocks, 256, 0, s>>>(N, M, scale, b);
-}
-
-void launch_vscale(hipStream_t s, int n, const double *scale, double *v) {
-  if (n > 0) k_vscale<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(n, scale, v);
 }
 
 }  // namespace mds

@@ -17,12 +17,6 @@ namespace {
 
 constexpr int kTile = 64;
 
-__global__ void k_inv_d(int ns, const double *__restrict__ dsbase, double dw,
-                        double *__restrict__ inv_d) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < ns) inv_d[i] = 1.0 / (dsbase[i] + dw);
-}
-
 // One 64 x 64 tile of M per workgroup (256 threads).  Everything but the
 // (1,2) block J_d' is read along columns (coalesced); the J_d' block is
 // transposed through LDS.
@@ -30,8 +24,18 @@ __global__ __launch_bounds__(256) void k_condense_dense(int nd, int m, int N,
                                                         const double *__restrict__ H,
                                                         const double *__restrict__ Jd,
                                                         const double *__restrict__ sig,
-                                                        double dw, double *__restrict__ M) {
+                                                        double dw, int ns,
+                                                        const double *__restrict__ dsbase,
+                                                        double *__restrict__ inv_d,
+                                                        double *__restrict__ M) {
   __shared__ double t[kTile][kTile + 1];
+  // D_s^{-1} beside the dense blocks (one launch less)
+  if (inv_d) {
+    const int64_t step = (int64_t)gridDim.x * gridDim.y * 256;
+    for (int64_t k = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x; k < ns;
+         k += step)
+      inv_d[k] = 1.0 / (dsbase[k] + dw);
+  }
   const int I0 = blockIdx.x * kTile, J0 = blockIdx.y * kTile;
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
   const bool has_t = (I0 < nd) && (J0 + kTile > nd);  // tile touches the J_d' block
@@ -100,32 +104,6 @@ __global__ void k_condense_schur(int nd, int m, int N, const int32_t *__restrict
   const size_t dpos = (size_t)(nd + r) + col;
   M[dpos] = M[dpos] - dc;
   if (dcv) M[dpos] = M[dpos] - dcv[r];
-}
-
-__global__ void k_rhs_condense(int m, const int32_t *__restrict__ rp,
-                               const int32_t *__restrict__ ci, const double *__restrict__ v,
-                               const double *__restrict__ inv_d,
-                               const double *__restrict__ r_s,
-                               const double *__restrict__ r_y, double *__restrict__ out) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= m) return;
-  double t = r_y[i];
-  for (int a = rp[i]; a < rp[i + 1]; ++a) {
-    const int k = ci[a];
-    t = t - v[a] * (inv_d[k] * r_s[k]);
-  }
-  out[i] = t;
-}
-
-__global__ void k_backsub(int ns, const int32_t *__restrict__ cptr,
-                          const int32_t *__restrict__ crow, const double *__restrict__ cval,
-                          const double *__restrict__ inv_d, const double *__restrict__ r_s,
-                          const double *__restrict__ dy, double *__restrict__ dx_s) {
-  int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= ns) return;
-  double t = r_s[k];
-  for (int e = cptr[k]; e < cptr[k + 1]; ++e) t = t - cval[e] * dy[crow[e]];
-  dx_s[k] = inv_d ? inv_d[k] * t : t;
 }
 
 // ---- column-compressed copy of J_s ----------------------------------------
@@ -256,17 +234,14 @@ inline unsigned grid1(int64_t n, int bs) { return (unsigned)((n + bs - 1) / bs);
 
 }  // namespace
 
-void launch_inv_d(hipStream_t s, int ns, const double *dsbase, double dw, double *inv_d) {
-  if (ns <= 0) return;
-  k_inv_d<<<grid1(ns, 256), 256, 0, s>>>(ns, dsbase, dw, inv_d);
-}
-
 void launch_condense_dense(hipStream_t s, int nd, int m, const double *H, const double *Jd,
-                           const double *sigma_d, double dw, double *M) {
+                           const double *sigma_d, double dw, int ns, const double *dsbase,
+                           double *inv_d, double *M) {
   const int N = nd + m;
-  if (N <= 0) return;
-  dim3 g(grid1(N, kTile), grid1(N, kTile));
-  k_condense_dense<<<g, 256, 0, s>>>(nd, m, N, H, Jd, sigma_d, dw, M);
+  if (N <= 0 && (ns <= 0 || !inv_d)) return;
+  // without dense rows one workgroup's worth of tiles still forms D_s^{-1}
+  dim3 g(N > 0 ? grid1(N, kTile) : 1, N > 0 ? grid1(N, kTile) : grid1(ns, 256));
+  k_condense_dense<<<g, 256, 0, s>>>(nd, m, N, H, Jd, sigma_d, dw, ns, dsbase, inv_d, M);
 }
 
 void launch_condense_schur(hipStream_t s, int nd, int m, int N, const int32_t *rp,
@@ -276,20 +251,6 @@ void launch_condense_schur(hipStream_t s, int nd, int m, int N, const int32_t *r
   if (m <= 0) return;
   k_condense_schur<<<grid1(m, 128), 128, 0, s>>>(nd, m, N, rp, ci, v, cptr, crow, cval, inv_d,
                                                  dc, dcv, M);
-}
-
-void launch_rhs_condense(hipStream_t s, int m, const int32_t *rp, const int32_t *ci,
-                         const double *v, const double *inv_d, const double *r_s,
-                         const double *r_y, double *out) {
-  if (m <= 0) return;
-  k_rhs_condense<<<grid1(m, 256), 256, 0, s>>>(m, rp, ci, v, inv_d, r_s, r_y, out);
-}
-
-void launch_backsub(hipStream_t s, int ns, const int32_t *cptr, const int32_t *crow,
-                    const double *cval, const double *inv_d, const double *r_s,
-                    const double *dy, double *dx_s) {
-  if (ns <= 0) return;
-  k_backsub<<<grid1(ns, 256), 256, 0, s>>>(ns, cptr, crow, cval, inv_d, r_s, dy, dx_s);
 }
 
 void launch_csc_build(hipStream_t s, int m, int ns, int64_t nnz, const int32_t *rp,

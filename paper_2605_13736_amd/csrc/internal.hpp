@@ -108,6 +108,8 @@ struct Work {
   int32_t *csc_fill;  // n_s scratch
   int32_t *flags;     // validation flags (16)
   double *red;        // reduction partials (kRedBlocks * 8)
+  double *rec;        // records of the fused passes (kRecBlocks * kRecStride)
+  int32_t *rec_count; // their arrival counter (zero between passes)
   double *scal;       // device scalars (64)
   double *z;          // N: condensed rhs / solution
   double *z2;         // N: permuted solve vector
@@ -173,6 +175,9 @@ struct mds_handle {
   int la_cus = 0, la_grid = 0;
   hipStream_t la_a = nullptr, la_b = nullptr;
   hipEvent_t la_ev[4] = {};
+  // pinned host memory the read-backs go to: kRecBlocks' combined record (16
+  // doubles) at 0, then scalars, the factorization's state
+  double *pin = nullptr;
   // captured launch sequence of one factorization (replayed without timing)
   hipGraphExec_t fac_exec = nullptr;
   hipStream_t cap_stream = nullptr;
@@ -236,19 +241,14 @@ void sblk_absrow(hipStream_t s, const SBlk &B, int ns, const double *dsb, double
                  double *dsb_eff);
 
 // condense.hip
-void launch_inv_d(hipStream_t s, int ns, const double *dsbase, double dw, double *inv_d);
+// ... and inv_d = 1 / (dsbase + dw) beside it (inv_d null: not written)
 void launch_condense_dense(hipStream_t s, int nd, int m, const double *H, const double *Jd,
-                           const double *sigma_d, double dw, double *M);
+                           const double *sigma_d, double dw, int ns, const double *dsbase,
+                           double *inv_d, double *M);
 void launch_condense_schur(hipStream_t s, int nd, int m, int N, const int32_t *rp,
                            const int32_t *ci, const double *v, const int32_t *cptr,
                            const int32_t *crow, const double *cval, const double *inv_d,
                            double dc, const double *dcv, double *M);
-void launch_rhs_condense(hipStream_t s, int m, const int32_t *rp, const int32_t *ci,
-                         const double *v, const double *inv_d, const double *r_s,
-                         const double *r_y, double *out);
-void launch_backsub(hipStream_t s, int ns, const int32_t *cptr, const int32_t *crow,
-                    const double *cval, const double *inv_d, const double *r_s,
-                    const double *dy, double *dx_s);
 void launch_csc_build(hipStream_t s, int m, int ns, int64_t nnz, const int32_t *rp,
                       const int32_t *ci, const double *v, int32_t *cptr, int32_t *crow,
                       double *cval, int32_t *fill);
@@ -256,6 +256,8 @@ void launch_validate(hipStream_t s, const mds_dims &d, const mds_problem &p, int
 
 // bk.hip
 void launch_fac_reset(hipStream_t s, FacState *st, int32_t *panel_k0);
+// *st to the host's pinned copy
+void launch_fac_publish(hipStream_t s, const FacState *st, FacState *host);
 void launch_bk_panel(hipStream_t s, int N, int nb, double alpha, double *M, double *W,
                      double *dd, double *ds, int32_t *ipiv, int32_t *blk, FacState *st,
                      int32_t *panel_k0);
@@ -346,7 +348,6 @@ void launch_trailing_lp_part(hipStream_t s, int mode, int N, int nb, long rem, i
                              const int32_t *panel_k0);
 // scale = 1/sqrt(row max |M|), b = FP32(S M S); v = scale .* v
 void launch_equilibrate_f32(hipStream_t s, int N, const double *M, double *scale, float *b);
-void launch_vscale(hipStream_t s, int n, const double *scale, double *v);
 
 // gmres.hip: Krylov products (partial[c * kDotBlocks + b]) and updates
 void launch_dots(hipStream_t s, int64_t n, int ncol, const double *V, int64_t ldv,
@@ -371,9 +372,20 @@ void launch_std_form(hipStream_t s, int N, const double *M0, const double *M1, i
 // out = M^{-1} v through P, L, D; z is scratch (N); trsv (std_trsv_bytes(N),
 // 8-byte aligned, zeroed once when the handle is made): epoch, error word,
 // pad, then the tagged solution words of the triangular solves
-void launch_std_solve(hipStream_t s, int N, const double *Lstd, const double *dd,
-                      const double *ds, const int32_t *blk, const int32_t *perm, const double *v,
-                      double *z, double *out, int32_t *trsv);
+struct StdSolveArgs {
+  // condensed right-hand side r_y - J D^{-1} r_sy (J CSR; with coupling blocks
+  // the transformed Jacobian and L^{-1} r_s)
+  const int32_t *rp, *ci;
+  const double *v, *inv_d, *r_d, *r_sy, *r_y;
+  const double *eq;  // mixed precision: equilibration (else null)
+  // back-substitution dx_s = inv_out .* (r_s - J_s' dy) (inv_out null: unscaled)
+  const int32_t *cptr, *crow;
+  const double *cval, *inv_out, *r_s;
+};
+void launch_std_solve(hipStream_t s, int N, int nd, int ns, const double *Lstd, const double *dd,
+                      const double *ds, const int32_t *blk, const int32_t *perm,
+                      const StdSolveArgs &a, double *z, double *z2, double *dx_d, double *dx_s,
+                      double *dy, int32_t *trsv);
 
 // vec.hip
 void launch_gemv_n(hipStream_t s, int rows, int cols, const double *A, int lda,

@@ -9,6 +9,58 @@
 
 namespace mds {
 
+// ---- fused.hip: fused passes (quadratic problem, no coupling blocks) ---------
+// Records of one block: 4 maxima, then sums; the combined record (kRecVals
+// values, then an error word) goes to pinned host memory.
+constexpr int kRecVals = 12, kRecStride = 16, kRecGrid = 512;
+constexpr int kRowRes = 0, kRowEval = 1, kRowMerit = 2;
+struct RowArgs {
+  int nd, ns, m, mE;
+  int nbD, nbY, nbS;  // blocks per range (set by the launcher)
+  const double *H, *Jd;
+  const int32_t *rp, *ci;
+  const double *v;
+  const int32_t *cptr, *crow;
+  const double *cval;
+  const double *x, *xs, *y;  // [x_d; x_s; slacks], its x_s, y (kRowRes: the direction, x_d only in x)
+  // kRowRes
+  const double *rd, *rs, *ry, *sig, *dsb, *dcv;
+  double dw, dc;
+  double *res;           // n_d + n_s + m
+  int norms;
+  // kRowEval, kRowMerit
+  const double *c, *w, *g, *b, *xl, *xu, *zl, *zu;  // zl null: no optimality error
+  double mu;
+  int pair;              // complementarity maxima at mu and at 0 instead of lower and upper
+  double *hx, *gf, *jty, *cx, *ryo;
+  const double *p;       // kRowMerit: trial point x + alpha p, written to xt
+  double alpha;
+  double *xt;
+  // records (out null: none)
+  double *rec, *out;
+  int32_t *counter;
+  const int32_t *err;
+};
+// records a pass may write (kRecStride values each)
+int rec_blocks(int nd, int ns, int m);
+void launch_rows(hipStream_t s, int mode, RowArgs a);
+struct DirArgs {
+  int nd, ns, nx, m, mE;
+  const double *x, *zl, *zu, *xl, *xu, *gf, *hx, *cx, *c, *w, *g, *rx, *dy, *dcv;
+  double mu, tau;
+  double *dx, *dzl, *dzu, *rec, *out;
+  int32_t *counter;
+};
+void launch_direction(hipStream_t s, const DirArgs &a);
+void launch_newton_rhs(hipStream_t s, int nd, int ns, int nx, int m, const double *x,
+                       const double *zl, const double *zu, const double *xl, const double *xu,
+                       const double *gf, const double *jty, const double *cx, const double *w,
+                       double mu, double *sigma, double *rx, double *dsb, double *ry);
+void launch_step_update(hipStream_t s, int nd, int ns, int m, const double *cor, double *prev,
+                        double *dxd, double *dxs, double *dy, bool back);
+void launch_ineq_rhs2(hipStream_t s, int m, int mE, const double *dcv, const double *rd,
+                      const double *ry, double *ry2);
+
 void ipm_init_point(hipStream_t s, int n, int m, const double *xl, const double *xu, double *x,
                     double *y, double *zl, double *zu);
 void ipm_init_warm(hipStream_t s, int nd, int ns, int m, const double *xl, const double *xu,

@@ -170,37 +170,43 @@ __global__ __launch_bounds__(AT) void k_std_apply(int N, const double *M0, const
   for (int y = k1 + tid; y < N; y += AT) Lstd[co + y] = s_col[y - k1];
 }
 
-// z[h(x)] = v[x]; also advances the solve epoch
-__global__ void k_perm_scatter(int N, const int32_t *__restrict__ perm,
-                               const double *__restrict__ v, double *__restrict__ z,
-                               int32_t *epoch) {
+// Condensed right-hand side into the solve's order, z[h(x)] = [r_d; r_y - J_s
+// D_s^{-1} r_s]_x (scaled by eq in mixed precision); also advances the solve
+// epoch.
+__global__ void k_solve_rhs(int N, int nd, const int32_t *__restrict__ perm,
+                            const int32_t *__restrict__ rp, const int32_t *__restrict__ ci,
+                            const double *__restrict__ v, const double *__restrict__ inv_d,
+                            const double *__restrict__ r_d, const double *__restrict__ r_s,
+                            const double *__restrict__ r_y, const double *__restrict__ eq,
+                            double *__restrict__ z, int32_t *epoch) {
   const int x = blockIdx.x * blockDim.x + threadIdx.x;
   if (x == 0) epoch[0] = epoch[0] + 1;
-  if (x < N) z[perm[x]] = v[x];
-}
-
-// v[x] = z[h(x)]
-__global__ void k_perm_gather(int N, const int32_t *__restrict__ perm,
-                              const double *__restrict__ z, double *__restrict__ v) {
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  if (x < N) v[x] = z[perm[x]];
-}
-
-// D^{-1}: 1x1 pivots divide, 2x2 pivots [a s; s c] by Cramer's rule
-__global__ void k_diag_solve(int N, const double *__restrict__ dd, const double *__restrict__ ds,
-                             const int32_t *__restrict__ blk, double *__restrict__ z) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= N) return;
-  const int bk = blk[k];
-  if (bk == 1) {
-    z[k] = z[k] / dd[k];
-  } else if (bk == 2) {
-    const double a = dd[k], c = dd[k + 1], s = ds[k];
-    const double det = a * c - s * s;
-    const double y0 = z[k], y1 = z[k + 1];
-    z[k] = (c * y0 - s * y1) / det;
-    z[k + 1] = (a * y1 - s * y0) / det;
+  if (x >= N) return;
+  double t;
+  if (x < nd) {
+    t = r_d[x];
+  } else {
+    const int i = x - nd;
+    t = r_y[i];
+    for (int a = rp[i]; a < rp[i + 1]; ++a) {
+      const int k = ci[a];
+      t = t - v[a] * (inv_d[k] * r_s[k]);
+    }
   }
+  if (eq) t = eq[x] * t;
+  z[perm[x]] = t;
+}
+
+// Entry k of D^{-1} z: 1x1 pivots divide, 2x2 pivots [a s; s c] by Cramer's rule
+__device__ inline double diag_solve(const double *dd, const double *ds, const int32_t *blk,
+                                    const double *z, int k) {
+  const int bk = blk[k];
+  if (bk == 1) return z[k] / dd[k];
+  const int f = (bk == 2) ? k : k - 1;
+  const double a = dd[f], c = dd[f + 1], s = ds[f];
+  const double det = a * c - s * s;
+  const double y0 = z[f], y1 = z[f + 1];
+  return (bk == 2) ? (c * y0 - s * y1) / det : (a * y1 - s * y0) / det;
 }
 
 // Solved values are published as tagged words: the double of row x goes
@@ -313,13 +319,18 @@ __global__ __launch_bounds__(TB) void k_trsv_fwd(int N, const double *__restrict
   }
 }
 
-// Backward L' x = z, in place.  Launch index b handles block i = nblk-1-b.
+// Backward L' out = D^{-1} z (D^{-1} as the rows are loaded; z is not written,
+// since a 2x2 pivot may span two blocks).  Launch index b handles block
+// i = nblk-1-b.
 // Lane r takes row q0 + r of a dependency block (contiguous in a column of
 // L) and waits for its solved value, wave g the 16 columns r0 + 16 g + t of
 // this block; the 64 lane partial sums of every column are reduced through
 // LDS at the end.
 __global__ __launch_bounds__(TB) void k_trsv_bwd(int N, int nblk, const double *__restrict__ L,
-                                                 double *z, uint64_t *tw,
+                                                 const double *z, const double *__restrict__ dd,
+                                                 const double *__restrict__ ds,
+                                                 const int32_t *__restrict__ blk,
+                                                 double *__restrict__ out, uint64_t *tw,
                                                  const int32_t *epoch_p, int32_t *err) {
   __shared__ double s_red[BS][BS + 1];
   __shared__ double s_d[BS][BS + 1];
@@ -335,7 +346,7 @@ __global__ __launch_bounds__(TB) void k_trsv_bwd(int N, int nblk, const double *
   }
   const int cbase = r0 + g * 16;  // this wave's 16 columns of the block
   // this row's right-hand side: only this workgroup writes it, at its end
-  const double zrow = (r0 + r < N) ? z[r0 + r] : 0.0;
+  const double zrow = (r0 + r < N) ? diag_solve(dd, ds, blk, z, r0 + r) : 0.0;
   double acc[16], pf[16];
 #pragma unroll
   for (int t = 0; t < 16; ++t) acc[t] = 0.0;
@@ -387,9 +398,36 @@ __global__ __launch_bounds__(TB) void k_trsv_bwd(int N, int nblk, const double *
       if (r < c) v = fma(-s_d[c][r], xc, v);
     }
     if (live) {
-      z[row] = v;
+      out[row] = v;
       pub_sol(tw, row, v, tag);
     }
+  }
+}
+
+// dx_d, dy from the solve's order, [dx_d; dy]_x = z[h(x)] (scaled by eq), and
+// the back-substitution dx_s = D_s^{-1} (r_s - J_s' dy) (inv_d null: unscaled)
+__global__ void k_solve_out(int N, int nd, int ns, const int32_t *__restrict__ perm,
+                            const double *__restrict__ z, const double *__restrict__ eq,
+                            const int32_t *__restrict__ cptr, const int32_t *__restrict__ crow,
+                            const double *__restrict__ cval, const double *__restrict__ inv_d,
+                            const double *r_s, double *__restrict__ dx_d, double *dx_s,
+                            double *__restrict__ dy) {
+  const int x = blockIdx.x * blockDim.x + threadIdx.x;
+  if (x < N) {
+    double t = z[perm[x]];
+    if (eq) t = eq[x] * t;
+    if (x < nd) dx_d[x] = t;
+    else dy[x - nd] = t;
+  }
+  if (x < ns) {
+    double t = r_s[x];
+    for (int e = cptr[x]; e < cptr[x + 1]; ++e) {
+      const int i = nd + crow[e];
+      double y = z[perm[i]];
+      if (eq) y = eq[i] * y;
+      t = t - cval[e] * y;
+    }
+    dx_s[x] = inv_d ? inv_d[x] * t : t;
   }
 }
 
@@ -421,18 +459,22 @@ void launch_std_form(hipStream_t s, int N, const double *M0, const double *M1, i
                                                                     colpanel, hmap, Lstd);
 }
 
-void launch_std_solve(hipStream_t s, int N, const double *Lstd, const double *dd,
-                      const double *ds, const int32_t *blk, const int32_t *perm, const double *v,
-                      double *z, double *out, int32_t *trsv) {
-  if (N <= 0) return;
-  const int nblk = std_solve_blocks(N);
+void launch_std_solve(hipStream_t s, int N, int nd, int ns, const double *Lstd, const double *dd,
+                      const double *ds, const int32_t *blk, const int32_t *perm,
+                      const StdSolveArgs &a, double *z, double *z2, double *dx_d, double *dx_s,
+                      double *dy, int32_t *trsv) {
+  const int nblk = std_solve_blocks(N), len = N > ns ? N : ns;
   int32_t *epoch = trsv, *err = trsv + 1;
   uint64_t *tw = reinterpret_cast<uint64_t *>(trsv + 4);
-  k_perm_scatter<<<grid1(N, 256), 256, 0, s>>>(N, perm, v, z, epoch);
-  k_trsv_fwd<<<(unsigned)nblk, TB, 0, s>>>(N, Lstd, z, tw, epoch, err);
-  k_diag_solve<<<grid1(N, 256), 256, 0, s>>>(N, dd, ds, blk, z);
-  k_trsv_bwd<<<(unsigned)nblk, TB, 0, s>>>(N, nblk, Lstd, z, tw, epoch, err);
-  k_perm_gather<<<grid1(N, 256), 256, 0, s>>>(N, perm, z, out);
+  if (N > 0) {
+    k_solve_rhs<<<grid1(N, 256), 256, 0, s>>>(N, nd, perm, a.rp, a.ci, a.v, a.inv_d, a.r_d, a.r_sy,
+                                              a.r_y, a.eq, z, epoch);
+    k_trsv_fwd<<<(unsigned)nblk, TB, 0, s>>>(N, Lstd, z, tw, epoch, err);
+    k_trsv_bwd<<<(unsigned)nblk, TB, 0, s>>>(N, nblk, Lstd, z, dd, ds, blk, z2, tw, epoch, err);
+  }
+  if (len > 0)
+    k_solve_out<<<grid1(len, 256), 256, 0, s>>>(N, nd, ns, perm, z2, a.eq, a.cptr, a.crow, a.cval,
+                                                a.inv_out, a.r_s, dx_d, dx_s, dy);
 }
 
 }  // namespace mds
