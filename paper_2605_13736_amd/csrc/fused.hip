@@ -48,23 +48,30 @@ __device__ inline void block_record(double (&v)[kRecVals], double *rec) {
     const int s = threadIdx.x;
     double t = sh[0][s];
     for (int q = 1; q < FW; ++q) t = (s < NMAX) ? f_max(t, sh[q][s]) : t + sh[q][s];
-    rec[(size_t)blockIdx.x * kRecStride + s] = t;
+    __hip_atomic_store(&rec[(size_t)blockIdx.x * kRecStride + s], t, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
 // The last block to arrive combines the records in block order into out
 // (pinned host memory) and clears the counter.  err: an error word passed on.
+// The first wave wrote this block's record with agent-scope stores, so its
+// arrival waits for those alone; a fence here would write back the second-level
+// cache for every block (a pass at N = 192: 18 -> 11 us; at N = 4096: 137 -> 32).
 __device__ inline void finish_records(const double *rec, int32_t *counter, double *out,
                                       const int32_t *err) {
   __shared__ int s_last;
   __shared__ double sh[64][kRecStride + 1];
   const int tid = threadIdx.x;
-  __threadfence();
-  __syncthreads();
-  if (tid == 0) s_last = (atomicAdd(counter, 1) == (int)gridDim.x - 1);
+  if (tid == 0) {
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_s_waitcnt(0);
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    s_last = (__hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+              (int)gridDim.x - 1);
+  }
   __syncthreads();
   if (!s_last) return;
-  __threadfence();
   const int s = tid & (kRecStride - 1), g = tid / kRecStride;
   double t = (s < NMAX) ? -INFINITY : 0.0;
   if (s < kRecVals)
@@ -77,12 +84,12 @@ __device__ inline void finish_records(const double *rec, int32_t *counter, doubl
   __syncthreads();
   if (tid < kRecVals) {
     double r = sh[0][tid];
+#pragma unroll 8
     for (int q = 1; q < 64; ++q) r = (tid < NMAX) ? f_max(r, sh[q][tid]) : r + sh[q][tid];
     out[tid] = r;
   }
   if (tid == kRecVals) out[kRecVals] = err ? (double)*err : 0.0;
   if (tid == 0) *counter = 0;
-  __threadfence_system();
 }
 
 // x_j of the pass: the vector itself, or x + a p (a trial point)
