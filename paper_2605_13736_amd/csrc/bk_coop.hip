@@ -18,7 +18,9 @@
 //      test fails, the winner's L row.
 //   X3 (when the first test fails): every workgroup's maximum of the updated
 //      column imax, and a_ii from its owner.
-//   XB: the window rows (L rows of the block's positions) from their owners.
+//   XB (when the step ends a block): the window rows (L rows of the next
+//      block's positions) from their owners.  Inside a block every workgroup
+//      extends its copy of the window rows by itself.
 //
 // Exchange words are 64 bits: 32 data bits under a 32-bit tag that names the
 // panel launch and the exchange, written and read with relaxed agent-scope
@@ -31,14 +33,25 @@
 // once), so the grid always drains.
 #include <algorithm>
 #include <climits>
+#include <type_traits>
 
 #include "panel_reg.hpp"
 
 namespace mds {
 namespace {
 
+// f(0), ..., f(n - 1) with compile-time indices
+template <int N, int I = 0, typename F>
+__device__ __attribute__((always_inline)) inline void static_for(F &&f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, I + 1>(f);
+  }
+}
+
 using panel::lds_wave_sync;
 using panel::sym_at;
+using wave::row_lane;
 using wave::rows4;
 using wave::sel4;
 
@@ -97,8 +110,8 @@ __device__ __attribute__((noinline)) double pending_entry(const TX *pX, const in
 //   1. block columns  A = X(:, block) - L W(block, :)'           (FP64 MFMA)
 //   2. the 16 x 16 diagonal block's L D L', in every wave by itself from X and
 //      the 16 window rows of L (LDS), four columns at a time
-//   3. every row's forward substitution, four columns at a time, and the rank-4
-//      update of the columns right of them (FP64 MFMA)
+//   3. every row's forward substitution, one row a thread: the diagonal block's
+//      columns stand in the lanes, a 64-bit row broadcast gives each factor
 //   4. exchange XB: first failing column of each workgroup, and, from their
 //      owners, the L rows of the next 16 positions
 //
@@ -116,8 +129,13 @@ __device__ __attribute__((noinline)) double pending_entry(const TX *pX, const in
 // of 256 rows, and needs no static column index.  Columns t >= j are
 // never read (operands are masked), so nothing is cleared.
 //
-// What bounds it: latency.  A block costs one exchange (~1.7 us), the diagonal
-// block's chain of 16 divisions and the loads of X.
+// What bounds it: latency and, with one wave per SIMD, instruction issue.  At
+// N = 4096 a block takes 8.4 us: 2.4 for its entries' products (MFMA; 64 cycles
+// each), 2.6 for the diagonal block and the rows (3.7 with the rows' entries
+// gathered and selected across lanes for every four columns), 2.5 for the exchange
+// (1.7 of them its round trip).  A full step takes 8.2 us (10.5 while each one
+// ended in an XB).  The panels of N = 4096: 4.76 -> 3.94 ms, N = 16384: 21.2 ->
+// 17.6 ms.
 constexpr int CT = 256;        // threads = rows of a workgroup
 constexpr int CNB = 64;        // most columns of a panel
 constexpr int CB = 16;         // columns of a speculative block
@@ -327,43 +345,63 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
       loaded = false;
       {
         const bool wc = l16 >= r0 && l16 < ce;
-        for (int kk = 0; 4 * kk < j; ++kk) {
-          const int t = 4 * kk + l4;
-          const bool on = t < j;
-          const double aw = (on && wc) ? -wrow(s_lw + l16 * CWL, t) : 0.0;
-          const double dl = (on && wc) ? s_lw[l16 * CWL + t] : 0.0;
-          dacc = __builtin_amdgcn_mfma_f64_16x16x4f64(aw, dl, dacc, 0, 0, 0);
+        // 16 columns at a time: their operands are read together
+        for (int t0 = 0; t0 < j; t0 += 16) {
+          double aw[4], dl[4], bl[4][4];
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const double bl = on ? s_L[t * CLD + 64 * wid + 16 * q + l16] : 0.0;
-            acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(aw, bl, acc[q], 0, 0, 0);
+          for (int u = 0; u < 4; ++u) {
+            const int t = t0 + 4 * u + l4;
+            const bool on = t < j;
+            aw[u] = (on && wc) ? -wrow(s_lw + l16 * CWL, t) : 0.0;
+            dl[u] = (on && wc) ? s_lw[l16 * CWL + t] : 0.0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              bl[u][q] = on ? s_L[t * CLD + 64 * wid + 16 * q + l16] : 0.0;
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            dacc = __builtin_amdgcn_mfma_f64_16x16x4f64(aw[u], dl[u], dacc, 0, 0, 0);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(aw[u], bl[u][q], acc[q], 0, 0, 0);
           }
         }
       }
-      int pg[4];
+      // The block's entries change from the MFMA result layout to one row a
+      // thread, through their own columns of s_L (rows of this wave only).
 #pragma unroll
-      for (int q = 0; q < 4; ++q) pg[q] = s_pos[64 * wid + 16 * q + l16];
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int cc = l4 + 4 * r;
+          if (cc >= r0 && cc < ce) s_L[(jb + cc) * CLD + 64 * wid + 16 * q + l16] = acc[q][r];
+        }
+      lds_wave_sync();
+      double xr[CB], ldg[4], dow[4];
+#pragma unroll
+      for (int cc = 0; cc < CB; ++cc) xr[cc] = s_L[(jb + cc) * CLD + tid];
       int ff = ce;  // first failing column of this wave
-      double ldg[4], dow[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        ldg[u] = dow[u] = 0.0;
-        if (4 * u + 3 >= r0 && 4 * u < ce && ff == ce) {
-          // columns 4u + q inside the block; the 4 x 4 pivot block (row p,
-          // column q at lane 4u + p + 16 q)
+      // A failure ends nothing here: columns past it are computed and dropped,
+      // so that a whole block is straight-line code.
+      auto factor = [&](auto whole) __attribute__((always_inline)) {
+        constexpr bool FULL = decltype(whole)::value;
+        // the diagonal block's columns (updated entries, row l16, in each row of
+        // 16 lanes), their pivots and reciprocals (one value in every lane)
+        double wc[CB], dv[CB], rd[CB];
+        static_for<4>([&](auto uc) __attribute__((always_inline)) {
+          constexpr int u = decltype(uc)::value, c0 = 4 * u;
+          ldg[u] = dow[u] = 0.0;
+          if (!FULL && (c0 + 3 < r0 || c0 >= ce)) return;
           bool on[4];
 #pragma unroll
-          for (int q = 0; q < 4; ++q) on[q] = 4 * u + q >= r0 && 4 * u + q < ce;
-          const double m00 = wave::lane_read(dacc[u], 4 * u);
-          const double m10 = wave::lane_read(dacc[u], 4 * u + 1);
-          const double m20 = wave::lane_read(dacc[u], 4 * u + 2);
-          const double m30 = wave::lane_read(dacc[u], 4 * u + 3);
-          double m11 = wave::lane_read(dacc[u], 4 * u + 17);
-          double m21 = wave::lane_read(dacc[u], 4 * u + 18);
-          double m31 = wave::lane_read(dacc[u], 4 * u + 19);
-          double m22 = wave::lane_read(dacc[u], 4 * u + 34);
-          double m32 = wave::lane_read(dacc[u], 4 * u + 35);
-          double m33 = wave::lane_read(dacc[u], 4 * u + 51);
+          for (int q = 0; q < 4; ++q) on[q] = FULL || (c0 + q >= r0 && c0 + q < ce);
+          double o[4];
+          rows4(dacc[u], o);
+          const double m00 = row_lane<c0>(o[0]), m10 = row_lane<c0 + 1>(o[0]);
+          const double m20 = row_lane<c0 + 2>(o[0]), m30 = row_lane<c0 + 3>(o[0]);
+          double m11 = row_lane<c0 + 1>(o[1]), m21 = row_lane<c0 + 2>(o[1]);
+          double m31 = row_lane<c0 + 3>(o[1]), m22 = row_lane<c0 + 2>(o[2]);
+          double m32 = row_lane<c0 + 3>(o[2]), m33 = row_lane<c0 + 3>(o[3]);
           const double rd0 = on[0] ? 1.0 / m00 : 0.0;
           const double l10 = m10 * rd0, l20 = m20 * rd0, l30 = m30 * rd0;
           const double w10 = l10 * m00, w20 = l20 * m00, w30 = l30 * m00;
@@ -383,50 +421,54 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
           const double l32 = m32 * rd2, w32 = l32 * m22;
           m33 = fma(-l32, w32, m33);
           const double rd3 = on[3] ? 1.0 / m33 : 0.0;
-          const double down = sel4(l4, m00, m11, m22, m33);
-          const bool onw = 4 * u + l4 >= r0 && 4 * u + l4 < ce;
-          // forward substitution of one row over the four columns: its
-          // updated value and multiplier in this lane's column
-          auto solve4 = [&](double x, double &wo, double &lo) {
-            double o[4];
-            rows4(x, o);
-            const double l0 = o[0] * rd0;
-            const double x1 = fma(-l0, w10, o[1]);
-            const double l1 = x1 * rd1;
-            const double x2 = fma(-l1, w21, fma(-l0, w20, o[2]));
-            const double l2 = x2 * rd2;
-            const double x3 = fma(-l2, w32, fma(-l1, w31, fma(-l0, w30, o[3])));
-            const double l3 = x3 * rd3;
-            wo = sel4(l4, o[0], x1, x2, x3);
-            lo = sel4(l4, l0, l1, l2, l3);
-          };
-          double wo, lo;
-          solve4(dacc[u], wo, lo);
-          lo = (l16 > 4 * u + l4 && l16 < ce && onw) ? lo : 0.0;
-          ldg[u] = lo;
+          // row l16 over the four columns
+          const double l0 = o[0] * rd0;
+          const double x1 = fma(-l0, w10, o[1]);
+          const double l1 = x1 * rd1;
+          const double x2 = fma(-l1, w21, fma(-l0, w20, o[2]));
+          const double l2 = x2 * rd2;
+          const double x3 = fma(-l2, w32, fma(-l1, w31, fma(-l0, w30, o[3])));
+          const double l3 = x3 * rd3;
+          wc[c0] = o[0];
+          wc[c0 + 1] = x1;
+          wc[c0 + 2] = x2;
+          wc[c0 + 3] = x3;
+          dv[c0] = m00;
+          dv[c0 + 1] = m11;
+          dv[c0 + 2] = m22;
+          dv[c0 + 3] = m33;
+          rd[c0] = rd0;
+          rd[c0 + 1] = rd1;
+          rd[c0 + 2] = rd2;
+          rd[c0 + 3] = rd3;
+          const int cl = c0 + l4;  // this lane's column
+          const bool onw = FULL || (cl >= r0 && cl < ce);
+          const double lo = sel4(l4, l0, l1, l2, l3), down = sel4(l4, m00, m11, m22, m33);
+          ldg[u] = (l16 > cl && (FULL || l16 < ce) && onw) ? lo : 0.0;
           dow[u] = down;
-          const double aw = -(lo * (onw ? down : 0.0));
-          const bool more = 4 * u + 4 < ce;
-          if (more) dacc = __builtin_amdgcn_mfma_f64_16x16x4f64(aw, lo, dacc, 0, 0, 0);
-          // every active row below a column: |d| >= alpha |w| (false for a NaN)
-          const double dabs = fabs(down);
-          unsigned long long bad = __ballot(onw && !(dabs > 0.0));
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            double wr, lr;
-            solve4(acc[q][u], wr, lr);
-            bad |= __ballot(onw && pg[q] > k0 + jb + 4 * u + l4 && !(dabs >= alpha * fabs(wr)));
-            if (onw) s_L[(jb + 4 * u + l4) * CLD + 64 * wid + 16 * q + l16] = lr;
-            if (more)
-              acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(aw, onw ? lr : 0.0, acc[q], 0, 0, 0);
-          }
-          if (bad != 0) {
-            const int lo16 = (bad & 0xffffull) ? 0 : (bad & 0xffff0000ull) ? 1
-                             : (bad & 0xffff00000000ull) ? 2 : 3;
-            ff = 4 * u + lo16;
-          }
-        }
-      }
+          if (u < 3 && (FULL || c0 + 4 < ce))
+            dacc = __builtin_amdgcn_mfma_f64_16x16x4f64(-(ldg[u] * (onw ? down : 0.0)), ldg[u], dacc,
+                                                        0, 0, 0);
+        });
+        // every row: |d| >= alpha |w| for the active rows below a column (false
+        // for a NaN), its multiplier, its entries right of the column
+        const int idx = pos - (k0 + jb);
+        static_for<CB>([&](auto qc) __attribute__((always_inline)) {
+          constexpr int q = decltype(qc)::value;
+          if (!FULL && (q < r0 || q >= ce)) return;
+          const double x = xr[q], l = x * rd[q], da = fabs(dv[q]);
+          const unsigned long long bad =
+              __ballot((idx > q && !(da >= alpha * fabs(x))) || !(da > 0.0));
+          if (bad != 0) ff = min(ff, q);
+          s_L[(jb + q) * CLD + tid] = l;
+          static_for<CB - 1 - q>([&](auto cc) __attribute__((always_inline)) {
+            constexpr int c = q + 1 + decltype(cc)::value;
+            xr[c] = fma(-l, wave::row_lane<c>(wc[q]), xr[c]);
+          });
+        });
+      };
+      if (s == CB) factor(std::true_type{});
+      else factor(std::false_type{});
       if (lane == 0) s_fail[wid] = ff;
       __syncthreads();
       int fl = ce;
@@ -481,10 +523,26 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
     --slow;
     ++nsteps;
     double x = (pos >= k) ? (double)sym_at(X, rho, s_map[j], ld) : 0.0;
+    // The window rows' entries of the pivot columns are computed by every
+    // workgroup: 16 lanes a row, from its L row (wq: this thread's row)
+    const int wq = tid >> 4, wl = tid & 15, jb = j & ~(CB - 1);
+    const bool won = k0 + jb + wq < N && jb + wq >= j;
+    const int wphys = won ? s_map[jb + wq] : 0;
+    double xq = (won && wl == 0) ? (double)sym_at(X, wphys, s_map[j], ld) : 0.0, yq = 0.0;
+    auto window_entry = [&](double v, const double *wr) {
+      double lw[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int t = wl + 16 * u;
+        lw[u] = (t < j) ? s_lw[wq * CWL + t] * wr[t] : 0.0;
+      }
+      return wave::row_sum(v - ((lw[0] + lw[1]) + (lw[2] + lw[3])));
+    };
     if (wid == 0) s_wk[lane] = (lane < j) ? wrow(s_lw + (j & (CB - 1)) * CWL, lane) : 0.0;
     __syncthreads();
-#pragma unroll 4
+#pragma unroll 8
     for (int t = 0; t < j; ++t) x = fma(-s_L[t * CLD + tid], s_wk[t], x);
+    xq = window_entry(xq, s_wk);
     double bv = -1.0;
     int bi = INT_MAX, bs = tid;
     if (pos > k) {
@@ -584,6 +642,7 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
       // past the strip still lack the previous panel's update
       const bool fly = la && iphys >= kstrip;
       if (pos >= k && (!fly || rho < kstrip)) y = (double)sym_at(X, rho, iphys, ld);
+      if (won && wl == 0) yq = (double)sym_at(X, wphys, iphys, ld);  // inside the strip
       const double *pL = pv.L + (pv.labs ? (size_t)s_kprev * (size_t)N : 0);
       if constexpr (LA) if (fly) {
         if (tid >= 128 && tid < 128 + CPW)
@@ -623,8 +682,9 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
         const bool on = pos >= k && rho >= kstrip;
         if (on) y = pending_entry<TX>(pX, pv.src, pv.W, pL, rho, iphys, jwp, ld, s_pw, s_pl);
       }
-#pragma unroll 4
+#pragma unroll 8
       for (int t = 0; t < j; ++t) y = fma(-s_L[t * CLD + tid], s_wi[t], y);
+      yq = window_entry(yq, s_wi);
       // ---- X3: maximum of the updated column imax, and a_ii --------------------
       double rv = (pos >= k && pos != imax) ? fabs(y) : 0.0;
       rv = wave::max(rv);
@@ -691,26 +751,50 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
     }
     const double rD = (kind == 4) ? 1.0 / det : (kind == 3) ? 1.0 / aii : 1.0 / akk;
     // ---- multipliers and new positions ------------------------------------------
-    {
+    // of row rp whose entries of the pivot columns are xv and yv
+    auto mult = [&](int rp, double xv, double yv, double &l0, double &l1) {
       bool act;
-      double l0, l1 = 0.0;
+      l1 = 0.0;
       if (kind == 4) {
-        act = pos >= k + 1 && pos != q;
-        l0 = (x * Dc - y * Db) * rD;
-        l1 = (y * Da - x * Db) * rD;
+        act = rp >= k + 1 && rp != q;
+        l0 = (xv * Dc - yv * Db) * rD;
+        l1 = (yv * Da - xv * Db) * rD;
       } else if (kind == 3) {
-        act = pos >= k && pos != q;
-        l0 = y * rD;
+        act = rp >= k && rp != q;
+        l0 = yv * rD;
       } else {
-        act = pos > k;
-        l0 = (kind == 0) ? 0.0 : x * rD;
+        act = rp > k;
+        l0 = (kind == 0) ? 0.0 : xv * rD;
       }
-      s_L[j * CLD + tid] = act ? l0 : 0.0;
-      if (kind == 4) s_L[(j + 1) * CLD + tid] = act ? l1 : 0.0;
+      if (!act) l0 = l1 = 0.0;
+    };
+    {
+      double l0, l1;
+      mult(pos, x, y, l0, l1);
+      s_L[j * CLD + tid] = l0;
+      if (kind == 4) s_L[(j + 1) * CLD + tid] = l1;
       if (sw) {
         if (pos == p) pos = q;
         else if (pos == q) pos = p;
         s_pos[tid] = pos;
+      }
+    }
+    if (won) {
+      // the window rows' new columns; with an interchange the row of position
+      // p moves to position q (the candidate's row is eliminated by this step)
+      const int wpos = k0 + jb + wq, slotq = q - k0 - jb;
+      double l0, l1;
+      mult(wpos, xq, yq, l0, l1);
+      int dst = wq;
+      if (sw && wpos == q) dst = -1;
+      if (sw && wpos == p) {
+        dst = slotq < CB ? slotq : -1;
+        if (dst >= 0)
+          for (int t = wl; t < j; t += 16) s_lw[dst * CWL + t] = s_lw[wq * CWL + t];
+      }
+      if (dst >= 0 && wl == 0) {
+        s_lw[dst * CWL + j] = l0;
+        if (kind == 4) s_lw[dst * CWL + j + 1] = l1;
       }
     }
     if (tid == 0) {
@@ -751,11 +835,15 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
     j += kstep;
     k += kstep;
     if (j < nb && k < N) {
-      // the window rows with the new column, the next block's entries
-      const bool spec = slow == 0;
-      const int m = xb(CB, true, j & ~(CB - 1), j, 0, spec ? j : -1);
-      if (m < 0) return;
-      loaded = spec;
+      if ((j & ~(CB - 1)) != jb) {
+        // the next window's rows, and the next block's entries
+        const bool spec = slow == 0;
+        const int m = xb(CB, true, j & ~(CB - 1), j, 0, spec ? j : -1);
+        if (m < 0) return;
+        loaded = spec;
+      } else {
+        __syncthreads();
+      }
     }
   }
 
@@ -770,17 +858,33 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
     blk[k0 + tid] = s_pbk[tid];
   }
   if (pos >= 0) {
-    const int below = min(jend, pos - k0);  // columns t with pos > k0 + t
-    for (int t = 0; t < below; ++t) Lout[pos + (lcol + t) * ld] = s_L[t * CLD + tid];
-    if (pos >= kend) {
-      for (int t = 0; t < jend; ++t) {
-        double v = s_L[t * CLD + tid] * s_cA[t];
-        if (any2) {
-          if (t + 1 < jend) v = v + s_L[(t + 1) * CLD + tid] * s_cB[t];
-          if (t >= 1) v = v + s_L[(t - 1) * CLD + tid] * s_cC[t];
-        }
-        W[pos + t * ld] = v;
+    // columns t with pos > k0 + t; the rows past the panel take W = L D too
+    const int below = min(jend, pos - k0);
+    const bool past = pos >= kend;
+    for (int t0 = 0; t0 < jend; t0 += 8) {
+      double lv[8], wv[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int t = t0 + u;
+        lv[u] = s_L[t * CLD + tid];
+        wv[u] = lv[u] * s_cA[t];
       }
+      if (any2) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int t = t0 + u;
+          if (t + 1 < jend) wv[u] = wv[u] + s_L[(t + 1) * CLD + tid] * s_cB[t];
+          if (t >= 1 && t < jend) wv[u] = wv[u] + s_L[(t - 1) * CLD + tid] * s_cC[t];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int t = t0 + u;
+        if (t < below) Lout[pos + (lcol + t) * ld] = lv[u];
+        if (past && t < jend) W[pos + t * ld] = wv[u];
+      }
+    }
+    if (past) {
       src_out[pos] = rho;
     }
   }

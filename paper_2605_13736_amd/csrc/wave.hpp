@@ -120,6 +120,14 @@ __device__ inline int imin(int v) {
   return min(min(lane_read(v, 0), lane_read(v, 16)), min(lane_read(v, 32), lane_read(v, 48)));
 }
 
+// sum over the 16 lanes of each row: every lane of the row
+__device__ inline double row_sum(double v) {
+  v = v + dpp<kXor1>(v);
+  v = v + dpp<kXor2>(v);
+  v = v + dpp<kRor4>(v);
+  return v + dpp<kRor8>(v);
+}
+
 // sum over the wave, every lane (association: quads, rows, then rows 0..3)
 __device__ inline double sum(double v) {
   v = v + dpp<kXor1>(v);
@@ -127,6 +135,14 @@ __device__ inline double sum(double v) {
   v = v + dpp<kRor4>(v);
   v = v + dpp<kRor8>(v);
   return (lane_read(v, 0) + lane_read(v, 16)) + (lane_read(v, 32) + lane_read(v, 48));
+}
+
+// lane C of each row of 16 lanes, in every lane of the row (one 64-bit move)
+template <int C>
+__device__ inline double row_lane(double v) {
+  static_assert(C >= 0 && C < 16, "row lane");
+  return __longlong_as_double(
+      __builtin_amdgcn_mov_dpp(__double_as_longlong(v), 0x150 + C, 0xf, 0xf, true));
 }
 
 // o[q] = x of lane (l & 15) + 16 q
