@@ -325,11 +325,20 @@ int condense_impl(mds_handle *h, double dw, double dc) {
 }
 
 // Slot plan of a factorization (fixed per handle): the rows that can remain
-// at each panel's start.
+// at each panel's start, and the leading slots factored in pairs.  A pair saves
+// a pass over the trailing matrix (0.25 ms at 16384 rows, 15 us at 4096) and
+// costs the strip's launch and the second panel's entries outside it, ~15 us:
+// N = 9001 takes 20.9 ms without pairs, 19.9 with pairs down to 6144 rows, 19.45
+// down to 4096 and 3072; N = 4096 5.8, and 6.1 with pairs down to 3072.
+constexpr long kPairRows = 4608;
 void make_plan(mds_handle *h) {
   h->plan.clear();
   for (long rows = h->N; rows > 0; rows -= h->adv)
     h->plan.push_back(SlotPlan{rows, rows - h->adv});
+  h->pair_slots = 0;
+  if (h->panel_coop && h->precision == MDS_FP64 && h->nb == bk_coop_nb())
+    while (h->pair_slots + 1 < (int)h->plan.size() && h->plan[h->pair_slots].rows >= kPairRows)
+      h->pair_slots += 2;
 }
 
 // Panel of slot b on the ping-pong layout: the cooperative panel or the
@@ -386,12 +395,42 @@ void factor_launches(mds_handle *h, hipStream_t s) {
     }
   }
   const bool fp64 = h->precision == MDS_FP64 || h->force64;
-  for (int b = 0; b < (fp64 && !h->panel_lds ? slots : 0); ++b) {
+  // Pairs: panel b's update goes to the strip that panel b + 1 reads; panel
+  // b + 1 computes entries of a candidate column outside it from panel b's
+  // input and multipliers (as in the look-ahead), and one pass over the
+  // trailing matrix then applies both panels.
+  const int np2 = fp64 ? h->pair_slots : 0;
+  for (int b = 0; b < np2; b += 2) {
+    double *X = (b & 2) ? h->w.M2 : h->w.M, *Y = (b & 2) ? h->w.M : h->w.M2;
+    Work &w = h->w;
+    {
+      TimedLaunch t(h, MDS_T_PANEL);
+      launch_reg_panel(h, s, b, (const double *)X, Y);
+    }
+    {
+      TimedLaunch t(h, MDS_T_NEAR);
+      launch_bk_trailing_coop(s, N, h->plan[b].rows_after, b, 1, false, w.W, X, Y, Y, w.src, w.fst,
+                              w.panel_k0);
+    }
+    {
+      TimedLaunch t(h, MDS_T_PANEL);
+      const PanelPrev pv{X, nullptr, w.src, w.W, Y, 1, ~15};
+      launch_bk_panel_coop_la(s, (int)h->plan[b + 1].rows, N, h->nb, h->alpha_bk, (const double *)Y,
+                              pv, w.lst[0], w.src2, w.W2, w.dd, w.ds, w.ipiv, w.blk, w.fst,
+                              w.panel_k0, w.xch);
+    }
+    TimedLaunch t(h, MDS_T_TRAILING);
+    launch_bk_trailing_pair(s, N, h->plan[b + 1].rows_after, b + 1, w.W2, X, Y, w.lst[0], w.src2,
+                            w.W, w.src, w.fst, w.panel_k0);
+  }
+  for (int b = np2; b < (fp64 && !h->panel_lds ? slots : 0); ++b) {
     // register panel: slot b reads buffer b%2 and writes its L and the
     // updated trailing matrix into the other buffer
+    // (after the pairs: their number is added)
     double *X = h->w.M, *Y = h->w.M;
-    if (h->panel_reg && (b & 1)) X = h->w.M2;
-    if (h->panel_reg && !(b & 1)) Y = h->w.M2;
+    const int p = (b - np2 / 2) & 1;
+    if (h->panel_reg && p) X = h->w.M2;
+    if (h->panel_reg && !p) Y = h->w.M2;
     {
       TimedLaunch t(h, MDS_T_PANEL);
       if (h->panel_reg)
@@ -403,7 +442,7 @@ void factor_launches(mds_handle *h, hipStream_t s) {
     if (h->plan[b].rows_after > 0) {
       TimedLaunch t(h, MDS_T_TRAILING);
       if (h->panel_coop)
-        launch_bk_trailing_coop(s, N, h->plan[b].rows_after, b, 0, h->w.W, X, Y, Y, h->w.src,
+        launch_bk_trailing_coop(s, N, h->plan[b].rows_after, b, 0, false, h->w.W, X, Y, Y, h->w.src,
                                 h->w.fst, h->w.panel_k0);
       else
         launch_bk_trailing(s, N, h->nb, h->plan[b].rows_after, b, h->w.W, X, Y, Y,
@@ -481,7 +520,7 @@ void factor_launches_la(mds_handle *h, hipStream_t s) {
           launch_trailing_lp_part(A, h->precision, N, nb, rem, b, 1, 2 * h->la_cus, Wb[p], X32,
                                   Y32, w.M, src[p], w.fst, w.panel_k0);
         else
-          launch_bk_trailing_coop(A, N, rem, b, 1, Wb[p], X, Y, w.lst[p], src[p], w.fst,
+          launch_bk_trailing_coop(A, N, rem, b, 1, true, Wb[p], X, Y, w.lst[p], src[p], w.fst,
                                   w.panel_k0);
       }
       (void)hipEventRecord(ev_near, A);
@@ -493,7 +532,7 @@ void factor_launches_la(mds_handle *h, hipStream_t s) {
           launch_trailing_lp_part(B, h->precision, N, nb, rem, b, 2, h->la_grid, Wb[p], X32,
                                   Y32, w.M, src[p], w.fst, w.panel_k0);
         else
-          launch_bk_trailing_coop(B, N, rem, b, 2, Wb[p], X, Y, w.lst[p], src[p], w.fst,
+          launch_bk_trailing_coop(B, N, rem, b, 2, true, Wb[p], X, Y, w.lst[p], src[p], w.fst,
                                   w.panel_k0);
       }
       (void)hipEventRecord(ev_far, B);
@@ -658,7 +697,8 @@ void ensure_std(mds_handle *h) {
   if (h->std_ready) return;
   TimedLaunch t(h, MDS_T_PERMUTE);
   const int pingpong = h->fac_pingpong ? 1 : 0;
-  launch_std_form(S(h), h->N, h->w.M, h->w.M2, pingpong, h->w.ipiv, h->w.blk,
+  const int np2 = (h->la_cus > 0) ? 0 : h->pair_slots;
+  launch_std_form(S(h), h->N, h->w.M, h->w.M2, pingpong, np2, h->w.ipiv, h->w.blk,
                   h->w.panel_k0, h->w.fst, h->w.hmap, h->w.perm, h->w.colpanel, h->w.M);
   h->std_ready = true;
 }

@@ -39,6 +39,8 @@
 #include <algorithm>
 #include <climits>
 
+#include <type_traits>
+
 #include "internal.hpp"
 #include "tile_order.hpp"
 #include "wave.hpp"
@@ -446,129 +448,144 @@ __global__ __launch_bounds__(256) void k_bk_trailing(int N, int nb, const double
 __device__ inline double ldb(const double *p, unsigned off) {
   return *(const double *)((const char *)p + off);
 }
-template <int TSC, bool IN>
-__device__ __forceinline__ void trailing_tile(int N, int kend, int jw, int lk0, int i0, int c0, bool diag,
-                                     const double *__restrict__ W, const double *X, double *Y,
-                                     const double *Lsrc, const int32_t *__restrict__ src,
-                                     double *s_w, double *s_l) {
-  constexpr int TS1 = TSC + 1, U = TT * TSC / 256;
+// One 64 x 64 tile of the update after one or (PAIR) two cooperative panels (at
+// most 64 columns each), in 16-column chunks, double-buffered in LDS (one barrier
+// a chunk; columns contiguous, stride 16 mod 32 doubles: no bank conflicts).
+// Interior tiles have no guards, and every address is a uniform base plus a
+// 32-bit byte offset (8 N^2 < 2^32).
+// No load is guarded (rows and columns are clamped to valid ones, columns past
+// the panel's end become zeros on the way to LDS): a guard is a branch, and
+// behind a branch the wait for the staging loads becomes one for every load in
+// flight.
+// The shape follows the FP64 matrix instruction, measured from registers alone:
+// 47 TFLOP/s with four waves per SIMD and four accumulators a wave, 36 with one
+// or two waves of sixteen.  128 x 128 tiles (persistent, the next tile's X in
+// registers) and 64 x 64 tiles a wave without LDS were slower for it: 41 and 45
+// ms of pair updates at N = 16384 against 37; vector FMAs (68 TFLOP/s from
+// registers, 56 with W broadcast from lanes) in 256 x 16 tiles a wave waited for
+// their loads: 49 ms, with W in scalar registers 55.
+struct PanelCols {
+  const double *W, *L;  // column t at t N
+  int j;                // columns
+};
+constexpr int TC = 16, TL = TT + 16, TNC = 64 / TC;
+template <bool PAIR>
+__device__ __forceinline__ void trailing_tile(int N, int kend, int i0, int c0, bool in,
+                                              const double *X, double *Y, const PanelCols p0,
+                                              const PanelCols p1, const int32_t *__restrict__ src,
+                                              const int32_t *__restrict__ srcp, double *s_buf) {
+  constexpr int U = TT * TC / 256, NC = (PAIR ? 2 : 1) * TNC;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int l16 = lane & 15, l4 = lane >> 4;
-  const int wc = c0 + (wv & 1) * 32, wi = i0 + (wv >> 1) * 32;
+  const int cw = (wv & 1) * 32, iw = (wv >> 1) * 32, wc = c0 + cw, wi = i0 + iw;
   const unsigned st8 = (unsigned)N * 8u;
+  const int sr = tid & 63, stt = tid >> 6;
+  auto row = [&](int i) { return min(max(i, kend), N - 1); };
+  const unsigned wof1 = (unsigned)row(c0 + sr) * 8u, lof1 = (unsigned)row(i0 + sr) * 8u;
+  unsigned wof0 = 0, lof0 = 0;
+  if constexpr (PAIR) {
+    wof0 = (unsigned)src[row(c0 + sr)] * 8u;
+    lof0 = (unsigned)src[row(i0 + sr)] * 8u;
+  }
+  double vw[U], vl[U];
+  auto stage_load = [&](int ch) {
+    const bool first = PAIR && ch < TNC;
+    const PanelCols &p = first ? p0 : p1;
+    const unsigned wo = first ? wof0 : wof1, lo = first ? lof0 : lof1;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const unsigned t = __umul24((unsigned)min((ch % TNC) * TC + 4 * u + stt, p.j - 1), st8);
+      vw[u] = ldb(p.W, wo + t);
+      vl[u] = ldb(p.L, lo + t);
+    }
+  };
+  stage_load(0);
   unsigned si[2], sc[2][4];
 #pragma unroll
   for (int b = 0; b < 2; ++b) {
-    const int i = wi + b * 16 + l16;
-    si[b] = (IN || (i >= kend && i < N)) ? (unsigned)src[i] : 0u;
+    si[b] = (unsigned)src[row(wi + b * 16 + l16)];
+    if constexpr (PAIR) si[b] = (unsigned)srcp[si[b]];
   }
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int c = wc + a * 16 + l4 + 4 * r;
-      sc[a][r] = (IN || (c >= kend && c < N)) ? (unsigned)src[c] : 0u;
+      sc[a][r] = (unsigned)src[row(wc + a * 16 + l4 + 4 * r)];
+      if constexpr (PAIR) sc[a][r] = (unsigned)srcp[sc[a][r]];
     }
-  const int sr = tid & 63, stt = tid >> 6;
-  const bool won = IN || (c0 + sr >= kend && c0 + sr < N), lon = IN || (i0 + sr >= kend && i0 + sr < N);
-  const unsigned wof = (unsigned)(c0 + sr) * 8u + (unsigned)stt * st8;
-  const unsigned lof = (unsigned)(i0 + sr) * 8u + (unsigned)stt * st8;
-  const double *Lb = Lsrc + (size_t)lk0 * N;
-  double vw[U], vl[U];
-  auto stage_load = [&](int tb) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const double *Wu = W + (size_t)(tb + 4 * u) * N, *Lu = Lb + (size_t)(tb + 4 * u) * N;
-      const bool ton = tb + 4 * u + stt < jw;
-      vw[u] = (won && ton) ? ldb(Wu, wof) : 0.0;
-      vl[u] = (lon && ton) ? ldb(Lu, lof) : 0.0;
-    }
-  };
-  stage_load(0);
   double xv[2][2][4];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const unsigned hi = max(si[b], sc[a][r]), lo = min(si[b], sc[a][r]);
-        const int c = wc + a * 16 + l4 + 4 * r, i = wi + b * 16 + l16;
-        const bool on = IN || (c >= kend && c < N && i < N && (!diag || i >= c));
-        xv[a][b][r] = on ? ldb(X, hi * 8u + __umul24(lo, st8)) : 0.0;
-      }
   d4 acc[2][2];
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
     for (int b = 0; b < 2; ++b) acc[a][b] = d4{0.0, 0.0, 0.0, 0.0};
-  const double *wr[2], *lr[2];
 #pragma unroll
-  for (int a = 0; a < 2; ++a) wr[a] = s_w + (wc - c0 + a * 16 + l16) * TS1 + l4;
-#pragma unroll
-  for (int b = 0; b < 2; ++b) lr[b] = s_l + (wi - i0 + b * 16 + l16) * TS1 + l4;
-  double *dw = s_w + sr * TS1 + stt, *dl = s_l + sr * TS1 + stt;
-  for (int tb = 0; tb < jw; tb += TSC) {
-    if (tb > 0) __syncthreads();
+  for (int ch = 0; ch < NC; ++ch) {
+    double *s_w = s_buf + (ch & 1) * 2 * TC * TL, *s_l = s_w + TC * TL;
+    const int jt = ((PAIR && ch < TNC) ? p0.j : p1.j) - (ch % TNC) * TC;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      dw[4 * u] = vw[u];
-      dl[4 * u] = vl[u];
+      const bool ton = 4 * u + stt < jt;
+      s_w[(4 * u + stt) * TL + sr] = ton ? vw[u] : 0.0;
+      s_l[(4 * u + stt) * TL + sr] = ton ? vl[u] : 0.0;
     }
     __syncthreads();
-    if (tb + TSC < jw) stage_load(tb + TSC);
+    if (ch + 1 < NC) stage_load(ch + 1);
+    // the tile's entries, a share behind every chunk's staging loads
 #pragma unroll
-    for (int t0 = 0; t0 < TSC; t0 += 4) {
-      if (tb + t0 < jw) {
-        double av[2], bv[2];
+    for (int e = 16 * ch / NC; e < 16 * (ch + 1) / NC; ++e) {
+      const int a = e >> 3, b = (e >> 2) & 1, r = e & 3;
+      const unsigned hi = max(si[b], sc[a][r]), lo = min(si[b], sc[a][r]);
+      xv[a][b][r] = ldb(X, hi * 8u + __umul24(lo, st8));
+    }
 #pragma unroll
-        for (int a = 0; a < 2; ++a) av[a] = wr[a][t0];
+    for (int t0 = 0; t0 < TC; t0 += 4) {
+      double av[2], bv[2];
 #pragma unroll
-        for (int b = 0; b < 2; ++b) bv[b] = lr[b][t0];
+      for (int a = 0; a < 2; ++a) av[a] = s_w[(t0 + l4) * TL + cw + a * 16 + l16];
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
+      for (int b = 0; b < 2; ++b) bv[b] = s_l[(t0 + l4) * TL + iw + b * 16 + l16];
 #pragma unroll
-          for (int b = 0; b < 2; ++b)
-            acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], acc[a][b], 0, 0, 0);
-      }
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+          acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], acc[a][b], 0, 0, 0);
     }
   }
   const unsigned yof = (unsigned)(wi + l16) * 8u + (unsigned)(wc + l4) * st8;
+  auto store = [&](auto all) __attribute__((always_inline)) {
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < 2; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+      for (int b = 0; b < 2; ++b)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int c = wc + a * 16 + l4 + 4 * r, i = wi + b * 16 + l16;
-        if (IN || (c >= kend && c < N && i < N && (!diag || i >= c))) {
-          double *Yu = Y + (size_t)(a * 16 + 4 * r) * N + b * 16;
-          *(double *)((char *)Yu + yof) = xv[a][b][r] - acc[a][b][r];
+        for (int r = 0; r < 4; ++r) {
+          const int c = wc + a * 16 + l4 + 4 * r, i = wi + b * 16 + l16;
+          if (decltype(all)::value || (c >= kend && i < N && i >= c)) {
+            double *Yu = Y + (size_t)(a * 16 + 4 * r) * N + b * 16;
+            *(double *)((char *)Yu + yof) = xv[a][b][r] - acc[a][b][r];
+          }
         }
-      }
+  };
+  if (in) store(std::true_type{});
+  else store(std::false_type{});
 }
 
-// Trailing update after a cooperative panel (at most 64 columns): one 64 x 64
-// lower tile per workgroup.  At K = 64 a tile moves 64 KB of X and Y, and the
-// copy rate of the device (4.9 TB/s) allows a compute unit 3.4 us for that, its
-// matrix cores 1.7 us, so what counts is that nothing else takes longer: four
-// workgroups per compute unit overlap each other's latencies (LDS staging in
-// 16-column chunks, 128 VGPRs), interior tiles have no guards, and every
-// address is a uniform base plus a 32-bit byte offset (8 N^2 < 2^32).  The
-// persistent form spent as long on 64-bit addresses and guards as on its
-// memory traffic: N = 16384, 51 against 60 ms per factorization (3.65 TB/s);
-// 32-column chunks (4 workgroups, spills) 67 ms, the XCD super-tile order 52 ms.
-// part: 0 every tile, 1 and 2 the look-ahead's parts (multipliers staged).
-constexpr int TSC = 16;
+// Trailing update after a cooperative panel: a 64 x 64 lower tile per workgroup,
+// four workgroups per compute unit.  A tile moves 64 KB of X and Y for 64
+// columns, 3.4 us of a compute unit's share of the copy rate (4.9 TB/s).
+// N = 16384: 46.4 ms a factorization (4.0 TB/s; 51 ms with guarded loads, all of X
+// ahead of the chunks and two barriers a chunk), N = 4096: 1.16 ms (1.42).
+// part: 0 every tile, 1 and 2 the look-ahead's parts; lstage: the multipliers
+// are staged.
 __global__ __launch_bounds__(256, 4) void k_bk_trailing_coop(int N, const double *__restrict__ W,
                                                              const double *X, double *Y,
                                                              const double *Lsrc,
                                                              const int32_t *__restrict__ src,
                                                              const FacState *__restrict__ st,
                                                              const int32_t *__restrict__ panel_k0,
-                                                             int slot, int part) {
-  __shared__ double s_buf[2 * TT * (TSC + 1)];
-  double *s_w = s_buf, *s_l = s_buf + TT * (TSC + 1);
+                                                             int slot, int part, int lstage) {
+  __shared__ double s_buf[4 * TC * TL];
   if (slot >= st->npanel) return;
   const int k0 = panel_k0[slot], kend = panel_k0[slot + 1];
   if (kend >= N || kend <= k0) return;
@@ -579,13 +596,44 @@ __global__ __launch_bounds__(256, 4) void k_bk_trailing_coop(int N, const double
   int ti, tj;
   if ((long)blockIdx.x >= part_slots(part, nt, false)) return;
   if (!part_tile(part, blockIdx.x, nt, false, ti, tj)) return;
-  const int lk0 = (part == 0) ? k0 : 0;
   const int i0 = a0 + ti * TT, c0 = a0 + tj * TT;
-  if (ti != tj && c0 >= kend && i0 + TT <= N)
-    trailing_tile<TSC, true>(N, kend, kend - k0, lk0, i0, c0, false, W, X, Y, Lsrc, src, s_w, s_l);
-  else
-    trailing_tile<TSC, false>(N, kend, kend - k0, lk0, i0, c0, ti == tj, W, X, Y, Lsrc, src, s_w,
-                              s_l);
+  const PanelCols p{W, Lsrc + (lstage ? 0 : (size_t)k0 * N), kend - k0};
+  trailing_tile<false>(N, kend, i0, c0, ti != tj && c0 >= kend && i0 + TT <= N, X, Y, p, p, src,
+                       nullptr, s_buf);
+}
+
+// Trailing update of two panels at once (slots slot - 1 and slot): X and Y move
+// once for 128 columns.  The first panel's W and L rows are in its own output
+// order, to which the second panel's map src leads; its L is in place (column t
+// at k0 + t), the second one's staged.  Workgroups past the tiles copy the
+// second panel's multipliers from their staging buffer into Y's columns.
+// N = 16384, pairs down to 4608 rows: 37.0 ms of updates a factorization against
+// 46.1 one by one (38 TFLOP/s), 60.7 against 67.9 ms a Newton pass.
+constexpr int kPairCopy = 128;  // workgroups of the copy
+__global__ __launch_bounds__(256, 4) void k_bk_trailing_pair(
+    int N, long tiles, const double *__restrict__ W, const double *X, double *Y, const double *Lst,
+    const int32_t *__restrict__ src, const double *__restrict__ Wp,
+    const int32_t *__restrict__ srcp, const FacState *__restrict__ st,
+    const int32_t *__restrict__ panel_k0, int slot) {
+  __shared__ double s_buf[4 * TC * TL];
+  if (slot >= st->npanel) return;
+  const int kp = panel_k0[slot - 1], k0 = panel_k0[slot], kend = panel_k0[slot + 1];
+  if ((long)blockIdx.x >= tiles) {
+    const int g = (int)((long)blockIdx.x - tiles);
+    for (int t = g & 1; t < kend - k0; t += 2)
+      for (int i = k0 + t + 1 + (g >> 1) * 256 + (int)threadIdx.x; i < N; i += (kPairCopy / 2) * 256)
+        Y[(size_t)i + (size_t)(k0 + t) * N] = Lst[(size_t)i + (size_t)t * N];
+    return;
+  }
+  if (kend >= N || kend <= k0) return;
+  const int a0 = kend & ~15;
+  const int nt = (N - a0 + TT - 1) / TT;
+  int ti, tj;
+  if (!tile_of(blockIdx.x, nt, false, ti, tj)) return;
+  const int i0 = a0 + ti * TT, c0 = a0 + tj * TT;
+  const PanelCols p0{Wp, Y + (size_t)kp * N, k0 - kp}, p1{W, Lst, kend - k0};
+  trailing_tile<true>(N, kend, i0, c0, ti != tj && c0 >= kend && i0 + TT <= N, X, Y, p0, p1, src,
+                      srcp, s_buf);
 }
 
 // Persistent form of k_bk_trailing for panels of at most TS - 1 columns
@@ -780,9 +828,9 @@ void launch_bk_trailing(hipStream_t s, int N, int nb, long rem, int slot, const 
   }
 }
 
-void launch_bk_trailing_coop(hipStream_t s, int N, long rem, int slot, int part, const double *W,
-                             const double *X, double *Y, const double *Lsrc, const int32_t *src,
-                             const FacState *st, const int32_t *panel_k0) {
+void launch_bk_trailing_coop(hipStream_t s, int N, long rem, int slot, int part, bool lstage,
+                             const double *W, const double *X, double *Y, const double *Lsrc,
+                             const int32_t *src, const FacState *st, const int32_t *panel_k0) {
   if (rem <= 0) return;
   const long nt = (rem + 15 + TT - 1) / TT;
   const long tiles = (part == 1)          ? kNearTiles * nt
@@ -791,7 +839,17 @@ void launch_bk_trailing_coop(hipStream_t s, int N, long rem, int slot, int part,
                                           : 0;
   if (tiles <= 0) return;
   k_bk_trailing_coop<<<(unsigned)tiles, 256, 0, s>>>(N, W, X, Y, Lsrc, src, st, panel_k0, slot,
-                                                     part);
+                                                     part, lstage ? 1 : 0);
+}
+
+void launch_bk_trailing_pair(hipStream_t s, int N, long rem, int slot, const double *W,
+                             const double *X, double *Y, const double *Lst, const int32_t *src,
+                             const double *Wp, const int32_t *srcp, const FacState *st,
+                             const int32_t *panel_k0) {
+  const long nt = rem > 0 ? (rem + 15 + TT - 1) / TT : 0;
+  const long tiles = nt * (nt + 1) / 2;
+  k_bk_trailing_pair<<<(unsigned)(tiles + kPairCopy), 256, 0, s>>>(N, tiles, W, X, Y, Lst, src, Wp,
+                                                                  srcp, st, panel_k0, slot);
 }
 
 void launch_lstage_copy(hipStream_t s, int N, long rows, int slot, const double *Lst, double *Lout,

@@ -40,15 +40,6 @@
 namespace mds {
 namespace {
 
-// f(0), ..., f(n - 1) with compile-time indices
-template <int N, int I = 0, typename F>
-__device__ __attribute__((always_inline)) inline void static_for(F &&f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for<N, I + 1>(f);
-  }
-}
-
 using panel::lds_wave_sync;
 using panel::sym_at;
 using wave::row_lane;

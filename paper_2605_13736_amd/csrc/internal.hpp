@@ -167,6 +167,7 @@ struct mds_handle {
   bool force64 = false;     // factor in FP64 in a mixed-precision handle
   bool coop_off = false;    // cooperative panel not co-resident: memory panel always
   bool fac_lowprec = false; // current factor is of the equilibrated FP32 matrix
+  int pair_slots = 0;       // leading slots factored two to a trailing update
   bool fac_pingpong = false;// current factor's L is spread over M and M2
   int64_t n_coop_abort = 0, n_fp64_refactor = 0;
   // look-ahead of the cooperative factorization: compute units reserved for
@@ -270,9 +271,14 @@ void launch_bk_trailing(hipStream_t s, int N, int nb, long rem, int slot, const 
 // the whole update, 1 and 2 the look-ahead's: the near strip (the first
 // kNearTiles tile columns) and the rest, with Lsrc the panel's staged
 // multipliers (row i, column t at Lsrc[i + t N])
-void launch_bk_trailing_coop(hipStream_t s, int N, long rem, int slot, int part, const double *W,
-                             const double *X, double *Y, const double *Lsrc, const int32_t *src,
-                             const FacState *st, const int32_t *panel_k0);
+void launch_bk_trailing_coop(hipStream_t s, int N, long rem, int slot, int part, bool lstage,
+                             const double *W, const double *X, double *Y, const double *Lsrc,
+                             const int32_t *src, const FacState *st, const int32_t *panel_k0);
+// two panels' update in one pass (slots slot - 1 and slot)
+void launch_bk_trailing_pair(hipStream_t s, int N, long rem, int slot, const double *W,
+                             const double *X, double *Y, const double *Lst, const int32_t *src,
+                             const double *Wp, const int32_t *srcp, const FacState *st,
+                             const int32_t *panel_k0);
 // staged multipliers of slot `slot` into their place in Lout (columns
 // k0 .. kend - 1, rows below the diagonal)
 void launch_lstage_copy(hipStream_t s, int N, long rows, int slot, const double *Lst, double *Lout,
@@ -358,15 +364,16 @@ void launch_add_cols(hipStream_t s, int64_t n, int ncol, const double *Z, int64_
                      const double *coef, double *x);
 void launch_scale(hipStream_t s, int64_t n, double alpha, const double *w, double *out);
 
-// solve_std.hip: standard form of the factor (L of panel b lives in M1 when
-// pingpong and b is even, else in M0; the result may be M0 itself) and the
-// multi-workgroup solve
+// solve_std.hip: standard form of the factor and the multi-workgroup solve.
+// With pingpong the outputs alternate between M1 and M0, a pair of panels
+// (of the first np2) counting once; without, L lives in M0.  The result may be
+// M0 itself.
 int std_max_n();
 int std_solve_blocks(int N);
 size_t std_trsv_bytes(int N);  // the solve's control words (trsv below)
 hipError_t std_prepare();
 void launch_std_form(hipStream_t s, int N, const double *M0, const double *M1, int pingpong,
-                     const int32_t *ipiv, const int32_t *blk, const int32_t *panel_k0,
+                     int np2, const int32_t *ipiv, const int32_t *blk, const int32_t *panel_k0,
                      const FacState *st, int32_t *hmap, int32_t *perm, int32_t *colpanel,
                      double *Lstd);
 // out = M^{-1} v through P, L, D; z is scratch (N); trsv (std_trsv_bytes(N),

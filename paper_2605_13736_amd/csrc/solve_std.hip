@@ -136,7 +136,7 @@ __global__ __launch_bounds__(SW) void k_std_sweep(int N, const int32_t *__restri
 // hb[x].  Reads column c from the buffer its panel wrote and writes column c
 // of Lstd; no other workgroup touches column c of either buffer.
 __global__ __launch_bounds__(AT) void k_std_apply(int N, const double *M0, const double *M1,
-                                                   int pingpong,
+                                                   int pingpong, int np2,
                                                    const int32_t *__restrict__ panel_k0,
                                                    const int32_t *__restrict__ colpanel,
                                                    const int32_t *__restrict__ hmap,
@@ -145,7 +145,9 @@ __global__ __launch_bounds__(AT) void k_std_apply(int N, const double *M0, const
   const int c = blockIdx.x, tid = threadIdx.x;
   const int b = colpanel[c];
   const int k1 = panel_k0[b + 1];
-  const double *src = (pingpong && (b & 1) == 0) ? M1 : M0;
+  // panels 0 .. np2 - 1 share their output buffer two by two
+  const int step = (b < np2) ? b >> 1 : b - (np2 >> 1);
+  const double *src = (pingpong && (step & 1) == 0) ? M1 : M0;
   const size_t co = (size_t)c * (size_t)N;
   const int32_t *hb = hmap + (size_t)b * N;
   // a column takes up to N * 8 B of LDS, so one workgroup may hold a whole
@@ -481,13 +483,13 @@ hipError_t std_prepare() {
 }
 
 void launch_std_form(hipStream_t s, int N, const double *M0, const double *M1, int pingpong,
-                     const int32_t *ipiv, const int32_t *blk, const int32_t *panel_k0,
+                     int np2, const int32_t *ipiv, const int32_t *blk, const int32_t *panel_k0,
                      const FacState *st, int32_t *hmap, int32_t *perm, int32_t *colpanel,
                      double *Lstd) {
   if (N <= 0) return;
   k_std_sweep<<<1, SW, sizeof(int32_t) * (size_t)N, s>>>(N, ipiv, blk, panel_k0, st, hmap, perm,
                                                          colpanel);
-  k_std_apply<<<(unsigned)N, AT, sizeof(double) * (size_t)N, s>>>(N, M0, M1, pingpong, panel_k0,
+  k_std_apply<<<(unsigned)N, AT, sizeof(double) * (size_t)N, s>>>(N, M0, M1, pingpong, np2, panel_k0,
                                                                     colpanel, hmap, Lstd);
 }
 

@@ -10,7 +10,19 @@
 // the same order in every lane.  All 64 lanes must be active.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 namespace mds {
+
+// f(0), ..., f(n - 1) with compile-time indices
+template <int N, int I = 0, typename F>
+__device__ __attribute__((always_inline)) inline void static_for(F &&f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, I + 1>(f);
+  }
+}
+
 namespace wave {
 
 constexpr int kXor1 = 0xB1;  // quad_perm [1, 0, 3, 2]
