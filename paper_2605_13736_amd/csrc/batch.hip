@@ -97,26 +97,71 @@ struct ResultDev {
   double residual;  // max |r - K x| / max |r| before the last correction
 };
 
+// The workgroup's element loops are bound by memory latency (one workgroup per
+// compute unit, 31 elements a thread at n_s = 16000), so they take EU elements
+// at a time: every load is issued before the first use.  use(i, v) sees a
+// thread's elements in ascending order, as a plain loop would.
+constexpr int EU = 8;
+template <int U = EU, typename LD, typename USE>
+__device__ __forceinline__ void each(int n, LD ld, USE use) {
+  for (int i0 = threadIdx.x; i0 < n; i0 += U * BT) {
+    decltype(ld(0)) v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = ld(min(i0 + u * BT, n - 1));
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (i0 + u * BT < n) use(i0 + u * BT, v[u]);
+  }
+}
+
+// sum over t < n of a[t st] b[t] added to s in ascending order, 16 loads ahead
+template <typename ADD>
+__device__ __forceinline__ double dot_run(double s, const double *a, size_t st, const double *b,
+                                          int n, ADD add) {
+  for (int t0 = 0; t0 < n; t0 += 16) {
+    double x[16], y[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int t = min(t0 + u, n - 1);
+      x[u] = a[(size_t)t * st];
+      y[u] = b ? b[t] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < 16; ++u)
+      if (t0 + u < n) s = add(s, x[u], y[u]);
+  }
+  return s;
+}
+
 // ---- condensation (bit-identical to k_condense_dense / k_condense_schur) ----
 __device__ __attribute__((noinline)) void condense_wg(const ProbDev &P, double *inv_d, double dw, double dc, double *M, bool full) {
   const int tid = threadIdx.x, nd = P.nd, m = P.m, N = nd + m;
-  for (int k = tid; k < P.ns; k += BT) inv_d[k] = 1.0 / (P.dsbase[k] + dw);
-  // the FP64 factorization reads the lower triangle only
-  for (int j = 0; j < N; ++j)
-  for (int i = (full ? 0 : j & ~63) + tid; i < N; i += BT) {
-    double v;
-    if (i < nd && j < nd) {
-      v = P.H[(size_t)i + (size_t)j * nd];
-      if (i == j) v = (v + P.sigma_d[i]) + dw;
-    } else if (j < nd) {
-      v = P.Jd[(size_t)(i - nd) + (size_t)j * m];
-    } else if (i < nd) {
-      v = P.Jd[(size_t)(j - nd) + (size_t)i * m];
-    } else {
-      v = 0.0;
+  each(P.ns, [&](int k) { return P.dsbase[k]; },
+       [&](int k, double v) { inv_d[k] = 1.0 / (v + dw); });
+  // columns j0 .. j0 + CU - 1 together: the [H; J_d] columns, then zeros (in
+  // the whole matrix below J_d').  The FP64 factorization reads the lower
+  // triangle only.
+  constexpr int CU = 8;
+  for (int j0 = 0; j0 < N; j0 += CU)
+    for (int i = (full ? 0 : j0 & ~63) + tid; i < N; i += BT) {
+      double v[CU];
+#pragma unroll
+      for (int u = 0; u < CU; ++u) {
+        const int j = min(j0 + u, N - 1);
+        const double *a = (j < nd) ? ((i < nd) ? P.H + i + (size_t)j * nd
+                                               : P.Jd + (i - nd) + (size_t)j * m)
+                                   : P.Jd + (j - nd) + (size_t)i * m;
+        v[u] = (i < nd || j < nd) ? *a : 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < CU; ++u) {
+        const int j = j0 + u;
+        if (j < N) {
+          if (i == j && i < nd) v[u] = (v[u] + P.sigma_d[i]) + dw;
+          M[(size_t)i + (size_t)j * N] = v[u];
+        }
+      }
     }
-    M[(size_t)i + (size_t)j * N] = v;
-  }
   __syncthreads();
   for (int r = tid; r < m; r += BT) {
     const size_t col = (size_t)(nd + r) * N;
@@ -451,6 +496,18 @@ __device__ __attribute__((noinline)) int panel_spec_wg(int N, int k0, int nbw, d
           const int px = s.map[x - k0];
           v[r] = gX[(unsigned)(max(px, pc) + min(px, pc) * N)];
         }
+      }
+      if (nr == 1) {
+        // at most BT rows left: all of a step's latency is this one chain
+        const unsigned x = (unsigned)min(k + tid, N - 1);
+        for (int t0 = 0; t0 < j; t0 += 32) {
+          double l[32];
+#pragma unroll
+          for (int u = 0; u < 32; ++u) l[u] = gY[x + (unsigned)((k0 + min(t0 + u, j - 1)) * N)];
+#pragma unroll
+          for (int u = 0; u < 32; ++u) v[0] = fma(-l[u], (t0 + u < j) ? w[t0 + u] : 0.0, v[0]);
+        }
+        return;
       }
       for (int t0 = 0; t0 < j; t0 += 8) {
 #pragma unroll
@@ -917,47 +974,66 @@ __device__ inline void diag_block(const double *Lb, size_t ld, int k0, int w, do
   }
 }
 
+// The panel's transpositions on z (one wave; lane e holds entry e of s_pq): only
+// those that move a row, in pivot order or reversed.
+__device__ inline void swap_rows(double *z, const int *s_pq, int w, bool reverse) {
+  const int lane = threadIdx.x & 63;
+  const int p = (lane < w) ? s_pq[2 * lane] : -1, q = (lane < w) ? s_pq[2 * lane + 1] : 0;
+  unsigned long long mv = __ballot(p >= 0 && p != q);
+  while (mv) {
+    const int e = reverse ? 63 - __clzll((long long)mv) : __ffsll((unsigned long long)mv) - 1;
+    mv &= ~(1ull << e);
+    const int pe = wave::lane_read(p, e), qe = wave::lane_read(q, e);
+    if (lane == 0) {
+      const double t = z[pe];
+      z[pe] = z[qe];
+      z[qe] = t;
+    }
+  }
+}
+
+// What bounds a solve: reading L twice (1.8 ms for N = 2048 at a compute unit's
+// share of the memory rate) and, in small problems, the chain over the panels;
+// so 32 entries of a row are loaded together, a wave holds its row (column) of
+// the diagonal block in registers before its 63 dependent steps, and only
+// transpositions that move a row are applied.
 __device__ __attribute__((noinline)) void solve_wg(int N, const SlotDev &S, double *z, double *s_part,
                                                    bool mixed, double *s_db, int *s_pq) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int np = S.st->npanel;
-  const size_t ld = (size_t)N;
   // forward: P_b, then L_b
   for (int b = 0; b < np; ++b) {
     const int k0 = S.pk0[b], k1 = S.pk0[b + 1];
     const int w = k1 - k0;
     const double *Lb = mixed ? S.buf[0] : S.buf[(b + 1) & 1];
+    gdouble *gL = (gdouble *)ubase(Lb);
     panel_records(S, k0, w, s_pq);
-    diag_block(Lb, ld, k0, w, s_db);
-    __syncthreads();
-    if (tid == 0) {
-      for (int e = 0; e < w; ++e) {
-        const int p = s_pq[2 * e], q = s_pq[2 * e + 1];
-        if (p >= 0 && p != q) {
-          const double t = z[p];
-          z[p] = z[q];
-          z[q] = t;
-        }
-      }
-    }
+    diag_block(Lb, (size_t)N, k0, w, s_db);
     __syncthreads();
     if (wv == 0) {
-      double v = (lane < w) ? z[k0 + lane] : 0.0;
-      for (int c = 0; c + 1 < w; ++c) {
-        const double zc = wave::lane_read(v, c);
-        if (lane > c && lane < w) v = fma(-s_db[lane * BDB + c], zc, v);
+      double dr[SNB];
+#pragma unroll
+      for (int c = 0; c < SNB; ++c) dr[c] = (lane > c && lane < w) ? s_db[lane * BDB + c] : 0.0;
+      swap_rows(z, s_pq, w, false);
+      __asm__ __volatile__("s_waitcnt lgkmcnt(0)" ::: "memory");
+      double v = (lane < w) ? z[k0 + lane] : 0.0, o = v;
+      // row c + 1 is final after step c (later steps multiply by zero there)
+#pragma unroll
+      for (int c = 0; c < SNB - 1; ++c) {
+        v = fma(-dr[c], wave::lane_read(v, c), v);
+        o = (lane == c + 1) ? v : o;
       }
-      if (lane < w) z[k0 + lane] = v;
+      if (lane < w) z[k0 + lane] = o;
     }
     __syncthreads();
     for (int x = k1 + tid; x < N; x += BT) {
       double v = z[x];
-      for (int c0 = k0; c0 < k1; c0 += 8) {
-        double l[8];
+      for (int c0 = k0; c0 < k1; c0 += 32) {
+        double l[32];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) l[u] = Lb[(size_t)x + (size_t)min(c0 + u, k1 - 1) * ld];
+        for (int u = 0; u < 32; ++u) l[u] = gL[(unsigned)(x + min(c0 + u, k1 - 1) * N)];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v = fma(-l[u], (c0 + u < k1) ? z[c0 + u] : 0.0, v);
+        for (int u = 0; u < 32; ++u) v = fma(-l[u], (c0 + u < k1) ? z[c0 + u] : 0.0, v);
       }
       z[x] = v;
     }
@@ -981,48 +1057,47 @@ __device__ __attribute__((noinline)) void solve_wg(int N, const SlotDev &S, doub
   for (int b = np - 1; b >= 0; --b) {
     const int k0 = S.pk0[b], k1 = S.pk0[b + 1], w = k1 - k0;
     const double *Lb = mixed ? S.buf[0] : S.buf[(b + 1) & 1];
+    gdouble *gL = (gdouble *)ubase(Lb);
     panel_records(S, k0, w, s_pq);
-    diag_block(Lb, ld, k0, w, s_db);
-    for (int cb = 0; cb < w; cb += 16) {
-      double acc[16];
+    diag_block(Lb, (size_t)N, k0, w, s_db);
+    for (int cb = 0; cb < w; cb += 32) {
+      double acc[32];
 #pragma unroll
-      for (int c = 0; c < 16; ++c) acc[c] = 0.0;
+      for (int c = 0; c < 32; ++c) acc[c] = 0.0;
       for (int x = k1 + tid; x < N; x += BT) {
         const double zx = z[x];
+        double l[32];
 #pragma unroll
-        for (int c = 0; c < 16; ++c)
-          acc[c] = fma(Lb[(size_t)x + (size_t)(k0 + min(cb + c, w - 1)) * ld], zx, acc[c]);
+        for (int c = 0; c < 32; ++c) l[c] = gL[(unsigned)(x + (k0 + min(cb + c, w - 1)) * N)];
+#pragma unroll
+        for (int c = 0; c < 32; ++c) acc[c] = fma(l[c], zx, acc[c]);
       }
 #pragma unroll
-      for (int c = 0; c < 16; ++c) {
+      for (int c = 0; c < 32; ++c) {
         const double v = wave::sum(acc[c]);
         if (lane == 0) s_part[wv * SNB + cb + c] = v;
       }
     }
     __syncthreads();
     if (wv == 0) {
+      double dr[SNB];
+#pragma unroll
+      for (int c = 0; c < SNB; ++c) dr[c] = (c > lane && c < w) ? s_db[c * BDB + lane] : 0.0;
       double v = 0.0;
       if (lane < w) {
         double s = 0.0;
         for (int q = 0; q < NWAVE; ++q) s += s_part[q * SNB + lane];
         v = z[k0 + lane] - s;
       }
-      for (int c = w - 1; c > 0; --c) {
-        const double xc = wave::lane_read(v, c);
-        if (lane < c) v = fma(-s_db[c * BDB + lane], xc, v);
+      double o = v;
+#pragma unroll
+      for (int c = SNB - 1; c > 0; --c) {
+        v = fma(-dr[c], wave::lane_read(v, c), v);
+        o = (lane == c - 1) ? v : o;
       }
-      if (lane < w) z[k0 + lane] = v;
-    }
-    __syncthreads();
-    if (tid == 0) {
-      for (int e = w - 1; e >= 0; --e) {
-        const int p = s_pq[2 * e], q = s_pq[2 * e + 1];
-        if (p >= 0 && p != q) {
-          const double t = z[p];
-          z[p] = z[q];
-          z[q] = t;
-        }
-      }
+      if (lane < w) z[k0 + lane] = o;
+      __asm__ __volatile__("s_waitcnt lgkmcnt(0)" ::: "memory");
+      swap_rows(z, s_pq, w, true);
     }
     __syncthreads();
   }
@@ -1081,15 +1156,23 @@ __device__ __attribute__((noinline)) void kkt_solve_wg(const ProbDev &P, const S
     cm = fmax(cm, fabs(c));
     xm = fmax(xm, fabs(v));
   }
-  for (int k = tid; k < P.ns; k += BT) {
-    double t = rs[k];
-    for (int e = P.cptr[k]; e < P.cptr[k + 1]; ++e) t = t - P.cval[e] * s_z[nd + P.crow[e]];
-    const double c = S.inv_d[k] * t;
-    const double v = accumulate ? P.dx_s[k] + c : c;
-    P.dx_s[k] = v;
-    cm = fmax(cm, fabs(c));
-    xm = fmax(xm, fabs(v));
-  }
+  struct Bs {
+    double rs, inv, x;
+    int e0, e1;
+  };
+  each(P.ns,
+       [&](int k) {
+         return Bs{rs[k], S.inv_d[k], accumulate ? P.dx_s[k] : 0.0, P.cptr[k], P.cptr[k + 1]};
+       },
+       [&](int k, const Bs &a) {
+         double t = a.rs;
+         for (int e = a.e0; e < a.e1; ++e) t = t - P.cval[e] * s_z[nd + P.crow[e]];
+         const double c = a.inv * t;
+         const double v = accumulate ? a.x + c : c;
+         P.dx_s[k] = v;
+         cm = fmax(cm, fabs(c));
+         xm = fmax(xm, fabs(v));
+       });
   __syncthreads();
   *cmax = block_max(cm, s_part);
   *xmax = block_max(xm, s_part);
@@ -1104,27 +1187,34 @@ __device__ __attribute__((noinline)) double residual_wg(const ProbDev &P, const 
   const int tid = threadIdx.x, nd = P.nd, ns = P.ns, m = P.m;
   double *res = S.res;
   double rm = 0.0, bm = 0.0;
+  auto sub = [](double t, double a, double b) { return t - a * b; };
   for (int i = tid; i < nd; i += BT) {
     double t = P.r_d[i];
     bm = fmax(bm, fabs(t));
-    for (int j = 0; j < nd; ++j) t = t - P.H[(size_t)i + (size_t)j * nd] * P.dx_d[j];
+    t = dot_run(t, P.H + i, (size_t)nd, P.dx_d, nd, sub);
     t = t - (P.sigma_d[i] + dw) * P.dx_d[i];
-    for (int r = 0; r < m; ++r) t = t - P.Jd[(size_t)r + (size_t)i * m] * P.dy[r];
+    t = dot_run(t, P.Jd + (size_t)i * m, 1, P.dy, m, sub);
     res[i] = t;
     rm = fmax(rm, fabs(t));
   }
-  for (int k = tid; k < ns; k += BT) {
-    double t = P.r_s[k];
-    bm = fmax(bm, fabs(t));
-    t = t - (P.dsbase[k] + dw) * P.dx_s[k];
-    for (int e = P.cptr[k]; e < P.cptr[k + 1]; ++e) t = t - P.cval[e] * P.dy[P.crow[e]];
-    res[nd + k] = t;
-    rm = fmax(rm, fabs(t));
-  }
+  struct Rs {
+    double rs, ds, x;
+    int e0, e1;
+  };
+  each(ns,
+       [&](int k) { return Rs{P.r_s[k], P.dsbase[k], P.dx_s[k], P.cptr[k], P.cptr[k + 1]}; },
+       [&](int k, const Rs &a) {
+         double t = a.rs;
+         bm = fmax(bm, fabs(t));
+         t = t - (a.ds + dw) * a.x;
+         for (int e = a.e0; e < a.e1; ++e) t = t - P.cval[e] * P.dy[P.crow[e]];
+         res[nd + k] = t;
+         rm = fmax(rm, fabs(t));
+       });
   for (int r = tid; r < m; r += BT) {
     double t = P.r_y[r];
     bm = fmax(bm, fabs(t));
-    for (int i = 0; i < nd; ++i) t = t - P.Jd[(size_t)r + (size_t)i * m] * P.dx_d[i];
+    t = dot_run(t, P.Jd + r, (size_t)m, P.dx_d, nd, sub);
     for (int a = P.rp[r]; a < P.rp[r + 1]; ++a) t = t - P.v[a] * P.dx_s[P.ci[a]];
     t = t + dc * P.dy[r];
     res[nd + ns + r] = t;
@@ -1296,28 +1386,29 @@ __device__ inline bool block_any(bool f, int *s_flag) {
 __device__ __attribute__((noinline)) void ipm_eval_wg(const ProbDev &P, const IpmDev &Q, const SlotDev &S, const double *x,
                             const double *y, double *gf, double *jty, double *cx) {
   const int tid = threadIdx.x, nd = P.nd, ns = P.ns, m = P.m;
+  auto add = [](double t, double a, double b) { return t + a * b; };
   for (int i = tid; i < nd; i += BT) {
-    double t = 0.0;
-    for (int j = 0; j < nd; ++j) t = t + P.H[(size_t)i + (size_t)j * nd] * x[j];
+    const double t = dot_run(0.0, P.H + i, (size_t)nd, x, nd, add);
     S.hx[i] = t;
     gf[i] = t + Q.c[i];
+    if (y) jty[i] = dot_run(0.0, P.Jd + (size_t)i * m, 1, y, m, add);
   }
-  for (int k = tid; k < ns; k += BT) gf[nd + k] = Q.w[k] * x[nd + k] + Q.g[k];
-  if (y) {
-    for (int j = tid; j < nd; j += BT) {
-      double t = 0.0;
-      for (int r = 0; r < m; ++r) t = t + P.Jd[(size_t)r + (size_t)j * m] * y[r];
-      jty[j] = t;
-    }
-    for (int k = tid; k < ns; k += BT) {
-      double t = 0.0;
-      for (int e = P.cptr[k]; e < P.cptr[k + 1]; ++e) t = t + P.cval[e] * y[P.crow[e]];
-      jty[nd + k] = t;
-    }
-  }
+  struct Gs {
+    double w, x, g;
+    int e0, e1;
+  };
+  each(ns,
+       [&](int k) { return Gs{Q.w[k], x[nd + k], Q.g[k], P.cptr[k], P.cptr[k + 1]}; },
+       [&](int k, const Gs &a) {
+         gf[nd + k] = a.w * a.x + a.g;
+         if (y) {
+           double t = 0.0;
+           for (int e = a.e0; e < a.e1; ++e) t = t + P.cval[e] * y[P.crow[e]];
+           jty[nd + k] = t;
+         }
+       });
   for (int r = tid; r < m; r += BT) {
-    double t = 0.0;
-    for (int j = 0; j < nd; ++j) t = t + P.Jd[(size_t)r + (size_t)j * m] * x[j];
+    double t = dot_run(0.0, P.Jd + r, (size_t)m, x, nd, add);
     for (int a = P.rp[r]; a < P.rp[r + 1]; ++a) t = t + P.v[a] * x[nd + P.ci[a]];
     cx[r] = t - Q.b[r];
   }
@@ -1334,21 +1425,26 @@ __device__ __attribute__((noinline)) void ipm_parts_wg(const ProbDev &P, const I
   const int tid = threadIdx.x, n = P.nd + P.ns, m = P.m;
   double dual = 0.0, z1 = 0.0, nz = 0.0, y1 = 0.0, prim = 0.0;
   bool bad = false;
-  for (int i = tid; i < n; i += BT) {
-    double r = S.gf[i] + S.jty[i];
-    if (isfinite(Q.xl[i])) {
-      r = r - zl[i];
-      z1 += fabs(zl[i]);
-      nz += 1.0;
-    }
-    if (isfinite(Q.xu[i])) {
-      r = r + zu[i];
-      z1 += fabs(zu[i]);
-      nz += 1.0;
-    }
-    bad = bad || !isfinite(r);
-    dual = fmax(dual, fabs(r));
-  }
+  struct Pt {
+    double g, j, l, u, zl, zu;
+  };
+  each(n,
+       [&](int i) { return Pt{S.gf[i], S.jty[i], Q.xl[i], Q.xu[i], zl[i], zu[i]}; },
+       [&](int, const Pt &a) {
+         double r = a.g + a.j;
+         if (isfinite(a.l)) {
+           r = r - a.zl;
+           z1 += fabs(a.zl);
+           nz += 1.0;
+         }
+         if (isfinite(a.u)) {
+           r = r + a.zu;
+           z1 += fabs(a.zu);
+           nz += 1.0;
+         }
+         bad = bad || !isfinite(r);
+         dual = fmax(dual, fabs(r));
+       });
   for (int r = tid; r < m; r += BT) {
     bad = bad || !isfinite(S.cx[r]) || !isfinite(y[r]);
     prim = fmax(prim, fabs(S.cx[r]));
@@ -1369,10 +1465,14 @@ __device__ __attribute__((noinline)) double ipm_compl_wg(const ProbDev &P, const
                                const double *zl, const double *zu, double mu, double *s_part) {
   const int tid = threadIdx.x, n = P.nd + P.ns;
   double c = 0.0;
-  for (int i = tid; i < n; i += BT) {
-    if (isfinite(Q.xl[i])) c = fmax(c, fabs((x[i] - Q.xl[i]) * zl[i] - mu));
-    if (isfinite(Q.xu[i])) c = fmax(c, fabs((Q.xu[i] - x[i]) * zu[i] - mu));
-  }
+  struct Cp {
+    double x, l, u, zl, zu;
+  };
+  each(n, [&](int i) { return Cp{x[i], Q.xl[i], Q.xu[i], zl[i], zu[i]}; },
+       [&](int, const Cp &a) {
+         if (isfinite(a.l)) c = fmax(c, fabs((a.x - a.l) * a.zl - mu));
+         if (isfinite(a.u)) c = fmax(c, fabs((a.u - a.x) * a.zu - mu));
+       });
   return block_max_from(c, 0.0, s_part);
 }
 
@@ -1392,27 +1492,30 @@ __device__ __attribute__((noinline)) void ipm_merit_wg(const ProbDev &P, const I
   const int tid = threadIdx.x, nd = P.nd, n = P.nd + P.ns, m = P.m;
   double f = 0.0, lg = 0.0, th = 0.0, sc = 0.0;
   bool bad = false;
-  for (int i = tid; i < n; i += BT) {
-    double t;
-    if (i < nd) {
-      t = x[i] * (0.5 * S.hx[i] + Q.c[i]);
-    } else {
-      const double xs = x[i];
-      t = xs * (0.5 * Q.w[i - nd] * xs + Q.g[i - nd]);
-    }
-    f += t;
-    sc += fabs(t);
-    if (isfinite(Q.xl[i])) {
-      const double l = log(x[i] - Q.xl[i]);
-      lg += l;
-      sc += mu * fabs(l);
-    }
-    if (isfinite(Q.xu[i])) {
-      const double l = log(Q.xu[i] - x[i]);
-      lg += l;
-      sc += mu * fabs(l);
-    }
-  }
+  struct Mt {
+    double x, l, u, a, b;
+  };
+  each(n,
+       [&](int i) {
+         const bool d = i < nd;
+         return Mt{x[i], Q.xl[i], Q.xu[i], d ? S.hx[i] : Q.w[i - nd], d ? Q.c[i] : Q.g[i - nd]};
+       },
+       [&](int i, const Mt &v) {
+         const double xs = v.x;
+         const double t = (i < nd) ? xs * (0.5 * v.a + v.b) : xs * (0.5 * v.a * xs + v.b);
+         f += t;
+         sc += fabs(t);
+         if (isfinite(v.l)) {
+           const double l = log(xs - v.l);
+           lg += l;
+           sc += mu * fabs(l);
+         }
+         if (isfinite(v.u)) {
+           const double l = log(v.u - xs);
+           lg += l;
+           sc += mu * fabs(l);
+         }
+       });
   for (int r = tid; r < m; r += BT) th += fabs(S.cx[r]);
   bad = !isfinite(f) || !isfinite(lg) || !isfinite(th);
   out[0] = block_sum(f, s_part);
@@ -1426,14 +1529,10 @@ __device__ __attribute__((noinline)) void ipm_merit_wg(const ProbDev &P, const I
 // J x - b and H x_d at x only (the trial points of the line search)
 __device__ __attribute__((noinline)) void ipm_constr_wg(const ProbDev &P, const IpmDev &Q, const SlotDev &S, const double *x) {
   const int tid = threadIdx.x, nd = P.nd, m = P.m;
-  for (int i = tid; i < nd; i += BT) {
-    double t = 0.0;
-    for (int j = 0; j < nd; ++j) t = t + P.H[(size_t)i + (size_t)j * nd] * x[j];
-    S.hx[i] = t;
-  }
+  auto add = [](double t, double a, double b) { return t + a * b; };
+  for (int i = tid; i < nd; i += BT) S.hx[i] = dot_run(0.0, P.H + i, (size_t)nd, x, nd, add);
   for (int r = tid; r < m; r += BT) {
-    double t = 0.0;
-    for (int j = 0; j < nd; ++j) t = t + P.Jd[(size_t)r + (size_t)j * m] * x[j];
+    double t = dot_run(0.0, P.Jd + r, (size_t)m, x, nd, add);
     for (int a = P.rp[r]; a < P.rp[r + 1]; ++a) t = t + P.v[a] * x[nd + P.ci[a]];
     S.cx[r] = t - Q.b[r];
   }
@@ -1444,24 +1543,27 @@ __device__ __attribute__((noinline)) void ipm_constr_wg(const ProbDev &P, const 
 __device__ __attribute__((noinline)) double ipm_knorm_wg(const ProbDev &P, double dw, double dc, double *s_part) {
   const int tid = threadIdx.x, nd = P.nd, ns = P.ns, m = P.m;
   double best = 0.0;
+  auto add = [](double t, double a, double) { return t + fabs(a); };
   for (int i = tid; i < nd; i += BT) {
-    double t = 0.0;
-    for (int j = 0; j < nd; ++j) {
-      double h = P.H[(size_t)i + (size_t)j * nd];
-      if (i == j) h = h + P.sigma_d[i] + dw;
-      t += fabs(h);
-    }
-    for (int r = 0; r < m; ++r) t += fabs(P.Jd[(size_t)r + (size_t)i * m]);
+    // the diagonal entry takes the barrier term in its place of the sum
+    double t = dot_run(0.0, P.H + i, (size_t)nd, nullptr, i, add);
+    t += fabs(P.H[(size_t)i + (size_t)i * nd] + P.sigma_d[i] + dw);
+    t = dot_run(t, P.H + i + (size_t)(i + 1) * nd, (size_t)nd, nullptr, nd - 1 - i, add);
+    t = dot_run(t, P.Jd + (size_t)i * m, 1, nullptr, m, add);
     best = fmax(best, t);
   }
-  for (int k = tid; k < ns; k += BT) {
-    double t = fabs(P.dsbase[k] + dw);
-    for (int e = P.cptr[k]; e < P.cptr[k + 1]; ++e) t += fabs(P.cval[e]);
-    best = fmax(best, t);
-  }
+  struct Kn {
+    double d;
+    int e0, e1;
+  };
+  each(ns, [&](int k) { return Kn{P.dsbase[k], P.cptr[k], P.cptr[k + 1]}; },
+       [&](int, const Kn &a) {
+         double t = fabs(a.d + dw);
+         for (int e = a.e0; e < a.e1; ++e) t += fabs(P.cval[e]);
+         best = fmax(best, t);
+       });
   for (int r = tid; r < m; r += BT) {
-    double t = fabs(dc);
-    for (int j = 0; j < nd; ++j) t += fabs(P.Jd[(size_t)r + (size_t)j * m]);
+    double t = dot_run(fabs(dc), P.Jd + r, (size_t)m, nullptr, nd, add);
     for (int a = P.rp[r]; a < P.rp[r + 1]; ++a) t += fabs(P.v[a]);
     best = fmax(best, t);
   }
@@ -1471,11 +1573,11 @@ __device__ __attribute__((noinline)) double ipm_knorm_wg(const ProbDev &P, doubl
 // max |v| over the Newton solution or right-hand side stored as three pieces
 __device__ __attribute__((noinline)) double amax3_wg(const double *a, int na, const double *b, int nb_, const double *c,
                            int nc, double *s_part) {
-  const int tid = threadIdx.x;
   double t = 0.0;
-  for (int i = tid; i < na; i += BT) t = fmax(t, fabs(a[i]));
-  for (int i = tid; i < nb_; i += BT) t = fmax(t, fabs(b[i]));
-  for (int i = tid; i < nc; i += BT) t = fmax(t, fabs(c[i]));
+  auto mx = [&](int, double v) { t = fmax(t, fabs(v)); };
+  each(na, [&](int i) { return a[i]; }, mx);
+  each(nb_, [&](int i) { return b[i]; }, mx);
+  each(nc, [&](int i) { return c[i]; }, mx);
   return block_max_from(t, 0.0, s_part);
 }
 
@@ -1616,22 +1718,30 @@ __global__ __launch_bounds__(BT) void k_batch_ipm(int count, const int32_t *__re
         nf = 0;
       }
       // barrier diagonal and Newton right-hand side; D_s base w + Sigma_s
-      for (int i = tid; i < n; i += BT) {
-        double sg = 0.0, gb = S.gf[i] + S.jty[i];
-        if (isfinite(Q.xl[i])) {
-          const double sl = x[i] - Q.xl[i];
-          sg = sg + zl[i] / sl;
-          gb = gb - mu / sl;
-        }
-        if (isfinite(Q.xu[i])) {
-          const double su = Q.xu[i] - x[i];
-          sg = sg + zu[i] / su;
-          gb = gb + mu / su;
-        }
-        S.sig[i] = sg;
-        S.rx[i] = -gb;
-        if (i >= nd) S.dsb[i - nd] = Q.w[i - nd] + sg;
-      }
+      struct Sg {
+        double g, j, l, u, x, zl, zu, w;
+      };
+      each<4>(n,
+              [&](int i) {
+                return Sg{S.gf[i], S.jty[i], Q.xl[i], Q.xu[i], x[i], zl[i], zu[i],
+                          i >= nd ? Q.w[i - nd] : 0.0};
+              },
+              [&](int i, const Sg &a) {
+                double sg = 0.0, gb = a.g + a.j;
+                if (isfinite(a.l)) {
+                  const double sl = a.x - a.l;
+                  sg = sg + a.zl / sl;
+                  gb = gb - mu / sl;
+                }
+                if (isfinite(a.u)) {
+                  const double su = a.u - a.x;
+                  sg = sg + a.zu / su;
+                  gb = gb + mu / su;
+                }
+                S.sig[i] = sg;
+                S.rx[i] = -gb;
+                if (i >= nd) S.dsb[i - nd] = a.w + sg;
+              });
       for (int r = tid; r < m; r += BT) S.ry[r] = -S.cx[r];
       __syncthreads();
       // inertia correction (Algorithm IC)
@@ -1661,24 +1771,29 @@ __global__ __launch_bounds__(BT) void k_batch_ipm(int count, const int32_t *__re
       ipm_refine_wg(P, S, dw, dc, prm.refine_steps, s_z, s_part, s_db, s_pq);
       // bound-multiplier steps and the fraction to the boundary
       double apr = -1.0, adu = -1.0;  // largest -(step limit)
-      for (int i = tid; i < n; i += BT) {
-        double a = 0.0, b = 0.0;
-        const double d = S.dx[i];
-        if (isfinite(Q.xl[i])) {
-          const double sl = x[i] - Q.xl[i];
-          a = mu / sl - zl[i] - (zl[i] / sl) * d;
-          if (d < 0.0) apr = fmax(apr, -(-tau * sl / d));
-          if (a < 0.0) adu = fmax(adu, -(-tau * zl[i] / a));
-        }
-        if (isfinite(Q.xu[i])) {
-          const double su = Q.xu[i] - x[i];
-          b = mu / su - zu[i] + (zu[i] / su) * d;
-          if (-d < 0.0) apr = fmax(apr, -(-tau * su / (-d)));
-          if (b < 0.0) adu = fmax(adu, -(-tau * zu[i] / b));
-        }
-        S.dzl[i] = a;
-        S.dzu[i] = b;
-      }
+      struct Ft {
+        double d, l, u, x, zl, zu;
+      };
+      each<4>(n,
+              [&](int i) { return Ft{S.dx[i], Q.xl[i], Q.xu[i], x[i], zl[i], zu[i]}; },
+              [&](int i, const Ft &v) {
+                double a = 0.0, b = 0.0;
+                const double d = v.d;
+                if (isfinite(v.l)) {
+                  const double sl = v.x - v.l;
+                  a = mu / sl - v.zl - (v.zl / sl) * d;
+                  if (d < 0.0) apr = fmax(apr, -(-tau * sl / d));
+                  if (a < 0.0) adu = fmax(adu, -(-tau * v.zl / a));
+                }
+                if (isfinite(v.u)) {
+                  const double su = v.u - v.x;
+                  b = mu / su - v.zu + (v.zu / su) * d;
+                  if (-d < 0.0) apr = fmax(apr, -(-tau * su / (-d)));
+                  if (b < 0.0) adu = fmax(adu, -(-tau * v.zu / b));
+                }
+                S.dzl[i] = a;
+                S.dzu[i] = b;
+              });
       const double a_pr = -block_max_from(apr, -1.0, s_part);
       const double a_du = -block_max_from(adu, -1.0, s_part);
       // merit at x and grad(phi)' dx
@@ -1687,12 +1802,16 @@ __global__ __launch_bounds__(BT) void k_batch_ipm(int count, const int32_t *__re
       const double th = mv[2], ph = mv[0] - mu * mv[1];
       const double ph_tol = 10.0 * DBL_EPSILON * mv[3];
       double gp = 0.0;
-      for (int i = tid; i < n; i += BT) {
-        double gi = S.gf[i];
-        if (isfinite(Q.xl[i])) gi = gi - mu / (x[i] - Q.xl[i]);
-        if (isfinite(Q.xu[i])) gi = gi + mu / (Q.xu[i] - x[i]);
-        gp += gi * S.dx[i];
-      }
+      struct Gp {
+        double g, l, u, x, d;
+      };
+      each(n, [&](int i) { return Gp{S.gf[i], Q.xl[i], Q.xu[i], x[i], S.dx[i]}; },
+           [&](int, const Gp &a) {
+             double gi = a.g;
+             if (isfinite(a.l)) gi = gi - mu / (a.x - a.l);
+             if (isfinite(a.u)) gi = gi + mu / (a.u - a.x);
+             gp += gi * a.d;
+           });
       const double gphi = block_sum(gp, s_part);
       double amin;
       if (gphi < 0.0) {
@@ -1706,7 +1825,11 @@ __global__ __launch_bounds__(BT) void k_batch_ipm(int count, const int32_t *__re
       bool accepted = false, augment = true;
       int nbt = 0;
       for (;;) {
-        for (int i = tid; i < n; i += BT) S.xt[i] = x[i] + alpha_s * S.dx[i];
+        struct Xd {
+          double x, d;
+        };
+        each(n, [&](int i) { return Xd{x[i], S.dx[i]}; },
+             [&](int i, const Xd &a) { S.xt[i] = a.x + alpha_s * a.d; });
         __syncthreads();
         ipm_constr_wg(P, Q, S, S.xt);
         ipm_merit_wg(P, Q, S, S.xt, mu, s_part, mv);
@@ -1757,18 +1880,25 @@ __global__ __launch_bounds__(BT) void k_batch_ipm(int count, const int32_t *__re
         nf++;
       }
       // accept: x, y, and the bound multipliers with the kappa_Sigma safeguard
-      for (int i = tid; i < n; i += BT) {
-        const double xi = S.xt[i];
-        x[i] = xi;
-        if (isfinite(Q.xl[i])) {
-          const double z = zl[i] + a_du * S.dzl[i], sl = xi - Q.xl[i];
-          zl[i] = fmax(fmin(z, kappa_sigma * mu / sl), mu / (kappa_sigma * sl));
-        }
-        if (isfinite(Q.xu[i])) {
-          const double z = zu[i] + a_du * S.dzu[i], su = Q.xu[i] - xi;
-          zu[i] = fmax(fmin(z, kappa_sigma * mu / su), mu / (kappa_sigma * su));
-        }
-      }
+      struct Ac {
+        double x, l, u, zl, zu, dl, du;
+      };
+      each<4>(n,
+              [&](int i) {
+                return Ac{S.xt[i], Q.xl[i], Q.xu[i], zl[i], zu[i], S.dzl[i], S.dzu[i]};
+              },
+              [&](int i, const Ac &a) {
+                const double xi = a.x;
+                x[i] = xi;
+                if (isfinite(a.l)) {
+                  const double z = a.zl + a_du * a.dl, sl = xi - a.l;
+                  zl[i] = fmax(fmin(z, kappa_sigma * mu / sl), mu / (kappa_sigma * sl));
+                }
+                if (isfinite(a.u)) {
+                  const double z = a.zu + a_du * a.du, su = a.u - xi;
+                  zu[i] = fmax(fmin(z, kappa_sigma * mu / su), mu / (kappa_sigma * su));
+                }
+              });
       for (int r = tid; r < m; r += BT) y[r] = y[r] + alpha_s * S.dy[r];
       __syncthreads();
     }
