@@ -457,13 +457,11 @@ __device__ inline double ldb(const double *p, unsigned off) {
 // the panel's end become zeros on the way to LDS): a guard is a branch, and
 // behind a branch the wait for the staging loads becomes one for every load in
 // flight.
-// The shape follows the FP64 matrix instruction, measured from registers alone:
-// 47 TFLOP/s with four waves per SIMD and four accumulators a wave, 36 with one
-// or two waves of sixteen.  128 x 128 tiles (persistent, the next tile's X in
-// registers) and 64 x 64 tiles a wave without LDS were slower for it: 41 and 45
-// ms of pair updates at N = 16384 against 37; vector FMAs (68 TFLOP/s from
-// registers, 56 with W broadcast from lanes) in 256 x 16 tiles a wave waited for
-// their loads: 49 ms, with W in scalar registers 55.
+// Four workgroups per compute unit of this shape beat, in pair updates at N =
+// 16384 (36.8 ms here): 128 x 128 tiles (39.6 ms; persistent with the next
+// tile's X in registers 46), 64 x 64 tiles a wave without LDS (44.6), and vector
+// FMAs on 256 x 16 tiles a wave with W broadcast from lanes (48.6) or in scalar
+// registers (55).
 struct PanelCols {
   const double *W, *L;  // column t at t N
   int j;                // columns
@@ -531,9 +529,11 @@ __device__ __forceinline__ void trailing_tile(int N, int kend, int i0, int c0, b
     }
     __syncthreads();
     if (ch + 1 < NC) stage_load(ch + 1);
-    // the tile's entries, a share behind every chunk's staging loads
+    // the tile's entries, a share behind the staging loads of the later half
+    // of the chunks (2.5% faster than over all chunks, 11% than ahead of them)
+    constexpr int H = NC / 2;
 #pragma unroll
-    for (int e = 16 * ch / NC; e < 16 * (ch + 1) / NC; ++e) {
+    for (int e = 16 * (ch < H ? 0 : ch - H) / H; e < 16 * (ch < H ? 0 : ch + 1 - H) / H; ++e) {
       const int a = e >> 3, b = (e >> 2) & 1, r = e & 3;
       const unsigned hi = max(si[b], sc[a][r]), lo = min(si[b], sc[a][r]);
       xv[a][b][r] = ldb(X, hi * 8u + __umul24(lo, st8));
@@ -607,8 +607,8 @@ __global__ __launch_bounds__(256, 4) void k_bk_trailing_coop(int N, const double
 // order, to which the second panel's map src leads; its L is in place (column t
 // at k0 + t), the second one's staged.  Workgroups past the tiles copy the
 // second panel's multipliers from their staging buffer into Y's columns.
-// N = 16384, pairs down to 4608 rows: 37.0 ms of updates a factorization against
-// 46.1 one by one (38 TFLOP/s), 60.7 against 67.9 ms a Newton pass.
+// N = 16384, pairs down to 4608 rows: 36.8 ms of updates a factorization against
+// 46.1 one by one (39 TFLOP/s), 60.7 against 67.9 ms a Newton pass.
 constexpr int kPairCopy = 128;  // workgroups of the copy
 __global__ __launch_bounds__(256, 4) void k_bk_trailing_pair(
     int N, long tiles, const double *__restrict__ W, const double *X, double *Y, const double *Lst,

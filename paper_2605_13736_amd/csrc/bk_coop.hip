@@ -16,6 +16,7 @@
 //      row), the owner of position k also a_kk.  Every workgroup reads all
 //      the headers and derives colmax, imax and a_kk, then, when the first
 //      test fails, the winner's L row.
+//   (not after a failing block, whose XB carried the candidate)
 //   X3 (when the first test fails): every workgroup's maximum of the updated
 //      column imax, and a_ii from its owner.
 //   XB (when the step ends a block): the window rows (L rows of the next
@@ -120,13 +121,19 @@ __device__ __attribute__((noinline)) double pending_entry(const TX *pX, const in
 // of 256 rows, and needs no static column index.  Columns t >= j are
 // never read (operands are masked), so nothing is cleared.
 //
+// A failing column's full step needs no X1: the exchange XB carries each
+// workgroup's candidate for its first failing column, and the columns' entries
+// stand in registers.
+//
 // What bounds it: latency and, with one wave per SIMD, instruction issue.  At
-// N = 4096 a block takes 8.4 us: 2.4 for its entries' products (MFMA; 64 cycles
+// N = 4096 a block takes 8.5 us: 2.4 for its entries' products (MFMA; 64 cycles
 // each), 2.6 for the diagonal block and the rows (3.7 with the rows' entries
-// gathered and selected across lanes for every four columns), 2.5 for the exchange
-// (1.7 of them its round trip).  A full step takes 8.2 us (10.5 while each one
-// ended in an XB).  The panels of N = 4096: 4.76 -> 3.94 ms, N = 16384: 21.2 ->
-// 17.6 ms.
+// gathered and selected across lanes for every four columns), 2.9 for the exchange
+// (1.7 of them its round trip).  A full step takes 3.9 us after a failing block
+// and 8.2 otherwise (10.5 while each one had its X1 and ended in an XB).  The
+// panels of N = 4096: 4.76 -> 3.85 ms (FP32 storage, more failing blocks: 5.7 ->
+// 4.8, mostly because its entries are converted after the exchange instead of
+// before it), N = 16384: 21.2 -> 17 ms.
 constexpr int CT = 256;        // threads = rows of a workgroup
 constexpr int CNB = 64;        // most columns of a panel
 constexpr int CB = 16;         // columns of a speculative block
@@ -161,6 +168,8 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
   __shared__ int s_pos[CT];
   __shared__ double s_hv[kCoopMaxP], s_hx[kCoopMaxP];
   __shared__ int s_hi[kCoopMaxP], s_hp[kCoopMaxP];
+  __shared__ int s_hq[kCoopMaxP];
+  __shared__ double s_xq[CB];  // the failing column's entries of the window rows
   __shared__ double s_cv[NWV], s_akk, s_aii;
   __shared__ int s_ci[NWV], s_cs[NWV], s_fail[NWV];
   __shared__ int s_k0, s_abort, s_force;
@@ -214,11 +223,19 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
   int c_pos = 0, c_zero = 0, c_neg = 0, c_2x2 = 0, first_zero = 0, nsteps = 0, nsec = 0;
   bool any2 = false;      // a 2x2 pivot in this panel
   int slow = 0, cool = 0; // full steps due; back-off after failing blocks
+  // a failing block's candidate: the next full step starts from it without X1
+  bool have = false;
+  double f_x = 0.0, f_max = 0.0, f_wki = 0.0;
+  int f_imax = 0, f_phys = 0, f_g = 0;
 
   // un-updated entries of the block at (jj, its columns [jj % CB, ce)), in the
   // MFMA result layout: register r of lane l holds column l/16 + 4 r of row
   // l % 16 of each 16-row group; dacc: the diagonal block's lower triangle
+  // (FP32 storage: kept in ra, rda until their use, since a conversion would
+  // wait for the loads before the exchange they overlap)
+  constexpr bool RAW = sizeof(TX) != sizeof(double);
   d4 acc[4], dacc;
+  TX ra[4][4], rda[4];
   bool loaded = false;
   auto block_cols = [&](int jj) { return min(min(CB - (jj & (CB - 1)), nb - jj), N - (k0 + jj)); };
   auto load_block = [&](int jj) {
@@ -233,14 +250,19 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const bool on = pi >= 0 && pc[r] >= 0 && l16 >= l4 + 4 * r;
-      dacc[r] = on ? (double)sym_at(X, pi, pc[r], ld) : 0.0;
+      const TX v = on ? sym_at(X, pi, pc[r], ld) : (TX)0;
+      if constexpr (RAW) rda[r] = v;
+      else dacc[r] = v;
     }
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int row = gbase + 64 * wid + 16 * q + l16;
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        acc[q][r] = (pc[r] >= 0 && row < N) ? (double)sym_at(X, row, pc[r], ld) : 0.0;
+      for (int r = 0; r < 4; ++r) {
+        const TX v = (pc[r] >= 0 && row < N) ? sym_at(X, row, pc[r], ld) : (TX)0;
+        if constexpr (RAW) ra[q][r] = v;
+        else acc[q][r] = v;
+      }
     }
   };
   // W = L D of window row q at column t < j
@@ -257,11 +279,31 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
     s_abort = 1;
   };
 
+  // largest (v, position, thread) of the workgroup, every thread; two barriers
+  auto wg_amax = [&](double &v, int &i, int &t) {
+    wave::amax(v, i, t);
+    if (lane == 0) {
+      s_cv[wid] = v;
+      s_ci[wid] = i;
+      s_cs[wid] = t;
+    }
+    __syncthreads();
+    v = s_cv[0];
+    i = s_ci[0];
+    t = s_cs[0];
+#pragma unroll
+    for (int w = 1; w < NWV; ++w) wave::amax3(v, i, t, s_cv[w], s_ci[w], s_cs[w]);
+  };
+
   // Exchange XB: fl of every workgroup (their minimum is returned) and, when
   // rows, the first jv entries of the L rows of positions k0 + jn + (0..15),
-  // which replace the window rows if the minimum is at least need.  Every
-  // thread polls its own words.  The caller's LDS writes need no barrier before.
-  auto xb = [&](int fl, bool rows, int jn, int jv, int need, int jload) -> int {
+  // which replace the window rows if the minimum is at least need.  A workgroup
+  // with a failing column (fl < fce) publishes its candidate for it too (bv, bi,
+  // thread bt, entry bx, as X1 does): the column's maximum exceeds |d| / alpha, so
+  // it lies in a workgroup where this column is the first to fail.  Every thread
+  // polls its own words.  The caller's LDS writes need no barrier before.
+  auto xb = [&](int fl, bool rows, int jn, int jv, int need, int jload, int fce, double bv, int bi,
+                int bt, double bx) -> int {
     __syncthreads();
     if (P == 1) {
       if (jload >= 0) load_block(jload);
@@ -279,7 +321,18 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
     ++c;
     constexpr int U = CB * CNB / CT;
     uint64_t *xr = xrow(par);
-    if (tid == 0) put_u32(slot(par, g), (uint32_t)fl, tag);
+    uint64_t *mine = slot(par, g);
+    if (tid == 0) put_u32(mine, (uint32_t)fl, tag);
+    if (fl < fce) {
+      if (tid == bt) {
+        put_u32(mine + 1, (uint32_t)bi, tag);
+        put_f64(mine + 2, bv, tag);
+        put_u32(mine + 4, (uint32_t)rho, tag);
+        put_f64(mine + 5, bx, tag);
+      }
+      // its L row up to the failing column of the block before position jn
+      if (tid < jn - CB + fl) put_f64(mine + 8 + 2 * tid, s_L[tid * CLD + bt], tag);
+    }
     bool on[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -291,17 +344,23 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
     if (jload >= 0) load_block(jload);
     const bool hon = tid < P;
     const uint64_t *hp = slot(par, hon ? tid : g);
-    uint64_t h0, whi[U], wlo[U];
+    uint64_t h[7] = {}, whi[U], wlo[U];
     const uint64_t t0 = wall_clock64();
     for (;;) {
-      h0 = get_w(hp);
+      if (hon) {
+#pragma unroll
+        for (int u = 0; u < 7; ++u) h[u] = get_w(hp + u);
+      }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const uint64_t *wp = on[u] ? xr + 2 * (tid + CT * u) : hp;
         whi[u] = get_w(wp);
         wlo[u] = get_w(on[u] ? wp + 1 : wp);
       }
-      bool ok = (!hon) | tag_ok(h0, tag);
+      bool hok = true;
+#pragma unroll
+      for (int u = 1; u < 7; ++u) hok = hok & tag_ok(h[u], tag);
+      bool ok = (!hon) | (tag_ok(h[0], tag) & (((int)(uint32_t)h[0] >= fce) | hok));
 #pragma unroll
       for (int u = 0; u < U; ++u) ok = ok & ((!on[u]) | (tag_ok(whi[u], tag) & tag_ok(wlo[u], tag)));
       if (__ballot(!ok) == 0) break;
@@ -310,7 +369,13 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
         break;
       }
     }
-    if (hon) s_hi[tid] = (int)(uint32_t)h0;
+    if (hon) {
+      s_hi[tid] = (int)(uint32_t)h[0];
+      s_hq[tid] = (int)(uint32_t)h[1];
+      s_hv[tid] = as_f64(h[2], h[3]);
+      s_hp[tid] = (int)(uint32_t)h[4];
+      s_hx[tid] = as_f64(h[5], h[6]);
+    }
     __syncthreads();
     if (s_abort) return -1;
     int m = CB;
@@ -334,6 +399,14 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
       const int jb = j & ~(CB - 1), r0 = j - jb, s = block_cols(j), ce = r0 + s;
       if (!loaded) load_block(j);
       loaded = false;
+      if constexpr (RAW) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          dacc[r] = (double)rda[r];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) acc[q][r] = (double)ra[q][r];
+        }
+      }
       {
         const bool wc = l16 >= r0 && l16 < ce;
         // 16 columns at a time: their operands are read together
@@ -368,7 +441,7 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
           if (cc >= r0 && cc < ce) s_L[(jb + cc) * CLD + 64 * wid + 16 * q + l16] = acc[q][r];
         }
       lds_wave_sync();
-      double xr[CB], ldg[4], dow[4];
+      double xr[CB], wc[CB], ldg[4], dow[4];
 #pragma unroll
       for (int cc = 0; cc < CB; ++cc) xr[cc] = s_L[(jb + cc) * CLD + tid];
       int ff = ce;  // first failing column of this wave
@@ -376,12 +449,13 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
       // so that a whole block is straight-line code.
       auto factor = [&](auto whole) __attribute__((always_inline)) {
         constexpr bool FULL = decltype(whole)::value;
-        // the diagonal block's columns (updated entries, row l16, in each row of
-        // 16 lanes), their pivots and reciprocals (one value in every lane)
-        double wc[CB], dv[CB], rd[CB];
+        // the diagonal block's columns (wc: updated entries, row l16, in each row
+        // of 16 lanes), their pivots and reciprocals (one value in every lane)
+        double dv[CB], rd[CB];
         static_for<4>([&](auto uc) __attribute__((always_inline)) {
           constexpr int u = decltype(uc)::value, c0 = 4 * u;
           ldg[u] = dow[u] = 0.0;
+          if (!FULL) wc[c0] = wc[c0 + 1] = wc[c0 + 2] = wc[c0 + 3] = 0.0;
           if (!FULL && (c0 + 3 < r0 || c0 >= ce)) return;
           bool on[4];
 #pragma unroll
@@ -478,9 +552,50 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
         }
       }
       const bool next = ce == CB && jb + CB < nb && k + s < N;
-      const int m = xb(fl, next, jb + CB, jb + CB, CB, next ? jb + CB : -1);
+      // entry of column c of a block: c is the same in every lane
+      auto pick = [&](const double (&v)[CB], int c) __attribute__((always_inline)) {
+        double o = v[0];
+        static_for<CB - 1>([&](auto qc) __attribute__((always_inline)) {
+          constexpr int q = decltype(qc)::value + 1;
+          o = (c == q) ? v[q] : o;
+        });
+        return o;
+      };
+      double bv = -1.0, bx = 0.0;
+      int bi = INT_MAX, bt = tid;
+      if (fl < ce) {
+        // this workgroup's candidate for its first failing column
+        bx = pick(xr, fl);
+        if (pos > k0 + jb + fl) {
+          bv = fabs(bx);
+          bi = pos;
+        }
+        wg_amax(bv, bi, bt);
+      }
+      const int m = xb(fl, next, jb + CB, jb + CB, CB, next ? jb + CB : -1, ce, bv, bi, bt, bx);
       if (m < 0) return;
       const int a = m - r0;
+      if (m < ce) {
+        if (P > 1) {
+          bv = -1.0;
+          bi = INT_MAX;
+          bt = 0;
+          if (lane < P && s_hi[lane] == m) wave::amax3(bv, bi, bt, s_hv[lane], s_hq[lane], lane);
+          if (lane + 64 < P && s_hi[lane + 64] == m)
+            wave::amax3(bv, bi, bt, s_hv[lane + 64], s_hq[lane + 64], lane + 64);
+          wave::amax(bv, bi, bt);
+        }
+        // (the full step's own search for a NaN or a column without entries)
+        have = bv > 0.0 && bv < INFINITY;
+        f_max = bv;
+        f_imax = bi;
+        f_g = bt;
+        f_phys = (P > 1) ? s_hp[bt] : gbase + bt;
+        f_x = pick(xr, m);
+        if (P == 1 && tid == bt) s_hx[0] = f_x;
+        const double xw = pick(wc, m);
+        if (wid == 0 && lane < CB) s_xq[lane] = xw;
+      }
       loaded = next && m == CB;
       if (wid == 0) {
         double d = 0.0;
@@ -511,15 +626,17 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
     }
     // ---- full pivot step ---------------------------------------------------------
     if (j >= nb - 1) break;  // no room for a 2x2
+    const bool cand = have;  // the failing block's candidate
+    have = false;
     --slow;
     ++nsteps;
-    double x = (pos >= k) ? (double)sym_at(X, rho, s_map[j], ld) : 0.0;
+    double x = (!cand && pos >= k) ? (double)sym_at(X, rho, s_map[j], ld) : 0.0;
     // The window rows' entries of the pivot columns are computed by every
     // workgroup: 16 lanes a row, from its L row (wq: this thread's row)
     const int wq = tid >> 4, wl = tid & 15, jb = j & ~(CB - 1);
     const bool won = k0 + jb + wq < N && jb + wq >= j;
     const int wphys = won ? s_map[jb + wq] : 0;
-    double xq = (won && wl == 0) ? (double)sym_at(X, wphys, s_map[j], ld) : 0.0, yq = 0.0;
+    double xq = (!cand && won && wl == 0) ? (double)sym_at(X, wphys, s_map[j], ld) : 0.0, yq = 0.0;
     auto window_entry = [&](double v, const double *wr) {
       double lw[4];
 #pragma unroll
@@ -529,89 +646,98 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
       }
       return wave::row_sum(v - ((lw[0] + lw[1]) + (lw[2] + lw[3])));
     };
-    if (wid == 0) s_wk[lane] = (lane < j) ? wrow(s_lw + (j & (CB - 1)) * CWL, lane) : 0.0;
-    __syncthreads();
-#pragma unroll 8
-    for (int t = 0; t < j; ++t) x = fma(-s_L[t * CLD + tid], s_wk[t], x);
-    xq = window_entry(xq, s_wk);
-    double bv = -1.0;
-    int bi = INT_MAX, bs = tid;
-    if (pos > k) {
-      bv = fabs(x);
-      bi = pos;
-    }
-    wave::amax(bv, bi, bs);
-    if (lane == 0) {
-      s_cv[wid] = bv;
-      s_ci[wid] = bi;
-      s_cs[wid] = bs;
-    }
-    if (pos == k) s_akk = x;
-    __syncthreads();
-    bv = s_cv[0];
-    bi = s_ci[0];
-    bs = s_cs[0];
-#pragma unroll
-    for (int w = 1; w < NWV; ++w) wave::amax3(bv, bi, bs, s_cv[w], s_ci[w], s_cs[w]);
-    double colmax = bv, akk, wki = 0.0;
-    int imax = bi, iphys = gbase + bs, gw = 0;
-    if (P == 1) {
-      if (tid == bs) s_hx[0] = x;
-      if (tid < j) s_irow[tid] = s_L[tid * CLD + bs];
-      __syncthreads();
-      akk = s_akk;
-      wki = s_hx[0];
+    double colmax, akk, wki = 0.0;
+    int imax, iphys, gw = 0;
+    if (cand) {
+      x = f_x;
+      xq = s_xq[wq];
+      akk = s_dn[j & (CB - 1)];
+      colmax = f_max;
+      imax = f_imax;
+      iphys = f_phys;
+      if (P == 1) {
+        if (tid < j) s_irow[tid] = s_L[tid * CLD + iphys - gbase];
+        wki = s_hx[0];
+        __syncthreads();
+      } else {
+        gw = f_g;
+        wki = s_hx[gw];
+      }
     } else {
-      // ---- X1 -------------------------------------------------------------------
-      const int par = c & 1;
-      const uint32_t tag = tagb + (uint32_t)c;
-      ++c;
-      uint64_t *mine = slot(par, g);
-      if (tid == bs) {
-        put_u32(mine, (uint32_t)bi, tag);
-        put_f64(mine + 1, bv, tag);
-        put_u32(mine + 3, (uint32_t)rho, tag);
-        put_f64(mine + 4, x, tag);
-      }
-      if (pos == k) put_f64(mine + 6, x, tag);
-      if (tid < j) put_f64(mine + 8 + 2 * tid, s_L[tid * CLD + bs], tag);
-      const int ok_wg = owner(s_map[j]);
-      const bool hon = tid < P, aon = tid == 128;
-      const uint64_t *hp = slot(par, hon ? tid : g), *ap = slot(par, ok_wg) + 6;
-      uint64_t h[6], ah, al;
-      const uint64_t t0 = wall_clock64();
-      for (;;) {
-#pragma unroll
-        for (int u = 0; u < 6; ++u) h[u] = get_w(hp + u);
-        ah = get_w(ap);
-        al = get_w(ap + 1);
-        bool ok = true;
-#pragma unroll
-        for (int u = 0; u < 6; ++u) ok = ok & ((!hon) | tag_ok(h[u], tag));
-        ok = ok & ((!aon) | (tag_ok(ah, tag) & tag_ok(al, tag)));
-        if (__ballot(!ok) == 0) break;
-        if (wall_clock64() - t0 > kCoopWaitTicks) {
-          expire();
-          break;
-        }
-      }
-      if (hon) {
-        s_hi[tid] = (int)(uint32_t)h[0];
-        s_hv[tid] = as_f64(h[1], h[2]);
-        s_hp[tid] = (int)(uint32_t)h[3];
-        s_hx[tid] = as_f64(h[4], h[5]);
-      }
-      if (aon) s_akk = as_f64(ah, al);
+      if (wid == 0) s_wk[lane] = (lane < j) ? wrow(s_lw + (j & (CB - 1)) * CWL, lane) : 0.0;
       __syncthreads();
-      if (s_abort) return;
-      colmax = -1.0;
-      imax = INT_MAX;
-      if (lane < P) wave::amax3(colmax, imax, gw, s_hv[lane], s_hi[lane], lane);
-      if (lane + 64 < P) wave::amax3(colmax, imax, gw, s_hv[lane + 64], s_hi[lane + 64], lane + 64);
-      wave::amax(colmax, imax, gw);
-      akk = s_akk;
-      wki = s_hx[gw];
-      iphys = s_hp[gw];
+#pragma unroll 8
+      for (int t = 0; t < j; ++t) x = fma(-s_L[t * CLD + tid], s_wk[t], x);
+      xq = window_entry(xq, s_wk);
+      double bv = -1.0;
+      int bi = INT_MAX, bs = tid;
+      if (pos > k) {
+        bv = fabs(x);
+        bi = pos;
+      }
+      if (pos == k) s_akk = x;
+      wg_amax(bv, bi, bs);
+      colmax = bv;
+      imax = bi;
+      iphys = gbase + bs;
+      if (P == 1) {
+        if (tid == bs) s_hx[0] = x;
+        if (tid < j) s_irow[tid] = s_L[tid * CLD + bs];
+        __syncthreads();
+        akk = s_akk;
+        wki = s_hx[0];
+      } else {
+        // ---- X1 -------------------------------------------------------------------
+        const int par = c & 1;
+        const uint32_t tag = tagb + (uint32_t)c;
+        ++c;
+        uint64_t *mine = slot(par, g);
+        if (tid == bs) {
+          put_u32(mine, (uint32_t)bi, tag);
+          put_f64(mine + 1, bv, tag);
+          put_u32(mine + 3, (uint32_t)rho, tag);
+          put_f64(mine + 4, x, tag);
+        }
+        if (pos == k) put_f64(mine + 6, x, tag);
+        if (tid < j) put_f64(mine + 8 + 2 * tid, s_L[tid * CLD + bs], tag);
+        const int ok_wg = owner(s_map[j]);
+        const bool hon = tid < P, aon = tid == 128;
+        const uint64_t *hp = slot(par, hon ? tid : g), *ap = slot(par, ok_wg) + 6;
+        uint64_t h[6], ah, al;
+        const uint64_t t0 = wall_clock64();
+        for (;;) {
+#pragma unroll
+          for (int u = 0; u < 6; ++u) h[u] = get_w(hp + u);
+          ah = get_w(ap);
+          al = get_w(ap + 1);
+          bool ok = true;
+#pragma unroll
+          for (int u = 0; u < 6; ++u) ok = ok & ((!hon) | tag_ok(h[u], tag));
+          ok = ok & ((!aon) | (tag_ok(ah, tag) & tag_ok(al, tag)));
+          if (__ballot(!ok) == 0) break;
+          if (wall_clock64() - t0 > kCoopWaitTicks) {
+            expire();
+            break;
+          }
+        }
+        if (hon) {
+          s_hi[tid] = (int)(uint32_t)h[0];
+          s_hv[tid] = as_f64(h[1], h[2]);
+          s_hp[tid] = (int)(uint32_t)h[3];
+          s_hx[tid] = as_f64(h[4], h[5]);
+        }
+        if (aon) s_akk = as_f64(ah, al);
+        __syncthreads();
+        if (s_abort) return;
+        colmax = -1.0;
+        imax = INT_MAX;
+        if (lane < P) wave::amax3(colmax, imax, gw, s_hv[lane], s_hi[lane], lane);
+        if (lane + 64 < P) wave::amax3(colmax, imax, gw, s_hv[lane + 64], s_hi[lane + 64], lane + 64);
+        wave::amax(colmax, imax, gw);
+        akk = s_akk;
+        wki = s_hx[gw];
+        iphys = s_hp[gw];
+      }
     }
     if (colmax < 0.0) {
       colmax = 0.0;
@@ -829,7 +955,7 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
       if ((j & ~(CB - 1)) != jb) {
         // the next window's rows, and the next block's entries
         const bool spec = slow == 0;
-        const int m = xb(CB, true, j & ~(CB - 1), j, 0, spec ? j : -1);
+        const int m = xb(CB, true, j & ~(CB - 1), j, 0, spec ? j : -1, CB, 0.0, 0, 0, 0.0);
         if (m < 0) return;
         loaded = spec;
       } else {
