@@ -3,7 +3,7 @@
 // problems from an atomic queue (largest first) and runs the whole Newton
 // system for each inside the workgroup:
 //   condense (same IEEE sequence as condense.hip, so M is bit-identical),
-//   blocked Bunch-Kaufman (FP64: speculative panels of 4 nb <= 64 columns,
+//   blocked Bunch-Kaufman (FP64: speculative panels of 4 nb or 8 nb columns,
 //   per-wave 64 x 64 trailing tiles on FP64 MFMA; mixed precision:
 //   panel::panel_reg_dev of nb columns; ping-pong buffers), inertia
 //   correction (Algorithm IC),
@@ -199,20 +199,22 @@ __device__ inline unsigned long long ubase(const void *p) {
   return ((unsigned long long)hi << 32) | lo;
 }
 
-// ---- FP64: speculative panel of up to 64 columns, multipliers in memory ----------
+// ---- FP64: speculative panel of up to 128 columns, multipliers in memory ---------
 // The workgroup's panel as in the cooperative panel (bk_coop.hip): 16-column
 // blocks factored as if every pivot passed the first Bunch-Kaufman test, each
 // row checking its own entries; the columns before the first failure stand
 // and the failing pivot is taken by a full step.  One workgroup holds all
 // rows, so nothing is exchanged, and at up to 2048 rows neither registers nor
-// LDS hold 64 columns: L and W = L D live in memory (L in Y, column t at
+// LDS hold them: L and W = L D live in memory (L in Y, column t at
 // (k0 + t) N, W at t N), in logical row order (an interchange swaps their
 // rows), and every block reads the ones before it once, as MFMA operands.
 // X keeps its physical order, s.map takes a logical position (less k0) to it.
 // Wave 0 factors the 16 x 16 diagonal block while the others bring their
 // first 64 rows up to date.
 constexpr int SB = 16;        // columns of a block
-constexpr int SNB = 64;       // most columns of a panel
+constexpr int SNB = 128;      // most columns of a panel
+constexpr int SDB = 64;       // columns of the solve's diagonal blocks
+constexpr int SWIDE = 1024;   // order from which panels take 8 nb columns
 constexpr int SWL = SNB + 2;  // stride of a window row
 struct PanelLds {
   double lw[SB * SWL], ww[SB * SWL];  // L and W rows of the block's positions
@@ -629,10 +631,10 @@ __device__ __attribute__((noinline)) int panel_spec_wg(int N, int k0, int nbw, d
         }
       }
     }
-    if (sw && lane < j && wv < 2) {
+    if (const int t = lane + 64 * (wv >> 1); sw && wv < 4 && t < j) {
       // the interchanged rows of the earlier columns
-      const unsigned cl = (unsigned)((wv == 0) ? (k0 + lane) * N : lane * N);
-      gdouble_out *o = (wv == 0) ? oY : oW;
+      const unsigned cl = (unsigned)(((wv & 1) == 0) ? (k0 + t) * N : t * N);
+      gdouble_out *o = ((wv & 1) == 0) ? oY : oW;
       const double a = o[cl + (unsigned)p], b = o[cl + (unsigned)q];
       o[cl + (unsigned)p] = b;
       o[cl + (unsigned)q] = a;
@@ -687,10 +689,11 @@ __device__ __attribute__((noinline)) int panel_spec_wg(int N, int k0, int nbw, d
 
 // FP64 trailing update, lower triangle: every wave takes 64 x 64 tiles on its
 // own (4 x 4 MFMA blocks), Y(i, c) = X(map i, map c) - sum_t W[c, t] L[i, t].
-// The operands come straight from memory, each used four times: per tile as
-// many operand bytes as X and Y bytes at 64 columns, against three times as
-// many for 32 x 32 tiles at 16 columns, whose launches moved 509 GB per 512
-// problems.  Rows past N are read clamped and not stored.
+// The operands come straight from memory, two steps of four columns ahead, each
+// used four times: per tile as many operand bytes as X and Y bytes at 64 columns.
+// Bound by moving X and Y: 512 problems up to N = 2048 took 38.2 ms with 64-column
+// panels, 30.2 with 128, 28.9 with the operands two steps ahead instead of one.
+// Rows past N are read clamped and not stored.
 __device__ __attribute__((noinline)) void trailing_wg(int N, int k0, int kend, const double *W,
                                                       const double *X, double *Y) {
   const PanelLds &s = panel_lds();
@@ -725,31 +728,31 @@ __device__ __attribute__((noinline)) void trailing_wg(int N, int k0, int kend, c
       wi[a] = (unsigned)min(c0 + 16 * a + l16, N - 1);
       li[a] = (unsigned)min(i0 + 16 * a + l16, N - 1);
     }
-    double av[4], bv[4];
-    auto operands = [&](int t0, double (&oa)[4], double (&ob)[4]) {
+    // operands TD steps of four columns ahead
+    constexpr int TD = 2;
+    double av[TD][4], bv[TD][4];
+    auto operands = [&](int u, int t0) {
       const int t = min(t0 + l4, jw - 1);
       const unsigned wo = (unsigned)(t * N), lo = (unsigned)((k0 + t) * N);
 #pragma unroll
-      for (int a = 0; a < 4; ++a) oa[a] = gW[wi[a] + wo];
+      for (int a = 0; a < 4; ++a) av[u][a] = gW[wi[a] + wo];
 #pragma unroll
-      for (int b = 0; b < 4; ++b) ob[b] = gL[li[b] + lo];
+      for (int b = 0; b < 4; ++b) bv[u][b] = gL[li[b] + lo];
     };
-    operands(0, av, bv);
-    for (int t0 = 0; t0 < jw; t0 += 4) {
-      double an[4], bn[4];
-      operands(t0 + 4, an, bn);  // clamped to the panel: the last one is not used
-      const bool on = t0 + l4 < jw;
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        const double w = on ? -av[a] : 0.0;
+    for (int u = 0; u < TD; ++u) operands(u, 4 * u);
+    for (int t0 = 0; t0 < jw; t0 += 4 * TD) {
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(w, on ? bv[b] : 0.0, acc[a][b], 0, 0, 0);
-      }
+      for (int u = 0; u < TD; ++u) {
+        const bool on = t0 + 4 * u + l4 < jw;
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        av[a] = an[a];
-        bv[a] = bn[a];
+        for (int a = 0; a < 4; ++a) {
+          const double w = on ? -av[u][a] : 0.0;
+#pragma unroll
+          for (int b = 0; b < 4; ++b)
+            acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(w, on ? bv[u][b] : 0.0, acc[a][b], 0, 0, 0);
+        }
+        operands(u, t0 + 4 * (u + TD));  // clamped to the panel: the last ones are not used
       }
     }
 #pragma unroll
@@ -937,7 +940,12 @@ __device__ void factor_wg(int N, int nb, double alpha, const SlotDev &S) {
     S.pk0[0] = 0;
   }
   __syncthreads();
-  const int nbw = min(4 * nb, SNB);
+  // A wider panel costs its blocks more of the columns before them and saves a
+  // pass of the trailing update over memory (16 bytes an entry, which bounds it
+  // at 64 columns): 512 problems up to N = 2048 take 34.9 ms at 64 columns and
+  // 30.0 at 128 from N = 1024, 512 or 0 on; 256 whole IPMs up to N = 320 take 28.0
+  // ms at 64 and 30.6 at 128.
+  const int nbw = min((N >= SWIDE ? 8 : 4) * nb, SNB);
   int k0 = 0;
   for (int b = 0; k0 < N; ++b) {
     const double *X = S.buf[b & 1];
@@ -956,7 +964,9 @@ __device__ void factor_wg(int N, int nb, double alpha, const SlotDev &S) {
 // one, p = -1 for its second row) and the panel's diagonal block of L into
 // s_db (w x w, one load per entry, all in flight at once); the sequential
 // steps then touch only LDS and broadcast a lane's value with readlane.
-constexpr int BDB = SNB + 1;  // row stride of the diagonal block (panels of at most SNB columns)
+// A panel of more than SDB columns is solved in SDB-column parts: its
+// transpositions come first, all of them.
+constexpr int BDB = SDB + 1;  // row stride of the diagonal block
 
 __device__ inline void panel_records(const SlotDev &S, int k0, int w, int *s_pq) {
   const int tid = threadIdx.x;
@@ -968,26 +978,29 @@ __device__ inline void panel_records(const SlotDev &S, int k0, int w, int *s_pq)
 }
 
 __device__ inline void diag_block(const double *Lb, size_t ld, int k0, int w, double *s_db) {
-  for (int e = threadIdx.x; e < w * SNB; e += BT) {
-    const int r = e % SNB, c = e / SNB;
+  for (int e = threadIdx.x; e < w * SDB; e += BT) {
+    const int r = e % SDB, c = e / SDB;
     if (r < w && r > c) s_db[r * BDB + c] = Lb[(size_t)(k0 + r) + (size_t)(k0 + c) * ld];
   }
 }
 
-// The panel's transpositions on z (one wave; lane e holds entry e of s_pq): only
-// those that move a row, in pivot order or reversed.
+// The panel's transpositions on z (one wave; lane e holds entries e and e + 64 of
+// s_pq): only those that move a row, in pivot order or reversed.
 __device__ inline void swap_rows(double *z, const int *s_pq, int w, bool reverse) {
   const int lane = threadIdx.x & 63;
-  const int p = (lane < w) ? s_pq[2 * lane] : -1, q = (lane < w) ? s_pq[2 * lane + 1] : 0;
-  unsigned long long mv = __ballot(p >= 0 && p != q);
-  while (mv) {
-    const int e = reverse ? 63 - __clzll((long long)mv) : __ffsll((unsigned long long)mv) - 1;
-    mv &= ~(1ull << e);
-    const int pe = wave::lane_read(p, e), qe = wave::lane_read(q, e);
-    if (lane == 0) {
-      const double t = z[pe];
-      z[pe] = z[qe];
-      z[qe] = t;
+  for (int h = 0; h < SNB; h += 64) {
+    const int e0 = (reverse ? SNB - 64 - h : h) + lane;
+    const int p = (e0 < w) ? s_pq[2 * e0] : -1, q = (e0 < w) ? s_pq[2 * e0 + 1] : 0;
+    unsigned long long mv = __ballot(p >= 0 && p != q);
+    while (mv) {
+      const int e = reverse ? 63 - __clzll((long long)mv) : __ffsll((unsigned long long)mv) - 1;
+      mv &= ~(1ull << e);
+      const int pe = wave::lane_read(p, e), qe = wave::lane_read(q, e);
+      if (lane == 0) {
+        const double t = z[pe];
+        z[pe] = z[qe];
+        z[qe] = t;
+      }
     }
   }
 }
@@ -1003,41 +1016,45 @@ __device__ __attribute__((noinline)) void solve_wg(int N, const SlotDev &S, doub
   const int np = S.st->npanel;
   // forward: P_b, then L_b
   for (int b = 0; b < np; ++b) {
-    const int k0 = S.pk0[b], k1 = S.pk0[b + 1];
-    const int w = k1 - k0;
+    const int kb = S.pk0[b], ke = S.pk0[b + 1];
     const double *Lb = mixed ? S.buf[0] : S.buf[(b + 1) & 1];
     gdouble *gL = (gdouble *)ubase(Lb);
-    panel_records(S, k0, w, s_pq);
-    diag_block(Lb, (size_t)N, k0, w, s_db);
-    __syncthreads();
-    if (wv == 0) {
-      double dr[SNB];
+    panel_records(S, kb, ke - kb, s_pq);
+    for (int k0 = kb; k0 < ke; k0 += SDB) {
+      const int k1 = min(k0 + SDB, ke), w = k1 - k0;
+      diag_block(Lb, (size_t)N, k0, w, s_db);
+      __syncthreads();
+      if (wv == 0) {
+        double dr[SDB];
 #pragma unroll
-      for (int c = 0; c < SNB; ++c) dr[c] = (lane > c && lane < w) ? s_db[lane * BDB + c] : 0.0;
-      swap_rows(z, s_pq, w, false);
-      __asm__ __volatile__("s_waitcnt lgkmcnt(0)" ::: "memory");
-      double v = (lane < w) ? z[k0 + lane] : 0.0, o = v;
-      // row c + 1 is final after step c (later steps multiply by zero there)
+        for (int c = 0; c < SDB; ++c) dr[c] = (lane > c && lane < w) ? s_db[lane * BDB + c] : 0.0;
+        if (k0 == kb) {
+          swap_rows(z, s_pq, ke - kb, false);
+          __asm__ __volatile__("s_waitcnt lgkmcnt(0)" ::: "memory");
+        }
+        double v = (lane < w) ? z[k0 + lane] : 0.0, o = v;
+        // row c + 1 is final after step c (later steps multiply by zero there)
 #pragma unroll
-      for (int c = 0; c < SNB - 1; ++c) {
-        v = fma(-dr[c], wave::lane_read(v, c), v);
-        o = (lane == c + 1) ? v : o;
+        for (int c = 0; c < SDB - 1; ++c) {
+          v = fma(-dr[c], wave::lane_read(v, c), v);
+          o = (lane == c + 1) ? v : o;
+        }
+        if (lane < w) z[k0 + lane] = o;
       }
-      if (lane < w) z[k0 + lane] = o;
-    }
-    __syncthreads();
-    for (int x = k1 + tid; x < N; x += BT) {
-      double v = z[x];
-      for (int c0 = k0; c0 < k1; c0 += 32) {
-        double l[32];
+      __syncthreads();
+      for (int x = k1 + tid; x < N; x += BT) {
+        double v = z[x];
+        for (int c0 = k0; c0 < k1; c0 += 32) {
+          double l[32];
 #pragma unroll
-        for (int u = 0; u < 32; ++u) l[u] = gL[(unsigned)(x + min(c0 + u, k1 - 1) * N)];
+          for (int u = 0; u < 32; ++u) l[u] = gL[(unsigned)(x + min(c0 + u, k1 - 1) * N)];
 #pragma unroll
-        for (int u = 0; u < 32; ++u) v = fma(-l[u], (c0 + u < k1) ? z[c0 + u] : 0.0, v);
+          for (int u = 0; u < 32; ++u) v = fma(-l[u], (c0 + u < k1) ? z[c0 + u] : 0.0, v);
+        }
+        z[x] = v;
       }
-      z[x] = v;
+      __syncthreads();
     }
-    __syncthreads();
   }
   // D
   for (int k = tid; k < N; k += BT) {
@@ -1055,51 +1072,56 @@ __device__ __attribute__((noinline)) void solve_wg(int N, const SlotDev &S, doub
   __syncthreads();
   // backward: L_b', then P_b'
   for (int b = np - 1; b >= 0; --b) {
-    const int k0 = S.pk0[b], k1 = S.pk0[b + 1], w = k1 - k0;
+    const int kb = S.pk0[b], ke = S.pk0[b + 1];
     const double *Lb = mixed ? S.buf[0] : S.buf[(b + 1) & 1];
     gdouble *gL = (gdouble *)ubase(Lb);
-    panel_records(S, k0, w, s_pq);
-    diag_block(Lb, (size_t)N, k0, w, s_db);
-    for (int cb = 0; cb < w; cb += 32) {
-      double acc[32];
+    panel_records(S, kb, ke - kb, s_pq);
+    for (int k0 = kb + (ke - kb - 1) / SDB * SDB; k0 >= kb; k0 -= SDB) {
+      const int k1 = min(k0 + SDB, ke), w = k1 - k0;
+      diag_block(Lb, (size_t)N, k0, w, s_db);
+      for (int cb = 0; cb < w; cb += 32) {
+        double acc[32];
 #pragma unroll
-      for (int c = 0; c < 32; ++c) acc[c] = 0.0;
-      for (int x = k1 + tid; x < N; x += BT) {
-        const double zx = z[x];
-        double l[32];
+        for (int c = 0; c < 32; ++c) acc[c] = 0.0;
+        for (int x = k1 + tid; x < N; x += BT) {
+          const double zx = z[x];
+          double l[32];
 #pragma unroll
-        for (int c = 0; c < 32; ++c) l[c] = gL[(unsigned)(x + (k0 + min(cb + c, w - 1)) * N)];
+          for (int c = 0; c < 32; ++c) l[c] = gL[(unsigned)(x + (k0 + min(cb + c, w - 1)) * N)];
 #pragma unroll
-        for (int c = 0; c < 32; ++c) acc[c] = fma(l[c], zx, acc[c]);
+          for (int c = 0; c < 32; ++c) acc[c] = fma(l[c], zx, acc[c]);
+        }
+#pragma unroll
+        for (int c = 0; c < 32; ++c) {
+          const double v = wave::sum(acc[c]);
+          if (lane == 0) s_part[wv * SDB + cb + c] = v;
+        }
       }
+      __syncthreads();
+      if (wv == 0) {
+        double dr[SDB];
 #pragma unroll
-      for (int c = 0; c < 32; ++c) {
-        const double v = wave::sum(acc[c]);
-        if (lane == 0) s_part[wv * SNB + cb + c] = v;
+        for (int c = 0; c < SDB; ++c) dr[c] = (c > lane && c < w) ? s_db[c * BDB + lane] : 0.0;
+        double v = 0.0;
+        if (lane < w) {
+          double s = 0.0;
+          for (int q = 0; q < NWAVE; ++q) s += s_part[q * SDB + lane];
+          v = z[k0 + lane] - s;
+        }
+        double o = v;
+#pragma unroll
+        for (int c = SDB - 1; c > 0; --c) {
+          v = fma(-dr[c], wave::lane_read(v, c), v);
+          o = (lane == c - 1) ? v : o;
+        }
+        if (lane < w) z[k0 + lane] = o;
+        if (k0 == kb) {
+          __asm__ __volatile__("s_waitcnt lgkmcnt(0)" ::: "memory");
+          swap_rows(z, s_pq, ke - kb, true);
+        }
       }
+      __syncthreads();
     }
-    __syncthreads();
-    if (wv == 0) {
-      double dr[SNB];
-#pragma unroll
-      for (int c = 0; c < SNB; ++c) dr[c] = (c > lane && c < w) ? s_db[c * BDB + lane] : 0.0;
-      double v = 0.0;
-      if (lane < w) {
-        double s = 0.0;
-        for (int q = 0; q < NWAVE; ++q) s += s_part[q * SNB + lane];
-        v = z[k0 + lane] - s;
-      }
-      double o = v;
-#pragma unroll
-      for (int c = SNB - 1; c > 0; --c) {
-        v = fma(-dr[c], wave::lane_read(v, c), v);
-        o = (lane == c - 1) ? v : o;
-      }
-      if (lane < w) z[k0 + lane] = o;
-      __asm__ __volatile__("s_waitcnt lgkmcnt(0)" ::: "memory");
-      swap_rows(z, s_pq, w, true);
-    }
-    __syncthreads();
   }
 }
 
@@ -1246,10 +1268,10 @@ __global__ __launch_bounds__(BT) void k_batch(int count, const int32_t *__restri
                                               ResultDev *results, int refine_max) {
   constexpr bool mixed = MIXED;
   const double dc_sing = *dc_sing_p;
-  __shared__ double s_db[SNB * BDB];
+  __shared__ double s_db[SDB * BDB];
   __shared__ int s_pq[2 * SNB];
   __shared__ double s_z[BMAX_N];
-  __shared__ double s_part[NWAVE * SNB];
+  __shared__ double s_part[NWAVE * SDB];
   __shared__ int s_p;
   const int tid = threadIdx.x;
   const SlotDev S = slots[blockIdx.x];
@@ -1635,10 +1657,10 @@ __global__ __launch_bounds__(BT) void k_batch_ipm(int count, const int32_t *__re
                                                   double alpha, IpmParams prm, int32_t *queue,
                                                   unsigned long long *t0, IpmResDev *results,
                                                   IpmIterDev *trace) {
-  __shared__ double s_db[SNB * BDB];
+  __shared__ double s_db[SDB * BDB];
   __shared__ int s_pq[2 * SNB];
   __shared__ double s_z[BMAX_N];
-  __shared__ double s_part[NWAVE * SNB];
+  __shared__ double s_part[NWAVE * SDB];
   __shared__ int s_p;
   const int tid = threadIdx.x;
   const SlotDev S = slots[blockIdx.x];
@@ -1997,7 +2019,7 @@ bool batch_layout(const mds_batch_problem *ps, int count, const mds_batch_opts *
   const int want = (o && o->grid > 0) ? o->grid : 256;
   L.nslots = std::max(1, std::min(count, want));
   const size_t N = (size_t)L.Nmax;
-  L.slot_bytes = 2 * al256(8 * N * N) + al256(8 * N * (kMaxNb + 2)) + al256(8 * 64) +
+  L.slot_bytes = 2 * al256(8 * N * N) + al256(8 * N * (SNB + 2)) + al256(8 * 64) +
                  2 * al256(8 * N) +
                  al256(8 * (size_t)std::max(L.nsmax, 1)) + 3 * al256(4 * N) + al256(4 * (N + 4)) +
                  al256(sizeof(FacState)) + al256(8 * N) + al256(8 * (N + (size_t)L.nsmax));
@@ -2218,7 +2240,7 @@ int mds_batch_create(mds_batch **out, const mds_batch_problem *probs_host, int32
     S.buf[1] = (double *)c;
     c += al256(8 * N * N);
     S.W = (double *)c;
-    c += al256(8 * N * (kMaxNb + 2));
+    c += al256(8 * N * (SNB + 2));
     S.zero = (double *)c;  // after both matrix buffers and W: every offset to it is positive
     c += al256(8 * 64);
     S.dd = (double *)c;

@@ -1,4 +1,4 @@
-"""FP64 scenario batch over speculative panels (4 nb <= 64 columns): sizes at
+"""FP64 scenario batch over speculative panels (4 nb columns, 8 nb from N = 1024 on): sizes at
 the edges of a block, a 64-row group, a panel and a thread's row count, panel
 widths that are no multiple of a block, and barrier states whose first test
 fails often.  Bars: the oracle's inertia, trials and shift, and its solution
