@@ -356,6 +356,23 @@ void launch_reg_panel(mds_handle *h, hipStream_t s, int b, const TX *X, double *
 
 void factor_launches_la(mds_handle *h, hipStream_t s);
 
+// Standard form of the current factor, in place in M.
+void std_launches(mds_handle *h, hipStream_t s, bool pingpong) {
+  TimedLaunch t(h, MDS_T_PERMUTE, s);
+  const int np2 = (h->la_cus > 0) ? 0 : h->pair_slots;
+  launch_std_form(s, h->N, h->w.M, h->w.M2, pingpong ? 1 : 0, np2, h->w.ipiv, h->w.blk,
+                  h->w.panel_k0, h->w.fst, h->w.hmap, h->w.perm, h->w.colpanel, h->w.M);
+}
+
+// Small factors are brought to standard form by the factorization's own
+// launches: 8 us more when no solve follows (a failed inertia trial), two
+// launches less when one does (N = 771: 1166 -> 1130 us a Newton pass, IPM at N =
+// 515: 19.1 -> 17.9 ms).
+constexpr int kStdWithFactor = 1024;
+bool std_with_factor(const mds_handle *h) {
+  return !h->panel_lds && h->la_cus == 0 && h->N <= kStdWithFactor;
+}
+
 // Blocked Bunch-Kaufman of the current M; reads back the inertia.
 // The launches of one factorization, on stream s.  Their number depends only
 // on N and the panel's least width, so the sequence is fixed per handle.
@@ -450,6 +467,7 @@ void factor_launches(mds_handle *h, hipStream_t s) {
     }
   }
   launch_fac_publish(s, h->w.fst, pin_fac(h));
+  if (std_with_factor(h)) std_launches(h, s, h->panel_reg && fp64);
 }
 
 // Look-ahead form of the cooperative factorization.  Stream A (the
@@ -688,18 +706,15 @@ int factor_impl(mds_handle *h, mds_inertia *out) {
   out->info = st.info;
   h->have_factor = true;
   h->have_M = false;
-  h->std_ready = h->panel_lds;  // that kernel writes the standard form itself
+  // (that kernel writes the standard form itself)
+  h->std_ready = h->panel_lds || (!mem && std_with_factor(h));
   return MDS_OK;
 }
 
 // Standard form of the current factor, in place in M (once per factorization).
 void ensure_std(mds_handle *h) {
   if (h->std_ready) return;
-  TimedLaunch t(h, MDS_T_PERMUTE);
-  const int pingpong = h->fac_pingpong ? 1 : 0;
-  const int np2 = (h->la_cus > 0) ? 0 : h->pair_slots;
-  launch_std_form(S(h), h->N, h->w.M, h->w.M2, pingpong, np2, h->w.ipiv, h->w.blk,
-                  h->w.panel_k0, h->w.fst, h->w.hmap, h->w.perm, h->w.colpanel, h->w.M);
+  std_launches(h, S(h), h->fac_pingpong);
   h->std_ready = true;
 }
 

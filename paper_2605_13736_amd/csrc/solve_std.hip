@@ -51,6 +51,9 @@ __global__ __launch_bounds__(SW) void k_std_sweep(int N, const int32_t *__restri
   __shared__ int s_p[kMaxNb + 2], s_q[kMaxNb + 2];
   static_assert(kMaxNb + 1 <= 128, "a panel's pivot entries fit two per lane of one wave");
   const int tid = threadIdx.x;
+  // a factorization that stopped early has no standard form (the launches follow
+  // it without the host's look at its state)
+  if (st->k != N) return;
   const int np = st->npanel;
   for (int x = tid; x < N; x += SW) s_h[x] = x;
   // panel b's bounds and pivot entries are loaded one panel ahead, so that
@@ -137,11 +140,13 @@ __global__ __launch_bounds__(SW) void k_std_sweep(int N, const int32_t *__restri
 // of Lstd; no other workgroup touches column c of either buffer.
 __global__ __launch_bounds__(AT) void k_std_apply(int N, const double *M0, const double *M1,
                                                    int pingpong, int np2,
+                                                   const FacState *__restrict__ st,
                                                    const int32_t *__restrict__ panel_k0,
                                                    const int32_t *__restrict__ colpanel,
                                                    const int32_t *__restrict__ hmap,
                                                    double *Lstd) {
   extern __shared__ double s_col[];
+  if (st->k != N) return;
   const int c = blockIdx.x, tid = threadIdx.x;
   const int b = colpanel[c];
   const int k1 = panel_k0[b + 1];
@@ -489,7 +494,7 @@ void launch_std_form(hipStream_t s, int N, const double *M0, const double *M1, i
   if (N <= 0) return;
   k_std_sweep<<<1, SW, sizeof(int32_t) * (size_t)N, s>>>(N, ipiv, blk, panel_k0, st, hmap, perm,
                                                          colpanel);
-  k_std_apply<<<(unsigned)N, AT, sizeof(double) * (size_t)N, s>>>(N, M0, M1, pingpong, np2, panel_k0,
+  k_std_apply<<<(unsigned)N, AT, sizeof(double) * (size_t)N, s>>>(N, M0, M1, pingpong, np2, st, panel_k0,
                                                                     colpanel, hmap, Lstd);
 }
 
