@@ -235,7 +235,10 @@ int panel_threads_of(const mds_options *o, int N) {
 // register / cooperative panel: N = 101 0.55 / 0.42 ms, 771 2.9 / 1.5, 2051
 // 8.6 (former cooperative panel and register tail) / 3.4.
 // Cooperative nb: 64 above N = 2048, where the trailing update's traffic
-// (inverse to the width) counts; 32 below, where it does not.
+// (inverse to the width) counts; 32 below.  There 64 saves half the launches
+// (N = 101: 222 -> 212 us a Newton pass) but costs the blocks that a failing
+// pivot starts again more columns (N = 771: no change; IPM at N = 192 and 515:
+// 6.14 -> 6.51 and 19.3 -> 19.8 ms).
 PanelChoice panel_of(const mds_dims &d, const mds_options *o) {
   const int N = d.n_d + d.m;
   const int popt = o ? o->panel : 0;

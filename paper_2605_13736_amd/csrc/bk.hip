@@ -521,14 +521,17 @@ __device__ __forceinline__ void trailing_tile(int N, int kend, int i0, int c0, b
   for (int ch = 0; ch < NC; ++ch) {
     double *s_w = s_buf + (ch & 1) * 2 * TC * TL, *s_l = s_w + TC * TL;
     const int jt = ((PAIR && ch < TNC) ? p0.j : p1.j) - (ch % TNC) * TC;
+    const bool on = PAIR || ch == 0 || jt > 0;  // (a pair's panels are of full width)
+    if (on) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const bool ton = 4 * u + stt < jt;
-      s_w[(4 * u + stt) * TL + sr] = ton ? vw[u] : 0.0;
-      s_l[(4 * u + stt) * TL + sr] = ton ? vl[u] : 0.0;
+      for (int u = 0; u < U; ++u) {
+        const bool ton = 4 * u + stt < jt;
+        s_w[(4 * u + stt) * TL + sr] = ton ? vw[u] : 0.0;
+        s_l[(4 * u + stt) * TL + sr] = ton ? vl[u] : 0.0;
+      }
+      __syncthreads();
+      if (ch + 1 < NC) stage_load(ch + 1);
     }
-    __syncthreads();
-    if (ch + 1 < NC) stage_load(ch + 1);
     // the tile's entries, a share behind the staging loads of the later half
     // of the chunks (2.5% faster than over all chunks, 11% than ahead of them)
     constexpr int H = NC / 2;
@@ -538,6 +541,7 @@ __device__ __forceinline__ void trailing_tile(int N, int kend, int i0, int c0, b
       const unsigned hi = max(si[b], sc[a][r]), lo = min(si[b], sc[a][r]);
       xv[a][b][r] = ldb(X, hi * 8u + __umul24(lo, st8));
     }
+    if (!on) continue;
 #pragma unroll
     for (int t0 = 0; t0 < TC; t0 += 4) {
       double av[2], bv[2];
