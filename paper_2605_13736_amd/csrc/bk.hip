@@ -458,10 +458,10 @@ __device__ inline double ldb(const double *p, unsigned off) {
 // behind a branch the wait for the staging loads becomes one for every load in
 // flight.
 // Four workgroups per compute unit of this shape beat, in pair updates at N =
-// 16384 (36.8 ms here): 128 x 128 tiles (39.6 ms; persistent with the next
-// tile's X in registers 46), 64 x 64 tiles a wave without LDS (44.6), and vector
-// FMAs on 256 x 16 tiles a wave with W broadcast from lanes (48.6) or in scalar
-// registers (55).
+// 16384 (36.8 ms in row-major order): 128 x 128 tiles (39.6 ms; persistent with
+// the next tile's X in registers 46), 64 x 64 tiles a wave without LDS (44.6),
+// and vector FMAs on 256 x 16 tiles a wave with W broadcast from lanes (48.6) or
+// in scalar registers (55).
 struct PanelCols {
   const double *W, *L;  // column t at t N
   int j;                // columns
@@ -611,8 +611,11 @@ __global__ __launch_bounds__(256, 4) void k_bk_trailing_coop(int N, const double
 // order, to which the second panel's map src leads; its L is in place (column t
 // at k0 + t), the second one's staged.  Workgroups past the tiles copy the
 // second panel's multipliers from their staging buffer into Y's columns.
-// N = 16384, pairs down to 4608 rows: 36.8 ms of updates a factorization against
-// 46.1 one by one (39 TFLOP/s), 60.7 against 67.9 ms a Newton pass.
+// The tiles go in super-tiles of one XCD each (tile_order.hpp): in row-major order
+// the second-level caches fetched W and L again for every tile (126 GB read for 45
+// GB of X at N = 16384).  N = 16384, pairs down to 4608 rows: 35.8 ms of updates a
+// factorization (36.8 row-major, 45.6 one by one), 59.0 against 66.8 ms a Newton
+// pass.
 constexpr int kPairCopy = 128;  // workgroups of the copy
 __global__ __launch_bounds__(256, 4) void k_bk_trailing_pair(
     int N, long tiles, const double *__restrict__ W, const double *X, double *Y, const double *Lst,
@@ -633,7 +636,7 @@ __global__ __launch_bounds__(256, 4) void k_bk_trailing_pair(
   const int a0 = kend & ~15;
   const int nt = (N - a0 + TT - 1) / TT;
   int ti, tj;
-  if (!tile_of(blockIdx.x, nt, false, ti, tj)) return;
+  if ((long)blockIdx.x >= tile_slots(nt, true) || !tile_of(blockIdx.x, nt, true, ti, tj)) return;
   const int i0 = a0 + ti * TT, c0 = a0 + tj * TT;
   const PanelCols p0{Wp, Y + (size_t)kp * N, k0 - kp}, p1{W, Lst, kend - k0};
   trailing_tile<true>(N, kend, i0, c0, ti != tj && c0 >= kend && i0 + TT <= N, X, Y, p0, p1, src,
@@ -851,7 +854,7 @@ void launch_bk_trailing_pair(hipStream_t s, int N, long rem, int slot, const dou
                              const double *Wp, const int32_t *srcp, const FacState *st,
                              const int32_t *panel_k0) {
   const long nt = rem > 0 ? (rem + 15 + TT - 1) / TT : 0;
-  const long tiles = nt * (nt + 1) / 2;
+  const long tiles = tile_slots((int)nt, true);
   k_bk_trailing_pair<<<(unsigned)(tiles + kPairCopy), 256, 0, s>>>(N, tiles, W, X, Y, Lst, src, Wp,
                                                                   srcp, st, panel_k0, slot);
 }

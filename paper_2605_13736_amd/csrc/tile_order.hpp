@@ -31,7 +31,7 @@ __device__ inline void tri_of(long x, int &ti, int &tj) {
 }
 
 // number of slots the walk visits for nt x nt tiles
-__device__ inline long tile_slots(int nt, bool xcd) {
+__host__ __device__ inline long tile_slots(int nt, bool xcd) {
   if (!xcd) return (long)nt * (nt + 1) / 2;
   const long ns = (nt + kSuperTile - 1) / kSuperTile;
   const long sup = ns * (ns + 1) / 2;
