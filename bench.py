@@ -43,14 +43,15 @@ FP32_MFMA_PEAK_TFS = 157.3
 # HBM bytes per launch from rocprofv3 FETCH_SIZE / WRITE_SIZE passes, scaled by
 # the counters of a 256 MiB copy (the profile file gives the commands and the
 # factors); valid for the kernel source and workload as profiled.
+# (one whole factorization's trailing updates).
 MEASURED_TRAFFIC = {
-    ("k_bk_trailing_la", 16384): (807272437.0, "profiles/bk_trailing_kkt_n16384.md"),
-    ("k_bk_trailing", 4096): (45959473.4, "profiles/bk_trailing_ipm_newton_step_n4096.md"),
-    ("k_bk_panel_coop", 4096): (4594730.0, "profiles/bk_panel_coop_ipm_newton_step_n4096.md"),
+    ("k_bk_trailing", 4096): (3.91e9, "profiles/newton_pass_kernels.md"),
 }
-KERNEL_OF_CLASS = {"panel_tail": "k_bk_panel_reg", "trailing": "k_bk_trailing",
+KERNEL_OF_CLASS = {"panel_tail": "k_bk_panel_reg", "trailing": "k_bk_trailing_coop",
                    "solve": "k_trsv_fwd+k_trsv_bwd", "condense": "k_condense_dense",
                    "permute": "k_std_sweep+k_std_apply"}
+PAIR_ROWS = 4608   # rows from which two panels share one trailing update
+STRIP_COLS = 128   # columns of the first panel's strip update in a pair
 
 
 def log(*a):
@@ -97,6 +98,29 @@ def slot_widths(N, nb=32, tail_rows=2048):
         ws.append(a)
         rows -= a
     return ws
+
+
+def trailing_plan(N, nb):
+    """Algorithmic bytes and flops of the trailing updates of one FP64
+    factorization by the cooperative panel, panels of nb columns: 16 B per lower
+    entry of the trailing matrix (read, write) and the panels' L and W; in a pair
+    of panels the first updates a strip only and one pass applies both."""
+    b = f = 0.0
+    k = 0
+    while k < N:
+        if nb == 64 and N - k >= PAIR_ROWS:
+            n1, n2 = N - k - nb, N - k - 2 * nb
+            b += STRIP_COLS * n1 * 16.0 + 16.0 * n1 * nb
+            f += 2.0 * nb * STRIP_COLS * n1
+            b += n2 * (n2 + 1) / 2 * 16.0 + 32.0 * n2 * nb
+            f += n2 * (n2 + 1) / 2 * 4.0 * nb
+            k += 2 * nb
+        else:
+            n = max(N - k - nb, 0)
+            b += n * (n + 1) / 2 * 16.0 + 16.0 * n * nb
+            f += n * (n + 1) / 2 * 2.0 * nb
+            k += nb
+    return b, f
 
 
 def trailing_bytes_plan(N, nb=32, elem=8.0):
@@ -235,8 +259,8 @@ def factor_ms_of(tim, efacs):
 
 
 def roofline_of(tim, efacs, N, nb, pstats=None, xfloor=None):
-    """The factorization, the step's dominant work (cooperative panel, its
-    register tail and the trailing updates), against FP64 MFMA; inside it the
+    """The factorization, the step's dominant work (cooperative panel and the
+    trailing updates), against FP64 MFMA; inside it the
     trailing update against HBM (its own roofline, with the counter traffic)
     and the panel's latency model (microseconds per pivot step against the
     measured exchange round trip)."""
@@ -244,28 +268,26 @@ def roofline_of(tim, efacs, N, nb, pstats=None, xfloor=None):
     factor_tfs = (N ** 3 / 3.0) / (fac_ms / 1e3) / 1e12
     trl = tim["trailing"]
     near = tim.get("near", {"ms": 0.0, "launches": 0})
-    la = near["launches"] > 0
+    efacs = max(efacs, 1)
+    # the updates of a whole factorization, strips of paired panels included
+    s_fac = (trl["ms"] + near["ms"]) / 1e3 / efacs
+    per_fac, flops = trailing_plan(N, nb)
+    meas = MEASURED_TRAFFIC.get(("k_bk_trailing", N))
     nl = max(trl["launches"], 1)
-    # with look-ahead one update is the near strip (reserved units) plus the
-    # rest (the other units, beside the next panel)
-    avg_s = (trl["ms"] + near["ms"]) / 1e3 / nl
-    # the slot plan's widths (cooperative panels, then the register tail)
-    per_launch, _ = trailing_bytes_plan(N, nb)
-    meas = MEASURED_TRAFFIC.get(("k_bk_trailing_la" if la else "k_bk_trailing", N))
-    trailing = dict(kernel="k_bk_trailing_ps" + (" (near strip + rest)" if la else ""),
-                    bound="hbm", achieved=per_launch / avg_s / 1e9,
-                    peak=HBM_PEAK_GBS, unit="GB/s", frac=per_launch / avg_s / 1e9 / HBM_PEAK_GBS,
-                    traffic=meas[0] if meas else None, bytes_per_launch=per_launch,
-                    flops_per_launch=trailing_flops_plan(N, nb),
-                    avg_launch_us=avg_s * 1e6, launches=nl,
-                    ms_per_factorization=(trl["ms"] + near["ms"]) / max(efacs, 1))
-    if la:
-        trailing["near_ms_per_factorization"] = near["ms"] / max(efacs, 1)
-    if meas and meas[0] is not None:
+    trailing = dict(kernel="k_bk_trailing_coop" + (", k_bk_trailing_pair" if near["launches"] else ""),
+                    bound="hbm", achieved=per_fac / s_fac / 1e9 if s_fac > 0 else 0.0,
+                    peak=HBM_PEAK_GBS, unit="GB/s",
+                    frac=per_fac / s_fac / 1e9 / HBM_PEAK_GBS if s_fac > 0 else 0.0,
+                    traffic=meas[0] if meas else None, bytes_per_factorization=per_fac,
+                    flops_per_factorization=flops,
+                    tflops=flops / s_fac / 1e12 if s_fac > 0 else 0.0,
+                    launches=nl, ms_per_factorization=s_fac * 1e3)
+    if near["launches"]:
+        trailing["near_ms_per_factorization"] = near["ms"] / efacs
+    if meas:
         trailing["traffic_source"] = meas[1]
-        trailing["traffic_over_algorithmic"] = meas[0] / per_launch
-    return dict(bound="mfma", kernel="factorization (k_bk_panel_coop, k_bk_panel_reg tail, "
-                                     "k_bk_trailing_ps" + (", look-ahead" if la else "") + ")",
+        trailing["traffic_over_algorithmic"] = meas[0] / per_fac
+    return dict(bound="mfma", kernel="factorization (k_bk_panel_coop, " + trailing["kernel"] + ")",
                 achieved=factor_tfs, peak=FP64_MFMA_PEAK_TFS, unit="TFLOP/s",
                 frac=factor_tfs / FP64_MFMA_PEAK_TFS, traffic=None,
                 flops_per_launch=N ** 3 / 3.0, avg_launch_us=fac_ms * 1e3, launches=efacs,
@@ -273,12 +295,11 @@ def roofline_of(tim, efacs, N, nb, pstats=None, xfloor=None):
 
 
 def panel_latency_model(tim, efacs, N, nb, pstats=None, xfloor=None):
-    """Microseconds per pivot step of the cooperative panel and of its
-    register tail (a latency-bound chain: one or two grid-wide exchanges and
-    one dependent column read per step), and, with the pivot statistics and
+    """Microseconds per pivot step of the cooperative panel (a latency-bound
+    chain: one grid-wide exchange per 16 columns whose pivots pass the first
+    test, one or two more where one fails), and, with the pivot statistics and
     the measured exchange round trip, the floor that the exchanges alone set
-    (first exchange every step, the second on the steps whose first test
-    fails)."""
+    (one per 16 steps, two more on the steps whose first test fails)."""
     out = {}
     for cls in ("panel", "panel_tail"):
         n = tim[cls]["launches"]
@@ -294,7 +315,8 @@ def panel_latency_model(tim, efacs, N, nb, pstats=None, xfloor=None):
         m = dict(steps_per_factorization=pstats["coop_steps"], second_exchange_frac=f2,
                  us_per_step=us_step, n2x2=pstats["n2x2"])
         if xfloor:
-            floor = xfloor["first_exchange_us"] + f2 * xfloor["second_exchange_us"]
+            floor = (xfloor["first_exchange_us"] / 16 +
+                     f2 * (xfloor["first_exchange_us"] + xfloor["second_exchange_us"]))
             m.update(exchange_floor_us_per_step=floor, step_over_floor=us_step / floor,
                      probe=xfloor)
         out["coop_model"] = m

@@ -240,12 +240,14 @@ typedef struct {       /* one IPM iteration (host) */
 
 /* Per-kernel-class device time, accumulated while timing is enabled
  * (hipEvents recorded around each launch on the stream it runs on).  PERMUTE
- * is the conversion of a new factor to standard form before its first solve;
+ * is the conversion of a new factor to standard form before its first solve
+ * (up to N = 1024 by the factorization's own launches);
  * SOLVE is one triangular-solve sequence (permute, L, D, L', permute);
  * PANEL_TAIL is unused (zero).  FACTOR is
  * each whole factorization on the handle's stream (with look-ahead its
- * classes overlap, so their sum exceeds it); NEAR the look-ahead's strip
- * updates (TRAILING then holds the rest of each trailing update). */
+ * classes overlap, so their sum exceeds it); NEAR the strip updates
+ * of the look-ahead and, without it, of paired panels (from 4608 remaining rows
+ * on two panels share one trailing update); TRAILING then holds the rest. */
 enum { MDS_T_CONDENSE = 0, MDS_T_PANEL = 1, MDS_T_TRAILING = 2, MDS_T_SOLVE = 3,
        MDS_T_PERMUTE = 4, MDS_T_PANEL_TAIL = 5, MDS_T_FACTOR = 6, MDS_T_NEAR = 7,
        MDS_T_CLASSES = 8 };
@@ -510,7 +512,7 @@ typedef struct {
   int32_t nb;           /* panel width limit                                  */
   int32_t min_width;    /* fewest columns a panel factors (except the last)   */
   int32_t panel;        /* 0: register-resident panel, 1: panel in memory,
-                           2: cooperative register-resident panel,
+                           2: cooperative panel,
                            3: whole M in one workgroup's LDS                 */
   int32_t precision;    /* MDS_FP64, MDS_FP32, MDS_BF16 or MDS_BF16X3          */
   int32_t panel_threads; /* workgroup size of the panel kernel                */
@@ -600,7 +602,8 @@ typedef struct {
 } mds_batch_result;
 
 typedef struct {
-  int32_t nb;         /* panel width, 2..16 (0: 16); FP64 panels hold 4 nb columns */
+  int32_t nb;         /* panel width, 2..16 (0: 16); FP64 panels hold 4 nb
+                         columns, 8 nb from order 1024 on                     */
   int32_t grid;       /* persistent workgroups = scratch slots (0: min(count, 256)) */
   int32_t use_graph;  /* 0: plain launches; otherwise replay a captured hipGraph */
   int32_t precision;  /* MDS_FP64 (0, default) or MDS_FP32: equilibrated S M S

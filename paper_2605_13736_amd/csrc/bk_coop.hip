@@ -225,7 +225,7 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
   int slow = 0, cool = 0; // full steps due; back-off after failing blocks
   // a failing block's candidate: the next full step starts from it without X1
   bool have = false;
-  double f_x = 0.0, f_max = 0.0, f_wki = 0.0;
+  double f_x = 0.0, f_max = 0.0;
   int f_imax = 0, f_phys = 0, f_g = 0;
 
   // un-updated entries of the block at (jj, its columns [jj % CB, ce)), in the

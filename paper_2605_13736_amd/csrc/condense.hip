@@ -119,32 +119,57 @@ __global__ void k_csc_count(int m, const int32_t *__restrict__ rp,
   for (int a = rp[r]; a < rp[r + 1]; ++a) atomicAdd(&cnt[ci[a]], 1);
 }
 
-// Exclusive scan of cnt[0..n) into ptr[0..n], single workgroup of 1024.
+// Exclusive scan of cnt[0..n) into ptr[0..n] by one workgroup, 8192 entries a
+// round: eight consecutive ones a thread, the next round's loaded ahead.  Part of
+// preparing a problem; a chunk of the whole array per thread (uncoalesced, the
+// 1024 sums added by one thread) took 365 us at n_s = 245760, 109 at 60000.
+constexpr int kScanPer = 8;
 __global__ __launch_bounds__(1024) void k_scan(int n, const int32_t *__restrict__ cnt,
                                                int32_t *__restrict__ ptr) {
-  __shared__ int64_t part[1024];
-  const int t = threadIdx.x;
-  const int64_t chunk = ((int64_t)n + 1023) / 1024;
-  const int64_t b = t * chunk, e = (b + chunk < n) ? b + chunk : n;
-  int64_t s = 0;
-  for (int64_t i = b; i < e; ++i) s += cnt[i];
-  part[t] = s;
-  __syncthreads();
-  if (t == 0) {
-    int64_t acc = 0;
-    for (int i = 0; i < 1024; ++i) {
-      int64_t x = part[i];
-      part[i] = acc;
-      acc += x;
+  __shared__ int32_t s_w[2][16];
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  int32_t carry = 0, v[kScanPer];
+  auto load = [&](int64_t base) {
+#pragma unroll
+    for (int u = 0; u < kScanPer; ++u) {
+      const int64_t i = base + (int64_t)t * kScanPer + u;
+      v[u] = (i < n) ? cnt[i] : 0;
     }
-    ptr[n] = (int32_t)acc;
+  };
+  load(0);
+  int par = 0;
+  for (int64_t base = 0; base < n; base += 1024 * kScanPer, par ^= 1) {
+    int32_t c[kScanPer], s = 0;
+#pragma unroll
+    for (int u = 0; u < kScanPer; ++u) {
+      c[u] = v[u];
+      s += v[u];
+    }
+    load(base + 1024 * kScanPer);
+    int32_t inc = s;  // inclusive over the wave's lanes
+#pragma unroll
+    for (int d = 1; d < 64; d *= 2) {
+      const int32_t o = __shfl_up(inc, d);
+      if (lane >= d) inc += o;
+    }
+    if (lane == 63) s_w[par][wv] = inc;
+    __syncthreads();
+    int32_t before = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+      before += (w < wv) ? s_w[par][w] : 0;
+      total += s_w[par][w];
+    }
+    int32_t acc = carry + before + inc - s;
+#pragma unroll
+    for (int u = 0; u < kScanPer; ++u) {
+      const int64_t i = base + (int64_t)t * kScanPer + u;
+      if (i < n) ptr[i] = acc;
+      acc += c[u];
+    }
+    carry += total;
   }
-  __syncthreads();
-  int64_t acc = part[t];
-  for (int64_t i = b; i < e; ++i) {
-    ptr[i] = (int32_t)acc;
-    acc += cnt[i];
-  }
+  if (t == 0) ptr[n] = carry;
 }
 
 __global__ void k_csc_fill(int m, const int32_t *__restrict__ rp, const int32_t *__restrict__ ci,
