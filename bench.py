@@ -46,6 +46,7 @@ FP32_MFMA_PEAK_TFS = 157.3
 # (one whole factorization's trailing updates).
 MEASURED_TRAFFIC = {
     ("k_bk_trailing", 4096): (3.91e9, "profiles/newton_pass_kernels.md"),
+    ("k_bk_trailing", 16384): (118.9e9, "profiles/newton_pass_kernels.md"),
 }
 KERNEL_OF_CLASS = {"panel_tail": "k_bk_panel_reg", "trailing": "k_bk_trailing_coop",
                    "solve": "k_trsv_fwd+k_trsv_bwd", "condense": "k_condense_dense",

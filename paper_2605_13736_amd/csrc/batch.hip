@@ -1485,7 +1485,7 @@ __device__ __attribute__((noinline)) void ipm_parts_wg(const ProbDev &P, const I
 // max |(x - l) zl - mu| and max |(u - x) zu - mu| over the finite bounds
 __device__ __attribute__((noinline)) double ipm_compl_wg(const ProbDev &P, const IpmDev &Q, const double *x,
                                const double *zl, const double *zu, double mu, double *s_part) {
-  const int tid = threadIdx.x, n = P.nd + P.ns;
+  const int n = P.nd + P.ns;
   double c = 0.0;
   struct Cp {
     double x, l, u, zl, zu;
