@@ -33,16 +33,16 @@ struct Prod {
   int K;
 };
 
-// acc += the product's 16 WB x 16 WB entries at (wi, wj) of an M x N result.
-// MODE 0: FP32 MFMA; MODE 1: BF16 MFMA, FP32 accumulate.
-// A product of these sizes is a few workgroups, bound by the latency of its
-// loads: KU k-steps of them leave together, unguarded (a guarded load waits
-// behind its own branch), at uniform offsets from the lane's address.  Mean
-// launch of a training step (128-256-256-193, batch 64): one guarded k-step
-// at a time 21 us, together 17, with 32 x 32 tiles 8.7.  The sums keep their
-// order.
+// acc += the product's 16 WB x 16 WB entries at (wi, wj) of an M x N result,
+// a wave's quarter of a 64 x 64 tile.  MODE 0: FP32 MFMA; MODE 1: BF16 MFMA,
+// FP32 accumulate.  KU k-steps' loads leave together, unguarded (a guarded
+// load waits behind its own branch), at uniform offsets from the lane's
+// address: one guarded k-step at a time the launches of a training step
+// (128-256-256-193, batch 64) took 21 us each, batched 17.  The sums keep the
+// order of k.
 constexpr int KU = 16;
-template <int MODE, int WB>
+constexpr int WB = 2;
+template <int MODE>
 __device__ inline void product(const Prod &p, int M, int N, int wi, int wj, int l16, int l4,
                                f4 (&acc)[WB][WB]) {
   const int K = p.K;
@@ -160,7 +160,7 @@ enum Kind : int {
 };
 struct Task {
   int kind, end;   // end: one past its last workgroup of the launch
-  int wb, nx;      // 64 x 64 (2), 32 x 32 (1) or 16 x 16 (0) tiles, tiles in a row
+  int big, nx;     // 64 x 64 tiles or 16 x 16, tiles in a row
   int M, N;
   Prod p, q;
   const float *bias, *T;
@@ -238,7 +238,7 @@ __device__ inline void record(const Task &t, int blk, double s, double *sh) {
 
 // 16 x 16 FP32-accumulating MFMA result: lane l, register r holds row
 // 4 (l / 16) + r, column l % 16.
-template <int MODE, int WB>
+template <int MODE>
 __device__ inline void tile(const Task &t, const Adam &ad, int blk, double *sh) {
   const int M = t.M, N = t.N;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -250,8 +250,8 @@ __device__ inline void tile(const Task &t, const Adam &ad, int blk, double *sh) 
   for (int a = 0; a < WB; ++a)
 #pragma unroll
     for (int b = 0; b < WB; ++b) acc[a][b] = acq[a][b] = f4{0.f, 0.f, 0.f, 0.f};
-  product<MODE, WB>(t.p, M, N, wi, wj, l16, l4, acc);
-  if (t.kind == kOut) product<MODE, WB>(t.q, M, N, wi, wj, l16, l4, acq);
+  product<MODE>(t.p, M, N, wi, wj, l16, l4, acc);
+  if (t.kind == kOut) product<MODE>(t.q, M, N, wi, wj, l16, l4, acq);
   Aux o[WB][WB][4];
 #pragma unroll
   for (int a = 0; a < WB; ++a)
@@ -276,14 +276,14 @@ __device__ inline void tile(const Task &t, const Adam &ad, int blk, double *sh) 
   record(t, blk, s, sh);
 }
 
-// A 16 x 16 tile of a sum over more than one batch of loads: the four waves
-// load a quarter of a chunk each, stage it in LDS in the operands' order, and
-// the first wave runs the chain of products in the order of k while the next
-// chunk's loads are in flight.  A wave alone waits for one batch after
+// A 16 x 16 tile where a launch is bound by the latency of its loads: the four
+// waves load a quarter of a chunk each, stage it in LDS in the operands' order,
+// and the first wave runs the chain of products in the order of k while the
+// next chunk's loads are in flight.  A wave alone waits for one batch after
 // another, and four tiles a workgroup share one compute unit's address units:
-// a launch over K = 256 13 us with 32 x 32 tiles, 7 so (128-256-256-193, batch
-// 64); one row through 3072-1024-1024-4097 in BF16 683 and 93 us.  The sums
-// are those of a wave alone, bit for bit.
+// a launch over K = 256 took 13 us with 32 x 32 tiles a workgroup, 7 so
+// (128-256-256-193, batch 64), one row through 3072-1024-1024-4097 in BF16 683
+// and 93.  The sums are those of a wave alone, bit for bit.
 constexpr int kChunk = 16 * KU;
 template <int MODE>
 __device__ inline void load_quarter(const Prod &p, int M, int N, int i, int j, int l4, int k0,
@@ -419,9 +419,8 @@ __global__ __launch_bounds__(256) void k_mlp(const Tasks L) {
   if (i > 0) blk -= L.t[i - 1].end;
   if (MODE == 0 && t.kind == kColsum) colsum(t, L.ad, blk);
   else if (MODE == 0 && t.kind == kUpdate) update(t, L.ad, blk);
-  else if (t.wb == 0) tile_chain<MODE>(t, L.ad, blk, sh, lds);
-  else if (t.wb == 1) tile<MODE, 1>(t, L.ad, blk, sh);
-  else tile<MODE, 2>(t, L.ad, blk, sh);
+  else if (t.big) tile<MODE>(t, L.ad, blk, sh);
+  else tile_chain<MODE>(t, L.ad, blk, sh, lds);
 }
 
 // The launch under construction: tasks in the order of their workgroups.
@@ -438,13 +437,14 @@ struct Launch {
     return t;
   }
   Task &gemm(int kind, int M, int N, const Prod &p, float *C) {
-    // 64 x 64 tiles, or smaller ones where those are too few to matter against
-    // 256 compute units: 32 x 32 where one batch of loads holds the whole sum,
-    // else 16 x 16, loaded by four waves (figures at tile_chain)
-    const int64_t big = (int64_t)((N + 63) / 64) * ((M + 63) / 64);
-    const int T = (big >= 128) ? 64 : (p.K <= 4 * KU) ? 32 : 16, nx = (N + T - 1) / T;
+    // 64 x 64 tiles, or 16 x 16 where those are too few against 256 compute
+    // units.  The line lies near 128 of them: the output layer of 3072-1024-
+    // 1024-4097 at batch 128 (130 tiles, K = 1024 and 3072) takes 60 us longer
+    // with 16 x 16, which read A and B four times as often.
+    const bool big = (int64_t)((N + 63) / 64) * ((M + 63) / 64) >= 128;
+    const int T = big ? 64 : 16, nx = (N + T - 1) / T;
     Task &t = add(kind, M, N, (int64_t)nx * ((M + T - 1) / T));
-    t.wb = T / 32;
+    t.big = big;
     t.nx = nx;
     t.p = p;
     t.C = C;
