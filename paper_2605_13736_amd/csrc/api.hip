@@ -291,6 +291,16 @@ constexpr size_t kPinBytes = 1024;
 static_assert(kRecVals < kPinScal && sizeof(FacState) <= 8 * (kPinErr - kPinFac), "pinned layout");
 inline FacState *pin_fac(mds_handle *h) { return reinterpret_cast<FacState *>(h->pin + kPinFac); }
 
+// Waits for the launches and copies that write to pin.  A launch error is
+// reported after the wait, so that nothing writes there once it has returned.
+int pin_wait(mds_handle *h) {
+  const hipError_t launched = hipGetLastError(), done = hipStreamSynchronize(S(h));
+  if (done != hipSuccess) h->pin_lost = true;
+  HIPCHK(launched);
+  HIPCHK(done);
+  return MDS_OK;
+}
+
 // ---- internal building blocks -------------------------------------------------
 
 int condense_impl(mds_handle *h, double dw, double dc) {
@@ -661,8 +671,7 @@ void factor_launches_mem(mds_handle *h, hipStream_t s) {
 
 // The factorization's state, which its last launch left in pinned memory.
 int read_fac_state(mds_handle *h, FacState *st) {
-  HIPCHK(hipGetLastError());
-  HIPCHK(hipStreamSynchronize(S(h)));
+  TRY(pin_wait(h));
   *st = *pin_fac(h);
   return MDS_OK;
 }
@@ -724,7 +733,7 @@ void ensure_std(mds_handle *h) {
 // Error word of the triangular solves (a bounded wait that expired).
 int solve_status(mds_handle *h) {
   HIPCHK(hipMemcpyAsync(h->pin + kPinErr, h->w.trsv + 1, 4, hipMemcpyDeviceToHost, S(h)));
-  HIPCHK(hipStreamSynchronize(S(h)));
+  TRY(pin_wait(h));
   if (*reinterpret_cast<const int32_t *>(h->pin + kPinErr)) return set_err(h, MDS_EHIP, "triangular solve: dependency wait timed out");
   return MDS_OK;
 }
@@ -831,7 +840,7 @@ void kkt_matvec(mds_handle *h, const double *dxd, const double *dxs, const doubl
 int read_scal(mds_handle *h, double *dst, int count) {
   HIPCHK(hipMemcpyAsync(h->pin + kPinScal, h->w.scal, 8 * (size_t)count, hipMemcpyDeviceToHost,
                         S(h)));
-  HIPCHK(hipStreamSynchronize(S(h)));
+  TRY(pin_wait(h));
   memcpy(dst, h->pin + kPinScal, 8 * (size_t)count);
   return MDS_OK;
 }
@@ -870,8 +879,7 @@ RowArgs row_args(mds_handle *h) {
 
 // Combined record of the last fused pass.
 int read_rec(mds_handle *h, double (&v)[kRecVals + 1]) {
-  HIPCHK(hipGetLastError());
-  HIPCHK(hipStreamSynchronize(S(h)));
+  TRY(pin_wait(h));
   memcpy(v, h->pin + kPinRec, sizeof(v));
   return MDS_OK;
 }
@@ -1566,9 +1574,9 @@ int mds_create(mds_handle **out, const mds_dims *dims, const mds_options *opts, 
           hipSuccess ||
       hipMemsetAsync(w.fst, 0, sizeof(FacState), h->stream) != hipSuccess ||
       hipMemsetAsync(w.rec_count, 0, 256, h->stream) != hipSuccess ||
-      hipHostMalloc((void **)&h->pin, kPinBytes, hipHostMallocDefault) != hipSuccess ||
+      !(h->pin = (double *)pinned_get(kPinBytes)) ||
       hipStreamSynchronize(h->stream) != hipSuccess) {
-    if (h->pin) (void)hipHostFree(h->pin);
+    pinned_put(h->pin, kPinBytes);
     delete h;
     return MDS_EHIP;
   }
@@ -1585,10 +1593,7 @@ int mds_create(mds_handle **out, const mds_dims *dims, const mds_options *opts, 
 void mds_destroy(mds_handle *h) {
   if (!h) return;
   for (hipEvent_t e : h->ev_pool) (void)hipEventDestroy(e);
-  if (h->pin) {
-    (void)hipStreamSynchronize(h->stream);  // its last writer
-    (void)hipHostFree(h->pin);
-  }
+  if (!h->pin_lost) pinned_put(h->pin, kPinBytes);
   if (h->fac_exec) (void)hipGraphExecDestroy(h->fac_exec);
   if (h->cap_stream) (void)hipStreamDestroy(h->cap_stream);
   if (h->la_a) (void)hipStreamDestroy(h->la_a);

@@ -179,6 +179,7 @@ struct mds_handle {
   // pinned host memory the read-backs go to: kRecBlocks' combined record (16
   // doubles) at 0, then scalars, the factorization's state
   double *pin = nullptr;
+  bool pin_lost = false;  // a wait failed: the device may still write to pin
   // captured launch sequence of one factorization (replayed without timing)
   hipGraphExec_t fac_exec = nullptr;
   hipStream_t cap_stream = nullptr;
@@ -393,6 +394,11 @@ void launch_std_solve(hipStream_t s, int N, int nd, int ns, const double *Lstd, 
                       const double *ds, const int32_t *blk, const int32_t *perm,
                       const StdSolveArgs &a, double *z, double *z2, double *dx_d, double *dx_s,
                       double *dy, int32_t *trsv);
+
+// pinned.hip: pinned host memory (nullptr: none left); the device must be done
+// with a block that is put back, of the size it was asked for
+void *pinned_get(size_t bytes);
+void pinned_put(void *p, size_t bytes);
 
 // vec.hip
 void launch_gemv_n(hipStream_t s, int rows, int cols, const double *A, int lda,

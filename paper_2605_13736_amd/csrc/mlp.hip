@@ -476,8 +476,10 @@ struct mds_mlp {
   // written by the step's third launch and read after its synchronization (a
   // copy of them from the device added 9 us to a step of 64)
   double *part = nullptr;
+  size_t part_bytes = 0;
+  bool part_lost = false;  // a wait failed: the device may still write to part
   ~mds_mlp() {
-    if (part) (void)hipHostFree(part);
+    if (!part_lost) pinned_put(part, part_bytes);
   }
 };
 
@@ -536,8 +538,9 @@ int mds_mlp_create(mds_mlp **out, const int32_t dims[4], int32_t max_batch, void
   p += (int64_t)max_batch * wmax;
   M->dB = p;
   p += (int64_t)max_batch * wmax;
-  const size_t records = (((size_t)max_batch + 15) / 16) * (((size_t)dims[3] + 15) / 16);
-  if (hipHostMalloc((void **)&M->part, 8 * records) != hipSuccess ||
+  M->part_bytes = 8 * (((size_t)max_batch + 15) / 16) * (((size_t)dims[3] + 15) / 16);
+  M->part = (double *)pinned_get(M->part_bytes);
+  if (!M->part ||
       hipMemsetAsync(M->m1, 0, 8 * (size_t)o, M->stream) != hipSuccess ||
       hipStreamSynchronize(M->stream) != hipSuccess) {
     delete M;
@@ -664,8 +667,9 @@ int mds_mlp_train_step(mds_mlp *M, const float *X, const float *T, int32_t batch
     a.go(s, 0);
     std::swap(dZ, dprev);
   }
-  if (hipGetLastError() != hipSuccess) return MDS_EHIP;
-  if (hipStreamSynchronize(s) != hipSuccess) return MDS_EHIP;
+  const hipError_t launched = hipGetLastError(), done = hipStreamSynchronize(s);
+  if (done != hipSuccess) M->part_lost = true;
+  if (launched != hipSuccess || done != hipSuccess) return MDS_EHIP;
   if (loss_host) {
     double t = 0.0;
     for (int b = 0; b < nblk; ++b) t += M->part[b];
