@@ -51,7 +51,8 @@ void *pinned_get(size_t bytes) {
     bytes = kMinBlock << c;
   }
   void *b = nullptr;
-  if (hipHostMalloc(&b, bytes, hipHostMallocPortable) != hipSuccess) {
+  // (other flags would make the memory non-coherent: 1 to 2 us more a read-back)
+  if (hipHostMalloc(&b, bytes, hipHostMallocDefault) != hipSuccess) {
     (void)hipGetLastError();
     return nullptr;
   }
