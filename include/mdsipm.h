@@ -101,9 +101,12 @@ enum { MDS_FP64 = 0, MDS_FP32 = 1, MDS_BF16 = 2, MDS_BF16X3 = 3 };
 
 typedef struct {
   int32_t nb;          /* panel width of the blocked factorization (0: default) */
-  int32_t panel;       /* 0: automatic (the cooperative panel; the register
-                          panel when panel_threads is set and its tile
-                          allows nb >= 16, i.e. N <= 2048),
+  int32_t panel;       /* 0: automatic (the cooperative panel, and the
+                          register panel for as long as most pivots of the
+                          x block fail the first test, over at most 2048
+                          rows; the register panel throughout when
+                          panel_threads is set and its tile allows nb >= 16,
+                          i.e. N <= 2048),
                           1: panel kept in device memory (FP64 only),
                           2: register-resident panel, one workgroup (N <= 4096),
                           3: cooperative panel over ceil(N / 256)
@@ -243,7 +246,8 @@ typedef struct {       /* one IPM iteration (host) */
  * is the conversion of a new factor to standard form before its first solve
  * (up to N = 1024 by the factorization's own launches);
  * SOLVE is one triangular-solve sequence (permute, L, D, L', permute);
- * PANEL_TAIL is unused (zero).  FACTOR is
+ * PANEL_TAIL holds the register panels of a factorization that changed to
+ * them (PANEL then holds the cooperative ones).  FACTOR is
  * each whole factorization on the handle's stream (with look-ahead its
  * classes overlap, so their sum exceeds it); NEAR the strip updates
  * of the look-ahead and, without it, of paired panels (from 4608 remaining rows
@@ -510,7 +514,8 @@ int mds_get_inv_ds(mds_handle *h, double *inv_d_host);
 /* Configuration chosen at mds_create (host). */
 typedef struct {
   int32_t nb;           /* panel width limit                                  */
-  int32_t min_width;    /* fewest columns a panel factors (except the last)   */
+  int32_t min_width;    /* fewest columns a panel of that kind factors (except
+                           the last, and where the automatic panel changes)  */
   int32_t panel;        /* 0: register-resident panel, 1: panel in memory,
                            2: cooperative panel,
                            3: whole M in one workgroup's LDS                 */

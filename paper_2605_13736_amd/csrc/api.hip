@@ -118,8 +118,11 @@ Layout make_layout(const mds_dims &d, int nb, bool pingpong, int precision, int 
   const size_t nd = d.n_d, ns = d.n_s, m = d.m, N = nd + m, n = nd + ns;
   const size_t nx = n + (size_t)d.m_I;
   const size_t nnz = (size_t)d.nnz_s;
-  // panels: at least nb - 1 columns each
-  const size_t maxp = N / (size_t)std::max(nb - 1, 1) + 2;
+  // panels: at least nb - 1 columns each; the register panel's narrowest tile
+  // (15) over the last rows, and the panels that end at a hand-over
+  const size_t maxp = N / (size_t)std::max(nb - 1, 1) + 2 +
+                      std::min(N, (size_t)kSwRows) / (size_t)std::max(std::min(nb, 16) - 1, 1) +
+                      kSwMax;
   size_t bytes[S_COUNT] = {};
   bytes[S_M] = 8 * N * N;
   const bool mixed = precision != MDS_FP64;
@@ -215,6 +218,7 @@ struct PanelChoice {
   bool coop;  // cooperative panel over several workgroups
   int nb, adv, threads;
   bool lds;   // unblocked factorization of the whole M in one workgroup's LDS
+  bool sw = false;  // cooperative: the register panel may take over the last rows
 };
 
 // workgroup size of the single-workgroup register panel: the option
@@ -269,6 +273,7 @@ PanelChoice panel_of(const mds_dims &d, const mds_options *o) {
     int nb = (o && o->nb > 0) ? o->nb : cnb;
     nb = std::min(std::max(nb, 2), cnb);
     c = {true, true, nb, std::max(nb - 1, 1), bk_coop_rows(), false};
+    c.sw = popt == 0;
   } else {
     int nb = (o && o->nb > 0) ? o->nb : default_nb(N);
     nb = std::min(std::max(nb, 2), kMaxNb);
@@ -361,10 +366,11 @@ void launch_reg_panel(mds_handle *h, hipStream_t s, int b, const TX *X, double *
   const int N = h->N;
   if (h->panel_coop)
     launch_bk_panel_coop(s, (int)h->plan[b].rows, N, h->nb, h->alpha_bk, X, Y, h->w.src, h->w.W,
-                         h->w.dd, h->w.ds, h->w.ipiv, h->w.blk, h->w.fst, h->w.panel_k0, h->w.xch);
+                         h->w.dd, h->w.ds, h->w.ipiv, h->w.blk, h->w.fst, h->w.panel_k0, h->w.xch,
+                         h->sw_cols);
   else
-    launch_bk_panel_reg(s, h->panel_threads, N, h->nb, h->alpha_bk, X, Y, h->w.src, h->w.W,
-                        h->w.dd, h->w.ds, h->w.ipiv, h->w.blk, h->w.fst, h->w.panel_k0);
+    launch_bk_panel_reg(s, h->panel_threads, N, N, h->nb, h->alpha_bk, X, Y, h->w.src, h->w.W,
+                        h->w.dd, h->w.ds, h->w.ipiv, h->w.blk, h->w.fst, h->w.panel_k0, 0);
 }
 
 void factor_launches_la(mds_handle *h, hipStream_t s);
@@ -481,6 +487,81 @@ void factor_launches(mds_handle *h, hipStream_t s) {
   }
   launch_fac_publish(s, h->w.fst, pin_fac(h));
   if (std_with_factor(h)) std_launches(h, s, h->panel_reg && fp64);
+}
+
+// One panel and its trailing update, slot b, while at most `rows` rows are
+// left: the register panel (sw as in launch_bk_panel_reg) or the cooperative
+// one (which hands over when sw).  panel false: the update alone.  Returns the
+// rows that can be left after it.
+template <typename TX>
+long rest_slot(mds_handle *h, hipStream_t s, int b, long rows, bool reg, int sw, bool panel,
+               const TX *X, TX *Y, double *L) {
+  const Work &w = h->w;
+  const int N = h->N, thr = panel_threads_of(nullptr, (int)rows);
+  const int nb = reg ? std::min(h->nb, bk_reg_nb((int)rows, thr)) : h->nb;
+  const long after = panel ? rows - std::max(nb - 1, 1) : rows;
+  if (panel) {
+    TimedLaunch t(h, reg ? MDS_T_PANEL_TAIL : MDS_T_PANEL, s);
+    if (reg)
+      launch_bk_panel_reg(s, thr, (int)rows, N, nb, h->alpha_bk, X, L, w.src, w.W, w.dd, w.ds,
+                          w.ipiv, w.blk, w.fst, w.panel_k0, sw);
+    else
+      launch_bk_panel_coop(s, (int)rows, N, nb, h->alpha_bk, X, L, w.src, w.W, w.dd, w.ds, w.ipiv,
+                           w.blk, w.fst, w.panel_k0, w.xch, sw ? h->sw_cols : 0);
+  }
+  if (after > 0) {
+    TimedLaunch t(h, MDS_T_TRAILING, s);
+    if constexpr (sizeof(TX) == 4)
+      launch_trailing_lp(s, h->precision, N, nb, reg ? nb + 1 : nb, after, b, w.W, X, Y, L, w.src,
+                         w.fst, w.panel_k0);
+    else if (reg)
+      launch_bk_trailing(s, N, nb, after, b, w.W, X, Y, Y, w.src, w.fst, w.panel_k0);
+    else
+      launch_bk_trailing_coop(s, N, after, b, 0, false, w.W, X, Y, Y, w.src, w.fst, w.panel_k0);
+  }
+  return after;
+}
+
+// Goes on with a factorization that its launches left at state st because the
+// panel changed: with the register panel while st.hand, else with the
+// cooperative one.
+//
+// Every launch sequence is fixed ahead of the pivots, and which panel is the
+// faster one depends on them.  A pivot that fails the first test costs the
+// cooperative panel a block's try (8.5 us) or a longer full step (4 to 8, two
+// exchanges), the register panel the same ~3 us as any other, up to the 2048
+// rows that one workgroup holds.  So the cooperative panel ends where sw_due says
+// so, the register panel gives back when its pivots pass again, the launches that
+// were queued behind return at once, and the host, which reads the state anyway,
+// queues the others.  Condense and factor of a dense matrix whose first test
+// always fails, register panel alone / cooperative panel alone / so, in us: N =
+// 101 265 / 464 / 308, 300 842 / 1531 / 884, 771 2360 / 4672 / 2398, 2048 8193 / 13246 /
+// 7938; N = 4096 (register panel for the last 2048 rows) 21167 / 28199 / 20499.
+// after: by slot, the rows that its launched update covers.  more: the panel
+// may change again.
+void rest_launches(mds_handle *h, hipStream_t s, const FacState &st, std::vector<long> &after,
+                   bool more) {
+  const bool lowp = h->precision != MDS_FP64 && !h->force64;
+  const int np2 = lowp ? 0 : h->pair_slots;
+  auto slot = [&](int b, long rows, bool reg, int sw, bool panel) {
+    const int p = lowp ? b & 1 : (b - np2 / 2) & 1;
+    if (lowp)
+      return rest_slot<float>(h, s, b, rows, reg, sw, panel, h->w.X32[p], h->w.X32[1 - p], h->w.M);
+    double *X = p ? h->w.M2 : h->w.M, *Y = p ? h->w.M : h->w.M2;
+    return rest_slot<double>(h, s, b, rows, reg, sw, panel, X, Y, Y);
+  };
+  int b = st.npanel;
+  long rows = h->N - st.k;
+  // a panel that ended early leaves more rows than its update was launched for:
+  // the whole update again (it reads one buffer and writes the other)
+  if (b > 0 && after[b - 1] < rows) slot(b - 1, rows, false, 0, false);
+  after.resize(b);
+  const int sw = st.hand ? (more ? 2 : 1) : (more ? 1 : 0);
+  for (; rows > 0; ++b) {
+    rows = slot(b, rows, st.hand != 0, sw, true);
+    after.push_back(rows);
+  }
+  launch_fac_publish(s, h->w.fst, pin_fac(h));
 }
 
 // Look-ahead form of the cooperative factorization.  Stream A (the
@@ -679,7 +760,7 @@ int read_fac_state(mds_handle *h, FacState *st) {
 int factor_impl(mds_handle *h, mds_inertia *out) {
   const int N = h->N;
   FacState st{};
-  bool mem = h->coop_off;
+  bool mem = h->coop_off, whole = true;  // whole: by factor_launches alone
   if (!mem) {
     // the look-ahead's CU masks belong to its streams, which a graph would
     // not keep: its launches go out one by one
@@ -693,6 +774,17 @@ int factor_impl(mds_handle *h, mds_inertia *out) {
       factor_launches(h, S(h));
     }
     TRY(read_fac_state(h, &st));
+    if (h->sw_cols > 0 && st.k < N && !st.xerr) {
+      TimedLaunch t(h, MDS_T_FACTOR);
+      if (h->timing) h->t_n[MDS_T_FACTOR]--;  // the same factorization
+      std::vector<long> after;
+      for (const SlotPlan &p : h->plan) after.push_back(p.rows_after);
+      for (int n = 1; st.k < N && !st.xerr && n <= kSwMax; ++n) {
+        rest_launches(h, S(h), st, after, n < kSwMax);
+        TRY(read_fac_state(h, &st));
+        whole = false;
+      }
+    }
     if (st.xerr && h->panel_coop) {
       // an exchange wait of the cooperative panel expired (its workgroups
       // were not all resident): condense again (the ping-pong buffers hold a
@@ -719,7 +811,7 @@ int factor_impl(mds_handle *h, mds_inertia *out) {
   h->have_factor = true;
   h->have_M = false;
   // (that kernel writes the standard form itself)
-  h->std_ready = h->panel_lds || (!mem && std_with_factor(h));
+  h->std_ready = h->panel_lds || (!mem && whole && std_with_factor(h));
   return MDS_OK;
 }
 
@@ -1586,6 +1678,7 @@ int mds_create(mds_handle **out, const mds_dims *dims, const mds_options *opts, 
   // the overlap saves (off / on: N = 4096 7.3 / 8.1 ms per Newton step, 9001
   // 26.0 / 27.3, 16384 86 / 96; FP32 storage 10.8 / 11.7, 32.9 / 33.1, 88 / 93)
   if (pc.coop && !coop_off && la_opt == 1) setup_lookahead(h);
+  h->sw_cols = (pc.sw && h->la_cus == 0) ? h->dims.n_d : 0;
   *out = h;
   return MDS_OK;
 }

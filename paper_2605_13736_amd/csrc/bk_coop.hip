@@ -140,6 +140,7 @@ constexpr int CB = 16;         // columns of a speculative block
 constexpr int CLD = CT + 17;   // LDS stride of a column of multipliers
 constexpr int CWL = CNB + 2;   // stride of a window row
 constexpr int CPW = 72;        // look-ahead: the candidate's W / L row, padded
+constexpr int kCoolMax = 255;  // back-off: at most 128 full steps to a try of a block
 static_assert(CNB <= kMaxNb && CNB % CB == 0 && CLD % 32 == 17, "tile");
 static_assert(8 + 2 * CNB <= kCoopSlotWords && CB * CNB * 2 <= kCoopRowWords, "exchange slot");
 
@@ -156,7 +157,8 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
                                                       int32_t *__restrict__ ipiv,
                                                       int32_t *__restrict__ blk, FacState *st,
                                                       int32_t *__restrict__ panel_k0,
-                                                      uint64_t *__restrict__ xch, int lstage) {
+                                                      uint64_t *__restrict__ xch, int lstage,
+                                                      int swcols) {
   constexpr int NWV = CT / 64;
   __shared__ double s_L[CNB * CLD];
   __shared__ double s_lw[CB * CWL];  // L rows of the block's positions
@@ -172,7 +174,7 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
   __shared__ double s_xq[CB];  // the failing column's entries of the window rows
   __shared__ double s_cv[NWV], s_akk, s_aii;
   __shared__ int s_ci[NWV], s_cs[NWV], s_fail[NWV];
-  __shared__ int s_k0, s_abort, s_force;
+  __shared__ int s_k0, s_abort, s_force, s_score, s_cool, s_slow;
   __shared__ uint32_t s_tag0;
   __shared__ double s_pw[CPW], s_pl[CPW];  // look-ahead: W and L rows of the candidate
   __shared__ int s_jwp, s_kprev;
@@ -185,6 +187,10 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
     s_tag0 = st->xtag;
     s_abort = st->xerr;
     s_force = st->xforce;
+    s_score = st->score;
+    s_cool = st->cool;
+    s_slow = st->slow;
+    if (swcols > 0 && st->hand) s_k0 = N;  // the register panel goes on
     const int np = st->npanel;
     const bool pvon = pv.X != nullptr || pv.Xf != nullptr;
     s_kprev = (pvon && np > 0) ? panel_k0[np - 1] : 0;
@@ -196,6 +202,12 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
   if (s_force) {
     // host-set test flag: report an expired exchange wait without waiting
     if (tid == 0) __hip_atomic_store(&st->xerr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return;
+  }
+  // hand over (below) at the panel's start
+  int score = s_score;
+  if (sw_due(swcols, N, k0, score)) {
+    if (g == 0 && tid == 0) st->hand = 1;  // (the others return by the score)
     return;
   }
   const int P = min((int)gridDim.x, (N - k0 + CT - 1) / CT);
@@ -222,7 +234,10 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
   int k = k0, j = 0, c = 0;
   int c_pos = 0, c_zero = 0, c_neg = 0, c_2x2 = 0, first_zero = 0, nsteps = 0, nsec = 0;
   bool any2 = false;      // a 2x2 pivot in this panel
-  int slow = 0, cool = 0; // full steps due; back-off after failing blocks
+  // full steps due; back-off after failing blocks (kept from panel to panel);
+  // full steps in a row that passed the first test
+  int slow = s_slow, cool = s_cool, npass = 0;
+  bool hand = false;      // the panel ends here, the register panel goes on
   // a failing block's candidate: the next full step starts from it without X1
   bool have = false;
   double f_x = 0.0, f_max = 0.0;
@@ -271,6 +286,21 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
     if (any2) {
       if (t + 1 < j) v = v + lr[t + 1] * s_cB[t];
       if (t >= 1) v = v + lr[t - 1] * s_cC[t];
+    }
+    return v;
+  };
+  // v - sum_t L(row, t) w[t], t < j, in the order of t: eight columns' reads
+  // together, the last ones (w is zero there) masked
+  auto minus_row = [&](double v, const double *w) {
+    for (int t0 = 0; t0 < j; t0 += 8) {
+      double l[8], wt[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        l[u] = s_L[(t0 + u) * CLD + tid];
+        wt[u] = w[t0 + u];
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v = fma(t0 + u < j ? -l[u] : 0.0, wt[u], v);
     }
     return v;
   };
@@ -616,11 +646,13 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
       k += a;
       nsteps += a;
       if (a < s) {
-        cool = (a == 0) ? min(2 * cool + 1, 15) : 0;
+        cool = (a == 0) ? min(2 * cool + 1, kCoolMax) : 0;
         slow = 1 + (cool >> 1);
       } else {
         cool = 0;
       }
+      npass = 0;
+      score = max(score - kSwPass * a, 0);
       __syncthreads();
       continue;
     }
@@ -666,8 +698,7 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
     } else {
       if (wid == 0) s_wk[lane] = (lane < j) ? wrow(s_lw + (j & (CB - 1)) * CWL, lane) : 0.0;
       __syncthreads();
-#pragma unroll 8
-      for (int t = 0; t < j; ++t) x = fma(-s_L[t * CLD + tid], s_wk[t], x);
+      x = minus_row(x, s_wk);
       xq = window_entry(xq, s_wk);
       double bv = -1.0;
       int bi = INT_MAX, bs = tid;
@@ -799,8 +830,7 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
         const bool on = pos >= k && rho >= kstrip;
         if (on) y = pending_entry<TX>(pX, pv.src, pv.W, pL, rho, iphys, jwp, ld, s_pw, s_pl);
       }
-#pragma unroll 8
-      for (int t = 0; t < j; ++t) y = fma(-s_L[t * CLD + tid], s_wi[t], y);
+      y = minus_row(y, s_wi);
       yq = window_entry(yq, s_wi);
       // ---- X3: maximum of the updated column imax, and a_ii --------------------
       double rv = (pos >= k && pos != imax) ? fabs(y) : 0.0;
@@ -951,6 +981,14 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
     any2 = any2 || kind == 4;
     j += kstep;
     k += kstep;
+    // two passes of the first test: blocks are worth a try again
+    npass = (kind == 1) ? npass + 1 : 0;
+    if (npass >= 2) slow = 0;
+    score = min(score + kSwStep, kSwScoreMax);
+    if (sw_due(swcols, N, k, score)) {
+      hand = true;
+      break;
+    }
     if (j < nb && k < N) {
       if ((j & ~(CB - 1)) != jb) {
         // the next window's rows, and the next block's entries
@@ -1018,6 +1056,10 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
     st->xtag = s_tag0 + 1u;
     st->csteps += nsteps;
     st->cx3 += nsec;
+    st->cool = cool;
+    st->slow = slow;
+    st->score = hand ? 0 : score;
+    if (hand) st->hand = 1;
   }
 }
 
@@ -1123,10 +1165,10 @@ template <typename TX, bool LA>
 static void panel_coop(hipStream_t s, int rows, int N, int nb, double alpha, const TX *X,
                        const PanelPrev &pv, double *Lout, int lstage, int32_t *src_out, double *W,
                        double *dd, double *ds, int32_t *ipiv, int32_t *blk, FacState *st,
-                       int32_t *panel_k0, uint64_t *xch) {
+                       int32_t *panel_k0, uint64_t *xch, int swcols = 0) {
   const int P = std::max(1, std::min(bk_coop_wgs(N), bk_coop_wgs(rows)));
   k_bk_panel_coop<TX, LA><<<P, CT, 0, s>>>(N, std::min(nb, CNB), alpha, X, pv, Lout, src_out, W, dd,
-                                           ds, ipiv, blk, st, panel_k0, xch, lstage);
+                                           ds, ipiv, blk, st, panel_k0, xch, lstage, swcols);
 }
 
 int bk_xch_probe(hipStream_t s, int P, int rounds, int words, uint64_t *xch, int32_t *err,
@@ -1142,17 +1184,17 @@ int bk_xch_probe(hipStream_t s, int P, int rounds, int words, uint64_t *xch, int
 void launch_bk_panel_coop(hipStream_t s, int rows, int N, int nb, double alpha, const double *X,
                           double *Lout, int32_t *src_out, double *W, double *dd, double *ds,
                           int32_t *ipiv, int32_t *blk, FacState *st, int32_t *panel_k0,
-                          uint64_t *xch) {
-  panel_coop<double, false>(s, rows, N, nb, alpha, X, PanelPrev{}, Lout, 0, src_out, W, dd, ds,
-                            ipiv, blk, st, panel_k0, xch);
+                          uint64_t *xch, int swcols) {
+  panel_coop<double, false>(s, rows, N, nb, alpha, X, PanelPrev{}, Lout, 0, src_out, W, dd, ds, ipiv,
+                        blk, st, panel_k0, xch, swcols);
 }
 
 void launch_bk_panel_coop(hipStream_t s, int rows, int N, int nb, double alpha, const float *X,
                           double *Lout, int32_t *src_out, double *W, double *dd, double *ds,
                           int32_t *ipiv, int32_t *blk, FacState *st, int32_t *panel_k0,
-                          uint64_t *xch) {
-  panel_coop<float, false>(s, rows, N, nb, alpha, X, PanelPrev{}, Lout, 0, src_out, W, dd, ds,
-                           ipiv, blk, st, panel_k0, xch);
+                          uint64_t *xch, int swcols) {
+  panel_coop<float, false>(s, rows, N, nb, alpha, X, PanelPrev{}, Lout, 0, src_out, W, dd, ds, ipiv,
+                        blk, st, panel_k0, xch, swcols);
 }
 
 void launch_bk_panel_coop_la(hipStream_t s, int rows, int N, int nb, double alpha, const double *X,

@@ -1,4 +1,6 @@
-// Register-resident Bunch-Kaufman panel kernel (Sec. 2.3): N <= 4096; the body is panel::panel_reg_dev.
+// Register-resident Bunch-Kaufman panel kernel (Sec. 2.3): at most 4096 rows left
+// (N <= 4096, or a factorization that the cooperative panel hands over); the body
+// is panel::panel_reg_dev.
 #include <algorithm>
 
 #include "panel_reg.hpp"
@@ -18,14 +20,14 @@ __global__ __launch_bounds__(T) void k_bk_panel_reg(int N, int nb, double alpha,
                                                     double *__restrict__ ds,
                                                     int32_t *__restrict__ ipiv,
                                                     int32_t *__restrict__ blk, FacState *st,
-                                                    int32_t *__restrict__ panel_k0) {
+                                                    int32_t *__restrict__ panel_k0, int sw) {
   panel::panel_reg_dev<T, R, NB, TX>(N, nb, alpha, X, Lout, src_out, W, dd, ds, ipiv, blk, st,
-                                     panel_k0);
+                                     panel_k0, sw);
 }
 
 }  // namespace
 
-// Panel variant for a matrix of order N and a workgroup of T threads: R rows
+// Panel variant for at most N rows left and a workgroup of T threads: R rows
 // per thread with R * T >= N, and the register tile NB chosen so that
 // R * NB = 64 doubles of L per thread at T = 512 (VGPR budget 256) and 32 at
 // T = 1024 (budget 128).  Workgroups of 64, 128 or 256 threads (one or two
@@ -53,13 +55,14 @@ int bk_reg_nb(int N, int threads) {
 }
 
 template <typename TX>
-static void panel_reg(hipStream_t s, int threads, int N, int nb, double alpha, const TX *X,
-                      double *Lout, int32_t *src_out, double *W, double *dd, double *ds,
-                      int32_t *ipiv, int32_t *blk, FacState *st, int32_t *panel_k0) {
+static void panel_reg(hipStream_t s, int threads, int rows, int N, int nb, double alpha,
+                      const TX *X, double *Lout, int32_t *src_out, double *W, double *dd,
+                      double *ds, int32_t *ipiv, int32_t *blk, FacState *st, int32_t *panel_k0,
+                      int sw) {
 #define MDS_PANEL_REG(T_, R_, NB_)                                                             \
   k_bk_panel_reg<T_, R_, NB_, TX><<<1, T_, 0, s>>>(N, nb, alpha, X, Lout, src_out, W, dd, ds, \
-                                                   ipiv, blk, st, panel_k0)
-  const int r = bk_reg_rows(N, threads);
+                                                   ipiv, blk, st, panel_k0, sw)
+  const int r = bk_reg_rows(rows, threads);
   if (threads == 64 || threads == 128 || threads == 256) {
     switch (threads * 10 + r) {
       case 641: MDS_PANEL_REG(64, 1, 32); break;
@@ -89,16 +92,20 @@ static void panel_reg(hipStream_t s, int threads, int N, int nb, double alpha, c
 #undef MDS_PANEL_REG
 }
 
-void launch_bk_panel_reg(hipStream_t s, int threads, int N, int nb, double alpha, const double *X,
-                         double *Lout, int32_t *src_out, double *W, double *dd, double *ds,
-                         int32_t *ipiv, int32_t *blk, FacState *st, int32_t *panel_k0) {
-  panel_reg(s, threads, N, nb, alpha, X, Lout, src_out, W, dd, ds, ipiv, blk, st, panel_k0);
+void launch_bk_panel_reg(hipStream_t s, int threads, int rows, int N, int nb, double alpha,
+                         const double *X, double *Lout, int32_t *src_out, double *W, double *dd,
+                         double *ds, int32_t *ipiv, int32_t *blk, FacState *st, int32_t *panel_k0,
+                         int sw) {
+  panel_reg(s, threads, rows, N, nb, alpha, X, Lout, src_out, W, dd, ds, ipiv, blk, st, panel_k0,
+            sw);
 }
 
-void launch_bk_panel_reg(hipStream_t s, int threads, int N, int nb, double alpha, const float *X,
-                         double *Lout, int32_t *src_out, double *W, double *dd, double *ds,
-                         int32_t *ipiv, int32_t *blk, FacState *st, int32_t *panel_k0) {
-  panel_reg(s, threads, N, nb, alpha, X, Lout, src_out, W, dd, ds, ipiv, blk, st, panel_k0);
+void launch_bk_panel_reg(hipStream_t s, int threads, int rows, int N, int nb, double alpha,
+                         const float *X, double *Lout, int32_t *src_out, double *W, double *dd,
+                         double *ds, int32_t *ipiv, int32_t *blk, FacState *st, int32_t *panel_k0,
+                         int sw) {
+  panel_reg(s, threads, rows, N, nb, alpha, X, Lout, src_out, W, dd, ds, ipiv, blk, st, panel_k0,
+            sw);
 }
 
 }  // namespace mds

@@ -22,6 +22,9 @@ constexpr int kProbeMaxP = 32;       // exchange probe: most workgroups
 constexpr int kCoopSlotWords = 512;  // cooperative panel: 64-bit exchange words per workgroup and parity
 constexpr int kCoopRowWords = 2048;  // ... and of the window rows, per parity
 constexpr size_t kCoopXchBytes = 8 * 2 * ((size_t)kCoopMaxP * kCoopSlotWords + kCoopRowWords);
+constexpr int kSwRows = 2048;        // most rows the register panel takes over from the cooperative
+constexpr int kSwMax = 8;            // most changes of the panel in a factorization
+constexpr int kSwMinRows = 32;       // fewest rows worth a change of the panel (a read-back)
 constexpr int kSBlkMax = 16;         // largest coupling block of the sparse Hessian
 
 // Coupling blocks of the sparse Hessian (sblock.hip) and the transformed
@@ -53,7 +56,30 @@ struct FacState {
   int32_t xforce; // host-set test flag: cooperative launches report an expired wait at once
   int32_t csteps; // cooperative panel: pivot steps of this factorization
   int32_t cx3;    // ... of which took the second exchange (the candidate column)
+  // which panel goes on (handles that may change it: see rest_launches)
+  int32_t hand;   // the one-workgroup register panel, from k on
+  int32_t score;  // what the other panel would have saved so far (sw_limit)
+  int32_t cool, slow;  // cooperative panel: back-off from speculative blocks, full steps due
 };
+
+// Change of the panel.  score counts how much oftener the pivots lately went
+// the way that suits the other panel, never below zero: while the cooperative
+// panel runs a full step adds kSwStep and a pivot of a block takes kSwPass away,
+// while the register panel runs the other way round.  sw_limit stands for the
+// cost of a change, a read-back and the launches queued behind, which grows with
+// the rows left.
+constexpr int kSwStep = 3, kSwPass = 1;
+constexpr int kSwScoreMax = 200;
+__host__ __device__ inline int sw_limit(int rows) { return 12 + rows / 16; }
+// Whether the cooperative panel hands over at column k.  Only the first cols
+// pivots, those of the x block, are expected to go on failing: what is past them
+// is negative definite once they are eliminated, and the late ones of a KKT
+// system fail for 32 to 100 columns just before that, where the change back
+// follows at once (IPM at N = 192 without the last condition: 6.7 -> 7.3 ms).
+__host__ __device__ inline bool sw_due(int cols, int N, int k, int score) {
+  const int rows = N - k;
+  return rows <= kSwRows && score >= sw_limit(rows) && cols - k >= 32 + rows / 8;
+}
 
 // Look-ahead of the cooperative factorization: while the trailing update of
 // panel b runs on part of the device, panel b + 1 factors its columns, which
@@ -168,6 +194,7 @@ struct mds_handle {
   bool coop_off = false;    // cooperative panel not co-resident: memory panel always
   bool fac_lowprec = false; // current factor is of the equilibrated FP32 matrix
   int pair_slots = 0;       // leading slots factored two to a trailing update
+  int sw_cols = 0;          // the register panel may take over in the first sw_cols columns
   bool fac_pingpong = false;// current factor's L is spread over M and M2
   int64_t n_coop_abort = 0, n_fp64_refactor = 0;
   // look-ahead of the cooperative factorization: compute units reserved for
@@ -289,12 +316,17 @@ void launch_lstage_copy(hipStream_t s, int N, long rows, int slot, const double 
 // workgroup of `threads` = 512 or 1024
 int bk_reg_rows(int N, int threads);
 int bk_reg_nb(int N, int threads);
-void launch_bk_panel_reg(hipStream_t s, int threads, int N, int nb, double alpha, const double *X,
-                         double *Lout, int32_t *src_out, double *W, double *dd, double *ds,
-                         int32_t *ipiv, int32_t *blk, FacState *st, int32_t *panel_k0);
-void launch_bk_panel_reg(hipStream_t s, int threads, int N, int nb, double alpha, const float *X,
-                         double *Lout, int32_t *src_out, double *W, double *dd, double *ds,
-                         int32_t *ipiv, int32_t *blk, FacState *st, int32_t *panel_k0);
+// rows: at least the rows left (they choose the tile); sw 0: always runs, 1:
+// only while FacState::hand, 2: and gives back to the cooperative panel
+// (hand = 0) when hardly a pivot of it failed the first test
+void launch_bk_panel_reg(hipStream_t s, int threads, int rows, int N, int nb, double alpha,
+                         const double *X, double *Lout, int32_t *src_out, double *W, double *dd,
+                         double *ds, int32_t *ipiv, int32_t *blk, FacState *st, int32_t *panel_k0,
+                         int sw);
+void launch_bk_panel_reg(hipStream_t s, int threads, int rows, int N, int nb, double alpha,
+                         const float *X, double *Lout, int32_t *src_out, double *W, double *dd,
+                         double *ds, int32_t *ipiv, int32_t *blk, FacState *st, int32_t *panel_k0,
+                         int sw);
 
 // bk_coop.hip: cooperative register panel over several workgroups (any N up
 // to the solver limit; X in FP64 or FP32); xch: kCoopXchBytes of exchange
@@ -312,7 +344,7 @@ int bk_xch_probe(hipStream_t s, int P, int rounds, int words, uint64_t *xch, int
 void launch_bk_panel_coop(hipStream_t s, int rows, int N, int nb, double alpha, const double *X,
                           double *Lout, int32_t *src_out, double *W, double *dd, double *ds,
                           int32_t *ipiv, int32_t *blk, FacState *st, int32_t *panel_k0,
-                          uint64_t *xch);
+                          uint64_t *xch, int swcols);
 // look-ahead form (FP64): X is valid in the near strip only, pv names the
 // previous panel's pending update, and the multipliers go to the staging
 // buffer Lst (row i, column t at Lst[i + t N])
@@ -332,7 +364,7 @@ int bk_coop_la_reserve(int N, int cus);
 void launch_bk_panel_coop(hipStream_t s, int rows, int N, int nb, double alpha, const float *X,
                           double *Lout, int32_t *src_out, double *W, double *dd, double *ds,
                           int32_t *ipiv, int32_t *blk, FacState *st, int32_t *panel_k0,
-                          uint64_t *xch);
+                          uint64_t *xch, int swcols);
 
 // bk_lds.hip: unblocked factorization of an M held whole in one
 // workgroup's LDS (N <= bk_lds_max_n(), threads 256 or 512); writes the

@@ -87,7 +87,7 @@ __device__ inline void panel_reg_dev(int N, int nb, double alpha,
                                                     double *__restrict__ ds,
                                                     int32_t *__restrict__ ipiv,
                                                     int32_t *__restrict__ blk, FacState *st,
-                                                    int32_t *__restrict__ panel_k0) {
+                                                    int32_t *__restrict__ panel_k0, int sw = 0) {
   constexpr int NWV = T / 64;
   static_assert(NB <= 64 && NB % 8 == 0, "one lane per panel column, chunks of 8");
   __shared__ double s_wk[NB], s_wi[NB];            // W rows of the pivot k and of imax
@@ -108,7 +108,8 @@ __device__ inline void panel_reg_dev(int N, int nb, double alpha,
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   if (tid == 0) {
     s_k0 = st->k;
-    s_err = st->xerr;  // an earlier panel of this factorization aborted
+    // an earlier panel of this factorization aborted, or gave back
+    s_err = st->xerr || (sw != 0 && !st->hand);
   }
   if (tid < NB) {
     s_wk[tid] = 0.0;
@@ -147,7 +148,7 @@ __device__ inline void panel_reg_dev(int N, int nb, double alpha,
   __syncthreads();
 
   int k = k0, j = 0;
-  int c_pos = 0, c_zero = 0, c_neg = 0, c_2x2 = 0, first_zero = 0;
+  int c_pos = 0, c_zero = 0, c_neg = 0, c_2x2 = 0, first_zero = 0, nsec = 0, nsteps = 0;
   // D of the previous step; thread 0 stores its coefficients at the start of
   // the next step (the W row of the next pivot takes them from registers)
   int pj = -1;
@@ -300,8 +301,10 @@ __device__ inline void panel_reg_dev(int N, int nb, double alpha,
         kstep = 2;
       }
     }
+    ++nsteps;
+    if (kind >= 2) ++nsec;
     const int p = k + kstep - 1;
-    const bool sw = (q != p);
+    const bool swap = (q != p);
     const int kn = k + kstep;
     // D of this step (identical in every thread)
     double Da = akk, Dc = 0.0, Db = 0.0, det = 1.0;
@@ -337,7 +340,7 @@ __device__ inline void panel_reg_dev(int N, int nb, double alpha,
         l0[r] = (kind == 0) ? 0.0 : s_wkc[r * T + tid] * rD;
       }
       int np = pr;
-      if (sw) {
+      if (swap) {
         if (pr == p) np = q;
         else if (pr == q) np = p;
       }
@@ -380,7 +383,7 @@ __device__ inline void panel_reg_dev(int N, int nb, double alpha,
 
     // ---- pivot records, map, and the W row of the next pivot -----------------
     if (tid == 0) {
-      if (sw) {
+      if (swap) {
         const int t0 = s_map[p - k0];
         s_map[p - k0] = s_map[q - k0];
         s_map[q - k0] = t0;
@@ -477,6 +480,13 @@ __device__ inline void panel_reg_dev(int N, int nb, double alpha,
     st->nneg += c_neg;
     st->n2x2 += c_2x2;
     if (st->info == 0 && first_zero != 0) st->info = first_zero;
+    if (sw == 2) {
+      // back to the cooperative panel
+      const int score = max(st->score + kSwPass * (nsteps - nsec) - kSwStep * nsec, 0);
+      const bool back = score >= sw_limit(N - kend) && N - kend >= kSwMinRows;
+      st->score = back ? 0 : score;
+      if (back) st->hand = st->cool = st->slow = 0;
+    }
   }
 }
 
