@@ -112,12 +112,20 @@ typedef struct {
                           3: cooperative panel over ceil(N / 256)
                              workgroups, nb <= 32 (64 above N = 2048; any N);
                              its workgroups exchange pivot data through the
-                             workspace and must run concurrently: when an
-                             exchange wait expires (~0.7 s) the matrix is
-                             condensed again and factored by the memory
-                             panel in FP64 (the factor then is an FP64 one
-                             in every precision mode; mds_get_fallbacks
-                             counts these),
+                             workspace and must run concurrently (each needs
+                             a compute unit's LDS, so a kernel on another
+                             stream can keep them apart; this holds for the
+                             automatic choice too): when an exchange wait
+                             expires (~0.7 s) the matrix is condensed again
+                             and factored by the memory panel in FP64 (the
+                             factor then is an FP64 one in every precision
+                             mode).  With the automatic choice up to N =
+                             2048 the wait for workgroups that have not
+                             started ends after ~20 ms and the register
+                             panel, which waits for nobody, factors this
+                             matrix in the handle's precision and the next
+                             1, 3, 7, .. 63 (after each expiry in a row).
+                             mds_get_fallbacks counts the expired waits,
                           4: unblocked factorization of the whole M held in
                              one workgroup's LDS (FP64, N <= 199; the
                              interchanges are applied to whole rows, so the
@@ -233,7 +241,7 @@ typedef struct {       /* one IPM iteration (host) */
                           its tolerance and the step was recomputed from an
                           FP64 factorization of the same Newton system;
                           bit 1: a cooperative panel's exchange wait expired
-                          and the memory panel refactored the matrix        */
+                          and another panel refactored the matrix           */
   int32_t nlp_event;   /* NLP mode (mds_set_nlp): 1 the accepted point came
                           from a second-order correction; 2 the iteration
                           ended in a feasibility restoration phase (x, z are
@@ -528,8 +536,8 @@ typedef struct {
 int mds_get_info(const mds_handle *h, mds_info *out_host);
 
 /* Robustness counters since mds_create (host): coop_aborts = cooperative
- * factorizations whose exchange wait expired and which the memory panel
- * redid; fp64_refactors = mixed-precision Newton solves of mds_ipm_step that
+ * factorizations whose exchange wait expired and which the memory or the
+ * register panel redid; fp64_refactors = mixed-precision Newton solves of mds_ipm_step that
  * were redone from an FP64 factorization. */
 typedef struct {
   int64_t coop_aborts, fp64_refactors;

@@ -537,10 +537,10 @@ long rest_slot(mds_handle *h, hipStream_t s, int b, long rows, bool reg, int sw,
 // always fails, register panel alone / cooperative panel alone / so, in us: N =
 // 101 265 / 464 / 308, 300 842 / 1531 / 884, 771 2360 / 4672 / 2398, 2048 8193 / 13246 /
 // 7938; N = 4096 (register panel for the last 2048 rows) 21167 / 28199 / 20499.
-// after: by slot, the rows that its launched update covers.  more: the panel
-// may change again.
+// after: by slot, the rows that its launched update covers.  sw: 0 the panel does
+// not change again, else as in launch_bk_panel_reg.
 void rest_launches(mds_handle *h, hipStream_t s, const FacState &st, std::vector<long> &after,
-                   bool more) {
+                   int sw) {
   const bool lowp = h->precision != MDS_FP64 && !h->force64;
   const int np2 = lowp ? 0 : h->pair_slots;
   auto slot = [&](int b, long rows, bool reg, int sw, bool panel) {
@@ -556,7 +556,6 @@ void rest_launches(mds_handle *h, hipStream_t s, const FacState &st, std::vector
   // the whole update again (it reads one buffer and writes the other)
   if (b > 0 && after[b - 1] < rows) slot(b - 1, rows, false, 0, false);
   after.resize(b);
-  const int sw = st.hand ? (more ? 2 : 1) : (more ? 1 : 0);
   for (; rows > 0; ++b) {
     rows = slot(b, rows, st.hand != 0, sw, true);
     after.push_back(rows);
@@ -757,11 +756,17 @@ int read_fac_state(mds_handle *h, FacState *st) {
   return MDS_OK;
 }
 
+constexpr int kRegDueMax = 63;
+
 int factor_impl(mds_handle *h, mds_inertia *out) {
   const int N = h->N;
   FacState st{};
   bool mem = h->coop_off, whole = true;  // whole: by factor_launches alone
-  if (!mem) {
+  // an expired wait: the register panel alone (it waits for nobody), now and for
+  // some factorizations more, twice as many after each expiry in a row
+  bool reg = !mem && h->reg_due > 0;
+  if (reg) h->reg_due--;
+  if (!mem && !reg) {
     // the look-ahead's CU masks belong to its streams, which a graph would
     // not keep: its launches go out one by one
     const bool graph = !h->timing && !h->panel_lds && !h->fac_graph_off && !h->force64 &&
@@ -780,7 +785,7 @@ int factor_impl(mds_handle *h, mds_inertia *out) {
       std::vector<long> after;
       for (const SlotPlan &p : h->plan) after.push_back(p.rows_after);
       for (int n = 1; st.k < N && !st.xerr && n <= kSwMax; ++n) {
-        rest_launches(h, S(h), st, after, n < kSwMax);
+        rest_launches(h, S(h), st, after, n < kSwMax ? 2 : st.hand);
         TRY(read_fac_state(h, &st));
         whole = false;
       }
@@ -788,13 +793,33 @@ int factor_impl(mds_handle *h, mds_inertia *out) {
     if (st.xerr && h->panel_coop) {
       // an exchange wait of the cooperative panel expired (its workgroups
       // were not all resident): condense again (the ping-pong buffers hold a
-      // partial factor) and factor in place with the memory panel
+      // partial factor) and factor with the register panel, past its rows
+      // in place with the memory panel
       h->n_coop_abort++;
-      mem = true;
+      reg = h->sw_cols > 0 && N <= kSwRows;
+      mem = !reg;
+      h->reg_last = std::min(2 * h->reg_last + 1, kRegDueMax);
+      if (reg) h->reg_due = h->reg_last;
       TRY(condense_impl(h, h->dw, h->dc));
     } else if (st.xerr) {
       return set_err(h, MDS_EHIP, "panel aborted: rows beyond the register tile");
+    } else {
+      h->reg_last = 0;
     }
+  }
+  if (reg) {
+    whole = false;
+    {
+      TimedLaunch t(h, MDS_T_FACTOR);
+      launch_fac_reset(S(h), h->w.fst, h->w.panel_k0);
+      if (h->precision != MDS_FP64 && !h->force64)
+        launch_equilibrate_f32(S(h), N, h->w.M, h->w.eq, h->w.X32[0]);
+      FacState from{};
+      from.hand = 1;
+      std::vector<long> after;
+      rest_launches(h, S(h), from, after, 0);
+    }
+    TRY(read_fac_state(h, &st));
   }
   if (mem) {
     factor_launches_mem(h, S(h));
@@ -1678,7 +1703,7 @@ int mds_create(mds_handle **out, const mds_dims *dims, const mds_options *opts, 
   // the overlap saves (off / on: N = 4096 7.3 / 8.1 ms per Newton step, 9001
   // 26.0 / 27.3, 16384 86 / 96; FP32 storage 10.8 / 11.7, 32.9 / 33.1, 88 / 93)
   if (pc.coop && !coop_off && la_opt == 1) setup_lookahead(h);
-  h->sw_cols = (pc.sw && h->la_cus == 0) ? h->dims.n_d : 0;
+  h->sw_cols = (pc.sw && h->la_cus == 0) ? std::max<int>(h->dims.n_d, 1) : 0;
   *out = h;
   return MDS_OK;
 }

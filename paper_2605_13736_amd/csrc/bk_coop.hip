@@ -48,6 +48,9 @@ using wave::rows4;
 using wave::sel4;
 
 constexpr unsigned long long kCoopWaitTicks = 1ull << 26;  // ~0.67 s of the 100 MHz clock
+// ... of a panel's first exchange, before which not all workgroups need have been
+// dispatched, where the register panel can take over at the price of its own time
+constexpr unsigned long long kCoopArriveTicks = 1ull << 21;  // ~21 ms
 
 __device__ inline void put_u32(uint64_t *p, uint32_t v, uint32_t tag) {
   __hip_atomic_store(p, ((uint64_t)tag << 32) | (uint64_t)v, __ATOMIC_RELAXED,
@@ -304,6 +307,9 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
     }
     return v;
   };
+  // of the exchange that has just been counted in c
+  const unsigned long long arrive = (swcols > 0 && N <= kSwRows) ? kCoopArriveTicks : kCoopWaitTicks;
+  auto wait_ticks = [&]() { return c == 1 ? arrive : kCoopWaitTicks; };
   auto expire = [&]() {
     __hip_atomic_store(&st->xerr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     s_abort = 1;
@@ -394,7 +400,7 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
 #pragma unroll
       for (int u = 0; u < U; ++u) ok = ok & ((!on[u]) | (tag_ok(whi[u], tag) & tag_ok(wlo[u], tag)));
       if (__ballot(!ok) == 0) break;
-      if (wall_clock64() - t0 > kCoopWaitTicks) {
+      if (wall_clock64() - t0 > wait_ticks()) {
         expire();
         break;
       }
@@ -746,7 +752,7 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
           for (int u = 0; u < 6; ++u) ok = ok & ((!hon) | tag_ok(h[u], tag));
           ok = ok & ((!aon) | (tag_ok(ah, tag) & tag_ok(al, tag)));
           if (__ballot(!ok) == 0) break;
-          if (wall_clock64() - t0 > kCoopWaitTicks) {
+          if (wall_clock64() - t0 > wait_ticks()) {
             expire();
             break;
           }
@@ -811,7 +817,7 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
             hi = get_w(rp);
             lo = get_w(lane < j ? rp + 1 : rp);
             if (__ballot(!(tag_ok(hi, tag) & tag_ok(lo, tag))) == 0) break;
-            if (wall_clock64() - t0 > kCoopWaitTicks) {
+            if (wall_clock64() - t0 > wait_ticks()) {
               expire();
               break;
             }
@@ -859,7 +865,7 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
           const bool ok = ((!hon) | (tag_ok(h0, tag) & tag_ok(h1, tag))) &
                           ((!aon) | (tag_ok(ah, tag) & tag_ok(al, tag)));
           if (__ballot(!ok) == 0) break;
-          if (wall_clock64() - t0 > kCoopWaitTicks) {
+          if (wall_clock64() - t0 > wait_ticks()) {
             expire();
             break;
           }

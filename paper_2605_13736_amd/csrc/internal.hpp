@@ -195,6 +195,7 @@ struct mds_handle {
   bool fac_lowprec = false; // current factor is of the equilibrated FP32 matrix
   int pair_slots = 0;       // leading slots factored two to a trailing update
   int sw_cols = 0;          // the register panel may take over in the first sw_cols columns
+  int reg_due = 0, reg_last = 0;  // factorizations due on it alone after an expired wait
   bool fac_pingpong = false;// current factor's L is spread over M and M2
   int64_t n_coop_abort = 0, n_fp64_refactor = 0;
   // look-ahead of the cooperative factorization: compute units reserved for

@@ -96,3 +96,36 @@ def test_passing_pivots_stay_on_the_cooperative_panel():
     S.factor_inertia()
     st = S.panel_stats()
     assert st["coop_steps"] == N and st["coop_second"] == 0
+
+
+@pytest.mark.parametrize("N,precision", [(300, "fp64"), (771, "fp64"), (2048, "fp64"), (600, "fp32")])
+def test_expired_wait_goes_to_the_register_panel(N, precision):
+    # up to 2048 rows the one-workgroup panel, which waits for nobody, factors
+    # what an expired exchange wait left; the next factorization does not try
+    # the exchange at once
+    A = _matrix(N, "head")
+    print(f"[gpu-case] expired wait N={N} {precision}", flush=True)
+    S = mds.solver_for(_dense_problem(A), precision=precision)
+    _, dd, ds, ipo, _, _ = oracle.bk(A)
+    io = tuple(oracle.inertia(ipo, dd, ds)[:3])
+    S.set_timing(True)
+    S.set_debug(mds.MDS_DEBUG_COOP_ABORT)
+    aborts = []
+    for _ in range(5):
+        before = S.get_timings()["panel_tail"]["launches"]
+        S.condense(np.zeros(N), np.zeros(0), 0.0, 0.0)
+        _, inn, _ = S.factor_inertia()
+        assert (inn["npos"], inn["nzero"], inn["nneg"]) == io
+        if precision == "fp64":
+            assert np.array_equal(S.get_pivots(), ipo)
+        assert S.get_timings()["panel_tail"]["launches"] - before >= N // 32
+        aborts.append(S.fallbacks()["coop_aborts"])
+    assert aborts == [1, 1, 2, 2, 2]
+    r = np.random.default_rng(N).standard_normal(N)
+    (x, _, _), info = S.refine(r, np.zeros(0), np.zeros(0), 60, 1e-13)
+    assert info["eta"] <= 1e-12
+    S.set_debug(0)
+    for _ in range(3):
+        S.condense(np.zeros(N), np.zeros(0), 0.0, 0.0)
+        S.factor_inertia()
+    assert S.fallbacks()["coop_aborts"] == 2 and S.panel_stats()["coop_steps"] > 0
