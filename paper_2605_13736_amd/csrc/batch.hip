@@ -3,8 +3,9 @@
 // problems from an atomic queue (largest first) and runs the whole Newton
 // system for each inside the workgroup:
 //   condense (same IEEE sequence as condense.hip, so M is bit-identical),
-//   blocked Bunch-Kaufman (FP64: speculative panels of 4 nb or 8 nb columns,
-//   per-wave 64 x 64 trailing tiles on FP64 MFMA; mixed precision:
+//   blocked Bunch-Kaufman (FP64: speculative panels of 4 nb or 8 nb columns, or
+//   register panels of 32 where most pivots fail the first test; per-wave 64 x
+//   64 trailing tiles on FP64 MFMA; mixed precision:
 //   panel::panel_reg_dev of nb columns; ping-pong buffers), inertia
 //   correction (Algorithm IC),
 //   LDL' solve in the panels' own row frames, back-substitution of dx_s.
@@ -414,8 +415,9 @@ __device__ inline void spec_rows(gdouble_out *oY, gdouble_out *oW, const PanelLd
 }
 
 // One panel of at most nbw columns from k0 on; returns its end (in every
-// thread) and records it in S.st and S.pk0.
-__device__ __attribute__((noinline)) int panel_spec_wg(int N, int k0, int nbw, double alpha,
+// thread) and records it in S.st and S.pk0.  It ends early, with S.st->hand set,
+// where the register panel should go on.
+__device__ __attribute__((noinline)) int panel_spec_wg(int N, int nd, int k0, int nbw, double alpha,
                                                        const double *X, double *Y,
                                                        const SlotDev &S) {
   PanelLds &s = panel_lds();
@@ -424,9 +426,12 @@ __device__ __attribute__((noinline)) int panel_spec_wg(int N, int k0, int nbw, d
   gdouble_out *oY = (gdouble_out *)ubase(Y), *oW = (gdouble_out *)ubase(S.W);
   for (int x = tid; x < N - k0; x += BT) s.map[x] = k0 + x;
   __syncthreads();
-  int k = k0, j = 0, slow = 0, cool = 0;
+  // full steps due and back-off (kept from panel to panel), full steps in a row
+  // that passed the first test, and what the register panel would have saved
+  int k = k0, j = 0, slow = S.st->slow, cool = S.st->cool, npass = 0, score = S.st->score;
+  bool hand = false;
   int c_pos = 0, c_zero = 0, c_neg = 0, c_2x2 = 0, first_zero = 0;
-  while (j < nbw && k < N) {
+  while (j < nbw && k < N && !hand) {
     if (slow == 0) {
       const int jb = j & ~(SB - 1), r0 = j - jb;
       const int len = min(min(SB - r0, nbw - j), N - k), ce = r0 + len;
@@ -475,11 +480,13 @@ __device__ __attribute__((noinline)) int panel_spec_wg(int N, int k0, int nbw, d
       j += a;
       k += a;
       if (a < len) {
-        cool = (a == 0) ? min(2 * cool + 1, 15) : 0;
+        cool = (a == 0) ? min(2 * cool + 1, 255) : 0;
         slow = 1 + (cool >> 1);
       } else {
         cool = 0;
       }
+      npass = 0;
+      score = max(score - kSwPass * a, 0);
       __syncthreads();
       continue;
     }
@@ -670,6 +677,10 @@ __device__ __attribute__((noinline)) int panel_spec_wg(int N, int k0, int nbw, d
     }
     j += kstep;
     k += kstep;
+    npass = (kind == 1) ? npass + 1 : 0;
+    if (npass >= 2) slow = 0;
+    score = min(score + kSwStep, kSwScoreMax);
+    hand = N - k <= BT && sw_due(nd, N, k, score);
     __syncthreads();
   }
   if (tid == 0) {
@@ -678,6 +689,10 @@ __device__ __attribute__((noinline)) int panel_spec_wg(int N, int k0, int nbw, d
     S.pk0[b + 1] = k;
     st->npanel = b + 1;
     st->k = k;
+    st->cool = cool;
+    st->slow = slow;
+    st->score = hand ? 0 : score;
+    st->hand = hand ? 1 : 0;
     st->npos += c_pos;
     st->nzero += c_zero;
     st->nneg += c_neg;
@@ -908,6 +923,24 @@ __device__ __attribute__((noinline)) void panel_call_lp(int N, int nb, double al
                                            S.ipiv, S.blk, S.st, S.pk0);
 }
 
+// The register panel over at most BT rows, one a thread, while most pivots fail
+// the first test: a full step of panel_spec_wg reads the panel's earlier columns
+// from memory twice and takes ~5 us, a step of this panel ~2.5.  64 problems that
+// always fail, ms a factorization, register panel of four rows a thread / the
+// speculative panel alone / so: N = 100 0.43 / 0.65 / 0.35, 200 0.90 / 1.36 / 0.69,
+// 400 2.27 / 2.91 / 1.52, 800 8.69 / 7.35 / 5.32.
+constexpr int RNB = 32;
+__device__ __attribute__((noinline)) void panel_reg_wg(int N, int k0, double alpha, const double *X,
+                                                       double *Y, const SlotDev &S) {
+  panel::panel_reg_dev<BT, 1, RNB, double>(N, RNB, alpha, X, Y, S.src, S.W, S.dd, S.ds, S.ipiv,
+                                           S.blk, S.st, S.pk0, 2);
+  __syncthreads();
+  // the trailing update's map
+  PanelLds &s = panel_lds();
+  for (int x = S.st->k + (int)threadIdx.x; x < N; x += BT) s.map[x - k0] = S.src[x];
+  __syncthreads();
+}
+
 // Mixed precision: blocked factorization of X32[0] = FP32(S M S); L (FP64)
 // of every panel lands in buf[0].
 __device__ void factor_wg_lp(int N, int nb, double alpha, const SlotDev &S) {
@@ -932,7 +965,7 @@ __device__ void factor_wg_lp(int N, int nb, double alpha, const SlotDev &S) {
 }
 
 // ---- blocked factorization of the slot's buf[0] --------------------------------
-__device__ void factor_wg(int N, int nb, double alpha, const SlotDev &S) {
+__device__ void factor_wg(int N, int nd, int nb, double alpha, const SlotDev &S) {
   const int tid = threadIdx.x;
   if (tid == 0) {
     FacState z{};
@@ -950,7 +983,13 @@ __device__ void factor_wg(int N, int nb, double alpha, const SlotDev &S) {
   for (int b = 0; k0 < N; ++b) {
     const double *X = S.buf[b & 1];
     double *Y = S.buf[(b + 1) & 1];
-    const int kend = panel_spec_wg(N, k0, nbw, alpha, X, Y, S);
+    int kend;
+    if (S.st->hand) {
+      panel_reg_wg(N, k0, alpha, X, Y, S);
+      kend = S.st->k;
+    } else {
+      kend = panel_spec_wg(N, nd, k0, nbw, alpha, X, Y, S);
+    }
     if (kend < N) trailing_wg(N, k0, kend, S.W, X, Y);
     k0 = kend;
     __syncthreads();
@@ -1295,7 +1334,7 @@ __global__ __launch_bounds__(BT) void k_batch(int count, const int32_t *__restri
       equilibrate_wg(N, S.buf[0], S.eq, S.x32[0]);
       factor_wg_lp(N, nb, alpha, S);
     } else {
-      factor_wg(N, nb, alpha, S);
+      factor_wg(N, P.nd, nb, alpha, S);
     }
     bool ok = S.st->npos == P.nd && S.st->nzero == 0 && S.st->nneg == P.m;
     if (!ok) {
@@ -1308,7 +1347,7 @@ __global__ __launch_bounds__(BT) void k_batch(int count, const int32_t *__restri
           equilibrate_wg(N, S.buf[0], S.eq, S.x32[0]);
           factor_wg_lp(N, nb, alpha, S);
         } else {
-          factor_wg(N, nb, alpha, S);
+          factor_wg(N, P.nd, nb, alpha, S);
         }
         ok = S.st->npos == P.nd && S.st->nzero == 0 && S.st->nneg == P.m;
         if (ok) break;
@@ -1646,7 +1685,7 @@ __device__ __attribute__((noinline)) void ipm_refine_wg(const ProbDev &P, const 
 __device__ inline bool ipm_factor_wg(const ProbDev &P, const SlotDev &S, int nb, double alpha,
                                      double dw, double dc) {
   condense_wg(P, S.inv_d, dw, dc, S.buf[0], false);
-  factor_wg(P.nd + P.m, nb, alpha, S);
+  factor_wg(P.nd + P.m, P.nd, nb, alpha, S);
   return S.st->npos == P.nd && S.st->nzero == 0 && S.st->nneg == P.m;
 }
 
