@@ -1191,7 +1191,7 @@ int refine_fused(mds_handle *h, const double *r_d, const double *r_s, const doub
   a.dc = h->dc;
   a.res = res;
   a.err = h->w.trsv + 1;
-  double nK = 0.0, nr = 0.0, eta_prev = INFINITY, eta = 0.0, rres = 0.0;
+  double nK = 0.0, nr = 0.0, eta_prev = INFINITY, eta = 0.0, rres = 0.0, rres_prev = 0.0;
   int steps = 0;
   for (;;) {
     a.norms = (steps == 0) ? 1 : 0;
@@ -1211,12 +1211,14 @@ int refine_fused(mds_handle *h, const double *r_d, const double *r_s, const doub
       // no decrease: keep the previous iterate
       launch_step_update(S(h), nd, ns, m, cor, prev, dx_d, dx_s, dy, true);
       eta = eta_prev;
+      rres = rres_prev;
       HIPCHK(hipGetLastError());
       HIPCHK(hipStreamSynchronize(S(h)));
       break;
     }
     if (eta <= eta_tol || steps >= max_steps) break;
     eta_prev = eta;
+    rres_prev = rres;
     TRY(solve_impl(h, res, res + nd, res + nd + ns, cor, cor + nd, cor + nd + ns));
     launch_step_update(S(h), nd, ns, m, cor, prev, dx_d, dx_s, dy, false);
     steps++;
@@ -1250,7 +1252,7 @@ int refine_impl(mds_handle *h, const double *r_d, const double *r_s, const doubl
   TRY(read_scal(h, s16, 16));
   const double nK = std::max(s16[0], std::max(s16[1], s16[2]));
   const double nr = std::max(s16[8], std::max(s16[9], s16[10]));
-  double eta_prev = INFINITY, eta = 0.0, rres = 0.0;
+  double eta_prev = INFINITY, eta = 0.0, rres = 0.0, rres_prev = 0.0;
   int steps = 0;
   for (;;) {
     kkt_matvec(h, dx_d, dx_s, dy, kx, kx + nd, kx + nd + ns);
@@ -1273,6 +1275,7 @@ int refine_impl(mds_handle *h, const double *r_d, const double *r_s, const doubl
       vec_copy(S(h), ns, prev + nd, dx_s);
       vec_copy(S(h), m, prev + nd + ns, dy);
       eta = eta_prev;
+      rres = rres_prev;
       break;
     }
     if (eta <= eta_tol || steps >= max_steps) break;
@@ -1280,6 +1283,7 @@ int refine_impl(mds_handle *h, const double *r_d, const double *r_s, const doubl
     vec_copy(S(h), ns, dx_s, prev + nd);
     vec_copy(S(h), m, dy, prev + nd + ns);
     eta_prev = eta;
+    rres_prev = rres;
     TRY(solve_impl(h, res, res + nd, res + nd + ns, cor, cor + nd, cor + nd + ns));
     vec_add_inplace(S(h), nd, cor, dx_d);
     vec_add_inplace(S(h), ns, cor + nd, dx_s);
