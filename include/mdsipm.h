@@ -145,10 +145,9 @@ typedef struct {
   int32_t lookahead;   /* cooperative factorization: 0 automatic (off: it
                           does not pay), 1 on, 2 off.  With look-ahead, panel
                           b + 1 and the update of the 128-column strip ahead
-                          of it run on a few reserved compute units (4 or 8
-                          per XCD, at least the panel's workgroups: N <=
-                          16384 on 256 units) while the
-                          rest of panel b's trailing update runs on the
+                          of it run on a few reserved compute units (4, 8
+                          or 16 per XCD, at least the panel's workgroups:
+                          any N on 256 units) while the rest of panel b's trailing update runs on the
                           others (two CU-masked streams the handle creates;
                           the handle's stream waits for both).  Panel b + 1
                           computes the entries it needs outside the strip

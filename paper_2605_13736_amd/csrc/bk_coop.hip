@@ -1220,13 +1220,13 @@ void launch_bk_panel_coop_la(hipStream_t s, int rows, int N, int nb, double alph
 }
 
 // One panel workgroup per compute unit (its LDS holds one), so the reserved
-// units must number at least the first panel's workgroups: 4 or 8 per XCD
+// units must number at least the first panel's workgroups: 4, 8 or 16 per XCD
 // (the near update runs on them too), so that every XCD keeps the same
-// share; no look-ahead when that is not enough (N > 16384 on 256 units).
+// share; no look-ahead where that is more than half of them.
 int bk_coop_la_reserve(int N, int cus) {
   const int P = bk_coop_wgs(N);
-  const int r = (P <= 32) ? 32 : 64;
-  return (P <= r && r <= cus / 4) ? r : 0;
+  const int r = (P <= 32) ? 32 : (P <= 64) ? 64 : 128;
+  return (P <= r && r <= cus / 2) ? r : 0;
 }
 
 }  // namespace mds
