@@ -10,6 +10,8 @@
 //   M22(i,j) = 0 - sum_k (J_ik * Dinv_k) * J_jk  over the shared columns k of
 //              rows i >= j in ascending k, then - dc on the diagonal and,
 //              when a per-row diagonal is set, - dcv[r] after it.
+#include <algorithm>
+
 #include "internal.hpp"
 
 namespace mds {
@@ -29,7 +31,8 @@ __global__ __launch_bounds__(256) void k_condense_dense(int nd, int m, int N,
                                                         double *__restrict__ inv_d,
                                                         double *__restrict__ M) {
   __shared__ double t[kTile][kTile + 1];
-  // D_s^{-1} beside the dense blocks (one launch less)
+  // D_s^{-1} beside the dense blocks (one launch less); workgroups past the tiles
+  // do nothing else
   if (inv_d) {
     const int64_t step = (int64_t)gridDim.x * gridDim.y * 256;
     for (int64_t k = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x; k < ns;
@@ -264,8 +267,12 @@ void launch_condense_dense(hipStream_t s, int nd, int m, const double *H, const 
                            double *inv_d, double *M) {
   const int N = nd + m;
   if (N <= 0 && (ns <= 0 || !inv_d)) return;
-  // without dense rows one workgroup's worth of tiles still forms D_s^{-1}
-  dim3 g(N > 0 ? grid1(N, kTile) : 1, N > 0 ? grid1(N, kTile) : grid1(ns, 256));
+  // as many workgroups as the tiles, and as D_s^{-1} wants: four entries a
+  // thread, at most 1024 workgroups (n_s = 10^6 at N = 4, one tile: 1100 us by
+  // the tile's workgroup alone, 10 so)
+  const unsigned gx = std::max(1u, grid1(N, kTile));
+  const unsigned wgs = inv_d ? std::min(grid1(ns, 1024), 1024u) : 0;
+  const dim3 g(gx, std::max(gx, (wgs + gx - 1) / gx));
   k_condense_dense<<<g, 256, 0, s>>>(nd, m, N, H, Jd, sigma_d, dw, ns, dsbase, inv_d, M);
 }
 
