@@ -1316,7 +1316,7 @@ void eval_grad_constr(mds_handle *h, const double *x, const double *y, double *r
     ipm_grad_finish(S(h), nd, ns, P.c, P.w, P.g, x, gf);
     if (h->sb.nblk > 0) sblk_matvec(S(h), h->sb, ns, x + nd, true, gf + nd);
   }
-  if (y) {
+  if (y || m == 0) {  // without rows J'y = 0, and y may be null
     if (nd > 0) {
       if (m > 0) launch_gemv_t(S(h), m, nd, P.J_d, m, y, 0.0, jty);
       else hipMemsetAsync(jty, 0, 8 * (size_t)nd, S(h));
