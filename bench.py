@@ -85,11 +85,11 @@ def trailing_bytes_per_launch(N, w, elem=8.0):
 
 
 def slot_widths(N, nb=32, tail_rows=2048):
-    """Columns each panel launch factors at least, in the library's slot plan
-    for the automatic cooperative factorization: nb - 1 while more than
-    tail_rows rows remain, then the register tail (16-column tile above 1024
-    rows, the 32-column one below).  Panels end on these widths except where
-    a 2x2 pivot closes a panel one column later."""
+    """Columns each panel launch factors at least in a factorization that the
+    register panel takes over at tail_rows rows: nb - 1 before, then its tiles'
+    (16 columns above 1024 rows, 32 below), one column more where a 2x2 pivot
+    closes a panel.  Where the panel changes depends on the pivots, so no figure
+    of the benchmark uses this; trailing_plan is the model of its roofline."""
     rows, ws = N, []
     while rows > 0:
         if rows <= tail_rows:
@@ -236,10 +236,7 @@ def kkt_step_section(args):
     # the cooperative panel at its first panels' width (outside the timed
     # regions)
     pstats = S.panel_stats()
-    P = min(32, (N + 1023) // 1024)
-    xfloor = dict(P=P, first_exchange_us=S.probe_exchange(P, 2000, 69),
-                  second_exchange_us=S.probe_exchange(P, 2000, 16),
-                  words=dict(first=69, second=16), rounds=2000)
+    xfloor = exchange_probe(S, N)
     out = dict(N=N, dt=dt, facs=facs, solves=solves, value=value, tim=tim, efacs=efacs,
                dte=dte, info=info0, eta=ri["eta"], inertia=inn, x64=x64, pstats=pstats,
                xfloor=xfloor)
@@ -295,12 +292,26 @@ def roofline_of(tim, efacs, N, nb, pstats=None, xfloor=None):
                 trailing=trailing, panel=panel_latency_model(tim, efacs, N, nb, pstats, xfloor))
 
 
+def exchange_probe(S, N):
+    """Round trips of the panel's exchanges, measured without other work: a
+    block's (7 words a workgroup; the window rows' words, up to 2048 for all,
+    come on top in the panel) and the candidate column's (4 words).  The panel
+    has a workgroup for each 256 rows, the probe at most 32 of them, so past
+    8192 rows it is a lower bound."""
+    P = min(32, (N + 255) // 256)
+    return dict(P=P, panel_workgroups=(N + 255) // 256,
+                block_exchange_us=S.probe_exchange(P, 2000, 7),
+                candidate_exchange_us=S.probe_exchange(P, 2000, 4),
+                words=dict(block=7, candidate=4), rounds=2000)
+
+
 def panel_latency_model(tim, efacs, N, nb, pstats=None, xfloor=None):
     """Microseconds per pivot step of the cooperative panel (a latency-bound
     chain: one grid-wide exchange per 16 columns whose pivots pass the first
-    test, one or two more where one fails), and, with the pivot statistics and
-    the measured exchange round trip, the floor that the exchanges alone set
-    (one per 16 steps, two more on the steps whose first test fails)."""
+    test, more where one fails), and, with the pivot statistics and the
+    measured exchange round trips, the floor that the exchanges alone set: a
+    block's for 16 steps, and for a step whose first test fails the candidate
+    column's (the failing block's exchange carried the candidate)."""
     out = {}
     for cls in ("panel", "panel_tail"):
         n = tim[cls]["launches"]
@@ -316,8 +327,8 @@ def panel_latency_model(tim, efacs, N, nb, pstats=None, xfloor=None):
         m = dict(steps_per_factorization=pstats["coop_steps"], second_exchange_frac=f2,
                  us_per_step=us_step, n2x2=pstats["n2x2"])
         if xfloor:
-            floor = (xfloor["first_exchange_us"] / 16 +
-                     f2 * (xfloor["first_exchange_us"] + xfloor["second_exchange_us"]))
+            floor = (xfloor["block_exchange_us"] / 16 +
+                     f2 * xfloor["candidate_exchange_us"])
             m.update(exchange_floor_us_per_step=floor, step_over_floor=us_step / floor,
                      probe=xfloor)
         out["coop_model"] = m
@@ -428,10 +439,7 @@ def opf_section(steps=10, warmup=2):
     tim = S.get_timings()
     S.set_timing(False)
     pstats = S.panel_stats()
-    P = (N + 1023) // 1024
-    xfloor = dict(P=P, first_exchange_us=S.probe_exchange(P, 2000, 69),
-                  second_exchange_us=S.probe_exchange(P, 2000, 16),
-                  words=dict(first=69, second=16), rounds=2000)
+    xfloor = exchange_probe(S, N)
     fac_ms = factor_ms_of(tim, efacs)
     # whole IPM
     r = S.ipm_solve()
