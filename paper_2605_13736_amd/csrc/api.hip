@@ -533,10 +533,11 @@ long rest_slot(mds_handle *h, hipStream_t s, int b, long rows, bool reg, int sw,
 // rows that one workgroup holds.  So the cooperative panel ends where sw_due says
 // so, the register panel gives back when its pivots pass again, the launches that
 // were queued behind return at once, and the host, which reads the state anyway,
-// queues the others.  Condense and factor of a dense matrix whose first test
-// always fails, register panel alone / cooperative panel alone / so, in us: N =
-// 101 265 / 464 / 308, 300 842 / 1531 / 884, 771 2360 / 4672 / 2398, 2048 8193 / 13246 /
-// 7938; N = 4096 (register panel for the last 2048 rows) 21167 / 28199 / 20499.
+// queues the others.  Condense and factor of a dense matrix with a zero diagonal,
+// whose first test always fails, register panel alone / cooperative panel alone /
+// so, in us: N = 101 265 / 389 / 286, 200 514 / 653 / 521, 300 842 / 1247 / 833, 771
+// 2360 / 3689 / 2301, 2048 8193 / 10982 / 7660; N = 4096 (register panel for the last
+// 2048 rows) 21167 / 24047 / 19694.
 // after: by slot, the rows that its launched update covers.  sw: 0 the panel does
 // not change again, else as in launch_bk_panel_reg.
 void rest_launches(mds_handle *h, hipStream_t s, const FacState &st, std::vector<long> &after,

@@ -428,7 +428,8 @@ __device__ __attribute__((noinline)) int panel_spec_wg(int N, int nd, int k0, in
   __syncthreads();
   // full steps due and back-off (kept from panel to panel), full steps in a row
   // that passed the first test, and what the register panel would have saved
-  int k = k0, j = 0, slow = S.st->slow, cool = S.st->cool, npass = 0, score = S.st->score;
+  int k = k0, j = 0, slow = S.st->slow, cool = S.st->cool, npass = 0, score = S.st->score,
+      run = S.st->run;
   bool hand = false;
   int c_pos = 0, c_zero = 0, c_neg = 0, c_2x2 = 0, first_zero = 0;
   while (j < nbw && k < N && !hand) {
@@ -487,6 +488,7 @@ __device__ __attribute__((noinline)) int panel_spec_wg(int N, int nd, int k0, in
       }
       npass = 0;
       score = max(score - kSwPass * a, 0);
+      run = score > 0 ? run : 0;
       __syncthreads();
       continue;
     }
@@ -680,7 +682,8 @@ __device__ __attribute__((noinline)) int panel_spec_wg(int N, int nd, int k0, in
     npass = (kind == 1) ? npass + 1 : 0;
     if (npass >= 2) slow = 0;
     score = min(score + kSwStep, kSwScoreMax);
-    hand = N - k <= BT && sw_due(nd, N, k, score);
+    ++run;
+    hand = N - k <= BT && sw_due(max(nd, 1), N, k, score, run);
     __syncthreads();
   }
   if (tid == 0) {
@@ -692,6 +695,7 @@ __device__ __attribute__((noinline)) int panel_spec_wg(int N, int nd, int k0, in
     st->cool = cool;
     st->slow = slow;
     st->score = hand ? 0 : score;
+    st->run = hand ? 0 : run;
     st->hand = hand ? 1 : 0;
     st->npos += c_pos;
     st->nzero += c_zero;

@@ -1,7 +1,9 @@
 // Cooperative Bunch-Kaufman panel (Sec. 2.3): P workgroups (one per CU) each
 // keep the multipliers of their own 256 rows in LDS and take the same pivot
 // decisions from data they exchange.  One workgroup (P = 1, at most 256 rows
-// left) needs no exchange.
+// left) needs no exchange and has an instance of its own (SOLO): its full steps
+// read any row's multipliers where they stand, and the window rows (below) are
+// gathered again only before the next block.
 //
 // Thread t of workgroup g owns the physical row rho = k0 + 256 g + t of the
 // buffer X (the trailing matrix in logical order at the panel start).
@@ -134,6 +136,9 @@ __device__ __attribute__((noinline)) double pending_entry(const TX *pX, const in
 // gathered and selected across lanes for every four columns), 2.9 for the exchange
 // (1.7 of them its round trip).  A full step takes 3.9 us after a failing block
 // and 8.2 otherwise (10.5 while each one had its X1 and ended in an XB).  The
+// A matrix whose pivots all fail, whole factorization a column: N = 200 (one
+// workgroup) 4.7 -> 3.3 us, 771 6.1 -> 4.8, 2048 6.5 -> 5.4, 4096 6.9 -> 5.9 (with the
+// search for the maximum as a maximum and then its least position, and SOLO).  The
 // panels of N = 4096: 4.76 -> 3.85 ms (FP32 storage, more failing blocks: 5.7 ->
 // 4.8, mostly because its entries are converted after the exchange instead of
 // before it), N = 16384: 21.2 -> 17 ms.
@@ -149,7 +154,9 @@ static_assert(8 + 2 * CNB <= kCoopSlotWords && CB * CNB * 2 <= kCoopRowWords, "e
 
 typedef double d4 __attribute__((ext_vector_type(4)));
 
-template <typename TX, bool LA>
+// SOLO: at most CT rows are left, one workgroup.  The exchanges fall away at compile
+// time: an IPM at N = 192 takes 6.64 -> 6.32 ms.
+template <typename TX, bool LA, bool SOLO = false>
 __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alpha,
                                                       const TX *__restrict__ X, const PanelPrev pv,
                                                       double *__restrict__ Lout,
@@ -170,27 +177,27 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
   __shared__ double s_pdd[CNB], s_pds[CNB], s_dn[CB];
   __shared__ int s_pip[CNB], s_pbk[CNB];
   __shared__ int s_map[CNB + 2];  // physical row of positions k0 .. k0 + CNB + 1
-  __shared__ int s_pos[CT];
   __shared__ double s_hv[kCoopMaxP], s_hx[kCoopMaxP];
   __shared__ int s_hi[kCoopMaxP], s_hp[kCoopMaxP];
   __shared__ int s_hq[kCoopMaxP];
   __shared__ double s_xq[CB];  // the failing column's entries of the window rows
   __shared__ double s_cv[NWV], s_akk, s_aii;
   __shared__ int s_ci[NWV], s_cs[NWV], s_fail[NWV];
-  __shared__ int s_k0, s_abort, s_force, s_score, s_cool, s_slow;
+  __shared__ int s_k0, s_abort, s_force, s_score, s_run, s_cool, s_slow;
   __shared__ uint32_t s_tag0;
   __shared__ double s_pw[CPW], s_pl[CPW];  // look-ahead: W and L rows of the candidate
   __shared__ int s_jwp, s_kprev;
 
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int l16 = lane & 15, l4 = lane >> 4;
-  const int g = blockIdx.x;
+  const int g = SOLO ? 0 : blockIdx.x;
   if (tid == 0) {
     s_k0 = st->k;
     s_tag0 = st->xtag;
     s_abort = st->xerr;
     s_force = st->xforce;
     s_score = st->score;
+    s_run = st->run;
     s_cool = st->cool;
     s_slow = st->slow;
     if (swcols > 0 && st->hand) s_k0 = N;  // the register panel goes on
@@ -208,12 +215,16 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
     return;
   }
   // hand over (below) at the panel's start
-  int score = s_score;
-  if (sw_due(swcols, N, k0, score)) {
+  int score = s_score, run = s_run;
+  if (sw_due(swcols, N, k0, score, run)) {
     if (g == 0 && tid == 0) st->hand = 1;  // (the others return by the score)
     return;
   }
-  const int P = min((int)gridDim.x, (N - k0 + CT - 1) / CT);
+  if (SOLO && N - k0 > CT) {  // not launched so: the rows would not fit
+    if (tid == 0) __hip_atomic_store(&st->xerr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return;
+  }
+  const int P = SOLO ? 1 : min((int)gridDim.x, (N - k0 + CT - 1) / CT);
   if (g >= P) return;
   const int ld = N;  // N <= 20480: every offset fits in 32 bits
   const int gbase = k0 + g * CT;
@@ -230,7 +241,6 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
   auto owner = [&](int phys) { return (phys - k0) / CT; };
 
   int pos = (rho < N) ? rho : -1;  // logical position of this thread's row
-  s_pos[tid] = pos;
   if (tid < CNB + 2) s_map[tid] = k0 + tid;
   __syncthreads();
 
@@ -240,6 +250,10 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
   // full steps due; back-off after failing blocks (kept from panel to panel);
   // full steps in a row that passed the first test
   int slow = s_slow, cool = s_cool, npass = 0;
+  // One workgroup has every row's multipliers: its full steps take L rows from
+  // there, and the window rows are read again before the next block (stale)
+  const bool solo = P == 1;
+  bool stale = false;
   bool hand = false;      // the panel ends here, the register panel goes on
   // a failing block's candidate: the next full step starts from it without X1
   bool have = false;
@@ -283,12 +297,12 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
       }
     }
   };
-  // W = L D of window row q at column t < j
-  auto wrow = [&](const double *lr, int t) {
-    double v = lr[t] * s_cA[t];
+  // W = L D of a row at column t < j, its L row at lr with stride st
+  auto wrow = [&](const double *lr, int t, int st = 1) {
+    double v = lr[t * st] * s_cA[t];
     if (any2) {
-      if (t + 1 < j) v = v + lr[t + 1] * s_cB[t];
-      if (t >= 1) v = v + lr[t - 1] * s_cC[t];
+      if (t + 1 < j) v = v + lr[(t + 1) * st] * s_cB[t];
+      if (t >= 1) v = v + lr[(t - 1) * st] * s_cC[t];
     }
     return v;
   };
@@ -435,6 +449,14 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
       const int jb = j & ~(CB - 1), r0 = j - jb, s = block_cols(j), ce = r0 + s;
       if (!loaded) load_block(j);
       loaded = false;
+      if (stale) {
+        for (int e = tid; e < CB * j; e += CT) {
+          const int q = e & (CB - 1), t = e / CB;
+          if (k0 + jb + q < N) s_lw[q * CWL + t] = s_L[t * CLD + s_map[jb + q] - gbase];
+        }
+        stale = false;
+        __syncthreads();
+      }
       if constexpr (RAW) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -659,6 +681,7 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
       }
       npass = 0;
       score = max(score - kSwPass * a, 0);
+      run = score > 0 ? run : 0;
       __syncthreads();
       continue;
     }
@@ -672,7 +695,7 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
     // The window rows' entries of the pivot columns are computed by every
     // workgroup: 16 lanes a row, from its L row (wq: this thread's row)
     const int wq = tid >> 4, wl = tid & 15, jb = j & ~(CB - 1);
-    const bool won = k0 + jb + wq < N && jb + wq >= j;
+    const bool won = !solo && k0 + jb + wq < N && jb + wq >= j;
     const int wphys = won ? s_map[jb + wq] : 0;
     double xq = (!cand && won && wl == 0) ? (double)sym_at(X, wphys, s_map[j], ld) : 0.0, yq = 0.0;
     auto window_entry = [&](double v, const double *wr) {
@@ -693,22 +716,21 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
       colmax = f_max;
       imax = f_imax;
       iphys = f_phys;
-      if (P == 1) {
-        if (tid < j) s_irow[tid] = s_L[tid * CLD + iphys - gbase];
-        wki = s_hx[0];
-        __syncthreads();
-      } else {
+      if (!solo) {
         gw = f_g;
         wki = s_hx[gw];
       }
     } else {
-      if (wid == 0) s_wk[lane] = (lane < j) ? wrow(s_lw + (j & (CB - 1)) * CWL, lane) : 0.0;
+      if (wid == 0) {
+        const double *lr = solo ? s_L + s_map[j] - gbase : s_lw + (j & (CB - 1)) * CWL;
+        s_wk[lane] = (lane < j) ? wrow(lr, lane, solo ? CLD : 1) : 0.0;
+      }
       __syncthreads();
       x = minus_row(x, s_wk);
-      xq = window_entry(xq, s_wk);
+      if (!solo) xq = window_entry(xq, s_wk);
       double bv = -1.0;
       int bi = INT_MAX, bs = tid;
-      if (pos > k) {
+      if (pos > k && !isnan(x)) {
         bv = fabs(x);
         bi = pos;
       }
@@ -717,12 +739,9 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
       colmax = bv;
       imax = bi;
       iphys = gbase + bs;
-      if (P == 1) {
-        if (tid == bs) s_hx[0] = x;
-        if (tid < j) s_irow[tid] = s_L[tid * CLD + bs];
-        __syncthreads();
+      if (solo) {
+        if (tid == bs) s_hx[0] = x;  // read past the next barrier
         akk = s_akk;
-        wki = s_hx[0];
       } else {
         // ---- X1 -------------------------------------------------------------------
         const int par = c & 1;
@@ -825,10 +844,12 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
           if (lane < j) s_irow[lane] = as_f64(hi, lo);
           lds_wave_sync();
         }
-        s_wi[lane] = (lane < j) ? wrow(s_irow, lane) : 0.0;
+        const double *lr = solo ? s_L + iphys - gbase : s_irow;
+        s_wi[lane] = (lane < j) ? wrow(lr, lane, solo ? CLD : 1) : 0.0;
       }
       __syncthreads();
       if (s_abort) return;
+      if (solo) wki = s_hx[0];
       if constexpr (LA) if (fly) {
         const TX *pX;
         if constexpr (sizeof(TX) == 8) pX = pv.X;
@@ -837,7 +858,7 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
         if (on) y = pending_entry<TX>(pX, pv.src, pv.W, pL, rho, iphys, jwp, ld, s_pw, s_pl);
       }
       y = minus_row(y, s_wi);
-      yq = window_entry(yq, s_wi);
+      if (!solo) yq = window_entry(yq, s_wi);
       // ---- X3: maximum of the updated column imax, and a_ii --------------------
       double rv = (pos >= k && pos != imax) ? fabs(y) : 0.0;
       rv = wave::max(rv);
@@ -929,7 +950,6 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
       if (sw) {
         if (pos == p) pos = q;
         else if (pos == q) pos = p;
-        s_pos[tid] = pos;
       }
     }
     if (won) {
@@ -991,12 +1011,20 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
     npass = (kind == 1) ? npass + 1 : 0;
     if (npass >= 2) slow = 0;
     score = min(score + kSwStep, kSwScoreMax);
-    if (sw_due(swcols, N, k, score)) {
+    ++run;
+    if (sw_due(swcols, N, k, score, run)) {
       hand = true;
       break;
     }
     if (j < nb && k < N) {
-      if ((j & ~(CB - 1)) != jb) {
+      if (solo) {
+        stale = true;
+        __syncthreads();
+        if (slow == 0) {
+          load_block(j);
+          loaded = true;
+        }
+      } else if ((j & ~(CB - 1)) != jb) {
         // the next window's rows, and the next block's entries
         const bool spec = slow == 0;
         const int m = xb(CB, true, j & ~(CB - 1), j, 0, spec ? j : -1, CB, 0.0, 0, 0, 0.0);
@@ -1065,6 +1093,7 @@ __global__ __launch_bounds__(CT) void k_bk_panel_coop(int N, int nb, double alph
     st->cool = cool;
     st->slow = slow;
     st->score = hand ? 0 : score;
+    st->run = hand ? 0 : run;
     if (hand) st->hand = 1;
   }
 }
@@ -1173,8 +1202,12 @@ static void panel_coop(hipStream_t s, int rows, int N, int nb, double alpha, con
                        double *dd, double *ds, int32_t *ipiv, int32_t *blk, FacState *st,
                        int32_t *panel_k0, uint64_t *xch, int swcols = 0) {
   const int P = std::max(1, std::min(bk_coop_wgs(N), bk_coop_wgs(rows)));
-  k_bk_panel_coop<TX, LA><<<P, CT, 0, s>>>(N, std::min(nb, CNB), alpha, X, pv, Lout, src_out, W, dd,
-                                           ds, ipiv, blk, st, panel_k0, xch, lstage, swcols);
+  auto go = [&](auto kernel) {
+    kernel<<<P, CT, 0, s>>>(N, std::min(nb, CNB), alpha, X, pv, Lout, src_out, W, dd, ds, ipiv, blk,
+                            st, panel_k0, xch, lstage, swcols);
+  };
+  if (!LA && P == 1) go(k_bk_panel_coop<TX, false, true>);
+  else go(k_bk_panel_coop<TX, LA>);
 }
 
 int bk_xch_probe(hipStream_t s, int P, int rounds, int words, uint64_t *xch, int32_t *err,

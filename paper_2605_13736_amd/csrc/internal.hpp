@@ -58,7 +58,7 @@ struct FacState {
   int32_t cx3;    // ... of which took the second exchange (the candidate column)
   // which panel goes on (handles that may change it: see rest_launches)
   int32_t hand;   // the one-workgroup register panel, from k on
-  int32_t score;  // what the other panel would have saved so far (sw_limit)
+  int32_t score, run;  // what the other panel would have saved so far (sw_limit), full steps since 0
   int32_t cool, slow;  // cooperative panel: back-off from speculative blocks, full steps due
 };
 
@@ -71,14 +71,17 @@ struct FacState {
 constexpr int kSwStep = 3, kSwPass = 1;
 constexpr int kSwScoreMax = 200;
 __host__ __device__ inline int sw_limit(int rows) { return 12 + rows / 16; }
-// Whether the cooperative panel hands over at column k.  Only the first cols
-// pivots, those of the x block, are expected to go on failing: what is past them
-// is negative definite once they are eliminated, and the late ones of a KKT
-// system fail for 32 to 100 columns just before that, where the change back
-// follows at once (IPM at N = 192 without the last condition: 6.7 -> 7.3 ms).
-__host__ __device__ inline bool sw_due(int cols, int N, int k, int score) {
+// Whether the cooperative panel hands over at column k.  What comes must be worth
+// the change: pivots of the x block, the first cols, are expected to go on
+// failing (what is past them is negative definite once they are eliminated), and
+// others after run full steps.  The late pivots of a KKT system's x block fail for
+// 32 to 130 columns, where the change back follows at once (whole IPMs without
+// the first condition: N = 192 6.7 -> 7.3 ms; with half of the second: N = 515
+// 16.7 -> 18.0).
+__host__ __device__ inline bool sw_due(int cols, int N, int k, int score, int run) {
   const int rows = N - k;
-  return rows <= kSwRows && score >= sw_limit(rows) && cols - k >= 32 + rows / 8;
+  return cols > 0 && rows <= kSwRows && score >= sw_limit(rows) &&
+         (cols - k >= 32 + rows / 8 || run >= 64 + rows / 4);
 }
 
 // Look-ahead of the cooperative factorization: while the trailing update of

@@ -485,7 +485,7 @@ __device__ inline void panel_reg_dev(int N, int nb, double alpha,
       const int score = max(st->score + kSwPass * (nsteps - nsec) - kSwStep * nsec, 0);
       const bool back = score >= sw_limit(N - kend) && N - kend >= kSwMinRows;
       st->score = back ? 0 : score;
-      if (back) st->hand = st->cool = st->slow = 0;
+      if (back) st->hand = st->run = st->cool = st->slow = 0;
     }
   }
 }

@@ -10,6 +10,7 @@
 // the same order in every lane.  All 64 lanes must be active.
 #include <hip/hip_runtime.h>
 
+#include <climits>
 #include <type_traits>
 
 namespace mds {
@@ -63,56 +64,6 @@ __device__ inline void amax3(double &v, int &i, int &s, double v2, int i2, int s
   }
 }
 
-template <int C>
-__device__ inline void amax_step(double &v, int &i) {
-  const double v2 = dpp<C>(v);
-  const int i2 = dpp<C>(i);
-  amax2(v, i, v2, i2);
-}
-template <int C>
-__device__ inline void amax_step(double &v, int &i, int &s) {
-  const double v2 = dpp<C>(v);
-  const int i2 = dpp<C>(i), s2 = dpp<C>(s);
-  amax3(v, i, s, v2, i2, s2);
-}
-
-// arg-max of (v, i) over the 16 lanes of each row: every lane of the row
-__device__ inline void row_amax(double &v, int &i) {
-  amax_step<kXor1>(v, i);
-  amax_step<kXor2>(v, i);
-  amax_step<kRor4>(v, i);
-  amax_step<kRor8>(v, i);
-}
-__device__ inline void row_amax(double &v, int &i, int &s) {
-  amax_step<kXor1>(v, i, s);
-  amax_step<kXor2>(v, i, s);
-  amax_step<kRor4>(v, i, s);
-  amax_step<kRor8>(v, i, s);
-}
-
-// arg-max over the wave, result in every lane (wave-uniform)
-__device__ inline void amax(double &v, int &i) {
-  row_amax(v, i);
-  double r = lane_read(v, 0);
-  int ri = lane_read(i, 0);
-  amax2(r, ri, lane_read(v, 16), lane_read(i, 16));
-  amax2(r, ri, lane_read(v, 32), lane_read(i, 32));
-  amax2(r, ri, lane_read(v, 48), lane_read(i, 48));
-  v = r;
-  i = ri;
-}
-__device__ inline void amax(double &v, int &i, int &s) {
-  row_amax(v, i, s);
-  double r = lane_read(v, 0);
-  int ri = lane_read(i, 0), rs = lane_read(s, 0);
-  amax3(r, ri, rs, lane_read(v, 16), lane_read(i, 16), lane_read(s, 16));
-  amax3(r, ri, rs, lane_read(v, 32), lane_read(i, 32), lane_read(s, 32));
-  amax3(r, ri, rs, lane_read(v, 48), lane_read(i, 48), lane_read(s, 48));
-  v = r;
-  i = ri;
-  s = rs;
-}
-
 // maximum over the wave (fmax: a NaN operand is ignored), every lane
 __device__ inline double max(double v) {
   v = fmax(v, dpp<kXor1>(v));
@@ -130,6 +81,24 @@ __device__ inline int imin(int v) {
   v = min(v, dpp<kRor4>(v));
   v = min(v, dpp<kRor8>(v));
   return min(min(lane_read(v, 0), lane_read(v, 16)), min(lane_read(v, 32), lane_read(v, 48)));
+}
+
+// arg-max over the wave, result in every lane (wave-uniform): the maximum, then
+// the least position that has it (a step of the pair together takes three
+// times the instructions).  A NaN is never the maximum.
+__device__ inline void amax(double &v, int &i) {
+  const double m = max(v);
+  i = imin(v == m ? i : INT_MAX);
+  v = m;
+}
+// ... with a value s of the lane that holds it (positions differ)
+__device__ inline void amax(double &v, int &i, int &s) {
+  const double m = max(v);
+  const int p = imin(v == m ? i : INT_MAX);
+  const unsigned long long at = __ballot(v == m && i == p);
+  s = lane_read(s, at ? __ffsll(at) - 1 : 0);
+  v = m;
+  i = p;
 }
 
 // sum over the 16 lanes of each row: every lane of the row
