@@ -102,9 +102,8 @@ enum { MDS_FP64 = 0, MDS_FP32 = 1, MDS_BF16 = 2, MDS_BF16X3 = 3 };
 typedef struct {
   int32_t nb;          /* panel width of the blocked factorization (0: default) */
   int32_t panel;       /* 0: automatic (the cooperative panel, and the
-                          register panel for as long as most pivots of the
-                          x block fail the first test, over at most 2048
-                          rows; the register panel throughout when
+                          register panel for as long as most pivots fail the
+                          first test, over at most 2048 rows; the register panel throughout when
                           panel_threads is set and its tile allows nb >= 16,
                           i.e. N <= 2048),
                           1: panel kept in device memory (FP64 only),
